@@ -1,4 +1,6 @@
-"""Thin ctypes binding of libppv_hip.so: argument marshalling only.
+"""Thin binding of libppv_hip.so: argument marshalling only, through ctypes for the calls that are made once per
+constraint set and through the native extension _ppv_call for those that are made at every step (ctypes and tensor
+attributes read from Python took 10 to 12 us per call, longer than the GPU needs for a small batch).
 
 Same names as the C ABI in include/ppv.h.  Tensors are torch tensors on the GPU (torch provides
 device memory and the current stream, nothing else); every step of the path runs in the library's
@@ -15,6 +17,7 @@ import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libppv_hip.so")
+CALL_PATH = os.path.join(_PKG, "_ppv_call.so")
 
 PPV_OK = 0
 PPV_F32, PPV_BF16 = 0, 1
@@ -35,6 +38,7 @@ PPV_NOALLOC_MAX_ROWS = 512
  PPV_TUNE_ROW_SPLIT) = range(6)
 
 _lib = None
+_call = None     # the native extension, bound to the library's entry points when the library is loaded
 
 
 class PPVError(RuntimeError):
@@ -45,12 +49,13 @@ class PPVError(RuntimeError):
 
 def load_library() -> C.CDLL:
     """Load libppv_hip.so (built by paper_2504_09135_amd.build); raises if it is not there."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise FileNotFoundError(f"{LIB_PATH} is missing: run `python -m paper_2504_09135_amd.build` "
-                                "(or __graft_entry__.build()) first; there is no fallback path")
+    for path in (LIB_PATH, CALL_PATH):
+        if not os.path.exists(path):
+            raise FileNotFoundError(f"{path} is missing: run `python -m paper_2504_09135_amd.build` "
+                                    "(or __graft_entry__.build()) first; there is no fallback path")
     lib = C.CDLL(LIB_PATH)
     p, i32, i64 = C.c_void_p, C.c_int32, C.c_int64
     lib.ppv_status_string.restype = C.c_char_p
@@ -93,8 +98,17 @@ def load_library() -> C.CDLL:
     lib.ppv_tuning_set.argtypes = [i32, i32]
     lib.ppv_tuning_get.restype = C.c_int
     lib.ppv_tuning_get.argtypes = [i32, C.POINTER(i32)]
+    from . import _ppv_call
+    _ppv_call.bind({name: C.cast(getattr(lib, name), p).value for name in SYMBOLS})
+    _call = _ppv_call
     _lib = lib
     return lib
+
+
+def _native():
+    """The native extension, with the library loaded."""
+    load_library()
+    return _call
 
 
 def status_string(status: int) -> str:
@@ -106,24 +120,12 @@ def _check(status: int, what: str):
         raise PPVError(status, what)
 
 
-def _dev(t: Optional[torch.Tensor], dtype, what: str):
-    if t is None:
-        return None
-    if not (t.is_cuda and t.dtype == dtype and t.is_contiguous()):
-        raise TypeError(f"{what}: need a contiguous GPU tensor of {dtype}, got {t.dtype} on {t.device}")
-    return C.c_void_p(t.data_ptr())
-
-
-def _stream(stream) -> C.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
-
-
 class PPVIndex:
     """Owner of a ppv_index_t handle."""
 
     def __init__(self, handle: int):
         self._h = C.c_void_p(handle)
+        self._address = handle      # what the native calls read; None once the index is freed
         self.n_distinct, self.l_max, self.vocab, self.n_prefixes, self.device_bytes = ppv_index_info(self)
         self.n_words = (self.vocab + 31) // 32
 
@@ -135,6 +137,7 @@ class PPVIndex:
 
     def free(self):
         if self._h:
+            self._address = None
             load_library().ppv_free_index(self._h)
             self._h = None
 
@@ -197,34 +200,9 @@ def ppv_next_token_mask(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Ten
                         member: Optional[torch.Tensor] = None, stream=None) -> None:
     """prefixes int32 [B, stride], lens int32 [B] -> mask int32 [B, ceil(V/32)] (bit pattern of
     uint32 words), range_lo/range_hi int32 [B] (bit pattern of uint32), member uint8 [B]."""
-    B, stride = (int(prefixes.shape[0]), int(prefixes.shape[1])) if prefixes.dim() == 2 else (0, 0)
-    if prefixes.dim() != 2 or tuple(lens.shape) != (B,) or tuple(mask.shape) != (B, index.n_words):
-        raise ValueError("ppv_next_token_mask: shape mismatch")
-    for t, nm in ((range_lo, "range_lo"), (range_hi, "range_hi"), (member, "member")):
-        if t is not None and tuple(t.shape) != (B,):
-            raise ValueError(f"ppv_next_token_mask: {nm} must have shape [B]")
-    st = load_library().ppv_next_token_mask(
-        index.handle, _dev(prefixes, torch.int32, "prefixes"), stride, _dev(lens, torch.int32, "lens"), B,
-        _dev(mask, torch.int32, "mask"), _dev(range_lo, torch.int32, "range_lo"),
-        _dev(range_hi, torch.int32, "range_hi"), _dev(member, torch.uint8, "member"), _stream(stream))
-    _check(st, "ppv_next_token_mask")
-
-
-def _logits_args(logits: torch.Tensor):
-    if logits.dim() != 2 or not logits.is_cuda or logits.stride(1) != 1:
-        raise ValueError("logits: need a 2-D GPU tensor with unit stride along the vocabulary")
-    if logits.dtype == torch.float32:
-        dt = PPV_F32
-    elif logits.dtype == torch.bfloat16:
-        dt = PPV_BF16
-    else:
-        raise TypeError(f"logits: float32 or bfloat16, got {logits.dtype}")
-    # a single row: torch's stride of a size-1 dimension carries no meaning unless it covers the row (a row cut out
-    # of a padded buffer keeps the buffer's stride, which is what says that the padding is there)
-    row_stride = int(logits.stride(0))
-    if logits.shape[0] <= 1 and row_stride < int(logits.shape[1]):
-        row_stride = int(logits.shape[1])
-    return C.c_void_p(logits.data_ptr()), dt, row_stride
+    st = (_call or _native()).next_token_mask(index, prefixes, lens, mask, range_lo, range_hi, member, stream)
+    if st:
+        _check(st, "ppv_next_token_mask")
 
 
 def constrained_sample(logits: torch.Tensor, mask: torch.Tensor, uniforms: torch.Tensor, ids: torch.Tensor,
@@ -232,16 +210,9 @@ def constrained_sample(logits: torch.Tensor, mask: torch.Tensor, uniforms: torch
                        temperature: float = 1.0, _noalloc: bool = False) -> None:
     """logits [B, V] f32/bf16, mask int32 [B, ceil(V/32)], uniforms f32 [B] -> ids int32 [B],
     logZ_valid f32 [B], logZ_all f32 [B] (optional); P = softmax(logits / temperature)."""
-    ptr, dt, row_stride = _logits_args(logits)
-    B, V = int(logits.shape[0]), int(logits.shape[1])
-    if tuple(mask.shape) != (B, (V + 31) // 32) or tuple(uniforms.shape) != (B,) or tuple(ids.shape) != (B,) \
-            or tuple(logZ_valid.shape) != (B,) or (logZ_all is not None and tuple(logZ_all.shape) != (B,)):
-        raise ValueError("constrained_sample: shape mismatch")
-    fn = load_library().constrained_sample_noalloc if _noalloc else load_library().constrained_sample
-    st = fn(ptr, dt, row_stride, _dev(mask, torch.int32, "mask"), _dev(uniforms, torch.float32, "uniforms"), B, V,
-            _dev(ids, torch.int32, "ids"), _dev(logZ_valid, torch.float32, "logZ_valid"),
-            _dev(logZ_all, torch.float32, "logZ_all"), float(temperature), _stream(stream))
-    _check(st, "constrained_sample_noalloc" if _noalloc else "constrained_sample")
+    st = (_call or _native()).sample(logits, mask, uniforms, ids, logZ_valid, logZ_all, stream, temperature, _noalloc)
+    if st:
+        _check(st, "constrained_sample_noalloc" if _noalloc else "constrained_sample")
 
 
 def constrained_sample_noalloc(logits: torch.Tensor, mask: torch.Tensor, uniforms: torch.Tensor, ids: torch.Tensor,
@@ -255,29 +226,18 @@ def ppv_decode_begin(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor
                      active: torch.Tensor, logx: Optional[torch.Tensor] = None, stream=None) -> None:
     """Locate every row's current prefix once: writes state int32 [B, PPV_STATE_WORDS], active uint8 [B]
     and zeroes logx f32 [B]."""
-    B, stride = int(prefixes.shape[0]), int(prefixes.shape[1])
-    if tuple(lens.shape) != (B,) or tuple(state.shape) != (B, PPV_STATE_WORDS) or tuple(active.shape) != (B,) \
-            or (logx is not None and tuple(logx.shape) != (B,)):
-        raise ValueError("ppv_decode_begin: shape mismatch")
-    st = load_library().ppv_decode_begin(
-        index.handle, _dev(prefixes, torch.int32, "prefixes"), stride, _dev(lens, torch.int32, "lens"), B,
-        _dev(state, torch.int32, "state"), _dev(active, torch.uint8, "active"), _dev(logx, torch.float32, "logx"),
-        _stream(stream))
-    _check(st, "ppv_decode_begin")
+    st = (_call or _native()).decode_begin(index, prefixes, lens, state, active, logx, stream)
+    if st:
+        _check(st, "ppv_decode_begin")
 
 
 def ppv_decode_begin_empty(index: PPVIndex, lens: torch.Tensor, state: torch.Tensor, active: torch.Tensor,
                            logx: Optional[torch.Tensor] = None, stream=None) -> None:
     """SampleCandidate initialisation from the empty candidate for every row: lens int32 [B] (written 0),
     state int32 [B, PPV_STATE_WORDS], active uint8 [B], logx f32 [B] (optional) are written."""
-    B = int(lens.shape[0])
-    if tuple(lens.shape) != (B,) or tuple(state.shape) != (B, PPV_STATE_WORDS) or tuple(active.shape) != (B,) \
-            or (logx is not None and tuple(logx.shape) != (B,)):
-        raise ValueError("ppv_decode_begin_empty: shape mismatch")
-    st = load_library().ppv_decode_begin_empty(
-        index.handle, B, _dev(lens, torch.int32, "lens"), _dev(state, torch.int32, "state"),
-        _dev(active, torch.uint8, "active"), _dev(logx, torch.float32, "logx"), _stream(stream))
-    _check(st, "ppv_decode_begin_empty")
+    st = (_call or _native()).decode_begin_empty(index, lens, state, active, logx, stream)
+    if st:
+        _check(st, "ppv_decode_begin_empty")
 
 
 def ppv_decode_step(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor, active: torch.Tensor,
@@ -287,23 +247,10 @@ def ppv_decode_step(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor,
                     _first: bool = False) -> None:
     """One fused constrained decoding step, in place on prefixes / lens / active / logx (and on
     state int32 [B, PPV_STATE_WORDS] from ppv_decode_begin when given); P = softmax(logits / temperature)."""
-    ptr, dt, row_stride = _logits_args(logits)
-    B, stride = int(prefixes.shape[0]), int(prefixes.shape[1])
-    if int(logits.shape[0]) != B or int(logits.shape[1]) != index.vocab or tuple(lens.shape) != (B,) \
-            or tuple(active.shape) != (B,) or tuple(uniforms.shape) != (B,) \
-            or (state is not None and tuple(state.shape) != (B, PPV_STATE_WORDS)):
-        raise ValueError("ppv_decode_step: shape mismatch")
-    for t, nm in ((ids, "ids"), (logZ_valid, "logZ_valid"), (logx, "logx")):
-        if t is not None and tuple(t.shape) != (B,):
-            raise ValueError(f"ppv_decode_step: {nm} must have shape [B]")
-    fn = load_library().ppv_decode_first_step if _first else load_library().ppv_decode_step
-    st = fn(
-        index.handle, _dev(prefixes, torch.int32, "prefixes"), stride, _dev(lens, torch.int32, "lens"),
-        _dev(active, torch.uint8, "active"), _dev(state, torch.int32, "state"), ptr, dt, row_stride,
-        _dev(uniforms, torch.float32, "uniforms"), B, _dev(ids, torch.int32, "ids"),
-        _dev(logZ_valid, torch.float32, "logZ_valid"), _dev(logx, torch.float32, "logx"), float(temperature),
-        _stream(stream))
-    _check(st, "ppv_decode_first_step" if _first else "ppv_decode_step")
+    st = (_call or _native()).decode_step(index, prefixes, lens, active, logits, uniforms, ids, logZ_valid, logx, state,
+                                          stream, temperature, _first)
+    if st:
+        _check(st, "ppv_decode_first_step" if _first else "ppv_decode_step")
 
 
 def ppv_decode_first_step(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor, active: torch.Tensor,
@@ -311,8 +258,10 @@ def ppv_decode_first_step(index: PPVIndex, prefixes: torch.Tensor, lens: torch.T
                           logZ_valid: Optional[torch.Tensor] = None, logx: Optional[torch.Tensor] = None,
                           state: Optional[torch.Tensor] = None, stream=None, temperature: float = 1.0) -> None:
     """ppv_decode_begin_empty and the first ppv_decode_step in one launch (state is required)."""
-    ppv_decode_step(index, prefixes, lens, active, logits, uniforms, ids, logZ_valid, logx, state, stream, temperature,
-                    _first=True)
+    st = (_call or _native()).decode_step(index, prefixes, lens, active, logits, uniforms, ids, logZ_valid, logx, state,
+                                          stream, temperature, True)
+    if st:
+        _check(st, "ppv_decode_first_step")
 
 
 def ppv_decode_loop(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor, active: torch.Tensor,
@@ -321,28 +270,10 @@ def ppv_decode_loop(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor,
                     state: Optional[torch.Tensor] = None, stream=None, temperature: float = 1.0) -> None:
     """The whole decode loop in one launch: logits [n_steps, B, V] (f32/bf16), uniforms f32 [n_steps, B],
     ids int32 / logZ_valid f32 [n_steps, B] (optional); everything else as ppv_decode_step."""
-    if logits.dim() != 3 or not logits.is_cuda or logits.stride(2) != 1:
-        raise ValueError("logits: need a 3-D GPU tensor [n_steps, B, V] with unit stride along the vocabulary")
-    n_steps, B, V = (int(x) for x in logits.shape)
-    dt = {torch.float32: PPV_F32, torch.bfloat16: PPV_BF16}.get(logits.dtype)
-    if dt is None:
-        raise TypeError(f"logits: float32 or bfloat16, got {logits.dtype}")
-    stride = int(prefixes.shape[1])
-    if int(prefixes.shape[0]) != B or V != index.vocab or tuple(lens.shape) != (B,) or tuple(active.shape) != (B,) \
-            or tuple(uniforms.shape) != (n_steps, B) \
-            or (state is not None and tuple(state.shape) != (B, PPV_STATE_WORDS)) \
-            or (logx is not None and tuple(logx.shape) != (B,)):
-        raise ValueError("ppv_decode_loop: shape mismatch")
-    for t, nm in ((ids, "ids"), (logZ_valid, "logZ_valid")):
-        if t is not None and tuple(t.shape) != (n_steps, B):
-            raise ValueError(f"ppv_decode_loop: {nm} must have shape [n_steps, B]")
-    st = load_library().ppv_decode_loop(
-        index.handle, _dev(prefixes, torch.int32, "prefixes"), stride, _dev(lens, torch.int32, "lens"),
-        _dev(active, torch.uint8, "active"), _dev(state, torch.int32, "state"), C.c_void_p(logits.data_ptr()), dt,
-        int(logits.stride(1)), int(logits.stride(0)), _dev(uniforms, torch.float32, "uniforms"), n_steps, B,
-        _dev(ids, torch.int32, "ids"), _dev(logZ_valid, torch.float32, "logZ_valid"),
-        _dev(logx, torch.float32, "logx"), float(temperature), _stream(stream))
-    _check(st, "ppv_decode_loop")
+    st = (_call or _native()).decode_loop(index, prefixes, lens, active, logits, uniforms, ids, logZ_valid, logx, state,
+                                          stream, temperature)
+    if st:
+        _check(st, "ppv_decode_loop")
 
 
 def ppv_topm_mask(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor, logits: torch.Tensor, M: int,
@@ -350,19 +281,9 @@ def ppv_topm_mask(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor, l
                   stream=None) -> None:
     """Algorithm 2 with M candidates: prefixes int32 [B, stride], lens int32 [B], logits [B, V] f32/bf16 ->
     mask int32 [B, ceil(V/32)], top_ids int32 [B, M] (optional), mask_V uint8 [B, M] (optional)."""
-    ptr, dt, row_stride = _logits_args(logits)
-    B, stride = (int(prefixes.shape[0]), int(prefixes.shape[1])) if prefixes.dim() == 2 else (0, 0)
-    if prefixes.dim() != 2 or tuple(lens.shape) != (B,) or tuple(mask.shape) != (B, index.n_words) \
-            or tuple(logits.shape) != (B, index.vocab):
-        raise ValueError("ppv_topm_mask: shape mismatch")
-    for t, nm in ((top_ids, "top_ids"), (mask_V, "mask_V")):
-        if t is not None and tuple(t.shape) != (B, M):
-            raise ValueError(f"ppv_topm_mask: {nm} must have shape [B, M]")
-    st = load_library().ppv_topm_mask(
-        index.handle, _dev(prefixes, torch.int32, "prefixes"), stride, _dev(lens, torch.int32, "lens"), ptr, dt,
-        row_stride, int(M), B, _dev(top_ids, torch.int32, "top_ids"), _dev(mask_V, torch.uint8, "mask_V"),
-        _dev(mask, torch.int32, "mask"), _stream(stream))
-    _check(st, "ppv_topm_mask")
+    st = (_call or _native()).topm_mask(index, prefixes, lens, logits, M, mask, top_ids, mask_V, stream)
+    if st:
+        _check(st, "ppv_topm_mask")
 
 
 def ppv_disc_select(logx: torch.Tensor, K: int, accept_u: torch.Tensor, resample_u: torch.Tensor,
@@ -370,15 +291,10 @@ def ppv_disc_select(logx: torch.Tensor, K: int, accept_u: torch.Tensor, resample
                     accepted: Optional[torch.Tensor] = None, reuse_rejected: bool = False, stream=None) -> None:
     """DISC accept/reject rounds + importance-resampling fallback: logx f32 [n_candidates, Q], accept_u f32 [K, Q],
     resample_u f32 [Q] -> chosen int32 [Q], n_draws int32 [Q], accepted uint8 [Q]."""
-    n_cand, Q = int(logx.shape[0]), int(logx.shape[1])
-    if tuple(accept_u.shape) != (K, Q) or tuple(resample_u.shape) != (Q,) or tuple(chosen.shape) != (Q,):
-        raise ValueError("ppv_disc_select: shape mismatch")
-    st = load_library().ppv_disc_select(
-        _dev(logx, torch.float32, "logx"), n_cand, int(K), Q, _dev(accept_u, torch.float32, "accept_u"),
-        _dev(resample_u, torch.float32, "resample_u"), 1 if reuse_rejected else 0,
-        _dev(chosen, torch.int32, "chosen"), _dev(n_draws, torch.int32, "n_draws"),
-        _dev(accepted, torch.uint8, "accepted"), _stream(stream))
-    _check(st, "ppv_disc_select")
+    st = (_call or _native()).disc_select(logx, K, accept_u, resample_u, chosen, n_draws, accepted, reuse_rejected,
+                                          stream)
+    if st:
+        _check(st, "ppv_disc_select")
 
 
 def ppv_tuning_set(knob: int, value: int) -> None:
@@ -397,14 +313,6 @@ def ppv_sample_next(index: PPVIndex, prefixes: torch.Tensor, lens: torch.Tensor,
                     temperature: float = 1.0) -> None:
     """Mask + sample fused, nothing of the caller's rows changed: prefixes int32 [B, stride], lens int32 [B],
     logits [B, V] f32/bf16, uniforms f32 [B] -> ids int32 [B], logZ_valid f32 [B] (optional)."""
-    ptr, dt, row_stride = _logits_args(logits)
-    B, stride = (int(prefixes.shape[0]), int(prefixes.shape[1])) if prefixes.dim() == 2 else (0, 0)
-    if prefixes.dim() != 2 or tuple(lens.shape) != (B,) or tuple(logits.shape) != (B, index.vocab) \
-            or tuple(uniforms.shape) != (B,) or tuple(ids.shape) != (B,) \
-            or (logZ_valid is not None and tuple(logZ_valid.shape) != (B,)):
-        raise ValueError("ppv_sample_next: shape mismatch")
-    st = load_library().ppv_sample_next(
-        index.handle, _dev(prefixes, torch.int32, "prefixes"), stride, _dev(lens, torch.int32, "lens"), B, ptr, dt,
-        row_stride, _dev(uniforms, torch.float32, "uniforms"), _dev(ids, torch.int32, "ids"),
-        _dev(logZ_valid, torch.float32, "logZ_valid"), float(temperature), _stream(stream))
-    _check(st, "ppv_sample_next")
+    st = (_call or _native()).sample_next(index, prefixes, lens, logits, uniforms, ids, logZ_valid, stream, temperature)
+    if st:
+        _check(st, "ppv_sample_next")

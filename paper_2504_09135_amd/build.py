@@ -1,15 +1,17 @@
-"""Builds libppv_hip.so (the C-ABI library) for gfx950 with hipcc, in-tree."""
+"""Builds libppv_hip.so (the C-ABI library) for gfx950 with hipcc, and _ppv_call.so (the Python side's native calls), in-tree."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libppv_hip.so")
+CALL = os.path.join(PKG, "_ppv_call.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -32,7 +34,25 @@ def build(verbose: bool = True) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_call(verbose)
     return LIB
+
+
+def build_call(verbose: bool = True) -> str:
+    """The CPython extension of binding.py: host code only, against torch's headers and libraries."""
+    import torch
+    at = os.path.dirname(torch.__file__)
+    include = [os.path.join(ROOT, "include"), os.path.join(at, "include"),
+               os.path.join(at, "include", "torch", "csrc", "api", "include"),
+               os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_path("include")]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", include[0], *[x for d in include[1:] for x in ("-isystem", d)], os.path.join(CSRC, "ppv_call.cpp"),
+           "-o", CALL, "-L", os.path.join(at, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return CALL
 
 
 if __name__ == "__main__":
