@@ -23,6 +23,9 @@ template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline u
 template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline float dpp0(float x) {
     return __int_as_float(dpp0<CTRL, ROW_MASK, BANK_MASK>(__float_as_int(x)));
 }
+template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline uint64_t dpp0(uint64_t x) {
+    return ((uint64_t)dpp0<CTRL, ROW_MASK, BANK_MASK>((uint32_t)(x >> 32)) << 32) | dpp0<CTRL, ROW_MASK, BANK_MASK>((uint32_t)x);
+}
 template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline double dpp0(double x) {
     return __hiloint2double(dpp0<CTRL, ROW_MASK, BANK_MASK>(__double2hiint(x)),
                             dpp0<CTRL, ROW_MASK, BANK_MASK>(__double2loint(x)));
@@ -35,6 +38,9 @@ template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline f
 __device__ inline float last_lane(float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63)); }
 __device__ inline int last_lane(int x) { return __builtin_amdgcn_readlane(x, 63); }
 __device__ inline uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+__device__ inline uint64_t last_lane(uint64_t x) {
+    return ((uint64_t)last_lane((uint32_t)(x >> 32)) << 32) | last_lane((uint32_t)x);
+}
 __device__ inline double last_lane(double x) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
                             __builtin_amdgcn_readlane(__double2loint(x), 63));

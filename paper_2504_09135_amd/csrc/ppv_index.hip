@@ -1,20 +1,23 @@
 // Index construction on the device (Algorithm 2, "Prepare"; Section 3.2 "Array Preparation"),
-// plus sizes, export and release.
+// plus sizes, export, files and release.
 //
-// The host hands over S as CSR; everything else runs in kernels:
-//   1. validate (no empty sequence, tokens inside [0, V));
-//   2. sort the rows lexicographically -- token order = integer order, left to right, a sequence
-//      that ends sorts before its extensions -- by a least-significant-digit radix sort over the
-//      columns from the last to the first (key of a row at column d: token + 1, or 0 past its end),
-//      8 bits per pass, each pass a stable counting sort (histogram / scan / scatter);
-//   3. longest common prefix of neighbouring sorted rows; duplicates dropped (S is a set);
-//   4. the per-depth arrays: row r opens a new prefix of length d+1 iff it is longer than d and
-//      shares at most d tokens with the row before it.  One exclusive scan over the depth-major
-//      flags (depth, row) numbers all prefixes in breadth-first order and, because every depth is
-//      sorted, gives each prefix its first child for free;
-//   5. rank ranges: lo = the opening row; hi bottom-up, deepest level first (a prefix ends where
-//      its last child ends, or one row after it opens if it has no child);
-//   6. images and per-word child counts of the heavy prefixes.
+// The host hands over S as CSR (packed and checked on the way to the device, ppv_pool.hip); the rest runs in kernels:
+//   1. sort the rows lexicographically -- token order = integer order, left to right, a sequence that ends sorts
+//      before its extensions.  A row's first tokens, as many as fit, make a 64-bit key (token + 1, or 0 past the
+//      row's end, most significant first); the keys are radix-sorted.  Rows with equal keys are neighbours then: groups
+//      of up to about a thousand of them are ordered by counting, for each row, the rows of its group that sort before it;
+//      larger groups take another round on their rows' next tokens, together with the group's number;
+//   2. longest common prefix of neighbouring sorted rows; duplicates dropped (S is a set);
+//   3. number the prefixes breadth-first.  Row r opens a new prefix of length d+1 iff it is longer than d and shares
+//      at most d tokens with the row before it.  One wavefront takes 64 rows, a lane each: a ballot per depth counts
+//      what the rows open there, one exclusive scan over (depth, 64 rows) gives every count's first number, and the
+//      ballots again give each row its place;
+//   4. the same wavefronts write the prefixes' entries, children, rank ranges and look-up entries;
+//   5. images and per-word child counts of the heavy prefixes.
+//
+// What bounds it: for 1M sequences of 18M tokens the arrays are 0.5 GB (0.1 ms at 5 TB/s).  The radix sort over all
+// columns that stood here before made 64 passes of five launches over the rows (3.8 ms) and one look-up entry per
+// prefix, 17M atomics on a 270 MB table (1.5 ms); see step 4 for which prefixes need an entry.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -41,373 +44,13 @@ extern "C" const char *ppv_status_string(ppv_status s) {
 namespace {
 
 constexpr int BT = 256;            // threads per workgroup of the build kernels
+constexpr int BW = BT / WAVE;      // wavefronts
 constexpr int SCAN_ITEMS = 8;      // consecutive items per thread in the scans
 constexpr int SCAN_CHUNK = BT * SCAN_ITEMS;
-constexpr int SORT_TILES = 16;     // tiles of BT rows per workgroup in a radix pass
-constexpr int SORT_CHUNK = BT * SORT_TILES;
+constexpr int SORT_ITEMS = 8;      // keys per thread in a radix pass
+constexpr int SORT_CHUNK = BT * SORT_ITEMS;
 constexpr int RADIX = 256;
 static_assert(RADIX == BT, "one thread per digit in the radix kernels");
-
-// ------------------------------------------------------------------------------------------
-// Exclusive scan of f(0..n-1) (uint32 sums; the callers keep totals below 2^32).
-// Three launches: per-chunk sums, scan of the chunk sums by one workgroup, per-chunk scan + base.
-__device__ inline uint32_t block_exclusive_scan(uint32_t x, uint32_t *wave_tot, uint32_t *block_total) {
-    // exclusive prefix of x over the workgroup's BT threads in thread order
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    const uint32_t incl = wave_incl_scan(x);
-    if (lane == WAVE - 1) wave_tot[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-    for (int w = 0; w < BT / WAVE; w++) {
-        const uint32_t t = wave_tot[w];
-        if (w < wave) before += t;
-        total += t;
-    }
-    __syncthreads();
-    *block_total = total;
-    return before + incl - x;
-}
-
-template <typename F> __global__ __launch_bounds__(BT) void scan_chunk_sums(uint64_t n, F f, uint32_t *__restrict__ sums) {
-    __shared__ uint32_t wave_tot[BT / WAVE];
-    const uint64_t base = (uint64_t)blockIdx.x * SCAN_CHUNK + (uint64_t)threadIdx.x * SCAN_ITEMS;
-    uint32_t s = 0;
-    for (int k = 0; k < SCAN_ITEMS; k++)
-        if (base + k < n) s += f(base + k);
-    s = wave_sum(s);
-    if ((threadIdx.x & (WAVE - 1)) == 0) wave_tot[threadIdx.x / WAVE] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t t = 0;
-        for (int w = 0; w < BT / WAVE; w++) t += wave_tot[w];
-        sums[blockIdx.x] = t;
-    }
-}
-
-// in place exclusive scan of m values by ONE workgroup; the grand total goes to *total
-__global__ __launch_bounds__(BT) void scan_of_sums(uint32_t *__restrict__ sums, uint64_t m, uint32_t *__restrict__ total) {
-    __shared__ uint32_t wave_tot[BT / WAVE];
-    uint32_t carry = 0;
-    for (uint64_t b0 = 0; b0 < m; b0 += SCAN_CHUNK) {
-        const uint64_t base = b0 + (uint64_t)threadIdx.x * SCAN_ITEMS;
-        uint32_t v[SCAN_ITEMS], s = 0;
-        for (int k = 0; k < SCAN_ITEMS; k++) {
-            v[k] = (base + k < m) ? sums[base + k] : 0u;
-            s += v[k];
-        }
-        uint32_t tot;
-        uint32_t ex = carry + block_exclusive_scan(s, wave_tot, &tot);
-        for (int k = 0; k < SCAN_ITEMS; k++) {
-            if (base + k < m) sums[base + k] = ex;
-            ex += v[k];
-        }
-        carry += tot;
-    }
-    if (threadIdx.x == 0) *total = carry;
-}
-
-template <typename F>
-__global__ __launch_bounds__(BT) void scan_apply(uint64_t n, F f, const uint32_t *__restrict__ sums, uint32_t *out) {
-    __shared__ uint32_t wave_tot[BT / WAVE];
-    const uint64_t base = (uint64_t)blockIdx.x * SCAN_CHUNK + (uint64_t)threadIdx.x * SCAN_ITEMS;
-    uint32_t v[SCAN_ITEMS], s = 0;
-    for (int k = 0; k < SCAN_ITEMS; k++) {
-        v[k] = (base + k < n) ? f(base + k) : 0u;
-        s += v[k];
-    }
-    uint32_t tot;
-    uint32_t ex = sums[blockIdx.x] + block_exclusive_scan(s, wave_tot, &tot);
-    for (int k = 0; k < SCAN_ITEMS; k++) {
-        if (base + k < n) out[base + k] = ex;
-        ex += v[k];
-    }
-}
-
-// out[i] = sum of f(0..i-1) for i in [0, n); *d_total = sum of all.  sums: scratch of ceil(n / SCAN_CHUNK) words.
-// f may read `out` only at the index it is asked for (the in-place scan of the radix histogram does).
-template <typename F>
-ppv_status exclusive_scan(uint64_t n, F f, uint32_t *out, uint32_t *sums, uint32_t *d_total, hipStream_t st) {
-    const uint64_t nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    if (nb == 0) {
-        hipLaunchKernelGGL(scan_of_sums, dim3(1), dim3(BT), 0, st, sums, (uint64_t)0, d_total);  // total = 0
-        PPV_HIP_TRY(hipGetLastError());
-        return PPV_OK;
-    }
-    hipLaunchKernelGGL(scan_chunk_sums<F>, dim3((unsigned)nb), dim3(BT), 0, st, n, f, sums);
-    hipLaunchKernelGGL(scan_of_sums, dim3(1), dim3(BT), 0, st, sums, nb, d_total);
-    hipLaunchKernelGGL(scan_apply<F>, dim3((unsigned)nb), dim3(BT), 0, st, n, f, (const uint32_t *)sums, out);
-    PPV_HIP_TRY(hipGetLastError());
-    return PPV_OK;
-}
-
-// ------------------------------------------------------------------------------------------
-// 1. validation and the longest row
-__global__ __launch_bounds__(BT) void check_rows(const int64_t *__restrict__ off, int64_t n, int32_t *__restrict__ err,
-                                                 int32_t *__restrict__ l_max) {
-    const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
-    int32_t len = 0;
-    if (i < n) {
-        const int64_t l = off[i + 1] - off[i];
-        if (l <= 0 || l > 0x7FFFFFFF) atomicOr(err, 1);
-        else len = (int32_t)l;
-    }
-    for (int o = WAVE / 2; o > 0; o >>= 1) len = max(len, __shfl_xor(len, o, WAVE));
-    if ((threadIdx.x & (WAVE - 1)) == 0 && len > 0) atomicMax(l_max, len);   // one atomic per wave
-}
-__global__ __launch_bounds__(BT) void check_tokens(const int32_t *__restrict__ tok, int64_t total, int32_t vocab,
-                                                   int32_t *__restrict__ err) {
-    const int64_t i = (int64_t)blockIdx.x * BT + threadIdx.x;
-    if (i < total && (tok[i] < 0 || tok[i] >= vocab)) atomicOr(err, 2);
-}
-__global__ __launch_bounds__(BT) void iota_rows(uint32_t *__restrict__ perm, uint32_t n) {
-    const uint32_t i = blockIdx.x * BT + threadIdx.x;
-    if (i < n) perm[i] = i;
-}
-
-// ------------------------------------------------------------------------------------------
-// 2. one stable counting-sort pass on 8 bits of the column key
-__device__ inline uint32_t column_key(const int32_t *__restrict__ tok, const int64_t *__restrict__ off, uint32_t row,
-                                      int col) {
-    const int64_t a = off[row], b = off[row + 1];
-    return (col < b - a) ? (uint32_t)tok[a + col] + 1u : 0u;  // 0: the row has ended; sorts first
-}
-
-__global__ __launch_bounds__(BT) void radix_histogram(const int32_t *__restrict__ tok, const int64_t *__restrict__ off,
-                                                      const uint32_t *__restrict__ perm, uint32_t n, int col, int shift,
-                                                      uint8_t *__restrict__ digits, uint32_t *__restrict__ hist,
-                                                      uint32_t n_blocks) {
-    __shared__ uint32_t h[RADIX];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const uint32_t start = blockIdx.x * SORT_CHUNK;
-    for (int t = 0; t < SORT_TILES; t++) {
-        const uint32_t i = start + t * BT + threadIdx.x;
-        if (i < n) {
-            const uint32_t d = (column_key(tok, off, perm[i], col) >> shift) & (RADIX - 1);
-            digits[i] = (uint8_t)d;
-            atomicAdd(&h[d], 1u);
-        }
-    }
-    __syncthreads();
-    hist[(size_t)threadIdx.x * n_blocks + blockIdx.x] = h[threadIdx.x];  // digit-major for the scan
-}
-
-__global__ __launch_bounds__(BT) void radix_scatter(const uint32_t *__restrict__ perm_in, uint32_t n,
-                                                    const uint8_t *__restrict__ digits,
-                                                    const uint32_t *__restrict__ hist_scanned, uint32_t n_blocks,
-                                                    uint32_t *__restrict__ perm_out) {
-    __shared__ uint32_t base[RADIX];               // next free slot per digit for this workgroup
-    __shared__ uint32_t cnt[BT / WAVE][RADIX];     // rows per digit in the current tile, per wave
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    base[threadIdx.x] = hist_scanned[(size_t)threadIdx.x * n_blocks + blockIdx.x];
-    const uint32_t start = blockIdx.x * SORT_CHUNK;
-    for (int t = 0; t < SORT_TILES; t++) {
-        for (int w = 0; w < BT / WAVE; w++) cnt[w][threadIdx.x] = 0;
-        __syncthreads();
-        const uint32_t i = start + t * BT + threadIdx.x;
-        const bool valid = i < n;
-        const uint32_t d = valid ? digits[i] : 0u;
-        // lanes of this wave that hold the same digit
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < 8; b++) {
-            const uint64_t bal = __ballot(valid && ((d >> b) & 1u));
-            peers &= ((d >> b) & 1u) ? bal : ~bal;
-        }
-        const uint32_t rank_in_wave = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
-        if (valid && rank_in_wave == 0) cnt[wave][d] = (uint32_t)__popcll(peers);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = base[d] + rank_in_wave;
-            for (int w = 0; w < wave; w++) pos += cnt[w][d];
-            perm_out[pos] = perm_in[i];            // stable: thread order within the tile is kept
-        }
-        __syncthreads();
-        uint32_t add = 0;
-        for (int w = 0; w < BT / WAVE; w++) add += cnt[w][threadIdx.x];
-        base[threadIdx.x] += add;
-        __syncthreads();
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// 3. common prefix with the previous sorted row; duplicates
-__global__ __launch_bounds__(BT) void neighbour_lcp(const int32_t *__restrict__ tok, const int64_t *__restrict__ off,
-                                                    const uint32_t *__restrict__ perm, uint32_t n,
-                                                    int32_t *__restrict__ lcp, uint8_t *__restrict__ keep) {
-    const uint32_t i = blockIdx.x * BT + threadIdx.x;
-    if (i >= n) return;
-    if (i == 0) { lcp[0] = 0; keep[0] = 1; return; }
-    const uint32_t r = perm[i], q = perm[i - 1];
-    const int32_t *a = tok + off[r], *b = tok + off[q];
-    const int32_t la = (int32_t)(off[r + 1] - off[r]), lb = (int32_t)(off[q + 1] - off[q]);
-    const int32_t m = la < lb ? la : lb;
-    int32_t c = 0;
-    while (c < m && a[c] == b[c]) c++;
-    lcp[i] = c;
-    keep[i] = (c == la && c == lb) ? 0 : 1;
-}
-struct HistValue {
-    const uint32_t *h;
-    __device__ uint32_t operator()(uint64_t i) const { return h[i]; }
-};
-struct KeepFlag {
-    const uint8_t *keep;
-    __device__ uint32_t operator()(uint64_t i) const { return keep[i]; }
-};
-struct KeptLen {  // length of sorted row i if it is kept, else 0
-    const uint8_t *keep;
-    const uint32_t *perm;
-    const int64_t *off;
-    __device__ uint32_t operator()(uint64_t i) const {
-        if (!keep[i]) return 0u;
-        const uint32_t r = perm[i];
-        return (uint32_t)(off[r + 1] - off[r]);
-    }
-};
-// kept sorted row i becomes row dst[i] of the index: its tokens, offset, common prefix
-__global__ __launch_bounds__(BT) void compact_rows(const int32_t *__restrict__ tok, const int64_t *__restrict__ off,
-                                                   const uint32_t *__restrict__ perm, uint32_t n,
-                                                   const uint8_t *__restrict__ keep, const uint32_t *__restrict__ dst,
-                                                   const uint32_t *__restrict__ tok_at, const int32_t *__restrict__ lcp,
-                                                   int32_t *__restrict__ x_tok, int64_t *__restrict__ x_off,
-                                                   int32_t *__restrict__ row_lcp, uint32_t n_rows, uint32_t n_tok) {
-    const uint32_t i = blockIdx.x * BT + threadIdx.x;
-    if (i == 0) x_off[n_rows] = n_tok;
-    if (i >= n || !keep[i]) return;
-    const uint32_t r = perm[i], d = dst[i], at = tok_at[i];
-    const int64_t a = off[r];
-    const int32_t len = (int32_t)(off[r + 1] - a);
-    x_off[d] = at;
-    row_lcp[d] = lcp[i];
-    for (int32_t k = 0; k < len; k++) x_tok[at + k] = tok[a + k];
-}
-
-// ------------------------------------------------------------------------------------------
-// 4. per-depth arrays.  Flattened depth-major index k = d * N + r.
-struct OpensPrefix {  // 1 iff row r opens a new prefix of length d+1
-    const int64_t *x_off;
-    const int32_t *row_lcp;
-    uint64_t n_rows;
-    __device__ uint32_t operator()(uint64_t k) const {
-        const uint64_t d = k / n_rows, r = k - d * n_rows;
-        const int64_t len = x_off[r + 1] - x_off[r];
-        return (len > (int64_t)d && row_lcp[r] <= (int32_t)d) ? 1u : 0u;
-    }
-};
-// pos[k] = prefixes numbered before (d, r); a prefix's number + 1 is its entry (entry 0 = the empty prefix)
-__global__ __launch_bounds__(BT) void fill_nodes(const int32_t *__restrict__ x_tok, const int64_t *__restrict__ x_off,
-                                                 const int32_t *__restrict__ row_lcp, const uint32_t *__restrict__ pos,
-                                                 uint64_t n_rows, int32_t l_max, uint32_t n_nodes,
-                                                 NodeEnt *__restrict__ ent, uint32_t *__restrict__ node_lo) {
-    const uint64_t k = (uint64_t)blockIdx.x * BT + threadIdx.x;
-    if (k == 0) {  // the empty prefix and the closing sentinel
-        ent[0].tok = 0u;
-        ent[0].child = 1u;
-        node_lo[0] = 0u;
-        ent[n_nodes].tok = PPV_NODE_TOKEN;
-        ent[n_nodes].child = n_nodes;
-    }
-    if (k >= n_rows * (uint64_t)l_max) return;
-    const uint64_t d = k / n_rows, r = k - d * n_rows;
-    const int64_t a = x_off[r];
-    const int64_t len = x_off[r + 1] - a;
-    if (!(len > (int64_t)d && row_lcp[r] <= (int32_t)d)) return;
-    const uint32_t g = 1u + pos[k];
-    uint32_t t = (uint32_t)x_tok[a + d];
-    if (len == (int64_t)d + 1) t |= PPV_NODE_TERMINAL;  // the opening row is the prefix itself
-    // first child: the first prefix of length d+2 at or after this row (this row itself if it goes on,
-    // else the next row); depth-major numbering makes that a plain look-up of the scan
-    uint32_t child = n_nodes;
-    if (d + 1 < (uint64_t)l_max) {
-        const uint64_t first = (len > (int64_t)d + 1) ? r : r + 1;   // first == n_rows: start of the next depth
-        child = 1u + pos[(d + 1) * n_rows + first];
-    }
-    ent[g].tok = t;
-    ent[g].child = child;
-    node_lo[g] = (uint32_t)r;
-}
-
-// 5. hi of the entries [g0, g1) of one depth, deeper levels already done
-__global__ __launch_bounds__(BT) void fill_hi(const NodeEnt *__restrict__ ent, const uint32_t *__restrict__ node_lo,
-                                              uint32_t g0, uint32_t g1, uint32_t *__restrict__ node_hi) {
-    const uint32_t g = g0 + blockIdx.x * BT + threadIdx.x;
-    if (g >= g1) return;
-    const uint32_t cb = ent[g].child, ce = ent[g + 1].child;
-    node_hi[g] = (ce > cb) ? node_hi[ce - 1] : node_lo[g] + 1u;
-}
-
-// 6. heavy prefixes
-struct IsHeavy {
-    const NodeEnt *ent;
-    uint32_t heavy_min;
-    __device__ uint32_t operator()(uint64_t g) const { return (ent[g + 1].child - ent[g].child > heavy_min) ? 1u : 0u; }
-};
-__global__ __launch_bounds__(BT) void mark_heavy(NodeEnt *__restrict__ ent, uint32_t n_nodes, uint32_t heavy_min,
-                                                 const uint32_t *__restrict__ slot_of, uint32_t heavy_limit,
-                                                 uint32_t *__restrict__ heavy_slot, uint32_t *__restrict__ heavy_node) {
-    const uint32_t g = blockIdx.x * BT + threadIdx.x;
-    if (g >= n_nodes) return;
-    const bool heavy = ent[g + 1].child - ent[g].child > heavy_min;
-    if (g < heavy_limit) heavy_slot[g] = heavy ? slot_of[g] : PPV_NO_SLOT;
-    if (heavy) {
-        heavy_node[slot_of[g]] = g;
-        atomicOr(&ent[g].tok, PPV_NODE_HEAVY);
-    }
-}
-// one workgroup per heavy prefix: OR its children into the image, then count children before each word
-__global__ __launch_bounds__(BT) void fill_heavy(const NodeEnt *__restrict__ ent, const uint32_t *__restrict__ heavy_node,
-                                                 int n_words, uint32_t *__restrict__ bits, uint32_t *__restrict__ rank) {
-    __shared__ uint32_t wave_tot[BT / WAVE];
-    const uint32_t g = heavy_node[blockIdx.x];
-    uint32_t *b = bits + (size_t)blockIdx.x * (size_t)n_words;
-    uint32_t *rk = rank + (size_t)blockIdx.x * (size_t)n_words;
-    for (uint32_t c = ent[g].child + threadIdx.x; c < ent[g + 1].child; c += BT) {
-        const uint32_t v = ent[c].tok & PPV_NODE_TOKEN;
-        atomicOr(&b[v >> 5], 1u << (v & 31u));   // the image was zeroed before the launch
-    }
-    __threadfence();
-    __syncthreads();
-    uint32_t carry = 0;
-    for (int w0 = 0; w0 < n_words; w0 += BT) {
-        const int w = w0 + threadIdx.x;
-        const uint32_t c = (w < n_words) ? (uint32_t)__popc(__builtin_nontemporal_load(&b[w])) : 0u;
-        uint32_t tot;
-        const uint32_t ex = carry + block_exclusive_scan(c, wave_tot, &tot);
-        if (w < n_words) rk[w] = ex;
-        carry += tot;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-struct DeviceBuffers {  // temporaries of the build, all released at the end
-    void *p[24];
-    int n = 0;
-    ~DeviceBuffers() {
-        for (int i = 0; i < n; i++) (void)hipFree(p[i]);
-    }
-    template <typename T> ppv_status alloc(T **out, size_t count) {
-        *out = nullptr;
-        if (n >= 24) return PPV_EDEVICE;
-        hipError_t e = hipMalloc((void **)out, (count ? count : 1) * sizeof(T));
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return e == hipErrorOutOfMemory ? PPV_ENOMEM : PPV_EDEVICE;
-        }
-        p[n++] = *out;
-        return PPV_OK;
-    }
-};
-
-template <typename T> ppv_status keep_alloc(T **out, size_t count, int64_t *bytes) {
-    *out = nullptr;
-    hipError_t e = hipMalloc((void **)out, (count ? count : 1) * sizeof(T));
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return e == hipErrorOutOfMemory ? PPV_ENOMEM : PPV_EDEVICE;
-    }
-    *bytes += (int64_t)((count ? count : 1) * sizeof(T));
-    return PPV_OK;
-}
 
 #define TRY(x)                          \
     do {                                \
@@ -417,159 +60,898 @@ template <typename T> ppv_status keep_alloc(T **out, size_t count, int64_t *byte
 
 inline unsigned blocks_for(uint64_t n) { return (unsigned)((n + BT - 1) / BT); }
 
-// 6. Images and per-word child counts of the heavy prefixes, from the finished entries (G of them plus the
-// sentinel).  Sets the heavy part of the index and of its view.
-ppv_status finish_heavy(ppv_index *ix, uint32_t G, int32_t vocab, hipStream_t st) {
-    DeviceBuffers tmp;
+// ------------------------------------------------------------------------------------------
+// Exclusive scan of f(0..n-1) (sums that the callers keep inside V).
+// Three launches: per-chunk sums, scan of the chunk sums by one workgroup, per-chunk scan + base.
+template <typename V> __device__ inline V block_exclusive_scan(V x, V *wave_tot, V *block_total) {
+    // exclusive prefix of x over the workgroup's BT threads in thread order
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    const V incl = wave_incl_scan(x);
+    if (lane == WAVE - 1) wave_tot[wave] = incl;
+    __syncthreads();
+    V before = 0, total = 0;
+    for (int w = 0; w < BW; w++) {
+        const V t = wave_tot[w];
+        if (w < wave) before += t;
+        total += t;
+    }
+    __syncthreads();
+    *block_total = total;
+    return before + incl - x;
+}
+
+template <typename V, typename F> __global__ __launch_bounds__(BT) void scan_chunk_sums(uint64_t n, F f, V *__restrict__ sums) {
+    __shared__ V wave_tot[BW];
+    const uint64_t base = (uint64_t)blockIdx.x * SCAN_CHUNK + (uint64_t)threadIdx.x * SCAN_ITEMS;
+    V s = 0;
+    for (int k = 0; k < SCAN_ITEMS; k++)
+        if (base + k < n) s += f(base + k);
+    s = wave_sum(s);
+    if ((threadIdx.x & (WAVE - 1)) == 0) wave_tot[threadIdx.x / WAVE] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        V t = 0;
+        for (int w = 0; w < BW; w++) t += wave_tot[w];
+        sums[blockIdx.x] = t;
+    }
+}
+
+// in place exclusive scan of m values by ONE workgroup; the grand total goes to *total
+template <typename V> __global__ __launch_bounds__(BT) void scan_of_sums(V *__restrict__ sums, uint64_t m, V *__restrict__ total) {
+    __shared__ V wave_tot[BW];
+    V carry = 0;
+    for (uint64_t b0 = 0; b0 < m; b0 += SCAN_CHUNK) {
+        const uint64_t base = b0 + (uint64_t)threadIdx.x * SCAN_ITEMS;
+        V v[SCAN_ITEMS], s = 0;
+        for (int k = 0; k < SCAN_ITEMS; k++) {
+            v[k] = (base + k < m) ? sums[base + k] : (V)0;
+            s += v[k];
+        }
+        V tot;
+        V ex = carry + block_exclusive_scan(s, wave_tot, &tot);
+        for (int k = 0; k < SCAN_ITEMS; k++) {
+            if (base + k < m) sums[base + k] = ex;
+            ex += v[k];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) *total = carry;
+}
+
+template <typename V, typename F>
+__global__ __launch_bounds__(BT) void scan_apply(uint64_t n, F f, const V *__restrict__ sums, V *out) {
+    __shared__ V wave_tot[BW];
+    const uint64_t base = (uint64_t)blockIdx.x * SCAN_CHUNK + (uint64_t)threadIdx.x * SCAN_ITEMS;
+    V v[SCAN_ITEMS], s = 0;
+    for (int k = 0; k < SCAN_ITEMS; k++) {
+        v[k] = (base + k < n) ? f(base + k) : (V)0;
+        s += v[k];
+    }
+    V tot;
+    V ex = sums[blockIdx.x] + block_exclusive_scan(s, wave_tot, &tot);
+    for (int k = 0; k < SCAN_ITEMS; k++) {
+        if (base + k < n) out[base + k] = ex;
+        ex += v[k];
+    }
+}
+
+// out[i] = sum of f(0..i-1) for i in [0, n); *d_total = sum of all.  sums: scratch of scan_words(n) values.
+// f may read `out` only at the index it is asked for (a scan in place).
+inline size_t scan_words(uint64_t n) { return (size_t)((n + SCAN_CHUNK - 1) / SCAN_CHUNK + 1); }
+template <typename V, typename F>
+ppv_status exclusive_scan(uint64_t n, F f, V *out, V *sums, V *d_total, hipStream_t st) {
+    const uint64_t nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    if (nb > 0) hipLaunchKernelGGL((scan_chunk_sums<V, F>), dim3((unsigned)nb), dim3(BT), 0, st, n, f, sums);
+    hipLaunchKernelGGL(scan_of_sums<V>, dim3(1), dim3(BT), 0, st, sums, nb, d_total);
+    if (nb > 0) hipLaunchKernelGGL((scan_apply<V, F>), dim3((unsigned)nb), dim3(BT), 0, st, n, f, (const V *)sums, out);
+    PPV_HIP_TRY(hipGetLastError());
+    return PPV_OK;
+}
+template <typename V> struct ValueAt {
+    const V *p;
+    __device__ V operator()(uint64_t i) const { return p[i]; }
+};
+
+// ------------------------------------------------------------------------------------------
+// S as it is on the device during a build: tokens in packed form, and rows by offset.
+struct PackedTokens {
+    const uint16_t *lo;
+    const uint8_t *hi;   // nullptr: every token fits 16 bits
+    __device__ uint32_t operator[](size_t i) const { return hi ? ((uint32_t)hi[i] << 16) | lo[i] : (uint32_t)lo[i]; }
+};
+struct FlatTokens {      // a loaded file's
+    const int32_t *t;
+    __device__ uint32_t operator[](size_t i) const { return (uint32_t)t[i]; }
+};
+struct KeyShape {
+    int bits;    // per token: keys run over 0 .. vocab
+    int slots;   // tokens per key
+};
+__device__ inline uint64_t row_key(const PackedTokens &tok, uint32_t a, uint32_t len, uint32_t from, KeyShape ks) {
+    uint64_t k = 0;
+    for (int s = 0; s < ks.slots; s++) {
+        const uint32_t d = from + (uint32_t)s;
+        k = (k << ks.bits) | (d < len ? tok[a + d] + 1u : 0u);   // 0: the row has ended; sorts first
+    }
+    return k;
+}
+
+// ------------------------------------------------------------------------------------------
+// 1. sort
+__global__ __launch_bounds__(BT) void first_keys(PackedTokens tok, const uint32_t *__restrict__ off, uint32_t n, KeyShape ks,
+                                                 uint64_t *__restrict__ key, uint32_t *__restrict__ row) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t a = off[i];
+    key[i] = row_key(tok, a, off[i + 1] - a, 0u, ks);
+    row[i] = i;
+}
+
+// One pass of a stable radix sort of (key, row) pairs by eight bits of the key: how often every workgroup's chunk
+// holds each digit (digit-major) ...
+__global__ __launch_bounds__(BT) void radix_count(const uint64_t *__restrict__ key, uint32_t n, int shift,
+                                                  uint32_t *__restrict__ hist, uint32_t n_chunks) {
+    __shared__ uint32_t h[RADIX];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t start = blockIdx.x * SORT_CHUNK;
+    uint32_t d[SORT_ITEMS];
+#pragma unroll
+    for (int j = 0; j < SORT_ITEMS; j++) {
+        const uint32_t i = start + j * BT + threadIdx.x;
+        d[j] = i < n ? (uint32_t)(key[i] >> shift) & (RADIX - 1) : RADIX;
+    }
+#pragma unroll
+    for (int j = 0; j < SORT_ITEMS; j++)
+        if (d[j] < RADIX) atomicAdd(&h[d[j]], 1u);
+    __syncthreads();
+    hist[(size_t)threadIdx.x * n_chunks + blockIdx.x] = h[threadIdx.x];
+}
+// ... for each digit (a workgroup each) what the chunks before hold of it, in place, and its total ...
+__global__ __launch_bounds__(BT) void radix_before(uint32_t *__restrict__ hist, uint32_t n_chunks, uint32_t *__restrict__ total) {
+    __shared__ uint32_t wave_tot[BW];
+    uint32_t *h = hist + (size_t)blockIdx.x * n_chunks;
+    uint32_t carry = 0;
+    for (uint32_t c0 = 0; c0 < n_chunks; c0 += BT) {
+        const uint32_t c = c0 + threadIdx.x;
+        const uint32_t v = c < n_chunks ? h[c] : 0u;
+        uint32_t tot;
+        const uint32_t ex = carry + block_exclusive_scan(v, wave_tot, &tot);
+        if (c < n_chunks) h[c] = ex;
+        carry += tot;
+    }
+    if (threadIdx.x == 0) total[blockIdx.x] = carry;
+}
+// ... and every pair to its place.  A wavefront ranks its 512 consecutive keys among themselves, 64 at a time: the
+// lanes with the same digit by ballots, after those of the 64s before (a counter per wavefront and digit in LDS).
+__global__ __launch_bounds__(BT) void radix_move(const uint64_t *__restrict__ key, const uint32_t *__restrict__ row, uint32_t n,
+                                                 int shift, const uint32_t *__restrict__ hist,
+                                                 const uint32_t *__restrict__ total, uint32_t n_chunks,
+                                                 uint64_t *__restrict__ key_out, uint32_t *__restrict__ row_out) {
+    __shared__ uint32_t cnt[BW][RADIX];
+    __shared__ uint32_t wave_tot[BW];
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    for (int w = 0; w < BW; w++) cnt[w][threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t start = blockIdx.x * SORT_CHUNK + wave * (SORT_ITEMS * WAVE) + lane;
+    uint64_t k[SORT_ITEMS];
+    uint32_t r[SORT_ITEMS], rank[SORT_ITEMS];
+#pragma unroll
+    for (int j = 0; j < SORT_ITEMS; j++) {
+        const uint32_t i = start + j * WAVE;
+        k[j] = i < n ? key[i] : 0ull;
+        r[j] = i < n ? row[i] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < SORT_ITEMS; j++) {
+        const bool valid = start + j * WAVE < n;
+        const uint32_t d = (uint32_t)(k[j] >> shift) & (RADIX - 1);
+        uint64_t peers = __ballot(valid);
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+            const uint64_t bal = __ballot((d >> b) & 1u);
+            peers &= ((d >> b) & 1u) ? bal : ~bal;
+        }
+        const int leader = peers ? __ffsll((long long)peers) - 1 : 0;
+        uint32_t before = 0;
+        if (valid && lane == leader) before = atomicAdd(&cnt[wave][d], (uint32_t)__popcll(peers));
+        before = (uint32_t)__shfl((int)before, leader, WAVE);
+        rank[j] = before + (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
+    }
+    __syncthreads();
+    {   // counts -> first places, per wavefront and digit (thread = digit)
+        uint32_t tot;
+        uint32_t at = block_exclusive_scan(total[threadIdx.x], wave_tot, &tot) + hist[(size_t)threadIdx.x * n_chunks + blockIdx.x];
+        for (int w = 0; w < BW; w++) {
+            const uint32_t c = cnt[w][threadIdx.x];
+            cnt[w][threadIdx.x] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < SORT_ITEMS; j++)
+        if (start + j * WAVE < n) {
+            const uint32_t at = cnt[wave][(uint32_t)(k[j] >> shift) & (RADIX - 1)] + rank[j];
+            key_out[at] = k[j];
+            row_out[at] = r[j];
+        }
+}
+
+// sorts (key, row)[n] by the lowest `bits` bits of the keys; the pairs of buffers take turns, the result ends in the first
+ppv_status radix_sort(uint64_t *&key, uint64_t *&key2, uint32_t *&row, uint32_t *&row2, uint32_t n, int bits,
+                      uint32_t *hist, uint32_t *total, hipStream_t st) {
+    const uint32_t nb = (n + SORT_CHUNK - 1) / SORT_CHUNK;
+    for (int shift = 0; shift < bits; shift += 8) {
+        hipLaunchKernelGGL(radix_count, dim3(nb), dim3(BT), 0, st, (const uint64_t *)key, n, shift, hist, nb);
+        hipLaunchKernelGGL(radix_before, dim3(RADIX), dim3(BT), 0, st, hist, nb, total);
+        hipLaunchKernelGGL(radix_move, dim3(nb), dim3(BT), 0, st, (const uint64_t *)key, (const uint32_t *)row, n, shift,
+                           (const uint32_t *)hist, (const uint32_t *)total, nb, key2, row2);
+        std::swap(key, key2);
+        std::swap(row, row2);
+    }
+    PPV_HIP_TRY(hipGetLastError());
+    return PPV_OK;
+}
+
+// Groups of rows whose tokens compared so far are equal: a byte per sorted position, and heads behind the last.
+constexpr int GROUP_PAD = 16;
+constexpr uint8_t GROUP_HEAD = 1;   // the first of its group
+constexpr uint8_t GROUP_DONE = 2;   // nothing left to order in this group (the rows have ended: they are duplicates)
+// Rows of a group are ordered by counting up to this size: size^2 comparisons, nearly all of them of two 64-bit
+// words that lie together.  (The largest group after four tokens of the 1M-sequence Zipf sets: about 500 rows.)  Rows
+// that agree in those words too are compared token by token, so a group of long rows has to be smaller.
+inline uint32_t group_max(int64_t tokens_left) {
+    return (uint32_t)std::max<int64_t>(8, std::min<int64_t>(1024, 16384 / std::max<int64_t>(tokens_left, 1)));
+}
+
+__global__ __launch_bounds__(BT) void mark_groups(const uint64_t *__restrict__ key, uint32_t n, uint64_t last_slot, int complete,
+                                                  uint8_t *__restrict__ group, uint8_t *__restrict__ group2) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i < GROUP_PAD) group[n + i] = group2[n + i] = GROUP_HEAD;
+    if (i >= n) return;
+    const uint64_t k = key[i];
+    group[i] = (uint8_t)(((i == 0u || key[i - 1] != k) ? GROUP_HEAD : 0) | ((complete || (k & last_slot) == 0ull) ? GROUP_DONE : 0));
+}
+__device__ inline bool unsettled(const uint8_t *__restrict__ group, uint32_t i, uint32_t n) {
+    const uint8_t g = group[i];
+    if (g & GROUP_DONE) return false;
+    return !(g & GROUP_HEAD) || (i + 1 < n && !(group[i + 1] & GROUP_HEAD));
+}
+// the next key of the rows that are still to be ordered
+__global__ __launch_bounds__(BT) void next_keys(PackedTokens tok, const uint32_t *__restrict__ off,
+                                                const uint32_t *__restrict__ row, const uint8_t *__restrict__ group, uint32_t n,
+                                                uint32_t depth, KeyShape ks, uint64_t *__restrict__ key) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n || !unsettled(group, i, n)) return;
+    const uint32_t r = row[i], a = off[r];
+    key[i] = row_key(tok, a, off[r + 1] - a, depth, ks);
+}
+// Orders the rows of every group of at most `most`; counts the rows of the larger ones.  depth: tokens that
+// `group` and `key` together have covered.
+__global__ __launch_bounds__(BT) void order_groups(PackedTokens tok, const uint32_t *__restrict__ off,
+                                                   const uint32_t *__restrict__ row, const uint8_t *__restrict__ group,
+                                                   const uint64_t *__restrict__ key, uint32_t n, uint32_t depth,
+                                                   uint64_t last_slot, uint32_t most, uint32_t *__restrict__ row_out,
+                                                   uint8_t *__restrict__ group_out, uint32_t *__restrict__ n_large) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    bool large = false;
+    if (i < n) {
+        const uint32_t r = row[i];
+        uint8_t g = group[i];
+        uint32_t to = i;
+        if (unsettled(group, i, n)) {
+            // the group's bounds, eight positions at a time
+            uint32_t a = i, b = i + 1;
+            const uint64_t heads = 0x0101010101010101ull * GROUP_HEAD;
+            if (!(g & GROUP_HEAD)) {
+                uint32_t w = i >> 3;   // (the bytes at and above i are not looked at)
+                uint64_t f = *(const uint64_t *)(group + 8ull * w) & heads & ((1ull << (8 * (i & 7u))) - 1ull);
+                while (f == 0ull && i - 8u * w <= most) f = *(const uint64_t *)(group + 8ull * --w) & heads;   // position 0 is a head
+                a = f ? 8u * w + (uint32_t)(63 - __clzll((long long)f)) / 8u : 0u;
+                large = f == 0ull;
+            }
+            while (b < n && (b & 7u) && !(group[b] & GROUP_HEAD)) b++;
+            if (b < n && !(b & 7u)) {
+                uint64_t f = *(const uint64_t *)(group + b) & heads;   // (bytes behind the last position: heads)
+                while (f == 0ull && b - i <= most) f = *(const uint64_t *)(group + (b += 8u)) & heads;
+                if (f) b += (uint32_t)(__ffsll((long long)f) - 1) / 8u;
+                if (b > n) b = n;
+            }
+            if (!large && b - a <= most) {
+                const uint64_t k = key[i];
+                uint32_t before = 0, equal = 0;
+#pragma unroll 8
+                for (uint32_t j = a; j < b; j++) {
+                    const uint64_t kj = key[j];
+                    before += kj < k ? 1u : 0u;
+                    equal += kj == k ? 1u : 0u;
+                }
+                if (equal > 1u) {   // rows that agree in this key too: token by token
+                    const uint32_t ra = off[r], rl = off[r + 1] - ra;
+                    for (uint32_t j = a; j < b; j++) {
+                        if (j == i || key[j] != k) continue;
+                        int order = 0;   // of row j against row i; -1: before
+                        if ((k & last_slot) != 0ull) {
+                            const uint32_t q = row[j], qa = off[q], ql = off[q + 1] - qa;
+                            const uint32_t m = rl < ql ? rl : ql;
+                            uint32_t d = depth;
+                            while (d < m && tok[ra + d] == tok[qa + d]) d++;
+                            if (d < m) order = tok[qa + d] < tok[ra + d] ? -1 : 1;
+                            else order = ql < rl ? -1 : (ql > rl ? 1 : 0);
+                        }
+                        before += (order < 0 || (order == 0 && j < i)) ? 1u : 0u;
+                    }
+                }
+                to = a + before;
+                g = GROUP_HEAD | GROUP_DONE;
+            } else {
+                large = true;
+            }
+        }
+        row_out[to] = r;
+        group_out[i] = g;
+    }
+    const uint64_t bal = __ballot(large);
+    if (bal && (threadIdx.x & (WAVE - 1)) == 0) atomicAdd(n_large, (uint32_t)__popcll(bal));
+}
+// what is left after order_groups (large groups): rows of it before each position | groups of it up to there
+struct LargeRows {
+    const uint8_t *group;
+    uint32_t n;
+    __device__ uint64_t operator()(uint64_t i) const {
+        if (!unsettled(group, (uint32_t)i, n)) return 0ull;
+        return (1ull << 32) | ((group[i] & GROUP_HEAD) ? 1ull : 0ull);
+    }
+};
+// their rows with the next key under the group's number
+__global__ __launch_bounds__(BT) void large_keys(PackedTokens tok, const uint32_t *__restrict__ off,
+                                                 const uint32_t *__restrict__ row, const uint8_t *__restrict__ group,
+                                                 const uint64_t *__restrict__ before, uint32_t n, uint32_t depth, KeyShape ks,
+                                                 uint64_t *__restrict__ key, uint32_t *__restrict__ at_row,
+                                                 uint32_t *__restrict__ place) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n || !unsettled(group, i, n)) return;
+    const uint32_t j = (uint32_t)(before[i] >> 32);
+    const uint64_t num = (before[i] & 0xFFFFFFFFull) - ((group[i] & GROUP_HEAD) ? 0ull : 1ull);
+    const uint32_t r = row[i], a = off[r];
+    key[j] = (num << (ks.bits * ks.slots)) | row_key(tok, a, off[r + 1] - a, depth, ks);
+    at_row[j] = r;
+    place[j] = i;
+}
+__global__ __launch_bounds__(BT) void large_back(const uint64_t *__restrict__ key, const uint32_t *__restrict__ at_row,
+                                                 const uint32_t *__restrict__ place, uint32_t m, uint64_t last_slot,
+                                                 int complete, uint32_t *__restrict__ row, uint8_t *__restrict__ group) {
+    const uint32_t j = blockIdx.x * BT + threadIdx.x;
+    if (j >= m) return;
+    const uint64_t k = key[j];
+    row[place[j]] = at_row[j];
+    group[place[j]] = (uint8_t)(((j == 0u || key[j - 1] != k) ? GROUP_HEAD : 0) |
+                                ((complete || (k & last_slot) == 0ull) ? GROUP_DONE : 0));
+}
+
+// ------------------------------------------------------------------------------------------
+// 2. common prefix with the previous sorted row; duplicates.  info: common prefix, 0xFFFFFFFF for a duplicate.
+constexpr uint32_t DUPLICATE = 0xFFFFFFFFu;
+__global__ __launch_bounds__(BT) void neighbour_lcp(PackedTokens tok, const uint32_t *__restrict__ off,
+                                                    const uint32_t *__restrict__ row, uint32_t n, uint32_t *__restrict__ info,
+                                                    uint64_t *__restrict__ kept) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t r = row[i], a = off[r], la = off[r + 1] - a;
+    uint32_t c = 0, lb = 0;
+    if (i > 0) {
+        const uint32_t q = row[i - 1], b = off[q];
+        lb = off[q + 1] - b;
+        const uint32_t m = la < lb ? la : lb;
+        while (c < m && tok[a + c] == tok[b + c]) c++;
+    }
+    const bool dup = i > 0 && c == la && c == lb;
+    info[i] = dup ? DUPLICATE : c;
+    kept[i] = dup ? 0ull : (1ull << 32) | la;   // rows | tokens: scanned together
+}
+// what the later steps know of a row of the index
+struct RowMeta {
+    uint32_t at;    // where its tokens start in the sorted S
+    uint32_t src;   // ... and in the tokens it was given in
+    uint32_t lcp;   // tokens shared with the row before
+    uint32_t len;
+};
+__global__ __launch_bounds__(BT) void compact_rows(const uint32_t *__restrict__ off, const uint32_t *__restrict__ row, uint32_t n,
+                                                   const uint32_t *__restrict__ info, const uint64_t *__restrict__ place,
+                                                   RowMeta *__restrict__ rows) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n || info[i] == DUPLICATE) return;
+    const uint32_t r = row[i];
+    RowMeta m;
+    m.at = (uint32_t)place[i];
+    m.src = off[r];
+    m.lcp = info[i];
+    m.len = off[r + 1] - m.src;
+    rows[place[i] >> 32] = m;
+}
+
+// ------------------------------------------------------------------------------------------
+// 3. how many prefixes each 64 rows open at each depth (depth-major), how many of them get a look-up entry (behind
+// the last depth), and the smallest common prefix of the 64.
+//
+// Look-up entries.  A prefix of one member only -- "alone": nearly all prefixes of long members -- needs no entry of its
+// own: the first alone prefix of a row (its "head") has one, and from there the row's tokens are compared and its
+// prefixes' numbers read off (node_at).  So a row gets entries for the prefixes it opens up to its head.  Prefixes
+// longer than a wavefront are never looked up.
+__device__ inline uint32_t shared_len(uint32_t lcp, uint32_t next_lcp) { return lcp > next_lcp ? lcp : next_lcp; }
+__device__ inline uint32_t last_entry(uint32_t shared, uint32_t len) {   // longest prefix of the row with an entry
+    uint32_t e = shared + 1u;
+    e = e < (uint32_t)WAVE ? e : (uint32_t)WAVE;
+    return e < len ? e : len;
+}
+__global__ __launch_bounds__(BT) void count_prefixes(const RowMeta *__restrict__ rows, const uint64_t *__restrict__ totals,
+                                                     uint32_t n_groups, int32_t l_max, uint32_t *__restrict__ counts,
+                                                     uint32_t *__restrict__ group_lcp) {
+    const uint32_t n_rows = (uint32_t)(totals[0] >> 32);
+    const int lane = threadIdx.x & (WAVE - 1);
+    const uint32_t c = blockIdx.x * BW + threadIdx.x / WAVE;
+    if (c >= n_groups) return;   // uniform per wavefront
+    const uint32_t r = c * WAVE + lane;
+    uint32_t lcp = 0xFFFFFFFFu, len = 0u, next = 0u;
+    if (r < n_rows) {
+        lcp = rows[r].lcp;
+        len = rows[r].len;
+        if (r + 1 < n_rows) next = rows[r + 1].lcp;
+    }
+    const uint32_t entries = r < n_rows && last_entry(shared_len(lcp, next), len) > lcp ? last_entry(shared_len(lcp, next), len) - lcp : 0u;
+    const uint32_t n_entries = wave_sum(entries);
+    const uint32_t lowest = ~wave_max(~lcp);
+    if (lane == 0) {
+        counts[(size_t)l_max * n_groups + c] = n_entries;
+        group_lcp[c] = lowest;
+    }
+    const int longest = (int)wave_max(len);
+    for (int d0 = 0; d0 < l_max; d0 += WAVE) {
+        uint32_t mine = 0u;
+        const int d1 = longest - d0 < WAVE ? longest - d0 : WAVE;
+        for (int k = 0; k < d1; k++) {
+            const uint32_t d = (uint32_t)(d0 + k);
+            const uint32_t opened = (uint32_t)__popcll(__ballot(lcp <= d && d < len));
+            if (lane == k) mine = opened;
+        }
+        if (d0 + lane < l_max) counts[(size_t)(d0 + lane) * n_groups + c] = mine;
+    }
+}
+
+// 4. entries, children, rank ranges, look-up entries
+struct TrieOut {
+    NodeEnt *ent;
+    uint32_t *node_lo, *node_hi;
+    int32_t *x_tok;
+    int64_t *x_off;
+    uint32_t *node_at;        // (with a look-up table) number of the alone prefix that ends at this token of the sorted S
+    LookupEntry *table;       // nullptr: none
+    uint32_t table_size, fp_mask;
+};
+__device__ inline void insert_entry(const TrieOut &o, const PrefixHash &h, uint32_t node, uint32_t at, uint32_t extent) {
+    uint32_t slot, fp;
+    prefix_hash_finish(h, o.table_size, o.fp_mask, &slot, &fp);
+    const unsigned long long key = ((unsigned long long)fp << 32) | node;
+    for (uint32_t n = 0; n < o.table_size; n++) {   // the table has twice as many slots as entries
+        if (atomicCAS((unsigned long long *)&o.table[slot].key, 0ull, key) == 0ull) {
+            o.table[slot].at = at;
+            o.table[slot].extent = extent;
+            return;
+        }
+        slot = slot + 1u == o.table_size ? 0u : slot + 1u;
+    }
+}
+// The tokens of 64 rows are one stretch of the sorted S.  They are gathered into LDS, 16 lanes to a row, and written from
+// there; the loop over the depths finds them there and leaves the alone prefixes' numbers in their places, which go
+// out as one stretch again.  (Token by token from and to memory, with a lane per row, the kernel took 513 us for 1M
+// sequences instead of 218, and gathering the tokens 55 us more.)  `room`: words of LDS per wavefront; rows that need
+// more are read from and written to memory as they come.
+template <typename TOK>
+__global__ __launch_bounds__(BT) void fill_prefixes(TOK tok, const RowMeta *__restrict__ rows, uint32_t n_rows,
+                                                    const uint32_t *__restrict__ base, uint32_t n_groups,
+                                                    const uint32_t *__restrict__ group_lcp, int32_t l_max, uint32_t n_nodes,
+                                                    uint32_t room, TrieOut o) {
+    extern __shared__ uint32_t stage_lds[];
+    const int lane = threadIdx.x & (WAVE - 1);
+    const uint32_t c = blockIdx.x * BW + threadIdx.x / WAVE;
+    const uint32_t r = c * WAVE + lane;
+    if (c * WAVE >= n_rows) return;   // uniform per wavefront
+    uint32_t *st = stage_lds + (threadIdx.x / WAVE) * room;
+    if (c == 0 && lane == 0) {        // the empty prefix and the closing sentinel
+        o.ent[0].tok = 0u;
+        o.ent[0].child = 1u;
+        o.node_lo[0] = 0u;
+        o.node_hi[0] = n_rows;
+        o.ent[n_nodes].tok = PPV_NODE_TOKEN;
+        o.ent[n_nodes].child = n_nodes;
+    }
+    RowMeta m = {0u, 0u, 0xFFFFFFFFu, 0u};
+    uint32_t next_lcp = 0u;   // of the row after this one
+    if (r < n_rows) {
+        m = rows[r];
+        if (r + 1 < n_rows) next_lcp = rows[r + 1].lcp;
+        o.x_off[r] = m.at;
+        if (r + 1 == n_rows) o.x_off[n_rows] = (int64_t)m.at + m.len;
+    }
+    // numbers of the first prefixes these rows open at depths 0 .. 63 (lane = depth), and so on for the next 64
+    auto firsts = [&](int d0) {
+        const int d = d0 + lane;
+        return d <= l_max ? base[(size_t)d * n_groups + (d < l_max ? c : 0u)] : 0u;   // behind the last depth: all prefixes
+    };
+    uint32_t first_at = firsts(0);
+    const uint32_t at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)m.at);
+    const uint32_t span = wave_max(r < n_rows ? m.at + m.len - at0 : 0u);
+    const bool staged = span <= room;
+    if (staged) {
+        constexpr int L = 16, ROWS = WAVE / L, BATCH = 4;   // lanes to a row, rows at a time, times whose loads go out together
+        const uint32_t k0 = lane % L;
+        for (int j0 = 0; j0 < WAVE; j0 += ROWS * BATCH) {
+            uint32_t src[BATCH], at[BATCH], len[BATCH], v[BATCH][2];
+#pragma unroll
+            for (int q = 0; q < BATCH; q++) {
+                const int from = j0 + q * ROWS + lane / L;
+                src[q] = (uint32_t)__shfl((int)m.src, from, WAVE);
+                at[q] = (uint32_t)__shfl((int)m.at, from, WAVE) - at0;
+                len[q] = (uint32_t)__shfl((int)m.len, from, WAVE);
+            }
+#pragma unroll
+            for (int q = 0; q < BATCH; q++)
+#pragma unroll
+                for (uint32_t h = 0; h < 2; h++) v[q][h] = k0 + h * L < len[q] ? tok[src[q] + k0 + h * L] : 0u;
+#pragma unroll
+            for (int q = 0; q < BATCH; q++) {
+#pragma unroll
+                for (uint32_t h = 0; h < 2; h++)
+                    if (k0 + h * L < len[q]) st[at[q] + k0 + h * L] = v[q][h];
+                for (uint32_t k = k0 + 2 * L; k < len[q]; k += L) st[at[q] + k] = tok[src[q] + k];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // other lanes' words from here on
+        for (uint32_t i = lane; i < span; i += WAVE) o.x_tok[at0 + i] = (int32_t)st[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    const uint32_t shared = r < n_rows ? shared_len(m.lcp, next_lcp) : 0u;
+    const uint32_t entries_to = o.table && r < n_rows ? last_entry(shared, m.len) : 0u;
+    const uint32_t after = (uint32_t)__builtin_amdgcn_readlane((int)next_lcp, WAVE - 1);   // (of the row after these 64)
+    const bool last_group = (c + 1) * WAVE >= n_rows;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const int longest = (int)wave_max(m.len);
+    PrefixHash h = {0u, 1u, 0u, 1u};   // the empty string
+    uint64_t opened = __ballot(m.lcp == 0u && m.len > 0u);
+    uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_at);
+    for (int di = 0; di < longest; di++) {
+        const uint32_t d = (uint32_t)di;
+        // what is opened one level down: the children of this level's prefixes
+        const uint64_t opened_next = __ballot(m.lcp <= d + 1u && d + 1u < m.len);
+        if (((di + 1) & (WAVE - 1)) == 0) first_at = firsts(di + 1);
+        const uint32_t first_next = lane_value(first_at, (di + 1) & (WAVE - 1));
+        const bool opens = m.lcp <= d && d < m.len;
+        const bool hashes = d < entries_to && m.lcp < entries_to;
+        uint32_t t = 0u;
+        if (staged) {
+            if (opens || hashes) t = st[m.at - at0 + d];
+        } else if (d < m.len) {
+            t = tok[m.src + d];
+            o.x_tok[m.at + d] = (int32_t)t;
+        }
+        if (hashes) h = d == 0u ? prefix_hash_token(t) : prefix_hash_join(h, prefix_hash_token(t));
+        // where the prefix's range ends: the next row that shares at most d tokens with the row before it
+        const uint64_t breaks = __ballot(m.lcp <= d) & ~below & ~(1ull << lane);
+        uint32_t hi = breaks ? c * WAVE + (uint32_t)__ffsll((long long)breaks) - 1u : n_rows;
+        const bool open_end = opens && !breaks && !last_group;
+        if (__ballot(open_end)) {   // (at most one lane) the range goes on behind these 64 rows
+            uint32_t end = n_rows;
+            if (after <= d) {
+                end = (c + 1) * WAVE;
+            } else {
+                for (uint32_t q = c + 1; q < n_groups; q += WAVE) {
+                    const bool found = q + lane < n_groups && group_lcp[q + lane] <= d;
+                    const uint64_t bal = __ballot(found);
+                    if (bal) {
+                        const uint32_t g0 = (q + (uint32_t)__ffsll((long long)bal) - 1u) * WAVE;
+                        const bool here = g0 + lane < n_rows && rows[g0 + lane].lcp <= d;
+                        const uint64_t bal2 = __ballot(here);
+                        if (bal2) end = g0 + (uint32_t)__ffsll((long long)bal2) - 1u;
+                        break;
+                    }
+                }
+            }
+            if (open_end) hi = end;
+        }
+        if (opens) {
+            const uint32_t g = 1u + first + (uint32_t)__popcll(opened & below);
+            const bool ends = m.len == d + 1u;   // the opening row is the prefix itself
+            // first child: the first prefix one token longer at or after this row (this row's if it goes on, else the
+            // next row's); numbers run on from 64 rows to the next and from a depth to the next
+            const uint64_t upto = ends ? below | (1ull << lane) : below;
+            NodeEnt e;
+            e.tok = ends ? t | PPV_NODE_TERMINAL : t;
+            e.child = 1u + first_next + (uint32_t)__popcll(opened_next & upto);
+            o.ent[g] = e;
+            o.node_lo[g] = r;
+            o.node_hi[g] = hi;
+            if (o.table && d < (uint32_t)WAVE) {
+                const bool alone = d >= shared;
+                if (alone) {
+                    if (staged) st[m.at - at0 + d] = g;
+                    else o.node_at[m.at + d] = g;
+                }
+                if (d < entries_to)
+                    insert_entry(o, h, g, m.at, (d + 1u) | (alone ? (m.len < (uint32_t)WAVE ? m.len : (uint32_t)WAVE) << 8 : 0u));
+            }
+        }
+        opened = opened_next;
+        first = first_next;
+    }
+    if (staged && o.table) {   // (places of prefixes that are not alone hold their tokens: they are not read)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (uint32_t i = lane; i < span; i += WAVE) o.node_at[at0 + i] = st[i];
+    }
+}
+
+// 5. heavy prefixes
+// how many each SCAN_CHUNK entries hold
+__global__ __launch_bounds__(BT) void count_heavy(const NodeEnt *__restrict__ ent, uint32_t n_nodes, uint32_t heavy_min,
+                                                  uint32_t *__restrict__ sums) {
+    __shared__ uint32_t total;
+    if (threadIdx.x == 0) total = 0u;
+    __syncthreads();
+    uint32_t s = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_ITEMS; k++) {
+        const uint64_t g = (uint64_t)blockIdx.x * SCAN_CHUNK + k * BT + threadIdx.x;
+        if (g < n_nodes && ent[g + 1].child - ent[g].child > heavy_min) s++;
+    }
+    s = wave_sum(s);
+    if ((threadIdx.x & (WAVE - 1)) == 0 && s) atomicAdd(&total, s);
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+// second pass over the chunks that hold any: their numbers in increasing order, and their flags
+__global__ __launch_bounds__(BT) void list_heavy(NodeEnt *__restrict__ ent, uint32_t n_nodes, uint32_t heavy_min,
+                                                 const uint32_t *__restrict__ sums, const uint32_t *__restrict__ n_heavy,
+                                                 uint32_t *__restrict__ heavy_node, uint32_t *__restrict__ heavy_limit) {
+    __shared__ uint32_t wave_tot[BW];
+    const uint32_t before = sums[blockIdx.x];
+    if ((blockIdx.x + 1 < gridDim.x ? sums[blockIdx.x + 1] : *n_heavy) == before) return;   // uniform: none here
+    const uint32_t base = blockIdx.x * SCAN_CHUNK + threadIdx.x * SCAN_ITEMS;
+    uint32_t is = 0, count = 0;
+    for (int k = 0; k < SCAN_ITEMS; k++)
+        if (base + k < n_nodes && ent[base + k + 1].child - ent[base + k].child > heavy_min) {
+            is |= 1u << k;
+            count++;
+        }
+    uint32_t tot;
+    uint32_t at = before + block_exclusive_scan(count, wave_tot, &tot);
+    for (int k = 0; k < SCAN_ITEMS; k++)
+        if ((is >> k) & 1u) {
+            heavy_node[at++] = base + k;
+            ent[base + k].tok |= PPV_NODE_HEAVY;
+            atomicMax(heavy_limit, base + k + 1);
+        }
+}
+// one workgroup per heavy prefix: its children into the image, the children before each word, its slot
+constexpr int HT = 1024;
+__global__ __launch_bounds__(HT) void fill_heavy(const NodeEnt *__restrict__ ent, const uint32_t *__restrict__ heavy_node,
+                                                 const uint32_t *__restrict__ n_heavy, int n_words,
+                                                 uint32_t *__restrict__ bits, uint32_t *__restrict__ rank,
+                                                 uint32_t *__restrict__ heavy_slot, uint32_t reach) {
+    extern __shared__ uint32_t img[];   // [n_words]
+    __shared__ uint32_t wave_tot[HT / WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+    if (blockIdx.x >= *n_heavy) return;
+    const uint32_t g = heavy_node[blockIdx.x];
+    if (threadIdx.x == 0 && g < reach) heavy_slot[g] = blockIdx.x;
+    for (int w = threadIdx.x; w < n_words; w += HT) img[w] = 0u;
+    __syncthreads();
+    for (uint32_t c = ent[g].child + threadIdx.x; c < ent[g + 1].child; c += HT) {
+        const uint32_t v = ent[c].tok & PPV_NODE_TOKEN;
+        atomicOr(&img[v >> 5], 1u << (v & 31u));
+    }
+    __syncthreads();
+    uint32_t *b = bits + (size_t)blockIdx.x * (size_t)n_words;
+    uint32_t *rk = rank + (size_t)blockIdx.x * (size_t)n_words;
+    uint32_t carry = 0;
+    for (int w0 = 0; w0 < n_words; w0 += HT) {
+        const int w = w0 + threadIdx.x;
+        const uint32_t word = w < n_words ? img[w] : 0u;
+        const uint32_t c = (uint32_t)__popc(word), incl = wave_incl_scan(c);
+        if (lane == WAVE - 1) wave_tot[wave] = incl;
+        __syncthreads();
+        uint32_t before = 0, total = 0;
+        for (int k = 0; k < HT / WAVE; k++) {
+            const uint32_t t = wave_tot[k];
+            before += k < wave ? t : 0u;
+            total += t;
+        }
+        __syncthreads();
+        if (w < n_words) {
+            b[w] = word;
+            rk[w] = carry + before + incl - c;
+        }
+        carry += total;
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// A block of device memory from the pool, cut into arrays: sizes first (add), then the block (take), then addresses.
+struct Arena {
+    static constexpr int MOST = 32;
+    void **slot[MOST];
+    size_t at[MOST];
+    int n = 0;
+    size_t bytes = 0;
+    void *block = nullptr;
+    template <typename T> void add(T **p, uint64_t count) {
+        slot[n] = (void **)p;
+        at[n++] = bytes;
+        bytes += ((size_t)(count ? count : 1) * sizeof(T) + 255) / 256 * 256;
+    }
+    ppv_status take() {
+        TRY(ppv_pool_take(&block, bytes));
+        for (int i = 0; i < n; i++) *slot[i] = (char *)block + at[i];
+        return PPV_OK;
+    }
+    void *keep() {   // the block belongs to the caller from here on
+        void *b = block;
+        block = nullptr;
+        return b;
+    }
+};
+struct TempArena : Arena {   // given back at the end of the build, when everything that used it has finished
+    ~TempArena() {
+        if (!block) return;
+        (void)hipStreamSynchronize(nullptr);
+        ppv_pool_give(block);
+    }
+};
+
+// What the host has to know of a build under way, written by a kernel into pinned memory.
+struct BuildWords {
+    uint64_t rows_tokens;                 // rows << 32 | tokens, without duplicates
+    uint32_t prefixes, all_counts;        // prefixes; prefixes and look-up entries
+    uint32_t large;                       // rows in groups too large to be ordered by counting
+    uint32_t heavy, heavy_limit;          // heavy prefixes, one past the last of them
+    int32_t err;
+};
+static_assert(sizeof(BuildWords) <= PPV_HOST_WORDS_BYTES, "one slot of pinned words");
+__global__ void publish(BuildWords *__restrict__ out, const uint64_t *__restrict__ rows_tokens, const uint32_t *__restrict__ prefixes,
+                        const uint32_t *__restrict__ all_counts, const uint32_t *__restrict__ large) {
+    out->rows_tokens = *rows_tokens;
+    out->prefixes = *prefixes;
+    out->all_counts = *all_counts;
+    out->large = *large;
+}
+__global__ void publish_heavy(BuildWords *__restrict__ out, const uint32_t *__restrict__ heavy) {
+    out->heavy = heavy[0];
+    out->heavy_limit = heavy[1];
+}
+struct HostWords {
+    volatile BuildWords *w = (volatile BuildWords *)ppv_host_words_take();
+    ~HostWords() { ppv_host_words_give((void *)w); }
+    BuildWords *dev() const { return (BuildWords *)w; }   // (mapped at the same address)
+};
+
+// device words read back by the host; a synchronisation
+template <typename T> ppv_status read_back(T *host, const void *dev, size_t count, hipStream_t st) {
+    PPV_HIP_TRY(hipMemcpyAsync(host, dev, count * sizeof(T), hipMemcpyDeviceToHost, st));
+    PPV_HIP_TRY(hipStreamSynchronize(st));
+    return PPV_OK;
+}
+
+// 5. Images and per-word child counts of the heavy prefixes, from the finished entries (G of them plus the sentinel).
+// Sets the heavy part of the index and of its view.  The index's block has room for HEAVY_GUESS of them among the first
+// HEAVY_REACH prefixes, which are filled before the host knows how many there are; more than that (small
+// vocabularies, where every second prefix is heavy) get a block of their own.  Ends with a synchronisation.
+constexpr uint32_t HEAVY_GUESS = 256, HEAVY_REACH = 1u << 20;
+ppv_status finish_heavy(ppv_index *ix, uint32_t G, int32_t vocab, const HostWords &words, hipStream_t st) {
     const int n_words = (vocab + 31) / 32;
     const uint32_t heavy_min = (uint32_t)std::min<int64_t>(vocab / 32, PPV_LIST_MAX);
-    uint32_t *slot_of, *sums, *d_total;
-    TRY(tmp.alloc(&slot_of, G));
-    TRY(tmp.alloc(&sums, (size_t)(((uint64_t)G + SCAN_CHUNK - 1) / SCAN_CHUNK)));
-    TRY(tmp.alloc(&d_total, 1));
-    TRY(exclusive_scan(G, IsHeavy{ix->d_ent, heavy_min}, slot_of, sums, d_total, st));
-    uint32_t n_heavy;
-    PPV_HIP_TRY(hipMemcpyAsync(&n_heavy, d_total, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    PPV_HIP_TRY(hipStreamSynchronize(st));
-    // Breadth-first order puts the heavy prefixes (shallow ones) at small entry numbers, so the slot
-    // table only has to reach past the last of them: the first entry that has all n_heavy before it.
-    uint32_t heavy_limit = 0;
-    if (n_heavy > 0) {
-        uint32_t lo = 0, hi = G;
-        while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo) / 2;
-            uint32_t v;
-            PPV_HIP_TRY(hipMemcpy(&v, slot_of + mid, sizeof(uint32_t), hipMemcpyDeviceToHost));
-            if (v >= n_heavy) hi = mid; else lo = mid + 1;
-        }
-        heavy_limit = lo;
+    const uint64_t chunks = ((uint64_t)G + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    const uint64_t bound = G / (heavy_min + 1ull) + 1;   // children are disjoint
+    TempArena tmp;
+    uint32_t *sums, *d_heavy, *heavy_node;               // d_heavy: heavy prefixes, one past the last of them
+    tmp.add(&sums, chunks + 1);
+    tmp.add(&d_heavy, 2);
+    tmp.add(&heavy_node, bound);
+    TRY(tmp.take());
+    PPV_HIP_TRY(hipMemsetAsync(d_heavy, 0, 2 * sizeof(uint32_t), st));
+    hipLaunchKernelGGL(count_heavy, dim3((unsigned)chunks), dim3(BT), 0, st, (const NodeEnt *)ix->d_ent, G, heavy_min, sums);
+    hipLaunchKernelGGL(scan_of_sums<uint32_t>, dim3(1), dim3(BT), 0, st, sums, chunks, d_heavy);
+    hipLaunchKernelGGL(list_heavy, dim3((unsigned)chunks), dim3(BT), 0, st, ix->d_ent, G, heavy_min, (const uint32_t *)sums,
+                       (const uint32_t *)d_heavy, heavy_node, d_heavy + 1);
+    hipLaunchKernelGGL(publish_heavy, dim3(1), dim3(1), 0, st, words.dev(), (const uint32_t *)d_heavy);
+    auto fill = [&](uint32_t most, uint32_t reach) {
+        PPV_HIP_TRY(hipMemsetAsync(ix->d_heavy_slot, 0xFF, (size_t)reach * sizeof(uint32_t), st));   // PPV_NO_SLOT
+        hipLaunchKernelGGL(fill_heavy, dim3(most), dim3(HT), (size_t)n_words * sizeof(uint32_t), st,
+                           (const NodeEnt *)ix->d_ent, (const uint32_t *)heavy_node, (const uint32_t *)d_heavy, n_words,
+                           ix->d_heavy_bits, ix->d_heavy_rank, ix->d_heavy_slot, reach);
+        PPV_HIP_TRY(hipGetLastError());
+        PPV_HIP_TRY(hipStreamSynchronize(st));
+        return PPV_OK;
+    };
+    TRY(fill(std::min(HEAVY_GUESS, (uint32_t)bound), std::min(G, HEAVY_REACH)));
+    const uint32_t n_heavy = words.w->heavy, limit = words.w->heavy_limit;
+    if (n_heavy > HEAVY_GUESS || limit > HEAVY_REACH) {
+        Arena keep;
+        keep.add(&ix->d_heavy_slot, limit);
+        keep.add(&ix->d_heavy_bits, (uint64_t)n_heavy * n_words);
+        keep.add(&ix->d_heavy_rank, (uint64_t)n_heavy * n_words);
+        TRY(keep.take());
+        ix->heavy_block = keep.keep();
+        ix->device_bytes += (int64_t)keep.bytes;
+        TRY(fill(n_heavy, limit));
     }
-    uint32_t *heavy_node;
-    TRY(tmp.alloc(&heavy_node, n_heavy));
-    TRY(keep_alloc(&ix->d_heavy_slot, heavy_limit, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_heavy_bits, (size_t)n_heavy * n_words, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_heavy_rank, (size_t)n_heavy * n_words, &ix->device_bytes));
-    PPV_HIP_TRY(hipMemsetAsync(ix->d_heavy_bits, 0, std::max<size_t>((size_t)n_heavy * n_words, 1) * sizeof(uint32_t), st));
-    hipLaunchKernelGGL(mark_heavy, dim3(blocks_for(G)), dim3(BT), 0, st, ix->d_ent, G, heavy_min,
-                       (const uint32_t *)slot_of, heavy_limit, ix->d_heavy_slot, heavy_node);
-    if (n_heavy > 0)
-        hipLaunchKernelGGL(fill_heavy, dim3(n_heavy), dim3(BT), 0, st, (const NodeEnt *)ix->d_ent,
-                           (const uint32_t *)heavy_node, n_words, ix->d_heavy_bits, ix->d_heavy_rank);
-    PPV_HIP_TRY(hipGetLastError());
-    PPV_HIP_TRY(hipStreamSynchronize(st));
     ix->n_heavy = n_heavy;
     ix->view.heavy_slot = ix->d_heavy_slot;
     ix->view.heavy_bits = ix->d_heavy_bits;
     ix->view.heavy_rank = ix->d_heavy_rank;
-    ix->view.heavy_limit = heavy_limit;
+    ix->view.heavy_limit = limit;
     ix->view.n_heavy = n_heavy;
     ix->view.heavy_min = heavy_min;
     ix->view.n_words = n_words;
     return PPV_OK;
 }
 
-// Nodes of depth d are h_base[d] .. h_base[d+1] (h_base has l_max + 2 entries): depth 0 is the empty prefix, and
-// the nodes of depth d+1 start where the children of the first node of depth d start.  Reads one child offset
-// per depth from the finished entries.
-ppv_status depth_bases(const ppv_index *ix, uint32_t G, int32_t l_max, uint32_t *h_base) {
-    h_base[0] = 0u;
-    h_base[1] = 1u;
-    for (int d = 1; d < l_max; d++) {
-        if (h_base[d] >= G) {
-            h_base[d + 1] = G;
-            continue;
-        }
-        PPV_HIP_TRY(hipMemcpy(&h_base[d + 1], &ix->d_ent[h_base[d]].child, sizeof(uint32_t), hipMemcpyDeviceToHost));
-        if (h_base[d + 1] < h_base[d] || h_base[d + 1] > G) return PPV_EINVAL;
-    }
-    h_base[l_max + 1] = G;
-    return PPV_OK;
-}
-
-// 7. Look-up table of whole prefixes: every node is entered under the hash of its token string (the first
-// tokens of the first member under it).  Also the per-depth node ranges the look-up checks a hit against.
-__global__ __launch_bounds__(BT) void insert_nodes(const uint32_t *__restrict__ node_lo, const int32_t *__restrict__ x_tok,
-                                                   const int64_t *__restrict__ x_off,
-                                                   const uint32_t *__restrict__ depth_base, int32_t l_max,
-                                                   uint32_t n_nodes, uint64_t *__restrict__ table, uint32_t size,
-                                                   uint32_t fp_mask, int32_t *__restrict__ err) {
-    const uint32_t g = 1u + blockIdx.x * BT + threadIdx.x;   // node 0 is the empty prefix: not looked up
-    if (g >= n_nodes) return;
-    int lo = 1, hi = l_max;                                   // depth d with depth_base[d] <= g < depth_base[d+1]
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (depth_base[mid] <= g) lo = mid; else hi = mid - 1;
-    }
-    const uint32_t r = node_lo[g];
-    const int64_t a = x_off[r];
-    if (x_off[r + 1] - a < lo) {   // (a loaded file) the first member under a node is at least as long as the node is deep
-        atomicOr(err, 4);
-        return;
-    }
-    PrefixHash h = prefix_hash_token((uint32_t)x_tok[a]);   // a node is at least one token deep
-    for (int i = 1; i < lo; i++) h = prefix_hash_join(h, prefix_hash_token((uint32_t)x_tok[a + i]));
-    uint32_t slot, fp;
-    prefix_hash_finish(h, size, fp_mask, &slot, &fp);
-    const unsigned long long entry = ((unsigned long long)fp << 32) | g;
-    for (uint32_t n = 0; n < size; n++) {   // the table has twice as many slots as nodes
-        if (atomicCAS((unsigned long long *)&table[slot], 0ull, entry) == 0ull) return;
-        slot = slot + 1u == size ? 0u : slot + 1u;
-    }
-}
-
-__global__ __launch_bounds__(BT) void fill_xpos(const uint32_t *__restrict__ node_lo, const int64_t *__restrict__ x_off,
-                                                uint32_t n_nodes, uint32_t *__restrict__ xpos) {
-    const uint32_t g = blockIdx.x * BT + threadIdx.x;
-    if (g < n_nodes) xpos[g] = (uint32_t)x_off[node_lo[g]];
-}
-
-ppv_status finish_lookup(ppv_index *ix, uint32_t G, int32_t l_max, hipStream_t st) {
-    uint32_t *h_base = new (std::nothrow) uint32_t[(size_t)l_max + 2];
-    if (!h_base) return PPV_ENOMEM;
-    ppv_status rc = depth_bases(ix, G, l_max, h_base);
-    if (rc == PPV_OK) rc = keep_alloc(&ix->d_depth_base, (size_t)l_max + 2, &ix->device_bytes);
-    if (rc == PPV_OK && hipMemcpy(ix->d_depth_base, h_base, ((size_t)l_max + 2) * sizeof(uint32_t), hipMemcpyHostToDevice) !=
-                            hipSuccess) {
-        (void)hipGetLastError();
-        rc = PPV_EDEVICE;
-    }
-    delete[] h_base;
-    if (rc != PPV_OK) return rc;
-    ix->view.depth_base = ix->d_depth_base;
-    ix->view.x_tok = ix->d_x_tok;
-    ix->view.x_off = ix->d_x_off;
-    ix->view.lookup = nullptr;
-    ix->view.lookup_size = 0;
-    ix->view.lookup_fp_mask = 0xFFFFFFFFu;
-    // PPV_TUNE_LOOKUP = 0: no table (every prefix is located by the descent; saves 16 bytes per prefix of device memory).
-    // PPV_TUNE_LOOKUP_WEAK = 1 (tests): one fingerprint for all, so that every probe is a false hit and the exact check
-    // has to turn it away.
-    if (ppv_tuning(PPV_TUNE_LOOKUP) == 0) return PPV_OK;
-    if (ppv_tuning(PPV_TUNE_LOOKUP_WEAK) == 1) ix->view.lookup_fp_mask = 0u;
-    const uint64_t want = 2ull * G;
-    const uint32_t size = (uint32_t)std::min<uint64_t>(want, 0xFFFFFFF0ull);
-    DeviceBuffers tmp;
-    int32_t *d_err;
-    TRY(tmp.alloc(&d_err, 1));
-    TRY(keep_alloc(&ix->d_lookup, size, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_node_xpos, G, &ix->device_bytes));
-    hipLaunchKernelGGL(fill_xpos, dim3(blocks_for(G)), dim3(BT), 0, st, (const uint32_t *)ix->d_node_lo,
-                       (const int64_t *)ix->d_x_off, G, ix->d_node_xpos);
-    PPV_HIP_TRY(hipMemsetAsync(d_err, 0, sizeof(int32_t), st));
-    PPV_HIP_TRY(hipMemsetAsync(ix->d_lookup, 0, (size_t)size * sizeof(uint64_t), st));
-    if (G > 1)
-        hipLaunchKernelGGL(insert_nodes, dim3(blocks_for(G - 1)), dim3(BT), 0, st, (const uint32_t *)ix->d_node_lo,
-                           (const int32_t *)ix->d_x_tok, (const int64_t *)ix->d_x_off,
-                           (const uint32_t *)ix->d_depth_base, l_max, G, ix->d_lookup, size, ix->view.lookup_fp_mask,
-                           d_err);
+// 3. and 4. for rows whose RowMeta is on the device.  counts: (l_max + 1) * n_groups words, already scanned, n_groups
+// for as many rows as `rows` has room for; n_prefixes, n_entries: what the scan found.
+template <typename TOK>
+ppv_status number_prefixes(ppv_index *ix, TOK tok, const RowMeta *rows, uint32_t n_rows, uint32_t n_tok, int32_t l_max,
+                           const uint32_t *counts, uint32_t n_groups, const uint32_t *group_lcp, uint32_t n_prefixes,
+                           uint32_t n_entries, int32_t vocab, const HostWords &words, hipStream_t st) {
+    if (n_prefixes > 0xFFFFFFF0u - 2) return PPV_ERANGE;
+    const uint32_t G = n_prefixes + 1;   // with the empty prefix
+    // PPV_TUNE_LOOKUP = 0: no table (every prefix is located by the descent).  PPV_TUNE_LOOKUP_WEAK = 1 (tests): one
+    // fingerprint for all, so that every probe is a false hit and the exact check has to turn it away.
+    const bool lookup = ppv_tuning(PPV_TUNE_LOOKUP) != 0;
+    const uint32_t size = lookup ? (uint32_t)std::min<uint64_t>(2ull * n_entries, 0xFFFFFFF0ull) : 0u;
+    Arena keep;
+    keep.add(&ix->d_ent, (uint64_t)G + 1);
+    keep.add(&ix->d_node_lo, G);
+    keep.add(&ix->d_node_hi, G);
+    keep.add(&ix->d_x_tok, n_tok);
+    keep.add(&ix->d_x_off, (uint64_t)n_rows + 1);
+    keep.add(&ix->d_node_at, lookup ? n_tok : 0);
+    keep.add(&ix->d_lookup, size);
+    const uint64_t n_words = ((uint64_t)vocab + 31) / 32;
+    keep.add(&ix->d_heavy_slot, std::min(G, HEAVY_REACH));
+    keep.add(&ix->d_heavy_bits, HEAVY_GUESS * n_words);
+    keep.add(&ix->d_heavy_rank, HEAVY_GUESS * n_words);
+    TRY(keep.take());
+    ix->block = keep.keep();
+    ix->device_bytes = (int64_t)keep.bytes;
+    if (lookup) PPV_HIP_TRY(hipMemsetAsync(ix->d_lookup, 0, (size_t)size * sizeof(LookupEntry), st));
+    TrieOut o;
+    o.ent = ix->d_ent;
+    o.node_lo = ix->d_node_lo;
+    o.node_hi = ix->d_node_hi;
+    o.x_tok = ix->d_x_tok;
+    o.x_off = ix->d_x_off;
+    o.node_at = ix->d_node_at;
+    o.table = lookup ? ix->d_lookup : nullptr;
+    o.table_size = size;
+    o.fp_mask = ppv_tuning(PPV_TUNE_LOOKUP_WEAK) == 1 ? 0u : 0xFFFFFFFFu;
+    // LDS for what 64 rows hold on average and a quarter more, or for 64 of the longest
+    const uint64_t mean = ((uint64_t)n_tok * WAVE + n_rows - 1) / n_rows;
+    const uint32_t room = (uint32_t)std::min<uint64_t>(std::min<uint64_t>(mean + mean / 4 + WAVE, (uint64_t)l_max * WAVE), 4096);
+    hipLaunchKernelGGL(fill_prefixes<TOK>, dim3(blocks_for(n_rows)), dim3(BT), BW * room * sizeof(uint32_t), st, tok, rows,
+                       n_rows, counts, n_groups, group_lcp, l_max, G, room, o);
     PPV_HIP_TRY(hipGetLastError());
-    int32_t err = 0;
-    PPV_HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    PPV_HIP_TRY(hipStreamSynchronize(st));
-    if (err != 0) return PPV_EINVAL;
-    ix->view.lookup = ix->d_lookup;
-    ix->view.node_xpos = ix->d_node_xpos;
+    TRY(finish_heavy(ix, G, vocab, words, st));
+    ix->n_tokens = n_tok;
+    ix->view.ent = ix->d_ent;
+    ix->view.node_lo = ix->d_node_lo;
+    ix->view.node_hi = ix->d_node_hi;
+    ix->view.n_nodes = G;
+    ix->view.n_rows = n_rows;
+    ix->view.vocab = vocab;
+    ix->view.l_max = l_max;
+    ix->view.x_tok = ix->d_x_tok;
+    ix->view.node_at = ix->d_node_at;
+    ix->view.lookup = o.table;
     ix->view.lookup_size = size;
+    ix->view.lookup_fp_mask = o.fp_mask;
     return PPV_OK;
 }
 
@@ -580,154 +962,144 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
     if (n_seq > 0xFFFFFFF0ll || total > 0xFFFFFFF0ll) return PPV_ERANGE;
     const uint32_t n = (uint32_t)n_seq;
     hipStream_t st = nullptr;
-    DeviceBuffers tmp;
 
     // ---- inputs to the device
-    int32_t *d_tok;
-    int64_t *d_off;
-    int32_t *d_flags;  // [0] error bits, [1] longest row
-    uint32_t *d_total;
-    TRY(tmp.alloc(&d_tok, (size_t)total));
-    TRY(tmp.alloc(&d_off, (size_t)n + 1));
-    TRY(tmp.alloc(&d_flags, 2));
-    TRY(tmp.alloc(&d_total, 4));
-    PPV_HIP_TRY(hipMemcpyAsync(d_tok, tokens, (size_t)total * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    PPV_HIP_TRY(hipMemcpyAsync(d_off, offsets, ((size_t)n + 1) * sizeof(int64_t), hipMemcpyHostToDevice, st));
-    PPV_HIP_TRY(hipMemsetAsync(d_flags, 0, 2 * sizeof(int32_t), st));
+    uint16_t *d_lo;
+    uint8_t *d_hi;
+    uint32_t *d_off;
+    const bool wide = vocab > 65536;
+    TempArena in;
+    in.add(&d_lo, (uint64_t)total);
+    in.add(&d_hi, wide ? (uint64_t)total : 0);
+    in.add(&d_off, (uint64_t)n + 1);
+    // ... and what sorting them needs
+    uint64_t *key, *key2, *place, *sums64, *d_tot64;
+    uint32_t *row, *row2, *hist, *digit_total, *info, *d_word;
+    uint8_t *group, *group2;
+    RowMeta *rows;
+    const uint32_t sort_chunks = (n + SORT_CHUNK - 1) / SORT_CHUNK;
+    in.add(&key, n);
+    in.add(&key2, n);
+    in.add(&row, n);
+    in.add(&row2, n);
+    in.add(&group, (uint64_t)n + GROUP_PAD);
+    in.add(&group2, (uint64_t)n + GROUP_PAD);
+    in.add(&hist, (uint64_t)RADIX * sort_chunks);
+    in.add(&digit_total, RADIX);
+    in.add(&info, n);
+    in.add(&place, n);
+    in.add(&sums64, scan_words(n));
+    in.add(&d_tot64, 1);
+    in.add(&d_word, 2);
+    in.add(&rows, n);
+    TRY(in.take());
+    if (!wide) d_hi = nullptr;
+    int32_t l_max = 0;
+    TRY(ppv_upload_set(tokens, offsets, n_seq, vocab, d_lo, d_hi, d_off, st, &l_max));   // EINVAL: empty sequence, token outside [0, vocab)
+    const PackedTokens tok = {d_lo, d_hi};
 
-    // ---- 1. validate
-    hipLaunchKernelGGL(check_rows, dim3(blocks_for(n)), dim3(BT), 0, st, (const int64_t *)d_off, (int64_t)n, d_flags,
-                       d_flags + 1);
-    hipLaunchKernelGGL(check_tokens, dim3(blocks_for((uint64_t)total)), dim3(BT), 0, st, (const int32_t *)d_tok, total,
-                       vocab, d_flags);
-    int32_t h_flags[2];
-    PPV_HIP_TRY(hipMemcpyAsync(h_flags, d_flags, sizeof(h_flags), hipMemcpyDeviceToHost, st));
-    PPV_HIP_TRY(hipStreamSynchronize(st));
-    if (h_flags[0] != 0) return PPV_EINVAL;                         // empty sequence or token outside [0, vocab)
-    const int32_t l_max = h_flags[1];
+    // ---- 1. sort
+    KeyShape ks;
+    ks.bits = 1;
+    while ((1ll << ks.bits) <= (int64_t)vocab) ks.bits++;           // keys run over 0 .. vocab
+    ks.slots = std::min(64 / ks.bits, l_max);
+    const uint64_t last_slot = (1ull << ks.bits) - 1ull;
+    const unsigned nb = blocks_for(n);
+    hipLaunchKernelGGL(first_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, n, ks, key, row);
+    TRY(radix_sort(key, key2, row, row2, n, ks.bits * ks.slots, hist, digit_total, st));
+    int64_t depth = ks.slots;                                       // tokens ordered so far
+    const uint32_t n_groups = (n + WAVE - 1) / WAVE;
+    const uint64_t n_counts = ((uint64_t)l_max + 1) * n_groups;
+    if (n_counts > 0xFFFFFFF0ull) return PPV_ERANGE;
+    uint32_t *counts, *group_lcp, *sums;
+    TempArena cnt;
+    cnt.add(&counts, n_counts);
+    cnt.add(&group_lcp, n_groups);
+    cnt.add(&sums, scan_words(n_counts));
+    TRY(cnt.take());
+    const HostWords words;
+    if (!words.w) return PPV_ENOMEM;
 
-    // ---- 2. sort rows: LSD radix over the columns, last column first
-    uint32_t *perm_a, *perm_b, *hist, *sums;
-    uint8_t *digits;
-    const uint32_t sort_blocks = (n + SORT_CHUNK - 1) / SORT_CHUNK;
-    const uint64_t hist_len = (uint64_t)RADIX * sort_blocks;
-    TRY(tmp.alloc(&perm_a, n));
-    TRY(tmp.alloc(&perm_b, n));
-    TRY(tmp.alloc(&digits, n));
-    TRY(tmp.alloc(&hist, (size_t)hist_len));
-    // scratch for every scan of the build: the largest one runs over l_max * n flags
-    const uint64_t biggest_scan = std::max<uint64_t>((uint64_t)l_max * n + 1, hist_len);
-    TRY(tmp.alloc(&sums, (size_t)((biggest_scan + SCAN_CHUNK - 1) / SCAN_CHUNK)));
-    hipLaunchKernelGGL(iota_rows, dim3(blocks_for(n)), dim3(BT), 0, st, perm_a, n);
-    int key_bits = 1;
-    while ((1ll << key_bits) <= (int64_t)vocab) key_bits++;         // keys run over 0 .. vocab
-    for (int col = l_max - 1; col >= 0; col--) {
-        for (int shift = 0; shift < key_bits; shift += 8) {
-            hipLaunchKernelGGL(radix_histogram, dim3(sort_blocks), dim3(BT), 0, st, (const int32_t *)d_tok,
-                               (const int64_t *)d_off, (const uint32_t *)perm_a, n, col, shift, digits, hist,
-                               sort_blocks);
-            TRY(exclusive_scan(hist_len, HistValue{hist}, hist, sums, d_total, st));
-            hipLaunchKernelGGL(radix_scatter, dim3(sort_blocks), dim3(BT), 0, st, (const uint32_t *)perm_a, n,
-                               (const uint8_t *)digits, (const uint32_t *)hist, sort_blocks, perm_b);
-            std::swap(perm_a, perm_b);
-        }
+    PPV_HIP_TRY(hipMemsetAsync(d_word, 0, 2 * sizeof(uint32_t), st));   // rows in large groups; all counts
+    auto order = [&] {   // groups of rows equal so far, small ones ordered, rows in large ones counted in *d_word
+        hipLaunchKernelGGL(next_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
+                           (const uint8_t *)group, n, (uint32_t)depth, ks, key);
+        hipLaunchKernelGGL(order_groups, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
+                           (const uint8_t *)group, (const uint64_t *)key, n, (uint32_t)(depth + ks.slots), last_slot,
+                           group_max(l_max - depth - ks.slots), row2, group2, d_word);
+        std::swap(row, row2);
+        std::swap(group, group2);
+    };
+    // Steps 2 and 3 up to the sizes of the arrays, and the host's look at them.  They are run before it is known
+    // whether large groups are left (a trip to the host), and again if there were any.
+    auto measure = [&] {
+        hipLaunchKernelGGL(neighbour_lcp, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row, n,
+                           info, place);
+        TRY(exclusive_scan<uint64_t>(n, ValueAt<uint64_t>{place}, place, sums64, d_tot64, st));
+        hipLaunchKernelGGL(compact_rows, dim3(nb), dim3(BT), 0, st, (const uint32_t *)d_off, (const uint32_t *)row, n,
+                           (const uint32_t *)info, (const uint64_t *)place, rows);
+        hipLaunchKernelGGL(count_prefixes, dim3((n_groups + BW - 1) / BW), dim3(BT), 0, st, (const RowMeta *)rows,
+                           (const uint64_t *)d_tot64, n_groups, l_max, counts, group_lcp);
+        TRY(exclusive_scan<uint32_t>(n_counts, ValueAt<uint32_t>{counts}, counts, sums, d_word + 1, st));
+        hipLaunchKernelGGL(publish, dim3(1), dim3(1), 0, st, words.dev(), (const uint64_t *)d_tot64,
+                           (const uint32_t *)(counts + (uint64_t)l_max * n_groups), (const uint32_t *)(d_word + 1),
+                           (const uint32_t *)d_word);
+        PPV_HIP_TRY(hipGetLastError());
+        PPV_HIP_TRY(hipStreamSynchronize(st));
+        return PPV_OK;
+    };
+    if (depth < l_max) {
+        hipLaunchKernelGGL(mark_groups, dim3(nb), dim3(BT), 0, st, (const uint64_t *)key, n, last_slot, 0, group, group2);
+        order();
     }
-    PPV_HIP_TRY(hipGetLastError());
-
-    // ---- 3. neighbours: common prefix, duplicates; compact into the flat sorted S
-    int32_t *lcp;
-    uint8_t *keep;
-    uint32_t *dst, *tok_at;
-    TRY(tmp.alloc(&lcp, n));
-    TRY(tmp.alloc(&keep, n));
-    TRY(tmp.alloc(&dst, n));
-    TRY(tmp.alloc(&tok_at, n));
-    hipLaunchKernelGGL(neighbour_lcp, dim3(blocks_for(n)), dim3(BT), 0, st, (const int32_t *)d_tok,
-                       (const int64_t *)d_off, (const uint32_t *)perm_a, n, lcp, keep);
-    TRY(exclusive_scan(n, KeepFlag{keep}, dst, sums, d_total, st));
-    TRY(exclusive_scan(n, KeptLen{keep, perm_a, d_off}, tok_at, sums, d_total + 1, st));
-    uint32_t h_tot[2];
-    PPV_HIP_TRY(hipMemcpyAsync(h_tot, d_total, sizeof(h_tot), hipMemcpyDeviceToHost, st));
-    PPV_HIP_TRY(hipStreamSynchronize(st));
-    const uint32_t n_rows = h_tot[0], n_tok = h_tot[1];
-    ix->device_bytes = 0;
-    TRY(keep_alloc(&ix->d_x_tok, n_tok, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_x_off, (size_t)n_rows + 1, &ix->device_bytes));
-    int32_t *row_lcp;
-    TRY(tmp.alloc(&row_lcp, n_rows));
-    hipLaunchKernelGGL(compact_rows, dim3(blocks_for(n)), dim3(BT), 0, st, (const int32_t *)d_tok,
-                       (const int64_t *)d_off, (const uint32_t *)perm_a, n, (const uint8_t *)keep,
-                       (const uint32_t *)dst, (const uint32_t *)tok_at, (const int32_t *)lcp, ix->d_x_tok, ix->d_x_off,
-                       row_lcp, n_rows, n_tok);
-
-    // ---- 4. number the prefixes breadth-first: one scan over the (depth, row) flags
-    const uint64_t n_flags = (uint64_t)l_max * n_rows;
-    if (n_flags + 1 > 0xFFFFFFF0ull) return PPV_ERANGE;
-    uint32_t *pos;
-    TRY(tmp.alloc(&pos, (size_t)n_flags + 1));
-    TRY(exclusive_scan(n_flags, OpensPrefix{ix->d_x_off, row_lcp, n_rows}, pos, sums, d_total + 2, st));
-    uint32_t n_pref;
-    PPV_HIP_TRY(hipMemcpyAsync(&n_pref, d_total + 2, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    PPV_HIP_TRY(hipStreamSynchronize(st));
-    if (n_pref > 0xFFFFFFF0u - 2) return PPV_ERANGE;
-    const uint32_t G = n_pref + 1;                                   // with the empty prefix
-    // the scan value one past the end closes the last depth
-    PPV_HIP_TRY(hipMemcpyAsync(pos + n_flags, d_total + 2, sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
-    TRY(keep_alloc(&ix->d_ent, (size_t)G + 1, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_node_lo, G, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_node_hi, G, &ix->device_bytes));
-    hipLaunchKernelGGL(fill_nodes, dim3(blocks_for(std::max<uint64_t>(n_flags, 1))), dim3(BT), 0, st,
-                       (const int32_t *)ix->d_x_tok, (const int64_t *)ix->d_x_off, (const int32_t *)row_lcp,
-                       (const uint32_t *)pos, (uint64_t)n_rows, l_max, G, ix->d_ent, ix->d_node_lo);
-
-    // ---- 5. hi, deepest depth first (a prefix ends where its last child ends, so the children's depth comes first)
-    uint32_t *h_base = new (std::nothrow) uint32_t[(size_t)l_max + 2];
-    if (!h_base) return PPV_ENOMEM;
-    PPV_HIP_TRY(hipStreamSynchronize(st));
-    const ppv_status rc_base = depth_bases(ix, G, l_max, h_base);
-    if (rc_base != PPV_OK) {
-        delete[] h_base;
-        return rc_base;
+    TRY(measure());
+    bool again = false;
+    for (uint32_t m = words.w->large; m > 0;) {
+        // rows in groups too large to count: sorted by their next tokens under the group's number
+        again = true;
+        TRY(exclusive_scan<uint64_t>(n, LargeRows{group, n}, place, sums64, d_tot64, st));
+        uint64_t tot;
+        TRY(read_back(&tot, d_tot64, 1, st));
+        int group_bits = 1;
+        while ((1ull << group_bits) < (tot & 0xFFFFFFFFull)) group_bits++;
+        KeyShape ls = ks;
+        ls.slots = (int)std::min<int64_t>((64 - group_bits) / ks.bits, l_max - depth);
+        uint32_t *lrow = row2, *lrow2 = info, *lplace = (uint32_t *)rows;   // (written by measure, which comes later)
+        uint64_t *lkey = key, *lkey2 = key2;
+        hipLaunchKernelGGL(large_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
+                           (const uint8_t *)group, (const uint64_t *)place, n, (uint32_t)depth, ls, lkey, lrow, lplace);
+        TRY(radix_sort(lkey, lkey2, lrow, lrow2, m, ls.bits * ls.slots + group_bits, hist, digit_total, st));
+        depth += ls.slots;
+        hipLaunchKernelGGL(large_back, dim3(blocks_for(m)), dim3(BT), 0, st, (const uint64_t *)lkey, (const uint32_t *)lrow,
+                           (const uint32_t *)lplace, m, last_slot, depth >= l_max ? 1 : 0, row, group);
+        if (depth >= l_max) break;
+        PPV_HIP_TRY(hipMemsetAsync(d_word, 0, sizeof(uint32_t), st));
+        order();
+        TRY(read_back(&m, d_word, 1, st));
     }
-    for (int d = l_max; d >= 1; d--) {
-        const uint32_t g0 = h_base[d], g1 = h_base[d + 1];
-        if (g1 > g0)
-            hipLaunchKernelGGL(fill_hi, dim3(blocks_for(g1 - g0)), dim3(BT), 0, st, (const NodeEnt *)ix->d_ent,
-                               (const uint32_t *)ix->d_node_lo, g0, g1, ix->d_node_hi);
-    }
-    delete[] h_base;
-    hipLaunchKernelGGL(fill_hi, dim3(1), dim3(BT), 0, st, (const NodeEnt *)ix->d_ent, (const uint32_t *)ix->d_node_lo,
-                       0u, 1u, ix->d_node_hi);                       // the empty prefix: all of S
-    PPV_HIP_TRY(hipGetLastError());
-
-    // ---- 6. heavy prefixes
-    TRY(finish_heavy(ix, G, vocab, st));
-    TRY(finish_lookup(ix, G, l_max, st));
-
-    ix->n_tokens = n_tok;
-    ix->view.ent = ix->d_ent;
-    ix->view.node_lo = ix->d_node_lo;
-    ix->view.node_hi = ix->d_node_hi;
-    ix->view.n_nodes = G;
-    ix->view.n_rows = n_rows;
-    ix->view.vocab = vocab;
-    ix->view.l_max = l_max;
-    return PPV_OK;
+    if (again) TRY(measure());
+    const uint32_t n_rows = (uint32_t)(words.w->rows_tokens >> 32), n_tok = (uint32_t)words.w->rows_tokens;
+    return number_prefixes(ix, tok, rows, n_rows, n_tok, l_max, counts, n_groups, group_lcp, words.w->prefixes,
+                           words.w->all_counts - words.w->prefixes, vocab, words, st);
 }
 
 void release(ppv_index *ix) {
     if (!ix) return;
-    (void)hipFree(ix->d_ent);
-    (void)hipFree(ix->d_node_lo);
-    (void)hipFree(ix->d_node_hi);
-    (void)hipFree(ix->d_heavy_slot);
-    (void)hipFree(ix->d_heavy_bits);
-    (void)hipFree(ix->d_heavy_rank);
-    (void)hipFree(ix->d_lookup);
-    (void)hipFree(ix->d_depth_base);
-    (void)hipFree(ix->d_node_xpos);
-    (void)hipFree(ix->d_x_tok);
-    (void)hipFree(ix->d_x_off);
+    if (ix->block || ix->heavy_block) {
+        // the blocks go to the next index, so every kernel that may still read them has to be over (as hipFree would
+        // wait for it); the wait is no part of a capture that another stream may be in
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        int dev = -1;
+        (void)hipGetDevice(&dev);
+        if (ix->device >= 0 && ix->device != dev) (void)hipSetDevice(ix->device);
+        (void)hipDeviceSynchronize();
+        if (ix->device >= 0 && ix->device != dev && dev >= 0) (void)hipSetDevice(dev);
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        (void)hipGetLastError();
+        ppv_pool_give(ix->block);
+        ppv_pool_give(ix->heavy_block);
+    }
     delete ix;
 }
 
@@ -772,26 +1144,37 @@ struct Section {
     bool entries;   // NodeEnt array: the heavy flag is not stored
 };
 
-// structural checks of a loaded index: whatever the file held, the kernels must stay inside the arrays
-__global__ __launch_bounds__(BT) void check_loaded_nodes(const NodeEnt *__restrict__ ent,
-                                                         const uint32_t *__restrict__ node_lo,
-                                                         const uint32_t *__restrict__ node_hi, uint32_t n_nodes,
-                                                         uint32_t n_rows, uint32_t vocab, int32_t *__restrict__ err) {
+// A loaded file is only believed as far as it can be checked: the rows have to be rows, in order, and everything else
+// in it has to be what numbering those rows' prefixes gives.
+__global__ __launch_bounds__(BT) void compare_loaded(const NodeEnt *__restrict__ ent, const uint32_t *__restrict__ node_lo,
+                                                     const uint32_t *__restrict__ node_hi, const NodeEnt *__restrict__ f_ent,
+                                                     const uint32_t *__restrict__ f_lo, const uint32_t *__restrict__ f_hi,
+                                                     uint32_t n_nodes, int32_t *__restrict__ err) {
     const uint32_t g = blockIdx.x * BT + threadIdx.x;
-    if (g >= n_nodes) return;
-    const uint32_t c0 = ent[g].child, c1 = ent[g + 1].child;
-    bool bad = c0 > c1 || c1 > n_nodes || (c1 > c0 && c0 <= g);   // children lie after their parent
-    bad = bad || (ent[g].tok & PPV_NODE_HEAVY) != 0u || (g > 0 && (ent[g].tok & PPV_NODE_TOKEN) >= vocab);
-    bad = bad || !(node_lo[g] < node_hi[g] && node_hi[g] <= n_rows);
-    if (g == 0) bad = bad || c0 != 1u;
-    if (g == n_nodes - 1) bad = bad || c1 != n_nodes || (ent[n_nodes].tok & PPV_NODE_HEAVY) != 0u;
-    if (!bad)
-        for (uint32_t c = c0; c + 1 < c1; c++)   // siblings in strictly increasing token order
-            if ((ent[c].tok & PPV_NODE_TOKEN) >= (ent[c + 1].tok & PPV_NODE_TOKEN)) {
-                bad = true;
-                break;
-            }
+    if (g > n_nodes) return;
+    bool bad = (ent[g].tok & ~PPV_NODE_HEAVY) != f_ent[g].tok || ent[g].child != f_ent[g].child;
+    if (g < n_nodes) bad = bad || node_lo[g] != f_lo[g] || node_hi[g] != f_hi[g];
     if (bad) atomicOr(err, 1);
+}
+// the rows of a checked file as the numbering wants them; they have to be in strictly increasing order
+__global__ __launch_bounds__(BT) void meta_of_rows(const int32_t *__restrict__ x_tok, const int64_t *__restrict__ x_off,
+                                                   uint32_t n_rows, RowMeta *__restrict__ rows, int32_t *__restrict__ err) {
+    const uint32_t i = blockIdx.x * BT + threadIdx.x;
+    if (i >= n_rows) return;
+    const uint32_t a = (uint32_t)x_off[i], la = (uint32_t)(x_off[i + 1] - x_off[i]);
+    uint32_t c = 0;
+    if (i > 0) {
+        const uint32_t b = (uint32_t)x_off[i - 1], lb = a - b;
+        const uint32_t m = la < lb ? la : lb;
+        while (c < m && x_tok[a + c] == x_tok[b + c]) c++;
+        if (c < m ? x_tok[a + c] < x_tok[b + c] : la <= lb) atomicOr(err, 4);
+    }
+    RowMeta r;
+    r.at = a;
+    r.src = a;
+    r.lcp = c;
+    r.len = la;
+    rows[i] = r;
 }
 __global__ __launch_bounds__(BT) void check_loaded_rows(const int32_t *__restrict__ x_tok, const int64_t *__restrict__ x_off,
                                                         uint64_t n_rows, uint64_t n_tokens, int32_t vocab, int32_t l_max,
@@ -880,13 +1263,30 @@ ppv_status load_from_file(FILE *f, ppv_index *ix) {
         (void)hipGetLastError();
         return PPV_EDEVICE;
     }
-    ix->device_bytes = 0;
-    TRY(keep_alloc(&ix->d_ent, (size_t)h.n_nodes + 1, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_node_lo, (size_t)h.n_nodes, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_node_hi, (size_t)h.n_nodes, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_x_off, (size_t)h.n_rows + 1, &ix->device_bytes));
-    TRY(keep_alloc(&ix->d_x_tok, (size_t)h.n_tokens, &ix->device_bytes));
-    void *dev[5] = {ix->d_ent, ix->d_node_lo, ix->d_node_hi, ix->d_x_off, ix->d_x_tok};
+    const uint32_t n_rows = (uint32_t)h.n_rows, n_groups = (n_rows + WAVE - 1) / WAVE;
+    const uint64_t n_counts = ((uint64_t)h.l_max + 1) * n_groups;
+    if (n_counts > 0xFFFFFFF0ull) return PPV_ERANGE;
+    NodeEnt *f_ent;
+    uint32_t *f_lo, *f_hi, *counts, *group_lcp, *sums, *d_word;
+    int64_t *f_off;
+    int32_t *f_tok, *d_err;
+    uint64_t *d_tot64;
+    RowMeta *rows;
+    TempArena tmp;
+    tmp.add(&f_ent, h.n_nodes + 1);
+    tmp.add(&f_lo, h.n_nodes);
+    tmp.add(&f_hi, h.n_nodes);
+    tmp.add(&f_off, h.n_rows + 1);
+    tmp.add(&f_tok, h.n_tokens);
+    tmp.add(&rows, n_rows);
+    tmp.add(&counts, n_counts);
+    tmp.add(&group_lcp, n_groups);
+    tmp.add(&sums, scan_words(n_counts));
+    tmp.add(&d_tot64, 1);
+    tmp.add(&d_word, 1);
+    tmp.add(&d_err, 1);
+    TRY(tmp.take());
+    void *dev[5] = {f_ent, f_lo, f_hi, f_off, f_tok};
     unsigned char *stage = new (std::nothrow) unsigned char[IO_CHUNK];
     if (!stage) return PPV_ENOMEM;
     ppv_status st = PPV_OK;
@@ -908,34 +1308,37 @@ ppv_status load_from_file(FILE *f, ppv_index *ix) {
     if (st != PPV_OK) return st;
     if (sum != h.checksum) return PPV_EINVAL;
 
+    const HostWords words;
+    if (!words.w) return PPV_ENOMEM;
     // the checksum guards against damage; these checks guard the kernels against a file that was wrong when written
     hipStream_t s0 = nullptr;
-    DeviceBuffers tmp;
-    int32_t *d_err;
-    TRY(tmp.alloc(&d_err, 1));
     PPV_HIP_TRY(hipMemsetAsync(d_err, 0, sizeof(int32_t), s0));
-    hipLaunchKernelGGL(check_loaded_nodes, dim3(blocks_for(h.n_nodes)), dim3(BT), 0, s0, (const NodeEnt *)ix->d_ent,
-                       (const uint32_t *)ix->d_node_lo, (const uint32_t *)ix->d_node_hi, (uint32_t)h.n_nodes,
-                       (uint32_t)h.n_rows, (uint32_t)h.vocab, d_err);
     hipLaunchKernelGGL(check_loaded_rows, dim3(blocks_for(std::max(h.n_rows, h.n_tokens))), dim3(BT), 0, s0,
-                       (const int32_t *)ix->d_x_tok, (const int64_t *)ix->d_x_off, h.n_rows, h.n_tokens, h.vocab, h.l_max,
-                       d_err);
+                       (const int32_t *)f_tok, (const int64_t *)f_off, h.n_rows, h.n_tokens, h.vocab, h.l_max, d_err);
     PPV_HIP_TRY(hipGetLastError());
     int32_t err = 0;
-    PPV_HIP_TRY(hipMemcpy(&err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost));
+    TRY(read_back(&err, d_err, 1, s0));
     if (err != 0) return PPV_EINVAL;
-
-    TRY(finish_heavy(ix, (uint32_t)h.n_nodes, h.vocab, s0));
-    TRY(finish_lookup(ix, (uint32_t)h.n_nodes, h.l_max, s0));
-    ix->n_tokens = (int64_t)h.n_tokens;
-    ix->view.ent = ix->d_ent;
-    ix->view.node_lo = ix->d_node_lo;
-    ix->view.node_hi = ix->d_node_hi;
-    ix->view.n_nodes = (uint32_t)h.n_nodes;
-    ix->view.n_rows = (uint32_t)h.n_rows;
-    ix->view.vocab = h.vocab;
-    ix->view.l_max = h.l_max;
-    return PPV_OK;
+    hipLaunchKernelGGL(meta_of_rows, dim3(blocks_for(n_rows)), dim3(BT), 0, s0, (const int32_t *)f_tok, (const int64_t *)f_off,
+                       n_rows, rows, d_err);
+    const uint64_t tot64 = h.n_rows << 32;
+    PPV_HIP_TRY(hipMemcpyAsync(d_tot64, &tot64, sizeof(tot64), hipMemcpyHostToDevice, s0));
+    hipLaunchKernelGGL(count_prefixes, dim3((n_groups + BW - 1) / BW), dim3(BT), 0, s0, (const RowMeta *)rows,
+                       (const uint64_t *)d_tot64, n_groups, h.l_max, counts, group_lcp);
+    TRY(exclusive_scan<uint32_t>(n_counts, ValueAt<uint32_t>{counts}, counts, sums, d_word, s0));
+    uint32_t n_all, n_pref;
+    PPV_HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof(err), hipMemcpyDeviceToHost, s0));
+    PPV_HIP_TRY(hipMemcpyAsync(&n_all, d_word, sizeof(n_all), hipMemcpyDeviceToHost, s0));
+    TRY(read_back(&n_pref, counts + (uint64_t)h.l_max * n_groups, 1, s0));
+    if (err != 0 || (uint64_t)n_pref + 1 != h.n_nodes) return PPV_EINVAL;
+    TRY(number_prefixes(ix, FlatTokens{f_tok}, (const RowMeta *)rows, n_rows, (uint32_t)h.n_tokens, h.l_max, counts, n_groups,
+                        group_lcp, n_pref, n_all - n_pref, h.vocab, words, s0));
+    hipLaunchKernelGGL(compare_loaded, dim3(blocks_for(h.n_nodes + 1)), dim3(BT), 0, s0, (const NodeEnt *)ix->d_ent,
+                       (const uint32_t *)ix->d_node_lo, (const uint32_t *)ix->d_node_hi, (const NodeEnt *)f_ent,
+                       (const uint32_t *)f_lo, (const uint32_t *)f_hi, (uint32_t)h.n_nodes, d_err);
+    PPV_HIP_TRY(hipGetLastError());
+    TRY(read_back(&err, d_err, 1, s0));
+    return err == 0 ? PPV_OK : PPV_EINVAL;
 }
 
 }  // namespace

@@ -28,6 +28,12 @@ struct NodeEnt {
     uint32_t child;  // first child; the children end where the next entry's children begin
 };
 
+struct alignas(16) LookupEntry {
+    uint64_t key;      // fingerprint << 32 | node; 0: empty
+    uint32_t at;       // where the first member under the node starts in x_tok
+    uint32_t extent;   // the prefix's length; << 8: that member's length (at most a wavefront's), if it is the only one
+};
+
 struct IndexView {
     const NodeEnt *ent;          // [n_nodes+1] (the last entry is a sentinel that closes the offsets)
     const uint32_t *node_lo;     // [n_nodes]   rank of the first member the prefix is a prefix of
@@ -35,14 +41,13 @@ struct IndexView {
     const uint32_t *heavy_slot;  // [heavy_limit] slot of a heavy node, PPV_NO_SLOT otherwise
     const uint32_t *heavy_bits;  // [n_heavy, n_words] valid-set images
     const uint32_t *heavy_rank;  // [n_heavy, n_words] children before each word
-    // Hashed look-up of whole prefixes (all lengths of a query are probed at once instead of one level after
-    // the other): open addressing, 8 bytes per slot = fingerprint << 32 | node, 0 = empty; lookup_size == 0:
-    // no table.  A hit is only a hint: it is checked against the node's depth and the tokens of its first member.
-    const uint64_t *lookup;      // [lookup_size]
-    const uint32_t *depth_base;  // [l_max + 2] nodes of depth d are depth_base[d] .. depth_base[d+1]
-    const uint32_t *node_xpos;   // [n_nodes] where the first member under the node starts in x_tok (with a table only)
-    const int32_t *x_tok;        // sorted S, flat: row r is x_tok[x_off[r] .. x_off[r+1])
-    const int64_t *x_off;        // [n_rows + 1]
+    // Hashed look-up of prefixes (all lengths of a query are probed at once instead of one level after the other):
+    // open addressing, lookup_size == 0: no table.  A hit is only a hint: it is checked against the tokens of the
+    // first member under the prefix it names.  Prefixes of one member only are entered up to the shortest of them
+    // (LookupEntry::extent); the longer ones are found by comparing that member's tokens and reading node_at.
+    const LookupEntry *lookup;   // [lookup_size]
+    const uint32_t *node_at;     // [tokens of S] (with a table) by position in x_tok: the node that ends there, for prefixes of one member
+    const int32_t *x_tok;        // sorted S, flat
     uint32_t lookup_size;
     uint32_t lookup_fp_mask;     // fingerprint bits in use (all of them; 0 in a test mode that makes every probe a false hit)
     uint32_t heavy_limit;        // nodes >= heavy_limit are not heavy
@@ -97,15 +102,29 @@ struct ppv_index {
     NodeEnt *d_ent;
     uint32_t *d_node_lo, *d_node_hi;
     uint32_t *d_heavy_slot, *d_heavy_bits, *d_heavy_rank;
-    uint64_t *d_lookup;
-    uint32_t *d_depth_base, *d_node_xpos;
+    LookupEntry *d_lookup;
+    uint32_t *d_node_at;
     int32_t *d_x_tok;    // sorted S, flat, no padding: row r is d_x_tok[d_x_off[r] .. d_x_off[r+1])
     int64_t *d_x_off;    // [n_rows + 1]
     int64_t n_tokens;
     int64_t n_heavy;
     int64_t device_bytes;
+    void *block, *heavy_block;   // the pool's blocks that the arrays above lie in
     int device;
 };
+
+// Device memory kept from one index to the next, and the upload of a set (ppv_pool.hip).  ppv_pool_give: the device has
+// finished with the block.
+ppv_status ppv_pool_take(void **out, size_t bytes);
+void ppv_pool_give(void *block);
+// A little pinned memory that kernels can write (nullptr: none to be had).
+constexpr int PPV_HOST_WORDS_BYTES = 64;
+void *ppv_host_words_take();
+void ppv_host_words_give(void *words);
+// Checks S (host CSR) and enqueues its copy to the device in packed form: the tokens' lower 16 bits, the bits above
+// them (d_hi, nullptr where the vocabulary has none), the offsets.  Returns when the host arrays have been read.
+ppv_status ppv_upload_set(const int32_t *tokens, const int64_t *offsets, int64_t n_seq, int32_t vocab, uint16_t *d_lo,
+                          uint8_t *d_hi, uint32_t *d_off, hipStream_t st, int32_t *l_max);
 
 // Current value of a tuning / test switch (PPV_TUNE_* of ppv.h): read from the environment once at load,
 // changed by ppv_tuning_set.

@@ -143,9 +143,11 @@ __device__ inline PrefixHash prefix_hash_scan(const PrefixHash &x) {
 
 // Locates the prefix.  With a look-up table every length of the prefix is probed at once (lane d hashes
 // tokens 0..d); the deepest hit is checked exactly -- its node must have that depth and the first member
-// under it must begin with these tokens -- and the descent then starts there: nothing is left to descend
-// when the whole prefix is in the index, one failing step (which yields the rank) when it is not.  A hit
-// that fails the check (a fingerprint collision) only costs the shortcut: the descent starts at the root.
+// under it must begin with these tokens.  If that member is the only one under the node, the tokens that follow are
+// compared with it in the same step, and the deepest node they reach is read off (node_at).  The descent then starts
+// there: nothing is left to descend when the whole prefix is in the index, one failing step (which yields the rank)
+// when it is not.  A hit that fails the check (a fingerprint collision) only costs the shortcut: the descent starts at
+// the root.
 // `mine` = first_tokens(prefix, stride, lane), requested by the caller before the prefix's length is known.
 __device__ inline int32_t first_tokens(const int32_t *__restrict__ prefix, int stride, int lane) {
     return (lane < stride) ? prefix[lane] : 0;
@@ -159,13 +161,15 @@ __device__ inline Walk walk_prefix(const IndexView &ix, const int32_t *__restric
         uint32_t slot, fp;
         prefix_hash_finish(prefix_hash_scan(prefix_hash_token((uint32_t)mine)), ix.lookup_size, ix.lookup_fp_mask, &slot,
                            &fp);
-        uint32_t cand = PPV_NO_SLOT;
+        uint32_t cand = PPV_NO_SLOT, at = 0u, extent = 0u;
         if (lane < tl) {
             for (uint32_t n = 0; n < ix.lookup_size; n++) {   // ends at the first empty slot (the table is half empty)
-                const uint64_t e = ix.lookup[slot];
-                if (e == 0ull) break;
-                if ((uint32_t)(e >> 32) == fp) {
-                    cand = (uint32_t)e;
+                const uint4 e = *(const uint4 *)&ix.lookup[slot];   // node, fingerprint, at, extent
+                if ((e.x | e.y) == 0u) break;
+                if (e.y == fp) {
+                    cand = e.x;
+                    at = e.z;
+                    extent = e.w;
                     break;
                 }
                 slot = slot + 1u == ix.lookup_size ? 0u : slot + 1u;
@@ -174,17 +178,20 @@ __device__ inline Walk walk_prefix(const IndexView &ix, const int32_t *__restric
         const uint64_t hits = __ballot(cand != PPV_NO_SLOT);
         if (hits) {
             const int D = 63 - __clzll((long long)hits);   // deepest level with a hit: prefix length D + 1
-            const uint32_t g = lane_value(cand, D);
-            // everything that depends on g alone goes out together (the table holds valid nodes only), the rank
-            // range included; the member's tokens wait for the depth check, which is what says they are there
-            const uint32_t d0 = ix.depth_base[D + 1], d1 = ix.depth_base[D + 2];
-            const NodeEnt e0 = ix.ent[g], e1 = ix.ent[g + 1];
-            const uint32_t a = ix.node_xpos[g];
-            const uint32_t g_lo = ix.node_lo[g], g_hi = ix.node_hi[g];
-            if (g >= d0 && g < d1) {   // a node of depth D+1: its first member has D+1 tokens or more
-                const bool same = lane > D || ix.x_tok[(size_t)a + lane] == mine;
-                if (__ballot(!same) == 0ull) {
-                    if (D + 1 == t) {   // the whole prefix: nothing left to descend
+            uint32_t g = lane_value(cand, D);
+            const uint32_t a = lane_value(at, D), ext = lane_value(extent, D);
+            if ((ext & 0xFFu) == (uint32_t)D + 1u) {   // a node of depth D+1: its first member has D+1 tokens or more
+                const int alone = (int)(ext >> 8);      // 0: several members
+                const int n = alone ? (alone < tl ? alone : tl) : D + 1;   // tokens to compare: all of them the member's
+                // everything that depends on the entry alone goes out together: the member's tokens, and what the walk
+                // returns if the n tokens agree
+                if (alone) g = ix.node_at[(size_t)a + n - 1];
+                const bool same = lane >= n || ix.x_tok[(size_t)a + lane] == mine;
+                const NodeEnt e0 = ix.ent[g], e1 = ix.ent[g + 1];
+                const uint32_t g_lo = ix.node_lo[g], g_hi = ix.node_hi[g];
+                const uint64_t differ = __ballot(!same);
+                if (differ == 0ull) {
+                    if (n == t) {   // the whole prefix: nothing left to descend
                         Walk w;
                         w.node = g;
                         w.cb = e0.child;
@@ -196,7 +203,12 @@ __device__ inline Walk walk_prefix(const IndexView &ix, const int32_t *__restric
                         w.member = (e0.tok & PPV_NODE_TERMINAL) != 0u;
                         return w;
                     }
-                    return walk_from(ix, prefix, t, lane, mine, D + 1, g, e0.tok, e0.child, e1.child);
+                    return walk_from(ix, prefix, t, lane, mine, n, g, e0.tok, e0.child, e1.child);
+                }
+                const int m = __ffsll((long long)differ) - 1;   // tokens that agree
+                if (m > D) {   // (alone) as far as the member goes along
+                    g = ix.node_at[(size_t)a + m - 1];
+                    return walk_from(ix, prefix, t, lane, mine, m, g, ix.ent[g].tok, ix.ent[g].child, ix.ent[g + 1].child);
                 }
             }
         }

@@ -1,0 +1,156 @@
+"""The index builder at the sizes where its steps change over: groups of equal first tokens at and beyond what is ordered
+by counting, several rounds of them, vocabularies at and beyond 16 bits, uploads of several slots and more than the ring
+holds, rows too long for the staging in LDS, more heavy prefixes than the index's block has room for, and prefixes that
+leave a member behind the point where it is alone.  Everything against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2504_09135_amd import binding as ppv
+from paper_2504_09135_amd import workloads as W
+
+from gpu_helpers import assert_query_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def csr(rows, lens):
+    offsets = np.zeros(len(lens) + 1, np.int64)
+    np.cumsum(lens, out=offsets[1:])
+    keep = np.arange(rows.shape[1])[None, :] < np.asarray(lens)[:, None]
+    return np.ascontiguousarray(rows[keep], dtype=np.int32), offsets
+
+
+def prefixes_of(tokens, offsets, V, rng, n, stride):
+    """Prefixes of members: as they are, with a wrong token at any place, and beyond a member's end."""
+    P = np.full((n, stride), W.PAD_TOKEN, np.int32)
+    L = np.zeros(n, np.int32)
+    who = rng.integers(0, len(offsets) - 1, n)
+    for i, w in enumerate(who):
+        row = tokens[offsets[w]:offsets[w + 1]][:stride]
+        k = int(rng.integers(0, len(row) + 1))
+        P[i, :k] = row[:k]
+        kind = i % 4
+        if kind == 1 and k:
+            P[i, int(rng.integers(0, k))] = int(rng.integers(0, V))
+        elif kind == 2 and k < stride:
+            P[i, k] = int(rng.integers(0, V))
+            k += 1
+        elif kind == 3 and k:
+            P[i, k - 1] = int(rng.integers(0, V))
+        L[i] = k
+    return P, L
+
+
+def check(tokens, offsets, V, rng, n_prefixes=300, stride=None):
+    trie = oracle.Trie(tokens, offsets, V)
+    index = ppv.ppv_build_index(tokens, offsets, V)
+    assert (index.n_distinct, index.l_max, index.n_prefixes) == (trie.n_members, trie.l_max, trie.n_nodes - 1)
+    got_t, got_o = ppv.ppv_index_export(index)
+    P, L = prefixes_of(tokens, offsets, V, rng, n_prefixes, stride or index.l_max + 2)
+    assert_query_parity(index, trie, P, L)
+    index.free()
+    return got_t, got_o
+
+
+@pytest.mark.parametrize("group", [2, 255, 512, 1024, 1025, 3000])
+@pytest.mark.parametrize("V,stem,tail", [(300, 6, 3), (32_000, 4, 1), (70_000, 9, 6), (1_000, 40, 30)])
+def test_groups_of_equal_first_tokens(group, V, stem, tail):
+    """`group` rows that share their first `stem` tokens (and some that are duplicates, or end there), among others."""
+    rng = np.random.default_rng(group * 7 + V)
+    s = rng.integers(0, V, stem)
+    rows = rng.integers(0, min(V, 40), (group + 500, stem + tail))
+    rows[:group, :stem] = s
+    lens = rng.integers(1, stem + tail + 1, group + 500)
+    lens[:group] = rng.integers(stem, stem + tail + 1, group)
+    rows[group // 2] = rows[0]
+    lens[group // 2] = lens[0]
+    order = rng.permutation(group + 500)
+    tokens, offsets = csr(rows[order], lens[order])
+    got_t, got_o = check(tokens, offsets, V, rng)
+    rows_out = [tuple(got_t[a:b]) for a, b in zip(got_o[:-1], got_o[1:])]
+    assert rows_out == sorted({tuple(tokens[a:b]) for a, b in zip(offsets[:-1], offsets[1:])})
+
+
+@pytest.mark.parametrize("V", [1, 2, 65_535, 65_536, 65_537, ppv.PPV_MAX_VOCAB])
+def test_vocabularies_at_the_edges_of_the_packed_forms(V):
+    rng = np.random.default_rng(V)
+    rows = rng.integers(max(0, V - 50), V, (2_000, 7))
+    rows[::3] = rng.integers(0, V, rows[::3].shape)
+    tokens, offsets = csr(rows, rng.integers(1, 8, 2_000))
+    check(tokens, offsets, V, rng)
+    for bad in (V, -1):
+        wrong = tokens.copy()
+        wrong[len(wrong) // 2] = bad
+        with pytest.raises(ppv.PPVError):
+            ppv.ppv_build_index(wrong, offsets, V)
+
+
+@pytest.mark.parametrize("n,L,V", [(131_071, 2, 500), (131_073, 2, 70_000), (600_000, 30, 70_000)])
+def test_uploads_of_several_slots(n, L, V):
+    """Around a slot of offsets, several slots of tokens, and 18M tokens (more slots than the ring has)."""
+    rng = np.random.default_rng(n)
+    rows = rng.integers(0, V, (n, L), dtype=np.int32)
+    lens = np.full(n, L)
+    tokens, offsets = csr(rows, lens)
+    index = ppv.ppv_build_index(tokens, offsets, V)
+    got_t, got_o = ppv.ppv_index_export(index)
+    # row order by the radix-free route: numpy's lexicographic sort
+    srt = rows[np.lexsort(rows.T[::-1])]
+    keep = np.concatenate([[True], (srt[1:] != srt[:-1]).any(axis=1)])
+    assert np.array_equal(got_t.reshape(-1, L), srt[keep]) and got_o[-1] == got_t.size
+    index.free()
+    for at in (0, n // 2, n - 1):
+        broken = offsets.copy()
+        broken[at + 1] = broken[at]                          # an empty sequence, in the first, a middle and the last slot
+        with pytest.raises(ppv.PPVError):
+            ppv.ppv_build_index(tokens, broken, V)
+    wrong = tokens.copy()
+    wrong[-1] = V
+    with pytest.raises(ppv.PPVError):
+        ppv.ppv_build_index(wrong, offsets, V)
+
+
+@pytest.mark.parametrize("lens_of_64", [(1, 1), (64, 64), (1, 64), (65, 66), (200, 400)])
+def test_rows_around_the_staging_in_lds(lens_of_64):
+    """64 rows that fit their wavefront's LDS and 64 that do not, next to each other."""
+    rng = np.random.default_rng(lens_of_64[1])
+    a, b = lens_of_64
+    lens = rng.integers(a, b + 1, 900)
+    lens[:300] = 1 + lens[:300] // 8
+    rows = rng.integers(0, 90, (900, int(lens.max())))
+    rows[:, 0] = np.arange(900) // 13
+    tokens, offsets = csr(rows, lens)
+    check(tokens, offsets, 90, rng)
+
+
+@pytest.mark.parametrize("heads", [250, 256, 257, 700])
+def test_number_of_heavy_prefixes(heads):
+    """`heads` second-level prefixes (and the root) with more than V / 32 children each."""
+    V = 1_024
+    rng = np.random.default_rng(heads)
+    first = rng.choice(V, heads - 1, replace=False)
+    rows = np.array([(f, c) for f in first for c in rng.choice(V, 40, replace=False)])
+    tokens, offsets = csr(rows, np.full(len(rows), 2))
+    check(tokens, offsets, V, rng)
+
+
+def test_builds_one_after_another_reuse_memory():
+    """Indices of different sizes built, queried and freed in turn, two of them alive at a time."""
+    rng = np.random.default_rng(5)
+    alive = []
+    for k in range(12):
+        n = int(rng.integers(10, 60_000))
+        V = int(rng.integers(5, 90_000))
+        rows = rng.integers(0, V, (n, 6), dtype=np.int32)
+        tokens, offsets = csr(rows, rng.integers(1, 7, n))
+        trie = oracle.Trie(tokens, offsets, V)
+        index = ppv.ppv_build_index(tokens, offsets, V)
+        P, L = prefixes_of(tokens, offsets, V, rng, 64, 8)
+        alive.append((index, trie, P, L))
+        for ix, t, p, l in alive:
+            assert_query_parity(ix, t, p, l)
+        if len(alive) == 2:
+            alive.pop(int(rng.integers(0, 2)))[0].free()
+    torch.cuda.synchronize()
