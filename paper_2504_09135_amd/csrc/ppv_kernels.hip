@@ -32,8 +32,8 @@ constexpr int MAX_TILES = PPV_MAX_TILES;
 constexpr float LN2F = 0.693147180559945309417f;
 static_assert(PPV_MAX_VOCAB <= MAX_TILES * 1024, "tile bookkeeping too small");
 
-__device__ inline float fast_exp2(float y) { return __builtin_amdgcn_exp2f(y); }  // v_exp_f32, 1 ulp
-__device__ inline float fast_log2(float y) { return __builtin_amdgcn_logf(y); }   // v_log_f32, 1 ulp (normal inputs)
+__device__ __forceinline__ float fast_exp2(float y) { return __builtin_amdgcn_exp2f(y); }  // v_exp_f32, 1 ulp
+__device__ __forceinline__ float fast_log2(float y) { return __builtin_amdgcn_logf(y); }   // v_log_f32, 1 ulp (normal inputs)
 // exp(d) for d <= 0 with the rounding of d*log2(e) compensated (used once per tile, not per token)
 // Temperature (Algorithm 1's input T): P = softmax(logits / T).  The division is folded into the constant of the
 // exponentials, c = log2(e) / T, so that it costs nothing per token; differences of logits that enter a result
@@ -41,10 +41,10 @@ __device__ inline float fast_log2(float y) { return __builtin_amdgcn_logf(y); } 
 struct Temper {
     float c;
     float inv;
-    float guard;   // how far above a tile's reference a logit may lie (REF_GUARD * T, see tile_stats)
+    float guard;   // how far above an image tile's reference a logit may lie (REF_GUARD * T, see tile_stats)
 };
 
-__device__ inline float exp_scale(float d, float c) {
+__device__ __forceinline__ float exp_scale(float d, float c) {
     float hi = d * c;
     float lo = fmaf(d, c, -hi);
     return fast_exp2(hi) * fmaf(lo, LN2F, 1.0f);
@@ -158,25 +158,40 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(IndexView ix, c
 // Tiles.  A tile is what one wavefront loads with four 16-byte loads per lane: 2048 bf16 or 1024
 // fp32 tokens.  Load j of lane l holds the EPL consecutive tokens starting at
 // tile*TILE + j*64*EPL + l*EPL, so token order inside a tile is (j, lane, k).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static constexpr int EPL = 4;  // tokens per 16-byte load
-    __device__ static inline void unpack(const uint4 &r, float x[4]) {
+    __device__ static __forceinline__ void unpack(const u32x4 &r, float x[4]) {
         x[0] = __uint_as_float(r.x); x[1] = __uint_as_float(r.y);
         x[2] = __uint_as_float(r.z); x[3] = __uint_as_float(r.w);
     }
-    __device__ static inline uint32_t pad() { return 0xFF800000u; }  // -inf
+    __device__ static __forceinline__ uint32_t pad() { return 0xFF800000u; }  // -inf
 };
 template <> struct Elem<uint16_t> {  // bf16: widening to fp32 is exact
     static constexpr int EPL = 8;
-    __device__ static inline void unpack(const uint4 &r, float x[8]) {
+    __device__ static __forceinline__ void unpack(const u32x4 &r, float x[8]) {
         x[0] = __uint_as_float(r.x << 16); x[1] = __uint_as_float(r.x & 0xFFFF0000u);
         x[2] = __uint_as_float(r.y << 16); x[3] = __uint_as_float(r.y & 0xFFFF0000u);
         x[4] = __uint_as_float(r.z << 16); x[5] = __uint_as_float(r.z & 0xFFFF0000u);
         x[6] = __uint_as_float(r.w << 16); x[7] = __uint_as_float(r.w & 0xFFFF0000u);
     }
-    __device__ static inline uint32_t pad() { return 0xFF80FF80u; }  // two bf16 -inf
+    __device__ static __forceinline__ uint32_t pad() { return 0xFF80FF80u; }  // two bf16 -inf
 };
+// The same as unpack, with values that the compiler takes for new ones each time: what is unpacked is used at once and
+// not kept in registers for another use of the tile (there is one in a rare case, and tiles are held packed).
+template <typename T> __device__ __forceinline__ void unpack_fresh(const u32x4 &r, float x[Elem<T>::EPL]) {
+    if (sizeof(T) == 4) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) x[i] = __uint_as_float(r[i]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            asm volatile("v_lshlrev_b32 %0, 16, %1" : "=v"(x[(2 * i) % Elem<T>::EPL]) : "v"(r[i]));
+            asm volatile("v_and_b32 %0, %2, %1" : "=v"(x[(2 * i + 1) % Elem<T>::EPL]) : "v"(r[i]), "s"(0xFFFF0000u));
+        }
+    }
+}
 template <typename T> struct TileGeom {
     static constexpr int EPL = Elem<T>::EPL;
     static constexpr int PER_LOAD = WAVE * EPL;   // tokens covered by one load of the wave
@@ -186,168 +201,169 @@ template <typename T> struct TileGeom {
 };
 
 struct RawTile {
-    uint4 r[4];
+    u32x4 r[4];
     uint32_t word;   // image path: this lane's word of the tile's mask (requested together with the tile)
 };
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
+// A tile is requested with four unconditional 16-byte loads wherever it lies, also at the row's end and behind it: a group
+// of tokens past the end is read from the row's last group instead, and pad_tile puts -inf there when the tile is
+// used.  Nothing is conditional between request and use, so the compiler can count the loads in flight and wait for
+// exactly the ones a use needs, and the ragged last tile is one like the others.  (A group that straddles the row's end
+// is read whole: rows start on 16-byte boundaries, so it lies inside the 16 bytes that hold the row's last token; what
+// is behind that token is not looked at.)
 template <typename T>
-__device__ inline void load_tile(const T *__restrict__ row, int V, int tile, int lane, RawTile &rt) {
+__device__ __forceinline__ void load_tile(const T *__restrict__ row, int V, int tile, int lane, RawTile &rt) {
     using G = TileGeom<T>;
-    const int base = tile * G::TILE + lane * G::EPL;
-    if ((tile + 1) * G::TILE <= V) {  // wave-uniform: whole tile inside the row
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            u32x4 v = __builtin_nontemporal_load((const u32x4 *)(row + base + j * G::PER_LOAD));
-            rt.r[j] = make_uint4(v.x, v.y, v.z, v.w);
-        }
-    } else {  // ragged tail: never touch memory at or beyond token V; missing tokens are -inf
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const int g = base + j * G::PER_LOAD;
-            if (g + G::EPL <= V) {
-                rt.r[j] = *(const uint4 *)(row + g);
-            } else {
-                uint32_t w[4] = {Elem<T>::pad(), Elem<T>::pad(), Elem<T>::pad(), Elem<T>::pad()};
-                if (sizeof(T) == 4) {
-                    for (int k = 0; k < 4; k++)
-                        if (g + k < V) w[k] = ((const uint32_t *)row)[g + k];
-                } else {
-                    for (int k = 0; k < 8; k++)
-                        if (g + k < V) {
-                            uint32_t h = ((const uint16_t *)row)[g + k];
-                            w[k >> 1] = (k & 1) ? ((w[k >> 1] & 0x0000FFFFu) | (h << 16))
-                                                : ((w[k >> 1] & 0xFFFF0000u) | h);
-                        }
-                }
-                rt.r[j] = make_uint4(w[0], w[1], w[2], w[3]);
-            }
-        }
-    }
-}
-
-// a tile known to lie wholly inside the row: four unconditional streaming loads
-template <typename T>
-__device__ inline void load_full_tile(const T *__restrict__ row, int tile, int lane, RawTile &rt) {
-    using G = TileGeom<T>;
-    const u32x4 *p = (const u32x4 *)(row + (size_t)tile * G::TILE + lane * G::EPL);
+    // byte offsets of 32 bits from a uniform address
+    const uint32_t last = (uint32_t)(V - 1) / G::EPL * 16u;
+    const uint32_t base = ((uint32_t)tile * (4 * WAVE) + (uint32_t)lane) * 16u;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-        u32x4 v = __builtin_nontemporal_load(p + j * WAVE);
-        rt.r[j] = make_uint4(v.x, v.y, v.z, v.w);
+        const uint32_t at = base + j * (WAVE * 16u);
+        rt.r[j] = __builtin_nontemporal_load((const u32x4 *)((const char *)row + (at < last ? at : last)));
+    }
+}
+// The tile's tokens that lie inside the row, counted from this lane's first one (PAD: what is behind the row's end counts
+// as -inf; only the row's last tile has any of that).
+template <typename T> __device__ __forceinline__ int tokens_left(int V, int tile, int lane) {
+    return V - tile * TileGeom<T>::TILE - lane * TileGeom<T>::EPL;
+}
+// group j of a tile, unpacked
+template <typename T, bool PAD> __device__ __forceinline__ void group_of(const RawTile &rt, int j, int left, float x[TileGeom<T>::EPL]) {
+    unpack_fresh<T>(rt.r[j], x);
+    if (PAD) {
+        int in = left - j * TileGeom<T>::PER_LOAD;
+        asm("" : "+v"(in));   // (or the compiler compares `left` with a constant for each token, each in a register of its own)
+#pragma unroll
+        for (int k = 0; k < TileGeom<T>::EPL; k++) x[k] = k < in ? x[k] : -INFINITY;
     }
 }
 
-// A tile requested with four unconditional 16-byte loads wherever it lies: a group of tokens past the row's end is
-// read from the row's last whole group instead (valid memory), and pad_tile_tail, called when the tile is used, puts
-// -inf there.  Nothing is conditional between request and use, so the compiler can count the loads in flight and
-// wait for exactly the ones a use needs.  Needs V % EPL == 0 (no group straddles the row's end).
-template <typename T>
-__device__ inline void load_tile_clamped(const T *__restrict__ row, int V, int tile, int lane, RawTile &rt) {
-    using G = TileGeom<T>;
-    const int base = tile * G::TILE + lane * G::EPL;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const int g = base + j * G::PER_LOAD;
-        const int gc = g < V ? g : V - G::EPL;
-        u32x4 v = __builtin_nontemporal_load((const u32x4 *)(row + gc));
-        rt.r[j] = make_uint4(v.x, v.y, v.z, v.w);
-    }
+// word wi of a V-bit image, with bits at positions >= V cleared (0 beyond the image), in two parts: the load, unconditional
+// (clamped index: a conditional load would make later waits conservative), and what is done to the word once it is
+// used (at the load it would wait for it, and for every tile asked for before).
+__device__ __forceinline__ uint32_t image_word_raw(const uint32_t *__restrict__ image, int wi, int V) {
+    const int last = (V + 31) / 32 - 1;
+    return image[wi < last ? wi : last];
 }
-template <typename T> __device__ inline void pad_tile_tail(RawTile &rt, int V, int tile, int lane) {
-    using G = TileGeom<T>;
-    const int base = tile * G::TILE + lane * G::EPL;
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-        if (base + j * G::PER_LOAD >= V) rt.r[j] = make_uint4(Elem<T>::pad(), Elem<T>::pad(), Elem<T>::pad(), Elem<T>::pad());
-}
-
-// word wi of a V-bit image, with bits at positions >= V cleared (0 beyond the image).  The load
-// itself is unconditional (clamped index): a conditional load would make later waits conservative.
-__device__ inline uint32_t image_word(const uint32_t *__restrict__ image, int wi, int V) {
-    const int n_words = (V + 31) / 32;
-    const int last = n_words - 1;
-    uint32_t w = image[wi < last ? wi : last];
+__device__ __forceinline__ uint32_t image_word_fix(uint32_t w, int wi, int V) {
+    const int last = (V + 31) / 32 - 1;
     if (wi == last && (V & 31)) w &= (1u << (V & 31)) - 1u;
     return wi <= last ? w : 0u;
 }
-// the tile's mask word for this lane (lane l < WORDS holds word l of the tile)
-template <typename T>
-__device__ inline uint32_t tile_mask_word(const uint32_t *__restrict__ image, int tile, int lane, int V) {
+__device__ __forceinline__ uint32_t image_word(const uint32_t *__restrict__ image, int wi, int V) {
+    return image_word_fix(image_word_raw(image, wi, V), wi, V);
+}
+// the tile's mask word for this lane (lane l < WORDS holds word l of the tile), in the same two parts
+template <typename T> __device__ __forceinline__ uint32_t tile_word_raw(const uint32_t *__restrict__ image, int tile, int lane, int V) {
     using G = TileGeom<T>;
-    const uint32_t w = image_word(image, tile * G::WORDS + (lane < G::WORDS ? lane : 0), V);
-    return lane < G::WORDS ? w : 0u;
+    return image_word_raw(image, tile * G::WORDS + (lane < G::WORDS ? lane : 0), V);
+}
+template <typename T> __device__ __forceinline__ uint32_t tile_word_fix(uint32_t w, int tile, int lane, int V) {
+    using G = TileGeom<T>;
+    return lane < G::WORDS ? image_word_fix(w, tile * G::WORDS + lane, V) : 0u;
+}
+template <typename T>
+__device__ __forceinline__ uint32_t tile_mask_word(const uint32_t *__restrict__ image, int tile, int lane, int V) {
+    return tile_word_fix<T>(tile_word_raw<T>(image, tile, lane, V), tile, lane, V);
 }
 
 // mask bits of this lane's EPL tokens of load j, from the tile's mask words (lane l < WORDS holds word l)
-template <typename T> __device__ inline uint32_t lane_bits(uint32_t tile_word, int j, int lane) {
+template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t tile_word, int j, int lane) {
     using G = TileGeom<T>;
     uint32_t w = (uint32_t)__shfl((int)tile_word, j * (G::WORDS / 4) + lane / G::LANES_PER_WORD, WAVE);
     return (w >> ((lane % G::LANES_PER_WORD) * G::EPL)) & ((1u << G::EPL) - 1u);
 }
 
 // Statistics of one tile: a reference m, sum_all = sum exp(x - m), and (IMAGE) sum_val over valid tokens.
-// Any reference near the tile's maximum gives the same sums up to rounding, so the reduction over the
-// wavefront that the exact maximum would need is avoided: m is the maximum of lane 0's own tokens (one
-// readfirstlane), as long as no token of the tile lies more than REF_GUARD * T above it (one compare over the
-// lanes' maxima); otherwise, and when lane 0 holds nothing but -inf, m is the exact maximum.  Either way m
-// depends on the row's values alone, not on how the row is split over wavefronts.  m = -inf: an empty tile.
+// Any reference gives the same sums up to rounding as long as they stay inside fp32's range, so neither the maximum nor
+// the reduction over the wavefront it would need are computed.
+//   without an image   only the sum over all tokens is wanted, and it only ever enters a logarithm: m is the largest of
+//          lane 0's first 16 bytes (one readfirstlane).  Where those hold nothing but -inf, or a token lies about 69 T
+//          above m, the sum is not inside SUM_MOST: the tile is then done again with its exact maximum (exact_stats),
+//          once per wavefront behind its tiles;
+//   IMAGE  the sums over valid tokens set the sampling threshold, and with tens of thousands of valid tokens another
+//          rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
+//          the tile lies more than REF_GUARD * T above it, else the exact maximum.
+// Either way m depends on the row's values alone, not on how the row is split over wavefronts.  m = -inf: an empty tile.
+// What bounds it: per bf16 token one unpacking, one fma, one exp (a quarter of the rate) and one addition, 0.35 us per
+// tile and wavefront.  The running maximum that stood here for all rows was one more instruction in eight and, because
+// every token was needed twice, 32 registers more: 79 to 94, now 60 (bf16), so that eight wavefronts fit a SIMD and all
+// rows of a batch of 2,048 are on the chip at once.
 constexpr float REF_GUARD = 40.f;   // exp(40) * 2048 tokens is far inside fp32
-template <typename T, bool IMAGE>
-__device__ inline void tile_stats(const RawTile &rt, uint32_t tile_word, int lane, const Temper &tp, float &m_out,
-                                  float &zall_out, float &zval_out) {
+constexpr float SUM_MOST = 1e30f;   // 256 tiles of it are still far inside fp32
+__device__ __forceinline__ bool in_range(float zall) { return zall <= SUM_MOST; }   // (not so: too large, or NaN)
+template <typename T, bool IMAGE, bool PAD>
+__device__ __forceinline__ void tile_sums(const RawTile &rt, uint32_t tile_word, int lane, int left, float ref, float c,
+                                          float &zall_out, float &zval_out) {
     using G = TileGeom<T>;
-    float x[4][G::EPL];
-    float mx = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        Elem<T>::unpack(rt.r[j], x[j]);
-#pragma unroll
-        for (int k = 0; k < G::EPL; k++) mx = fmaxf(mx, x[j][k]);
-    }
-    float ref = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
-    if (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull) ref = wave_max(mx);   // wave-uniform branch
-    m_out = ref;
-    if (ref == -INFINITY) {  // nothing but -inf in this tile
-        zall_out = 0.f;
-        zval_out = 0.f;
-        return;
-    }
     // exp(x - m) = 2^(x*c - m*c); m*c is rounded once (mc), its residual is folded into the tile sums
-    const float c = tp.c;
     const float mc = ref * c;
-    const float resid = fmaf(ref, c, -mc);
+    const float fix = fast_exp2(-fmaf(ref, c, -mc));
     float zall = 0.f, zval = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
+        float x[G::EPL];
+        group_of<T, PAD>(rt, j, left, x);
         uint32_t bits = 0;
         if (IMAGE) bits = lane_bits<T>(tile_word, j, lane);
 #pragma unroll
         for (int k = 0; k < G::EPL; k++) {
-            float e = fast_exp2(fmaf(x[j][k], c, -mc));
+            float e = fast_exp2(fmaf(x[k], c, -mc));
             zall += e;
             if (IMAGE) {
                 uint32_t keep = (uint32_t)(-(int32_t)((bits >> k) & 1u));
                 zval += __uint_as_float(__float_as_uint(e) & keep);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);   // one group's tokens in registers at a time
     }
-    const float fix = fast_exp2(-resid);
     zall_out = wave_sum(zall) * fix;
     zval_out = IMAGE ? wave_sum(zval) * fix : 0.f;
+}
+template <typename T, bool PAD, int GROUPS> __device__ __forceinline__ float lane_max(const RawTile &rt, int left) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < GROUPS; j++) {
+        float x[TileGeom<T>::EPL];
+        group_of<T, PAD>(rt, j, left, x);
+#pragma unroll
+        for (int k = 0; k < TileGeom<T>::EPL; k++) mx = fmaxf(mx, x[k]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return mx;
+}
+template <typename T, bool IMAGE, bool PAD>
+__device__ __forceinline__ void tile_stats(const RawTile &rt, uint32_t tile_word, int lane, int left, const Temper &tp,
+                                           float &m_out, float &zall_out, float &zval_out) {
+    const float mx = lane_max<T, PAD, IMAGE ? 4 : 1>(rt, left);
+    float ref = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
+    if (IMAGE && (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull)) ref = wave_max(mx);   // wave-uniform branch
+    m_out = ref;
+    if (IMAGE && ref == -INFINITY) {   // nothing but -inf in this tile
+        zall_out = zval_out = 0.f;
+        return;
+    }
+    tile_sums<T, IMAGE, PAD>(rt, tile_word, lane, left, ref, tp.c, zall_out, zval_out);   // (m = -inf: NaN)
+}
+template <typename T>
+__device__ __forceinline__ void exact_stats(const RawTile &rt, int lane, int left, const Temper &tp, float &m_out, float &zall_out) {
+    m_out = wave_max(lane_max<T, true, 4>(rt, left));
+    float none;
+    zall_out = 0.f;
+    if (m_out != -INFINITY) tile_sums<T, false, true>(rt, 0u, lane, left, m_out, tp.c, zall_out, none);
 }
 
 // Rare path of the image mode (the valid tokens lie far below the row maximum, so sums relative
 // to the tile maxima would lose them): maximum over the valid tokens of a tile ...
 template <typename T>
-__device__ inline float tile_valid_max(const RawTile &rt, uint32_t tile_word, int lane) {
+__device__ __forceinline__ float tile_valid_max(const RawTile &rt, uint32_t tile_word, int lane) {
     using G = TileGeom<T>;
     float mv = -INFINITY;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         float x[G::EPL];
-        Elem<T>::unpack(rt.r[j], x);
+        unpack_fresh<T>(rt.r[j], x);
         const uint32_t bits = lane_bits<T>(tile_word, j, lane);
 #pragma unroll
         for (int k = 0; k < G::EPL; k++)
@@ -357,7 +373,7 @@ __device__ inline float tile_valid_max(const RawTile &rt, uint32_t tile_word, in
 }
 // ... and the valid sum of a tile relative to a given reference (finite)
 template <typename T>
-__device__ inline float tile_valid_sum(const RawTile &rt, uint32_t tile_word, int lane, float ref, float c) {
+__device__ __forceinline__ float tile_valid_sum(const RawTile &rt, uint32_t tile_word, int lane, float ref, float c) {
     using G = TileGeom<T>;
     const float mc = ref * c;
     const float fix = fast_exp2(-fmaf(ref, c, -mc));
@@ -365,7 +381,7 @@ __device__ inline float tile_valid_sum(const RawTile &rt, uint32_t tile_word, in
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         float x[G::EPL];
-        Elem<T>::unpack(rt.r[j], x);
+        unpack_fresh<T>(rt.r[j], x);
         const uint32_t bits = lane_bits<T>(tile_word, j, lane);
 #pragma unroll
         for (int k = 0; k < G::EPL; k++)
@@ -379,7 +395,7 @@ __device__ inline float tile_valid_sum(const RawTile &rt, uint32_t tile_word, in
 // token with positive weight.  When rounding lets no token exceed the target, the last valid token
 // with positive weight is returned.
 template <typename T>
-__device__ inline int locate_in_tile(const RawTile &rt, uint32_t tile_word, int tile, int lane, float m,
+__device__ __forceinline__ int locate_in_tile(const RawTile &rt, uint32_t tile_word, int tile, int lane, float m,
                                      double target, float tc) {
     using G = TileGeom<T>;
     const float mc = m * tc;
@@ -387,8 +403,9 @@ __device__ inline int locate_in_tile(const RawTile &rt, uint32_t tile_word, int 
     double before = 0.0;  // valid weight of the loads already passed
     int last_valid = -1;
     for (int j = 0; j < 4; j++) {
+        __builtin_amdgcn_sched_barrier(0);   // (one group at a time, as in tile_sums)
         float x[G::EPL], e[G::EPL];
-        Elem<T>::unpack(rt.r[j], x);
+        unpack_fresh<T>(rt.r[j], x);
         const uint32_t bits = lane_bits<T>(tile_word, j, lane);
         float grp = 0.f;
         int my_last = -1;
@@ -459,11 +476,11 @@ struct RowOut {
 // Words that the workgroups of a split row hand to one another are written and read with device-scope accesses
 // (each goes to the level of the memory system that all compute units share), so that no fence over the whole
 // cache is needed: a device-wide fence per wavefront cost 30 us per launch, these cost about two.
-__device__ inline void shared_put(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline float shared_get(const float *p) {
+__device__ __forceinline__ void shared_put(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float shared_get(const float *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline void shared_put_tile(SplitRow *r, int k, float m, float zall, float zval, float ref) {
+__device__ __forceinline__ void shared_put_tile(SplitRow *r, int k, float m, float zall, float zval, float ref) {
     float *t = (float *)&r->tile[k];
     shared_put(t + 0, m);
     shared_put(t + 1, zall);
@@ -485,29 +502,26 @@ enum ValidMode { VALID_NONE = 0, VALID_LIST = 1, VALID_IMAGE = 2 };
 // Streams a row's tiles through one wavefront's share of the work: wave `wave` of `nw` takes the
 // tiles wave, wave+nw, ...  Per tile the statistics go to LDS.
 //
-// Full tiles go through a software pipeline of three register tiles X, Y, Z.  Each is reduced and
-// then at once reloaded with the tile three turns ahead, so that two tiles (8 KB per wavefront)
-// are always in flight behind the one being reduced.  The steady loop has no conditional load:
-// every wait in it is for loads issued a known number of loads ago, so the compiler's wait
-// counters leave the younger loads in flight (a conditional load anywhere on the way to a use
-// makes it wait for everything).  The row's ragged last tile, if any, is taken with the guarded
-// loader by the wave whose turn it is.
-// `mid` is work of the caller's that needs no tile (the sums over the listed tokens): it is run once, at the first
-// point where this wavefront has just asked for a tile and would only wait for it; never, if there is no such point.
+// Two register tiles take turns: while one is reduced, the other is on its way.  No load is conditional (see load_tile:
+// a tile that is not there costs one line of the row), so every wait is for loads issued a known number of loads ago.
+// `mid` is work of the caller's that needs no tile (the sums over the listed tokens): it is run once, where this
+// wavefront has just asked for a tile and would only wait for it.
 // `wave_v` of `nw`: the wavefront's number among all wavefronts that share the row (over all its workgroups);
 // `pub`: where a split row's statistics are left for the workgroup that finishes it (nullptr: not split).
-template <typename T, bool IMAGE, bool PIPE, typename SH, typename MID>
-__device__ inline void stream_tiles(const T *__restrict__ row, int V, const RawTile &first,
+// IMAGE: the row may have an image (nullptr: it has none; one loop for both, so that the tiles stay in their registers).
+template <typename T, bool IMAGE, typename SH, typename MID>
+__device__ __forceinline__ void stream_tiles(const T *__restrict__ row, int V, RawTile &X,
                                     const uint32_t *__restrict__ image, SH &sh, int lane, int wave_v,
                                     int nw, const Temper &tp, MID &mid, SplitRow *pub) {
     using G = TileGeom<T>;
     const int wave = __builtin_amdgcn_readfirstlane(wave_v);   // scalar: loop control stays uniform
     const int nt = (V + G::TILE - 1) / G::TILE;
-    const int nfull = V / G::TILE;
-    if (wave >= nt) return;
-    auto reduce_tile = [&](const RawTile &t, int k) {
-        float m, zall, zval;
-        tile_stats<T, IMAGE>(t, IMAGE ? t.word : 0u, lane, tp, m, zall, zval);
+    if (wave >= nt) {
+        mid();
+        return;
+    }
+    bool again = false;   // some tile has to be done again
+    auto record = [&](int k, float m, float zall, float zval) __attribute__((always_inline)) {
         if (lane == 0) {
             sh.tile_m[k] = m;
             sh.tile_zall[k] = zall;
@@ -516,78 +530,51 @@ __device__ inline void stream_tiles(const T *__restrict__ row, int V, const RawT
             if (pub) shared_put_tile(pub, k, m, zall, zval, m);
         }
     };
-    auto fetch = [&](RawTile &t, int k) {   // a full tile and, on the image path, its mask word
-        load_full_tile<T>(row, k, lane, t);
-        if (IMAGE) t.word = tile_mask_word<T>(image, k, lane, V);
+    auto reduce_tile = [&](const RawTile &t, int k, auto pad) __attribute__((always_inline)) {
+        constexpr bool PAD = decltype(pad)::value;
+        const int left = PAD ? tokens_left<T>(V, k, lane) : 0;
+        float m, zall, zval;
+        if (IMAGE && image) tile_stats<T, true, PAD>(t, tile_word_fix<T>(t.word, k, lane, V), lane, left, tp, m, zall, zval);
+        else tile_stats<T, false, PAD>(t, 0u, lane, left, tp, m, zall, zval);
+        if (!(IMAGE && image)) again = again || !in_range(zall);
+        record(k, m, zall, zval);
     };
-    // this wave's full tiles are wave + i*nw for i in [0, cnt); `first` is i = 0 (or the ragged tile)
-    const int cnt = wave < nfull ? (nfull - wave + nw - 1) / nw : 0;
-    int i = 0;
-    bool mid_done = false;
-    RawTile X = first, Y, Z;   // the same three register tiles serve every path below
-    if (IMAGE) X.word = tile_mask_word<T>(image, wave, lane, V);
-    if (PIPE && cnt >= 6) {
-        fetch(Y, wave + nw);
-        fetch(Z, wave + 2 * nw);
-        mid();
-        mid_done = true;
-        while (i + 5 < cnt) {
-            reduce_tile(X, wave + i * nw);
-            fetch(X, wave + (i + 3) * nw);
-            reduce_tile(Y, wave + (i + 1) * nw);
-            fetch(Y, wave + (i + 4) * nw);
-            reduce_tile(Z, wave + (i + 2) * nw);
-            fetch(Z, wave + (i + 5) * nw);
-            i += 3;
-        }
-        reduce_tile(X, wave + i * nw);
-        reduce_tile(Y, wave + (i + 1) * nw);
-        reduce_tile(Z, wave + (i + 2) * nw);
-        i += 3;
-    } else if (!PIPE && cnt >= 2) {
-        // a short turn (in the kernels without the three-tile pipeline, which have the registers for it): two tiles take turns in X and Y, the next one asked for before this one is reduced.  Every
-        // fetch stands in straight-line code with the reduction that follows it, so the waits stay exact.
-        while (i + 2 < cnt) {   // X holds tile i
-            fetch(Y, wave + (i + 1) * nw);
-            if (!mid_done) {
-                mid();
-                mid_done = true;
-            }
-            reduce_tile(X, wave + i * nw);
-            fetch(X, wave + (i + 2) * nw);
-            reduce_tile(Y, wave + (i + 1) * nw);
-            i += 2;
-        }
-        if (i + 1 < cnt) {
-            fetch(Y, wave + (i + 1) * nw);
-            if (!mid_done) {
-                mid();
-                mid_done = true;
-            }
-            reduce_tile(X, wave + i * nw);
-            reduce_tile(Y, wave + (i + 1) * nw);
-            i += 2;
-        } else {
-            reduce_tile(X, wave + i * nw);
-            i += 1;
-        }
-    } else if (cnt > 0 || wave == nfull) {
-        reduce_tile(X, wave);   // a single full tile, or the ragged one when the wave has nothing else
-        i = 1;
+    auto reduce_last = [&](const RawTile &t, int k) __attribute__((always_inline)) {   // the row's last tile is the last one of its wavefront
+        if ((k + 1) * G::TILE > V) reduce_tile(t, k, std::true_type());
+        else reduce_tile(t, k, std::false_type());
+    };
+    // a tile and its mask word (without an image: a word of the row, so that the number of loads is the same)
+    const uint32_t *words = image ? image : (const uint32_t *)row;
+    const int n_words = image ? V : 32;
+    auto fetch_word = [&](RawTile &t, int k) __attribute__((always_inline)) {
+        if (IMAGE) t.word = tile_word_raw<T>(words, k, lane, n_words);
+    };
+    auto fetch = [&](RawTile &t, int k) __attribute__((always_inline)) {
+        load_tile<T>(row, V, k, lane, t);
+        fetch_word(t, k);
+    };
+    int left = (nt - wave + nw - 1) / nw;   // tiles of this wavefront
+    int k = wave;
+    fetch_word(X, k);
+    RawTile Y;
+    fetch(Y, k + nw);
+    mid();
+    for (; left > 2; left -= 2, k += 2 * nw) {
+        reduce_tile(X, k, std::false_type());
+        fetch(X, k + 2 * nw);
+        reduce_tile(Y, k + nw, std::false_type());
+        fetch(Y, k + 3 * nw);
     }
-    // what is left (a short turn in a kernel with the three-tile pipeline, tile by tile), and perhaps the ragged tail
-    for (; i < cnt; i++) {
-        fetch(Z, wave + i * nw);
-        if (!mid_done) {
-            mid();
-            mid_done = true;
+    reduce_last(X, k);
+    if (left == 2) reduce_last(Y, k + nw);
+    if (__builtin_expect(again, 0)) {   // (wave-uniform)
+        for (k = wave; k < nt; k += nw) {
+            if (in_range(sh.tile_zall[k])) continue;
+            load_tile<T>(row, V, k, lane, Y);
+            float m, zall;
+            exact_stats<T>(Y, lane, tokens_left<T>(V, k, lane), tp, m, zall);
+            record(k, m, zall, 0.f);
         }
-        reduce_tile(Z, wave + i * nw);
-    }
-    if (nfull < nt && nfull % nw == wave && wave != nfull) {
-        load_tile<T>(row, V, nfull, lane, Z);
-        if (IMAGE) Z.word = tile_mask_word<T>(image, nfull, lane, V);
-        reduce_tile(Z, nfull);
     }
 }
 
@@ -596,7 +583,7 @@ __device__ inline void stream_tiles(const T *__restrict__ row, int V, const RawT
 // all tokens only ever enters a logarithm, so it is added up in fp32 (a tree over at most 256 positive terms: a few
 // 1e-7 relative); the valid sum sets the sampling threshold and is added up in fp64.
 template <typename SH>
-__device__ inline void combine_tiles(const SH &sh, int nt, int lane, const Temper &tp, bool image, float &M, float &za,
+__device__ __forceinline__ void combine_tiles(const SH &sh, int nt, int lane, const Temper &tp, bool image, float &M, float &za,
                                      double &zv) {
     if (nt <= WAVE) {   // (uniform) one tile per lane at most: both words in one round of LDS reads, no loops; the
                         // same operations in the same order as below, so the same bits
@@ -647,7 +634,7 @@ struct ListPick {
     float Mv;        // largest listed logit (-inf: no listed token has positive weight)
     double zvl;      // sum of the listed tokens' weights relative to Mv
 };
-__device__ inline ListPick reg_list_pick(float gx, uint32_t tokw, int n_list, float u, int lane, const Temper &tp) {
+__device__ __forceinline__ ListPick reg_list_pick(float gx, uint32_t tokw, int n_list, float u, int lane, const Temper &tp) {
     ListPick pk;
     pk.id = -1;
     pk.pos = -1;
@@ -709,8 +696,8 @@ __device__ inline ListPick reg_list_pick(float gx, uint32_t tokw, int n_list, fl
 //   sp           the row's split over workgroups: `first` is then tile sp.part * nw + wave, and only the
 //                workgroup that arrives last goes on to sample (the others return with mine == false)
 //   SPLIT        compiled in only for kernels that may share a row between workgroups (the others pay nothing for it)
-template <typename T, bool PIPE, typename SH, bool ALL, bool SPLIT>
-__device__ inline RowOut row_sample(const T *__restrict__ row, int V, const RawTile &first, int mode, int n_list,
+template <typename T, typename SH, bool ALL, bool SPLIT>
+__device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, RawTile &first, int mode, int n_list,
                                     const uint32_t *__restrict__ image, float u, SH &sh, int tid, int nw,
                                     const Temper &tp, const Split &sp, const T *__restrict__ next_row = nullptr,
                                     RawTile *next_first = nullptr) {
@@ -737,9 +724,7 @@ __device__ inline RowOut row_sample(const T *__restrict__ row, int V, const RawT
 
     // ---- list path, part 2: sums per slice of 64 listed tokens, relative to the slice maximum.  Run from inside
     // the stream, while the wavefront waits for a tile it has just asked for; after it when there is no such wait.
-    bool list_done = false;
     auto list_sums = [&]() {
-        list_done = true;
         if (mode != VALID_LIST) return;
         for (int s = vwave; s < ns; s += vnw) {
             const int i = s * WAVE + lane;
@@ -775,9 +760,7 @@ __device__ inline RowOut row_sample(const T *__restrict__ row, int V, const RawT
         }
     };
     // ---- stream: every tile once
-    if (mode == VALID_IMAGE) stream_tiles<T, true, PIPE, SH>(row, V, first, image, sh, lane, vwave, vnw, tp, list_sums, pub);
-    else stream_tiles<T, false, PIPE, SH>(row, V, first, image, sh, lane, vwave, vnw, tp, list_sums, pub);
-    if (!list_done) list_sums();
+    stream_tiles<T, true, SH>(row, V, first, mode == VALID_IMAGE ? image : nullptr, sh, lane, vwave, vnw, tp, list_sums, pub);
     // (decode loop) the row of the next step is known already: ask for this wave's first tile of it
     // now, so that it travels while this row is combined and sampled
     if (next_row && wave < nt) load_tile<T>(next_row, V, wave, lane, *next_first);
@@ -836,7 +819,7 @@ __device__ inline RowOut row_sample(const T *__restrict__ row, int V, const RawT
         __syncthreads();  // everyone has read tile_zval
         RawTile rt;
         for (int k = wave; k < nt; k += nw) {
-            load_tile<T>(row, V, k, lane, rt);
+            load_tile<T>(row, V, k, lane, rt);   // (what lies behind the row's end has no mask bit)
             const uint32_t word = tile_mask_word<T>(image, k, lane, V);
             const float mv = tile_valid_max<T>(rt, word, lane);
             if (lane == 0) sh.tile_ref[k] = mv;
@@ -992,7 +975,7 @@ __device__ inline RowOut row_sample(const T *__restrict__ row, int V, const RawT
 // ------------------------------------------------------------------------------------------
 // constrained_sample: the valid set arrives as a packed mask.  Count its bits; a small set is
 // unpacked into the token list, a large one is used as an image.
-template <typename T, bool SMALL, bool PIPE, bool SPLIT>
+template <typename T, bool SMALL, bool SPLIT>
 __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void sample_kernel(const T *__restrict__ logits, int64_t row_stride,
                                                                   const uint32_t *__restrict__ mask,
                                                                   const float *__restrict__ uniforms, int V,
@@ -1042,7 +1025,7 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
     auto bits_of = [](const Quad &q) { return (int)(__popc(q.w[0]) + __popc(q.w[1]) + __popc(q.w[2]) + __popc(q.w[3])); };
     const Quad q0 = load_quad(wave), q1 = load_quad(wave + nw);   // (a group past the row: all zero)
     RawTile first;
-    if (vwave < nt) load_tile<T>(row, V, vwave, lane, first);   // in flight during the mask work
+    load_tile<T>(row, V, vwave, lane, first);   // in flight during the mask work
 
     // valid tokens per group of 64 quads (kept in the tile_cnt array: there are fewer groups than tiles)
     const int incl0 = wave_incl_scan(bits_of(q0));
@@ -1084,7 +1067,7 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
         }
         __syncthreads();
     }
-    RowOut r = row_sample<T, PIPE, SH, false, SPLIT>(row, V, first, mode, mode == VALID_LIST ? total : 0, mrow, uniforms[b], sh, tid, nw, tp, sp);
+    RowOut r = row_sample<T, SH, false, SPLIT>(row, V, first, mode, mode == VALID_LIST ? total : 0, mrow, uniforms[b], sh, tid, nw, tp, sp);
     if (r.mine && tid == 0) {
         ids[b] = r.id;
         logZ_valid[b] = r.logZ_valid;
@@ -1111,8 +1094,10 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_one_tile_kernel(co
     const float u = uniforms[b];
     RawTile rt;
     load_tile<T>(row, V, 0, lane, rt);
+    const int left = tokens_left<T>(V, 0, lane);
     float m, zall, zval;
-    tile_stats<T, true>(rt, word, lane, tp, m, zall, zval);
+    if (V == TileGeom<T>::TILE) tile_stats<T, true, false>(rt, word, lane, left, tp, m, zall, zval);
+    else tile_stats<T, true, true>(rt, word, lane, left, tp, m, zall, zval);
     const float l2za = fast_log2(zall);
     int id = -1;
     float lzv = -INFINITY, ref = m;
@@ -1163,8 +1148,10 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
             if ((uint32_t)lane == (v >> 5)) word |= 1u << (v & 31u);
         }
     }
+    const int left = tokens_left<T>(V, 0, lane);
     float m, zall, zval;
-    tile_stats<T, true>(rt, word, lane, tp, m, zall, zval);
+    if (V == TileGeom<T>::TILE) tile_stats<T, true, false>(rt, word, lane, left, tp, m, zall, zval);
+    else tile_stats<T, true, true>(rt, word, lane, left, tp, m, zall, zval);
     const float l2za = fast_log2(zall);
     int id = -1;
     float lzv = -INFINITY, ref = m;
@@ -1238,7 +1225,7 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(IndexV
 // the cursor lives in registers and the next step's first tiles are requested before the current
 // step is sampled (only when no child of the current prefix is a member, i.e. the row is certain to
 // go on, so nothing is fetched in vain).
-template <typename T, bool LOOP, bool PIPE, bool SPLIT, bool REG>
+template <typename T, bool LOOP, bool SPLIT, bool REG>
 __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MAX_WAVES * WAVE) void decode_kernel(
     IndexView ix, int32_t *__restrict__ prefixes, int32_t stride, int32_t *__restrict__ lens,
     uint8_t *__restrict__ active, RowState *__restrict__ state, const T *__restrict__ logits, int64_t row_stride,
@@ -1267,15 +1254,15 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
     sp.row = SPLIT ? &scratch->row[b] : nullptr;
     sp.arrivals = SPLIT ? &scratch->arrivals[b] : nullptr;
     const int vwave = sp.part * nw + wave;
-    // REG: the per-step kernel of small batches keeps a list of at most 63 children in wavefront 0's registers and
-    // looks one level ahead for the next cursor (see RowState); the loop kernel, split rows, long rows and large
-    // batches (where the registers this costs would mean fewer rows per compute unit) use the list in LDS
-    static_assert(!REG || (!SPLIT && !PIPE), "the register list is for short turns in unsplit rows");
+    // REG: there is a cursor, and a list of at most 63 children is kept in wavefront 0's registers, with a look one level
+    // ahead for the next cursor (see RowState); split rows, large batches of the loop kernel and calls without a cursor
+    // use the list in LDS.  (C3, B = 2,048, the loop step by step: 594 us with the list in LDS, 559 like this.)
+    static_assert(!REG || !SPLIT, "the register list is for unsplit rows");
     // the independent per-row loads go out together
     uint8_t on = active ? active[b] : (uint8_t)1;
     int t = lens[b];
     RowState st;
-    if (state) st = state[b];
+    if (REG || state) st = state[b];
     else st.flags = 0u;
     float u = uniforms[b];
     // the running score is read now, not when it is updated at the very end (a load there would stand between the
@@ -1329,7 +1316,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             ahead_next = ix.ent[a1].child;
         }
     };
-    if (STEP_REG && state) {
+    if (STEP_REG) {
         // with a cursor the small loads go out before the 4 KB tile: memory answers a wavefront in request order
         check_cursor();
         const uint32_t nc = st.ce - st.cb;
@@ -1354,9 +1341,9 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         rl.have_gx = __builtin_amdgcn_readfirstlane(rl.have_gx ? 1 : 0) != 0 && wave == 0;
     }
     RawTile first;
-    if (vwave < nt) load_tile<T>(row, V, vwave, lane, first);   // in flight during the index work
+    load_tile<T>(row, V, vwave, lane, first);   // in flight during the index work
     t = t < 0 ? 0 : (t > stride ? stride : t);
-    if (!state) {  // no cursor: locate the prefix from the root (wave 0), then share it
+    if (!REG && !state) {  // no cursor: locate the prefix from the root (wave 0), then share it
         if (wave == 0) {
             const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
             const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
@@ -1373,7 +1360,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         st.slot = (st.node != PPV_NO_SLOT && st.ce - st.cb > ix.heavy_min) ? heavy_slot_of(ix, st.node) : PPV_NO_SLOT;
         __syncthreads();
     }
-    if (!(STEP_REG && state)) check_cursor();
+    if (!STEP_REG) check_cursor();
     if (STEP_REG && rl.on) {
         // ---- a short list in wavefront 0's registers.  The sample depends on the listed logits alone, not on the
         // row's totals: wavefront 0 draws the token and works out the next cursor while its tile is still on its
@@ -1416,7 +1403,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         struct {
             __device__ void operator()() const {}
         } nothing;
-        stream_tiles<T, false, false, RowShared>(row, V, first, nullptr, sh, lane, wave, nw, tp, nothing, nullptr);
+        stream_tiles<T, false, RowShared>(row, V, first, nullptr, sh, lane, wave, nw, tp, nothing, nullptr);
         __syncthreads();
         if (wave != 0) return;
         if (lane == 0) {
@@ -1465,7 +1452,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         const uint32_t cb = st.cb, ce = st.ce, slot = st.slot;
         const int nchild = (int)(ce - cb);
         const int mode = nchild == 0 ? VALID_NONE : (slot != PPV_NO_SLOT ? VALID_IMAGE : VALID_LIST);
-        if (LOOP_REG && mode == VALID_LIST && nchild == 1 && st.flags == 1u && V % G::EPL == 0 && nw >= 2 &&
+        if (LOOP_REG && mode == VALID_LIST && nchild == 1 && st.flags == 1u && nw >= 2 &&
             nt <= 2 * (nw - 1)) {
             // ---- A chain of prefixes with one child each, the cursor knowing the child (nearly all of a long
             // sequence below its first levels).  Wavefront 0 only draws tokens: each step it takes the listed
@@ -1563,27 +1550,31 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             } else {
                 const int k0 = wave_s - 1, k1 = wave_s - 1 + ntw;   // (a tile past the row reads as -inf and is not recorded)
                 RawTile A0, A1, B0, B1;
-                load_tile_clamped<T>(row, V, k0, lane, A0);
-                load_tile_clamped<T>(row, V, k1, lane, A1);
-                auto reduce = [&](RawTile &tile, int k, RowShared &cur) {
-                    pad_tile_tail<T>(tile, V, k, lane);
+                load_tile<T>(row, V, k0, lane, A0);
+                load_tile<T>(row, V, k1, lane, A1);
+                auto reduce = [&](const RawTile &tile, int k, RowShared &cur) __attribute__((always_inline)) {
+                    const int left = tokens_left<T>(V, k, lane);
                     float m, zall, zval;
-                    tile_stats<T, false>(tile, 0u, lane, tp, m, zall, zval);
-                    if (lane == 0 && k < nt) {
-                        cur.tile_m[k] = m;
-                        cur.tile_zall[k] = zall;
-                        cur.tile_zval[k] = zval;
-                        cur.tile_ref[k] = m;
+                    if ((k + 1) * G::TILE > V) tile_stats<T, false, true>(tile, 0u, lane, left, tp, m, zall, zval);
+                    else tile_stats<T, false, false>(tile, 0u, lane, left, tp, m, zall, zval);
+                    if (k < nt) {
+                        if (!in_range(zall)) exact_stats<T>(tile, lane, left, tp, m, zall);
+                        if (lane == 0) {
+                            cur.tile_m[k] = m;
+                            cur.tile_zall[k] = zall;
+                            cur.tile_zval[k] = zval;
+                            cur.tile_ref[k] = m;
+                        }
                     }
                 };
                 // one step on the tiles (c0, c1), the next row's tiles requested into (n0, n1) first.
                 // Returns true while the chain goes on.
-                auto chain_step = [&](RawTile &c0, RawTile &c1, RawTile &n0, RawTile &n1) {
+                auto chain_step = [&](RawTile &c0, RawTile &c1, RawTile &n0, RawTile &n1) __attribute__((always_inline)) {
                     const bool more = row_goes_on();
                     const T *nrow = more ? row + step_stride : row;   // no next row: one line of this one (same loads,
                     const int Vn = more ? V : G::EPL;                 // all clamped to the row's first 16 bytes)
-                    load_tile_clamped<T>(nrow, Vn, k0, lane, n0);
-                    load_tile_clamped<T>(nrow, Vn, k1, lane, n1);
+                    load_tile<T>(nrow, Vn, k0, lane, n0);
+                    load_tile<T>(nrow, Vn, k1, lane, n1);
                     reduce(c0, k0, shs[s & 1]);
                     reduce(c1, k1, shs[s & 1]);
                     __syncthreads();
@@ -1679,7 +1670,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             struct {
                 __device__ void operator()() const {}
             } nothing;
-            stream_tiles<T, false, false, RowShared>(row, V, first, nullptr, cur, lane, wave, nw, tp, nothing, nullptr);
+            stream_tiles<T, false, RowShared>(row, V, first, nullptr, cur, lane, wave, nw, tp, nothing, nullptr);
             __syncthreads();
             done = hand[s & 1].done != 0;
             const bool drew = hand[s & 1].drew != 0;
@@ -1723,7 +1714,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         const T *next_row = more ? row + step_stride : nullptr;
         float next_u = 0.f;
         if (more) next_u = uniforms[(size_t)(s + 1) * (size_t)B + b];
-        RowOut r = row_sample<T, PIPE, RowShared, LOOP, SPLIT>(row, V, first, mode, mode == VALID_LIST ? nchild : 0, image, u, sh,
+        RowOut r = row_sample<T, RowShared, LOOP, SPLIT>(row, V, first, mode, mode == VALID_LIST ? nchild : 0, image, u, sh,
                                                   tid, nw, tp, sp, next_row, &next_first);
         if (r.mine && tid == 0) {
             const bool room = t < stride || !advance;
@@ -1855,14 +1846,6 @@ int waves_for(int V, ppv_dtype dt, int B, int parts = 1, bool cursor_step = fals
     return nw;
 }
 
-// Whether some wavefront's turn has six tiles or more, i.e. whether the three-tile pipeline of stream_tiles can
-// run at all.  Kernels for shorter turns are compiled without it: 62 instead of 92 registers (bf16), which is
-// two more rows in flight per compute unit when a large batch keeps every compute unit full.
-bool long_turns(int V, ppv_dtype dt, int nw) {   // nw: wavefronts per row over all its workgroups
-    const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
-    return (V / tile + nw - 1) / nw >= 6;
-}
-
 // Workgroups per row.  A batch of fewer rows than the chip has compute units leaves most of it idle with one
 // workgroup per row, and a long row alone on a compute unit is bound by that unit's arithmetic (about 4.8 us per
 // 256 KB of bf16 logits).  Such a row is spread over 2 .. 16 workgroups: a power of two, six tiles or more each, at
@@ -1902,40 +1885,34 @@ int shift_of(int parts) {
 }
 
 template <typename T>
-void launch_sample(bool small, bool pipe, dim3 grid, dim3 block, hipStream_t hs, const T *lg, int64_t row_stride,
+void launch_sample(bool small, dim3 grid, dim3 block, hipStream_t hs, const T *lg, int64_t row_stride,
                    const uint32_t *mask, const float *uniforms, int V, int n_words, int list_max, int32_t *ids,
                    float *logZ_valid, float *logZ_all, Temper tp, int split_shift, SplitScratch *scratch) {
-    if (split_shift)   // (a split row's turns are short; the kernel without the three-tile pipeline serves all of them)
-        hipLaunchKernelGGL((sample_kernel<T, false, false, true>), grid, block, 0, hs, lg, row_stride, mask, uniforms, V,
-                           n_words, list_max, ids, logZ_valid, logZ_all, tp, split_shift, scratch);
-    else if (small)
-        hipLaunchKernelGGL((sample_kernel<T, true, false, false>), grid, block, 0, hs, lg, row_stride, mask, uniforms, V, n_words,
-                           list_max, ids, logZ_valid, logZ_all, tp, split_shift, scratch);
-    else if (pipe)
-        hipLaunchKernelGGL((sample_kernel<T, false, true, false>), grid, block, 0, hs, lg, row_stride, mask, uniforms, V, n_words,
-                           list_max, ids, logZ_valid, logZ_all, tp, split_shift, scratch);
-    else
-        hipLaunchKernelGGL((sample_kernel<T, false, false, false>), grid, block, 0, hs, lg, row_stride, mask, uniforms, V,
-                           n_words, list_max, ids, logZ_valid, logZ_all, tp, split_shift, scratch);
+#define PPV_LAUNCH_SAMPLE(SMALL, SPLIT)                                                                                  \
+    hipLaunchKernelGGL((sample_kernel<T, SMALL, SPLIT>), grid, block, 0, hs, lg, row_stride, mask, uniforms, V, n_words, \
+                       list_max, ids, logZ_valid, logZ_all, tp, split_shift, scratch)
+    if (split_shift) PPV_LAUNCH_SAMPLE(false, true);
+    else if (small) PPV_LAUNCH_SAMPLE(true, false);
+    else PPV_LAUNCH_SAMPLE(false, false);
+#undef PPV_LAUNCH_SAMPLE
 }
 
-constexpr int REG_MAX_ROWS = 1024;   // batches up to here run the per-step kernel with the list in registers
+constexpr int REG_MAX_ROWS = 1024;   // batches up to here run the loop kernel with the list in registers (two sets of statistics in LDS: fewer rows per compute unit)
 template <typename T>
-void launch_decode_kernel(bool loop, bool pipe, dim3 grid, dim3 block, hipStream_t hs, const IndexView &view,
+void launch_decode_kernel(bool loop, dim3 grid, dim3 block, hipStream_t hs, const IndexView &view,
                           int32_t *prefixes, int32_t stride, int32_t *lens, uint8_t *active, RowState *rs, const T *lg,
                           int64_t row_stride, int64_t step_stride, const float *uniforms, int n_steps, int B, int32_t *ids,
                           float *logZ_valid, float *logx, Temper tp, int split_shift, SplitScratch *scratch, int flags) {
-#define PPV_LAUNCH_DECODE(LOOP, PIPE, SPLIT, REG)                                                                     \
-    hipLaunchKernelGGL((decode_kernel<T, LOOP, PIPE, SPLIT, REG>), grid, block, 0, hs, view, prefixes, stride, lens,   \
-                       active, rs, lg, row_stride, step_stride, uniforms, n_steps, B, ids, logZ_valid, logx, tp,        \
-                       split_shift, scratch, flags)
-    if (split_shift && !loop) PPV_LAUNCH_DECODE(false, false, true, false);   // (a split row's turns are short)
-    else if (loop && pipe) PPV_LAUNCH_DECODE(true, true, false, false);
-    else if (loop && rs && B <= REG_MAX_ROWS) PPV_LAUNCH_DECODE(true, false, false, true);
-    else if (loop) PPV_LAUNCH_DECODE(true, false, false, false);
-    else if (pipe) PPV_LAUNCH_DECODE(false, true, false, false);
-    else if (rs && B <= REG_MAX_ROWS) PPV_LAUNCH_DECODE(false, false, false, true);
-    else PPV_LAUNCH_DECODE(false, false, false, false);
+    const bool reg = rs && (!loop || B <= REG_MAX_ROWS);
+#define PPV_LAUNCH_DECODE(LOOP, SPLIT, REG)                                                                            \
+    hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, view, prefixes, stride, lens, active, \
+                       rs, lg, row_stride, step_stride, uniforms, n_steps, B, ids, logZ_valid, logx, tp, split_shift,   \
+                       scratch, flags)
+    if (split_shift && !loop) PPV_LAUNCH_DECODE(false, true, false);
+    else if (loop && reg) PPV_LAUNCH_DECODE(true, false, true);
+    else if (loop) PPV_LAUNCH_DECODE(true, false, false);
+    else if (reg) PPV_LAUNCH_DECODE(false, false, true);
+    else PPV_LAUNCH_DECODE(false, false, false);
 #undef PPV_LAUNCH_DECODE
 }
 
@@ -2011,7 +1988,6 @@ ppv_status sample_call(const void *logits, ppv_dtype dt, int64_t row_stride, con
         parts = parts_for(V, dt, B, hs, &scratch);
     }
     const int threads = waves_for(V, dt, B, parts) * WAVE;
-    const bool pipe = long_turns(V, dt, parts * threads / WAVE);
     const dim3 grid((unsigned)B * (unsigned)parts), block(threads);
     if (V <= tile) {   // the whole row is one tile
         const dim3 g1((unsigned)((B + ONE_TILE_ROWS - 1) / ONE_TILE_ROWS)), b1(ONE_TILE_ROWS * WAVE);
@@ -2025,10 +2001,10 @@ ppv_status sample_call(const void *logits, ppv_dtype dt, int64_t row_stride, con
         return PPV_OK;
     }
     if (dt == PPV_F32)
-        launch_sample<float>(small, pipe, grid, block, hs, (const float *)logits, row_stride, mask, uniforms, V, n_words,
+        launch_sample<float>(small, grid, block, hs, (const float *)logits, row_stride, mask, uniforms, V, n_words,
                              list_max, ids, logZ_valid, logZ_all, tp, shift_of(parts), scratch);
     else
-        launch_sample<uint16_t>(small, pipe, grid, block, hs, (const uint16_t *)logits, row_stride, mask, uniforms, V,
+        launch_sample<uint16_t>(small, grid, block, hs, (const uint16_t *)logits, row_stride, mask, uniforms, V,
                                 n_words, list_max, ids, logZ_valid, logZ_all, tp, shift_of(parts), scratch);
     PPV_HIP_TRY(hipGetLastError());
     return PPV_OK;
@@ -2101,20 +2077,19 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
     {   // the loop kernel with the list in registers: one wavefront draws, the others stream two tiles each
         const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
         const int nt = (ix->view.vocab + tile - 1) / tile;
-        if (loop && state && B <= REG_MAX_ROWS && !long_turns(ix->view.vocab, dt, nw) && nt >= 2 && (nt + 1) / 2 + 1 <= CHAIN_WAVES &&
+        if (loop && state && B <= REG_MAX_ROWS && nt >= 2 && (nt + 1) / 2 + 1 <= CHAIN_WAVES &&
             ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0)
             nw = (nt + 1) / 2 + 1;
     }
     const dim3 grid((unsigned)B * (unsigned)parts), block(nw * WAVE);
     RowState *rs = (RowState *)state;
-    const bool pipe = long_turns(ix->view.vocab, dt, parts * nw);
     if (!loop) n_steps = 1;
     if (dt == PPV_F32)
-        launch_decode_kernel<float>(loop, pipe, grid, block, hs, ix->view, prefixes, prefix_stride, lens, active, rs,
+        launch_decode_kernel<float>(loop, grid, block, hs, ix->view, prefixes, prefix_stride, lens, active, rs,
                                     (const float *)logits, row_stride, step_stride, uniforms, n_steps, B, ids, logZ_valid,
                                     logx, tp, shift_of(parts), scratch, (advance ? 1 : 0) | (fresh ? 2 : 0));
     else
-        launch_decode_kernel<uint16_t>(loop, pipe, grid, block, hs, ix->view, prefixes, prefix_stride, lens, active, rs,
+        launch_decode_kernel<uint16_t>(loop, grid, block, hs, ix->view, prefixes, prefix_stride, lens, active, rs,
                                        (const uint16_t *)logits, row_stride, step_stride, uniforms, n_steps, B, ids,
                                        logZ_valid, logx, tp, shift_of(parts), scratch, (advance ? 1 : 0) | (fresh ? 2 : 0));
     PPV_HIP_TRY(hipGetLastError());

@@ -1,0 +1,80 @@
+"""constrained_sample at the edges of its tiles: rows that end inside, at and behind a tile and a 16-byte group, one to five
+tiles per wavefront, and tiles whose cheap reference (the largest of the first 16 bytes) is no use: nothing but -inf
+there, tokens far above it, tokens far below it.  Sums and samples against double precision."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_09135_amd import binding as ppv
+from paper_2504_09135_amd import workloads as W
+
+from gpu_helpers import CDF_BAND, DEV, LOGZ_TOL, to_dev, tuning
+
+pytestmark = pytest.mark.gpu
+
+
+def rows_for(V, tile, rng):
+    """One row per kind of reference."""
+    base = rng.normal(0, 2, size=(8, V)).astype(np.float32)
+    base[1, ::tile] = -np.inf                                   # the very first token of each tile
+    for at in range(0, V, tile):
+        base[2, at:at + 8] = -np.inf                            # all of the first group
+        base[3, at:at + 8] = -1e9                               # ... masked the other way
+        base[4, at:at + 8] -= 100.0                             # the rest 100 above it: beyond the sums' range
+        base[5, at:at + 8] += 60.0                              # the rest far below it
+        base[6, at + (tile - 1) % min(tile, V - at)] = 90.0     # one token far above, at the tile's end
+    base[7, :V - 1] = -np.inf                                   # tiles of nothing, and a single token at the row's end
+    return base
+
+
+@pytest.mark.parametrize("waves", [1, 2, 4, 16])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("over", [-9, -8, -1, 0, 1, 7, 8, 9])
+@pytest.mark.parametrize("tiles", [1, 2, 5])
+def test_row_ends_and_references(tiles, over, dtype, waves):
+    tile = 1024 if dtype == "f32" else 2048
+    V = tiles * tile + over
+    rng = np.random.default_rng(V + waves)
+    lg = rows_for(V, tile, rng)
+    B = lg.shape[0]
+    bits = W.f32_to_bf16_bits(lg)
+    x = (W.bf16_bits_to_f32(bits) if dtype == "bf16" else lg).astype(np.float64)
+    per = 8 if dtype == "bf16" else 4
+    Vp = -(-V // per) * per
+    buf = np.full((B, Vp), np.inf, np.float32)                  # behind the row's end: never looked at
+    buf[:, :V] = lg
+    if dtype == "bf16":
+        raw = np.full((B, Vp), 0x7F80, np.uint16)
+        raw[:, :V] = bits
+        ld = to_dev(raw.view(np.int16)).view(torch.bfloat16)[:, :V]
+    else:
+        ld = to_dev(buf)[:, :V]
+    for n_valid in (5, V // 2):                                 # a list, an image
+        mask = np.zeros((B, V), np.uint8)
+        for b in range(B):
+            mask[b, rng.choice(V, n_valid, replace=False)] = 1
+            mask[b, V - 1] = 1
+        words = np.packbits(np.pad(mask, ((0, 0), (0, (-V) % 32))), axis=1, bitorder="little").view(np.int32)
+        un = rng.random(B, dtype=np.float32)
+        ids = torch.full((B,), -9, dtype=torch.int32, device=DEV)
+        lzv = torch.zeros(B, device=DEV)
+        lza = torch.zeros(B, device=DEV)
+        with tuning(ppv.PPV_TUNE_WAVES_PER_ROW, waves):
+            ppv.constrained_sample(ld, to_dev(words), to_dev(un), ids, lzv, lza)
+        torch.cuda.synchronize()
+        ids, lzv, lza = ids.cpu().numpy(), lzv.cpu().numpy(), lza.cpu().numpy()
+        for b in range(B):
+            top = x[b].max()
+            za = np.exp(x[b] - top).sum()
+            valid = np.flatnonzero(mask[b])
+            vtop = x[b, valid].max()
+            w = np.exp(x[b, valid] - vtop)
+            cdf = np.cumsum(w) / w.sum()
+            all_ref, val_ref = top + np.log(za), vtop + np.log(w.sum()) - top - np.log(za)
+            tol = LOGZ_TOL["f32"]                               # (the reference has the rounded logits)
+            assert abs(lza[b] - all_ref) <= tol * max(1.0, abs(all_ref)), (b, n_valid, lza[b], all_ref)
+            assert abs(lzv[b] - val_ref) <= tol * max(1.0, abs(val_ref)), (b, n_valid, lzv[b], val_ref)
+            at = int(np.searchsorted(cdf, un[b], side="right"))
+            near = [i for i in (at - 1, at, at + 1) if 0 <= i < len(valid)]
+            assert ids[b] in valid[near] and (ids[b] == valid[min(at, len(valid) - 1)] or
+                                              np.abs(cdf - un[b]).min() < CDF_BAND), (b, n_valid, ids[b], valid[near])
