@@ -527,19 +527,21 @@ struct TrieOut {
     int64_t *x_off;
     uint32_t *node_at;        // (with a look-up table) number of the alone prefix that ends at this token of the sorted S
     LookupEntry *table;       // nullptr: none
-    uint32_t table_size, fp_mask;
+    uint32_t buckets, fp_mask;
 };
 __device__ inline void insert_entry(const TrieOut &o, const PrefixHash &h, uint32_t node, uint32_t at, uint32_t extent) {
-    uint32_t slot, fp;
-    prefix_hash_finish(h, o.table_size, o.fp_mask, &slot, &fp);
+    uint32_t bucket, fp;
+    prefix_hash_finish(h.h1, h.h2, o.buckets, o.fp_mask, &bucket, &fp);
     const unsigned long long key = ((unsigned long long)fp << 32) | node;
-    for (uint32_t n = 0; n < o.table_size; n++) {   // the table has twice as many slots as entries
-        if (atomicCAS((unsigned long long *)&o.table[slot].key, 0ull, key) == 0ull) {
-            o.table[slot].at = at;
-            o.table[slot].extent = extent;
-            return;
-        }
-        slot = slot + 1u == o.table_size ? 0u : slot + 1u;
+    for (uint32_t n = 0; n < o.buckets; n++) {   // the table has four times as many places as entries
+        LookupEntry *e = o.table + (size_t)bucket * LOOKUP_BUCKET;
+        for (uint32_t k = 0; k < LOOKUP_BUCKET; k++)
+            if (atomicCAS((unsigned long long *)&e[k].key, 0ull, key) == 0ull) {
+                e[k].at = at;
+                e[k].extent = extent;
+                return;
+            }
+        bucket = bucket + 1u == o.buckets ? 0u : bucket + 1u;
     }
 }
 // The tokens of 64 rows are one stretch of the sorted S.  They are gathered into LDS, 16 lanes to a row, and written from
@@ -617,7 +619,7 @@ __global__ __launch_bounds__(BT) void fill_prefixes(TOK tok, const RowMeta *__re
     const bool last_group = (c + 1) * WAVE >= n_rows;
     const uint64_t below = (1ull << lane) - 1ull;
     const int longest = (int)wave_max(m.len);
-    PrefixHash h = {0u, 1u, 0u, 1u};   // the empty string
+    PrefixHash h = prefix_hash_empty();
     uint64_t opened = __ballot(m.lcp == 0u && m.len > 0u);
     uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_at);
     for (int di = 0; di < longest; di++) {
@@ -635,7 +637,7 @@ __global__ __launch_bounds__(BT) void fill_prefixes(TOK tok, const RowMeta *__re
             t = tok[m.src + d];
             o.x_tok[m.at + d] = (int32_t)t;
         }
-        if (hashes) h = d == 0u ? prefix_hash_token(t) : prefix_hash_join(h, prefix_hash_token(t));
+        if (hashes) prefix_hash_add(h, t);
         // where the prefix's range ends: the next row that shares at most d tokens with the row before it
         const uint64_t breaks = __ballot(m.lcp <= d) & ~below & ~(1ull << lane);
         uint32_t hi = breaks ? c * WAVE + (uint32_t)__ffsll((long long)breaks) - 1u : n_rows;
@@ -678,7 +680,7 @@ __global__ __launch_bounds__(BT) void fill_prefixes(TOK tok, const RowMeta *__re
                     else o.node_at[m.at + d] = g;
                 }
                 if (d < entries_to)
-                    insert_entry(o, h, g, m.at, (d + 1u) | (alone ? (m.len < (uint32_t)WAVE ? m.len : (uint32_t)WAVE) << 8 : 0u));
+                    insert_entry(o, h, alone ? r : g, m.at, (d + 1u) | (alone ? (m.len < (uint32_t)WAVE ? m.len : (uint32_t)WAVE) << 8 : 0u));
             }
         }
         opened = opened_next;
@@ -905,7 +907,9 @@ ppv_status number_prefixes(ppv_index *ix, TOK tok, const RowMeta *rows, uint32_t
     // PPV_TUNE_LOOKUP = 0: no table (every prefix is located by the descent).  PPV_TUNE_LOOKUP_WEAK = 1 (tests): one
     // fingerprint for all, so that every probe is a false hit and the exact check has to turn it away.
     const bool lookup = ppv_tuning(PPV_TUNE_LOOKUP) != 0;
-    const uint32_t size = lookup ? (uint32_t)std::min<uint64_t>(2ull * n_entries, 0xFFFFFFF0ull) : 0u;
+    // A bucket per entry: one in fifty is full, so that a query of ten lengths is rarely kept by one of them.
+    const uint32_t buckets = lookup ? std::min(n_entries, 0xFFFFFFF0u / LOOKUP_BUCKET) : 0u;
+    const uint64_t size = (uint64_t)buckets * LOOKUP_BUCKET;
     Arena keep;
     keep.add(&ix->d_ent, (uint64_t)G + 1);
     keep.add(&ix->d_node_lo, G);
@@ -930,7 +934,7 @@ ppv_status number_prefixes(ppv_index *ix, TOK tok, const RowMeta *rows, uint32_t
     o.x_off = ix->d_x_off;
     o.node_at = ix->d_node_at;
     o.table = lookup ? ix->d_lookup : nullptr;
-    o.table_size = size;
+    o.buckets = buckets;
     o.fp_mask = ppv_tuning(PPV_TUNE_LOOKUP_WEAK) == 1 ? 0u : 0xFFFFFFFFu;
     // LDS for what 64 rows hold on average and a quarter more, or for 64 of the longest
     const uint64_t mean = ((uint64_t)n_tok * WAVE + n_rows - 1) / n_rows;
@@ -950,7 +954,7 @@ ppv_status number_prefixes(ppv_index *ix, TOK tok, const RowMeta *rows, uint32_t
     ix->view.x_tok = ix->d_x_tok;
     ix->view.node_at = ix->d_node_at;
     ix->view.lookup = o.table;
-    ix->view.lookup_size = size;
+    ix->view.lookup_buckets = buckets;
     ix->view.lookup_fp_mask = o.fp_mask;
     return PPV_OK;
 }

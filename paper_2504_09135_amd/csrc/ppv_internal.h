@@ -29,10 +29,11 @@ struct NodeEnt {
 };
 
 struct alignas(16) LookupEntry {
-    uint64_t key;      // fingerprint << 32 | node; 0: empty
+    uint64_t key;      // fingerprint << 32 | node (or the member's rank, if there is only one under the node); 0: empty
     uint32_t at;       // where the first member under the node starts in x_tok
     uint32_t extent;   // the prefix's length; << 8: that member's length (at most a wavefront's), if it is the only one
 };
+constexpr uint32_t LOOKUP_BUCKET = 4;   // entries that are looked at together: 64 bytes
 
 struct IndexView {
     const NodeEnt *ent;          // [n_nodes+1] (the last entry is a sentinel that closes the offsets)
@@ -41,14 +42,15 @@ struct IndexView {
     const uint32_t *heavy_slot;  // [heavy_limit] slot of a heavy node, PPV_NO_SLOT otherwise
     const uint32_t *heavy_bits;  // [n_heavy, n_words] valid-set images
     const uint32_t *heavy_rank;  // [n_heavy, n_words] children before each word
-    // Hashed look-up of prefixes (all lengths of a query are probed at once instead of one level after the other):
-    // open addressing, lookup_size == 0: no table.  A hit is only a hint: it is checked against the tokens of the
-    // first member under the prefix it names.  Prefixes of one member only are entered up to the shortest of them
-    // (LookupEntry::extent); the longer ones are found by comparing that member's tokens and reading node_at.
-    const LookupEntry *lookup;   // [lookup_size]
+    // Hashed look-up of prefixes (all lengths of a query are probed at once instead of one level after the other): buckets
+    // filled from the front, a full one overflows into the next; lookup_buckets == 0: no table.  A hit is only a hint: it
+    // is checked against the tokens of the first member under the prefix it names.  Prefixes of one member only are
+    // entered up to the shortest of them (LookupEntry::extent); the longer ones are found by comparing that member's
+    // tokens, and their nodes, where they are wanted, by node_at.
+    const LookupEntry *lookup;   // [lookup_buckets * LOOKUP_BUCKET]
     const uint32_t *node_at;     // [tokens of S] (with a table) by position in x_tok: the node that ends there, for prefixes of one member
     const int32_t *x_tok;        // sorted S, flat
-    uint32_t lookup_size;
+    uint32_t lookup_buckets;
     uint32_t lookup_fp_mask;     // fingerprint bits in use (all of them; 0 in a test mode that makes every probe a false hit)
     uint32_t heavy_limit;        // nodes >= heavy_limit are not heavy
     uint32_t heavy_min;          // a node is heavy iff it has more than heavy_min children

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(IndexView ix, const 
     extern __shared__ __align__(16) uint32_t smem[];
     const int n_words = ix.n_words;
     uint32_t *img = smem;            // [n_words]
-    uint32_t *bc = smem + n_words;   // [4]: node, found, cb, ce
+    uint32_t *bc = smem + n_words;   // [5]: node, found, cb, ce, only
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (wave == 0) {
         const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
@@ -73,6 +73,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(IndexView ix, const 
             bc[1] = w.found ? 1u : 0u;
             bc[2] = w.found ? w.cb : 0u;
             bc[3] = w.found ? w.ce : 0u;
+            bc[4] = w.only;
             if (range_lo) range_lo[b] = w.lo;
             if (range_hi) range_hi[b] = w.hi;
             if (member) member[b] = w.member ? 1 : 0;
@@ -86,6 +87,19 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(IndexView ix, const 
     // rows are written 16 bytes per lane when every row starts on a 16-byte boundary
     const bool wide = (n_words & 3) == 0 && (((uintptr_t)mask) & 15u) == 0;
     const int n_quads = n_words >> 2;
+    const uint32_t only = bc[4];
+    if (only != PPV_NO_SLOT) {   // one bit
+        const int at = (int)((only & PPV_NODE_TOKEN) >> 5);
+        const uint32_t bit = 1u << (only & 31u);
+        auto word = [&](int i) { return i == at ? bit : 0u; };
+        if (wide) {
+            for (int i = tid; i < n_quads; i += MASK_THREADS)
+                ((uint4 *)out)[i] = make_uint4(word(4 * i), word(4 * i + 1), word(4 * i + 2), word(4 * i + 3));
+        } else {
+            for (int i = tid; i < n_words; i += MASK_THREADS) out[i] = word(i);
+        }
+        return;
+    }
     if (found && ce - cb > ix.heavy_min) {  // ready-made image: plain copy
         const uint32_t *src = ix.heavy_bits + (size_t)heavy_slot_of(ix, node) * (size_t)n_words;
         if (wide && (((uintptr_t)ix.heavy_bits) & 15u) == 0) {
@@ -142,7 +156,9 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(IndexView ix, c
     }
     uint32_t word = 0u;
     const uint32_t nchild = w.found ? w.ce - w.cb : 0u;
-    if (nchild > ix.heavy_min) {   // ready-made image
+    if (w.only != PPV_NO_SLOT) {
+        if ((uint32_t)lane == (w.only & PPV_NODE_TOKEN) >> 5) word = 1u << (w.only & 31u);
+    } else if (nchild > ix.heavy_min) {   // ready-made image
         if (lane < n_words) word = ix.heavy_bits[(size_t)heavy_slot_of(ix, w.node) * (size_t)n_words + lane];
     } else if (nchild > 0u) {      // nchild <= heavy_min <= 64
         const uint32_t tok = (uint32_t)lane < nchild ? (ix.ent[w.cb + (uint32_t)lane].tok & PPV_NODE_TOKEN) : 0u;
@@ -1139,7 +1155,9 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
     uint32_t word = 0u;
     const uint32_t nchild = w.found ? w.ce - w.cb : 0u;
-    if (nchild > ix.heavy_min) {   // ready-made image
+    if (w.only != PPV_NO_SLOT) {
+        if ((uint32_t)lane == (w.only & PPV_NODE_TOKEN) >> 5) word = 1u << (w.only & 31u);
+    } else if (nchild > ix.heavy_min) {   // ready-made image
         if (lane < n_words) word = ix.heavy_bits[(size_t)heavy_slot_of(ix, w.node) * (size_t)n_words + lane];
     } else if (nchild > 0u) {      // nchild <= heavy_min <= 64: one child per lane
         const uint32_t tok = (uint32_t)lane < nchild ? (ix.ent[w.cb + (uint32_t)lane].tok & PPV_NODE_TOKEN) : 0u;
@@ -1185,7 +1203,7 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_kernel(IndexView ix
     const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
     int t = lens[b];
     t = t < 0 ? 0 : (t > stride ? stride : t);
-    const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
+    const Walk w = walk_prefix<true>(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
     if (lane == 0) {
         RowState st;
         st.node = w.found ? w.node : PPV_NO_SLOT;
@@ -1343,24 +1361,29 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
     RawTile first;
     load_tile<T>(row, V, vwave, lane, first);   // in flight during the index work
     t = t < 0 ? 0 : (t > stride ? stride : t);
+    uint32_t only = PPV_NO_SLOT;   // without a cursor, the one child of a prefix of a single member: no node is looked at then
     if (!REG && !state) {  // no cursor: locate the prefix from the root (wave 0), then share it
         if (wave == 0) {
             const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
-            const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
+            const Walk w = walk_prefix<LOOP>(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
             if (lane == 0) {
                 sh.bc_i[4] = (int)(w.found ? w.node : PPV_NO_SLOT);
                 sh.bc_i[5] = (int)(w.found ? w.cb : 0u);
                 sh.bc_i[6] = (int)(w.found ? w.ce : 0u);
+                sh.bc_i[7] = (int)w.only;
             }
         }
         __syncthreads();
         st.node = (uint32_t)sh.bc_i[4];
         st.cb = (uint32_t)sh.bc_i[5];
         st.ce = (uint32_t)sh.bc_i[6];
-        st.slot = (st.node != PPV_NO_SLOT && st.ce - st.cb > ix.heavy_min) ? heavy_slot_of(ix, st.node) : PPV_NO_SLOT;
+        only = (uint32_t)sh.bc_i[7];
+        st.slot = (st.node != PPV_NO_SLOT && only == PPV_NO_SLOT && st.ce - st.cb > ix.heavy_min)
+                      ? heavy_slot_of(ix, st.node)
+                      : PPV_NO_SLOT;
         __syncthreads();
     }
-    if (!STEP_REG) check_cursor();
+    if (!STEP_REG && (LOOP || only == PPV_NO_SLOT)) check_cursor();
     if (STEP_REG && rl.on) {
         // ---- a short list in wavefront 0's registers.  The sample depends on the listed logits alone, not on the
         // row's totals: wavefront 0 draws the token and works out the next cursor while its tile is still on its
@@ -1700,11 +1723,18 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         if (mode == VALID_LIST) {
             // children are sorted by token: the list is ready as it is.  One entry more than the
             // children is taken along: it closes the last child's own children range.
-            for (int i = tid; i <= nchild; i += nw * WAVE) {
-                const NodeEnt e = ix.ent[cb + i];
-                sh.list_tok[i] = e.tok;
-                sh.list_child[i] = e.child;
-                if (i < nchild && (e.tok & PPV_NODE_TERMINAL)) member_child = 1;
+            if (!LOOP && only != PPV_NO_SLOT) {
+                if (tid == 0) {
+                    sh.list_tok[0] = only;
+                    sh.list_child[0] = sh.list_child[1] = 0u;
+                }
+            } else {
+                for (int i = tid; i <= nchild; i += nw * WAVE) {
+                    const NodeEnt e = ix.ent[cb + i];
+                    sh.list_tok[i] = e.tok;
+                    sh.list_child[i] = e.child;
+                    if (i < nchild && (e.tok & PPV_NODE_TERMINAL)) member_child = 1;
+                }
             }
             if (LOOP) member_child = __syncthreads_or(member_child);
             else __syncthreads();
@@ -1930,7 +1960,7 @@ extern "C" ppv_status ppv_next_token_mask(const ppv_index_t *ix, const int32_t *
                            (hipStream_t)stream, ix->view, prefixes, prefix_stride, lens, B, mask, range_lo, range_hi,
                            member);
     } else {
-        const size_t lds = ((size_t)ix->view.n_words + 4) * sizeof(uint32_t);
+        const size_t lds = ((size_t)ix->view.n_words + 5) * sizeof(uint32_t);
         hipLaunchKernelGGL(mask_kernel, dim3((unsigned)B), dim3(MASK_THREADS), lds, (hipStream_t)stream, ix->view,
                            prefixes, prefix_stride, lens, mask, range_lo, range_hi, member);
     }

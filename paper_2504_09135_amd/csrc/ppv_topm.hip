@@ -675,18 +675,18 @@ __device__ inline void count_chunk(const uint4 &raw, int V, int c, int lane, int
     }
 }
 
-// The mask row of a prefix with n <= TOPM_COUNT_MAX children (entries cb .. cb + n - 1), restricted to the m most
-// probable tokens.  Every thread of the workgroup calls; r holds the wavefront's first TOPM_HELD chunks; tot[] was
+// The mask row of a prefix with n <= TOPM_COUNT_MAX children (entries cb .. cb + n - 1, or the one child `only`),
+// restricted to the m most probable tokens.  Every thread of the workgroup calls; r holds the wavefront's first TOPM_HELD chunks; tot[] was
 // cleared before the last barrier.
 template <typename T>
 __device__ inline void count_children(const IndexView &ix, const T *__restrict__ row, int V, int nc, int c0, int c1,
-                                      int m, uint32_t cb, int n, uint4 (&r)[TOPM_HELD], uint32_t *tot,
+                                      int m, uint32_t cb, uint32_t only, int n, uint4 (&r)[TOPM_HELD], uint32_t *tot,
                                       uint32_t *__restrict__ out, int n_words, int lane, int nthreads) {
     // child j in lane j: its token and that token's logit
     uint32_t ctok = 0u;
     float cthr = 0.f;
     if (lane < n) {
-        ctok = ix.ent[cb + (uint32_t)lane].tok & PPV_NODE_TOKEN;
+        ctok = (only != PPV_NO_SLOT ? only : ix.ent[cb + (uint32_t)lane].tok) & PPV_NODE_TOKEN;
         ctok = ctok < (uint32_t)V ? ctok : 0u;   // (always inside for an index that was built or loaded)
         cthr = __uint_as_float(KeyChunk<T>::bits_of(row, (int)ctok));
     }
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(IndexView ix, co
                                                                 uint8_t *__restrict__ mask_V,
                                                                 uint32_t *__restrict__ mask) {
     constexpr int EPL = KeyChunk<T>::EPL;
-    extern __shared__ __align__(16) uint32_t smem[];  // max(TOPM_BINS, n_words) words, then heavy_min words for kids
+    extern __shared__ __align__(16) uint32_t smem[];  // max(TOPM_BINS, n_words) words, then heavy_min (1 at least) words for kids
     uint32_t *img = smem;                             // [n_words] the row of the mask, once the histogram is done with
     __shared__ uint32_t list_tok[LIST], list_key[LIST];
     __shared__ uint32_t hist2[TOPM_CBINS], hist3[32];
@@ -791,12 +791,13 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(IndexView ix, co
             bc[1] = w.found ? 1u : 0u;
             bc[2] = w.found ? w.cb : 0u;
             bc[3] = w.found ? w.ce : 0u;
+            bc[7] = w.only;
         }
     }
     __syncthreads();   // the walk's verdict
     const uint32_t node = bc[0];
     const bool found = bc[1] != 0u;
-    const uint32_t cb = bc[2], ce = bc[3];
+    const uint32_t cb = bc[2], ce = bc[3], only = bc[7];
     const int n = (int)(ce - cb);
     if (counting) {
         uint32_t *out = mask + (size_t)b * (size_t)n_words;
@@ -813,16 +814,19 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(IndexView ix, co
         // that the selection reads once (bound from its first chunks alone, see select_listed) is no faster counted
         // (V = 256k: 120 against 117 us).
         const bool select_reads_once = listed && (cpw <= TOPM_HELD || (long long)m * cpw <= 4ll * LIST);
-        if (n <= TOPM_COUNT_MAX && (uint32_t)n <= ix.heavy_min && (cpw <= TOPM_HELD || !select_reads_once)) {
-            count_children<T>(ix, row, V, nc, c0, c1, m, cb, n, r, seg_a, out, n_words, lane, nthreads);
+        if (n <= TOPM_COUNT_MAX && (only != PPV_NO_SLOT || (uint32_t)n <= ix.heavy_min) && (cpw <= TOPM_HELD || !select_reads_once)) {
+            count_children<T>(ix, row, V, nc, c0, c1, m, cb, only, n, r, seg_a, out, n_words, lane, nthreads);
             return;
         }
     }
     // the children's tokens go to LDS while the row is on its way: the candidates are then looked up there
-    const bool kids_listed = found && (uint32_t)n <= ix.heavy_min;
-    if (kids_listed)
+    const bool kids_listed = found && (only != PPV_NO_SLOT || (uint32_t)n <= ix.heavy_min);
+    if (only != PPV_NO_SLOT) {
+        if (tid == 0) kids[0] = only & PPV_NODE_TOKEN;
+    } else if (kids_listed) {
         for (int i = tid; i < n; i += nthreads) kids[i] = ix.ent[cb + (uint32_t)i].tok & PPV_NODE_TOKEN;
-    const uint32_t slot = (found && (uint32_t)n > ix.heavy_min) ? heavy_slot_of(ix, node) : PPV_NO_SLOT;
+    }
+    const uint32_t slot = (found && !kids_listed) ? heavy_slot_of(ix, node) : PPV_NO_SLOT;
     // ---- select
     bool done = false;
     if (listed) done = select_listed<T, LIST>(row, V, c0, c1, m, lds, lane, wave, nthreads, r);
@@ -898,7 +902,7 @@ extern "C" ppv_status ppv_topm_mask(const ppv_index_t *ix, const int32_t *prefix
     // testing aid: PPV_TUNE_TOPM_STREAMING = 1 sends every row through the whole-row radix select; 2 keeps the usual
     // select but takes the top M also where counting would do (mask-only calls)
     const int force_streaming = ppv_tuning(PPV_TUNE_TOPM_STREAMING);
-    const size_t lds = ((size_t)(ix->view.n_words > TOPM_BINS ? ix->view.n_words : TOPM_BINS) + ix->view.heavy_min) * sizeof(uint32_t);
+    const size_t lds = ((size_t)(ix->view.n_words > TOPM_BINS ? ix->view.n_words : TOPM_BINS) + (ix->view.heavy_min ? ix->view.heavy_min : 1u)) * sizeof(uint32_t);
     const dim3 grid((unsigned)B), block(threads);
     hipStream_t hs = (hipStream_t)stream;
 #define PPV_LAUNCH_TOPM(T, LIST)                                                                                      \
