@@ -804,8 +804,7 @@ struct Arena {
 struct TempArena : Arena {   // given back at the end of the build, when everything that used it has finished
     ~TempArena() {
         if (!block) return;
-        (void)hipStreamSynchronize(nullptr);
-        ppv_pool_give(block);
+        ppv_pool_give(block, hipStreamSynchronize(nullptr) == hipSuccess);
     }
 };
 
@@ -1097,12 +1096,12 @@ void release(ppv_index *ix) {
         int dev = -1;
         (void)hipGetDevice(&dev);
         if (ix->device >= 0 && ix->device != dev) (void)hipSetDevice(ix->device);
-        (void)hipDeviceSynchronize();
+        const bool over = hipDeviceSynchronize() == hipSuccess;
         if (ix->device >= 0 && ix->device != dev && dev >= 0) (void)hipSetDevice(dev);
         (void)hipThreadExchangeStreamCaptureMode(&mode);
         (void)hipGetLastError();
-        ppv_pool_give(ix->block);
-        ppv_pool_give(ix->heavy_block);
+        ppv_pool_give(ix->block, over);
+        ppv_pool_give(ix->heavy_block, over);
     }
     delete ix;
 }

@@ -115,10 +115,10 @@ struct ppv_index {
     int device;
 };
 
-// Device memory kept from one index to the next, and the upload of a set (ppv_pool.hip).  ppv_pool_give: the device has
-// finished with the block.
+// Device memory kept from one index to the next, and the upload of a set (ppv_pool.hip).  ppv_pool_give:
+// `over` says that the device has finished with the block; where the caller's wait failed, the block is not kept.
 ppv_status ppv_pool_take(void **out, size_t bytes);
-void ppv_pool_give(void *block);
+void ppv_pool_give(void *block, bool over);
 // A little pinned memory that kernels can write (nullptr: none to be had).
 constexpr int PPV_HOST_WORDS_BYTES = 64;
 void *ppv_host_words_take();

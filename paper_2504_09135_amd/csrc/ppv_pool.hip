@@ -7,7 +7,8 @@
 // Device blocks: ppv_pool_take hands out a block of at least the size asked for, from the blocks that were given back
 // or from hipMalloc; ppv_pool_give keeps it for the next taker.  At most POOL_KEEP bytes are kept per process, for at
 // most POOL_SECONDS from their last use (looked at when a block is taken or given), and all of them go back to the
-// system when an allocation fails.  Whoever gives a block back has made sure that the device is done with it.
+// system when an allocation fails.  Whoever gives a block back has waited for the device to be done with it;
+// a block whose wait failed goes to hipFree, which waits by itself.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -100,7 +101,7 @@ ppv_status ppv_pool_take(void **out, size_t bytes) {
     }
 }
 
-void ppv_pool_give(void *q) {
+void ppv_pool_give(void *q, bool over) {
     if (!q) return;
     Pool &p = pool();
     std::lock_guard<std::mutex> lock(p.mu);
@@ -109,7 +110,7 @@ void ppv_pool_give(void *q) {
     const size_t bytes = it->second.first;
     const int dev = it->second.second;
     p.out.erase(it);
-    if (bytes > POOL_KEEP) {
+    if (bytes > POOL_KEEP || !over) {
         (void)hipFree(q);
     } else {
         p.kept.push_back({q, bytes, dev, Clock::now()});
