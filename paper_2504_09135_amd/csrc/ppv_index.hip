@@ -1082,6 +1082,7 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
     }
     if (again) TRY(measure());
     const uint32_t n_rows = (uint32_t)(words.w->rows_tokens >> 32), n_tok = (uint32_t)words.w->rows_tokens;
+    if ((uint64_t)l_max * n_rows + 1 > 0xFFFFFFF0ull) return PPV_ERANGE;   // (depth, row) pairs are limited to 32 bits
     return number_prefixes(ix, tok, rows, n_rows, n_tok, l_max, counts, n_groups, group_lcp, words.w->prefixes,
                            words.w->all_counts - words.w->prefixes, vocab, words, st);
 }

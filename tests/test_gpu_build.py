@@ -154,3 +154,18 @@ def test_builds_one_after_another_reuse_memory():
         if len(alive) == 2:
             alive.pop(int(rng.integers(0, 2)))[0].free()
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,ok", [(60_000, True), (61_400, False)])
+def test_sets_beyond_the_limit_of_depths_times_rows_are_refused(n, ok):
+    """One row of 70,000 tokens among rows of one token: accepted while depths x rows stay below 2^32 (4.2e9 and 4.298e9)."""
+    long = np.arange(70_000, dtype=np.int32)
+    tokens = np.concatenate([long, np.arange(1, n, dtype=np.int32)])
+    offsets = np.concatenate([[0], 70_000 + np.arange(n)]).astype(np.int64)
+    if not ok:
+        with pytest.raises(ppv.PPVError, match="ERANGE"):
+            ppv.ppv_build_index(tokens, offsets, 70_000)
+        return
+    index = ppv.ppv_build_index(tokens, offsets, 70_000)
+    assert (index.n_distinct, index.l_max, index.n_prefixes) == (n, 70_000, 70_000 + n - 1)
+    index.free()
