@@ -1870,6 +1870,12 @@ int waves_for(int V, ppv_dtype dt, int B, int parts = 1, bool cursor_step = fals
     // long rows in a small batch: one row per compute unit, all of it in flight (constrained_sample, B = 256, us per
     // call with 8 / 16 wavefronts: 32 tiles: 13.2 / 12.0 (fp32 V = 32k), 15.2 / 14.2 (bf16 V = 64k); 63 tiles: 23.6 / 20.6)
     if (nt >= 32 && B <= 256) cap = 16;
+    // long rows in a large batch: the loads in flight are the same with fewer rows at a time, and each of these is over
+    // sooner.  us with 4 / 8 / 16 wavefronts, decoding loops: V = 200k bf16, B = 1,000: 326 / 289 / 319; V = 128k bf16,
+    // B = 1,024: 298 / 287 / 321, B = 1,800: 358 / 341 / 378; V = 50k fp32, B = 1,024: 363 / 352 / 371; V = 32k bf16 (16
+    // tiles), B = 1,024: 211 / 219 / 279.  Mask + sample, B = 1,024: V = 200k 92.3 / 89.1 / 88.9, V = 50k fp32
+    // 40.7 / 39.5 / 41.7; ppv_sample_next: V = 128k 49.1 / 48.8 / 56.6, V = 50k fp32 36.7 / 37.0 / 40.6.
+    if (nt >= 48 && B > 512) cap = 8;
     if (const int v = ppv_tuning(PPV_TUNE_WAVES_PER_ROW)) cap = v;   // tuning aid (0: the table above)
     int nw = 1;
     while (nw < nt && nw * 2 <= cap) nw <<= 1;
@@ -2099,6 +2105,7 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
     const int parts = (loop || fresh) ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch);
     int nw = waves_for(ix->view.vocab, dt, B, parts, !loop && state != nullptr);
     if (loop && nw > LOOP_WAVES) nw = LOOP_WAVES;
+    if (loop && B > 512 && nw > 4 && ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0) nw = 4;   // (its rows stay: see below)
     // The loop kernel in a large batch: a workgroup stays with its row for every step, so what hides one row's
     // dependent phases (cursor, barrier, draw) is other rows on the same compute unit, and two wavefronts per row
     // put twice as many there as four (C3 replicas, M prefix-steps/s with 1 / 2 / 4 / 8 wavefronts per row:
