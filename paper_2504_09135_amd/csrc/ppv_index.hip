@@ -506,16 +506,15 @@ __global__ __launch_bounds__(BT) void count_prefixes(const RowMeta *__restrict__
         counts[(size_t)l_max * n_groups + c] = n_entries;
         group_lcp[c] = lowest;
     }
-    const int longest = (int)wave_max(len);
-    for (int d0 = 0; d0 < l_max; d0 += WAVE) {
+    const uint32_t longest = wave_max(len), depths = (uint32_t)l_max;
+    for (uint32_t d0 = 0; d0 < depths; d0 += WAVE) {   // (unsigned: the step past the longest row there can be is no overflow)
         uint32_t mine = 0u;
-        const int d1 = longest - d0 < WAVE ? longest - d0 : WAVE;
-        for (int k = 0; k < d1; k++) {
-            const uint32_t d = (uint32_t)(d0 + k);
+        const uint32_t d1 = d0 + WAVE < longest ? d0 + WAVE : longest;
+        for (uint32_t d = d0; d < d1; d++) {
             const uint32_t opened = (uint32_t)__popcll(__ballot(lcp <= d && d < len));
-            if (lane == k) mine = opened;
+            if ((uint32_t)lane == d - d0) mine = opened;
         }
-        if (d0 + lane < l_max) counts[(size_t)(d0 + lane) * n_groups + c] = mine;
+        if (d0 + lane < depths) counts[(size_t)(d0 + lane) * n_groups + c] = mine;
     }
 }
 
@@ -577,11 +576,12 @@ __global__ __launch_bounds__(BT) void fill_prefixes(TOK tok, const RowMeta *__re
         if (r + 1 == n_rows) o.x_off[n_rows] = (int64_t)m.at + m.len;
     }
     // numbers of the first prefixes these rows open at depths 0 .. 63 (lane = depth), and so on for the next 64
-    auto firsts = [&](int d0) {
-        const int d = d0 + lane;
-        return d <= l_max ? base[(size_t)d * n_groups + (d < l_max ? c : 0u)] : 0u;   // behind the last depth: all prefixes
+    const uint32_t depths = (uint32_t)l_max;
+    auto firsts = [&](uint32_t d0) {
+        const uint32_t d = d0 + (uint32_t)lane;
+        return d <= depths ? base[(size_t)d * n_groups + (d < depths ? c : 0u)] : 0u;   // behind the last depth: all prefixes
     };
-    uint32_t first_at = firsts(0);
+    uint32_t first_at = firsts(0u);
     const uint32_t at0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)m.at);
     const uint32_t span = wave_max(r < n_rows ? m.at + m.len - at0 : 0u);
     const bool staged = span <= room;
@@ -618,16 +618,15 @@ __global__ __launch_bounds__(BT) void fill_prefixes(TOK tok, const RowMeta *__re
     const uint32_t after = (uint32_t)__builtin_amdgcn_readlane((int)next_lcp, WAVE - 1);   // (of the row after these 64)
     const bool last_group = (c + 1) * WAVE >= n_rows;
     const uint64_t below = (1ull << lane) - 1ull;
-    const int longest = (int)wave_max(m.len);
+    const uint32_t longest = wave_max(m.len);
     PrefixHash h = prefix_hash_empty();
     uint64_t opened = __ballot(m.lcp == 0u && m.len > 0u);
     uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first_at);
-    for (int di = 0; di < longest; di++) {
-        const uint32_t d = (uint32_t)di;
+    for (uint32_t d = 0; d < longest; d++) {
         // what is opened one level down: the children of this level's prefixes
         const uint64_t opened_next = __ballot(m.lcp <= d + 1u && d + 1u < m.len);
-        if (((di + 1) & (WAVE - 1)) == 0) first_at = firsts(di + 1);
-        const uint32_t first_next = lane_value(first_at, (di + 1) & (WAVE - 1));
+        if (((d + 1u) & (WAVE - 1)) == 0u) first_at = firsts(d + 1u);
+        const uint32_t first_next = lane_value(first_at, (int)((d + 1u) & (WAVE - 1)));
         const bool opens = m.lcp <= d && d < m.len;
         const bool hashes = d < entries_to && m.lcp < entries_to;
         uint32_t t = 0u;
@@ -1182,13 +1181,14 @@ __global__ __launch_bounds__(BT) void meta_of_rows(const int32_t *__restrict__ x
 }
 __global__ __launch_bounds__(BT) void check_loaded_rows(const int32_t *__restrict__ x_tok, const int64_t *__restrict__ x_off,
                                                         uint64_t n_rows, uint64_t n_tokens, int32_t vocab, int32_t l_max,
-                                                        int32_t *__restrict__ err) {
+                                                        int32_t *__restrict__ err, int32_t *__restrict__ reached) {
     const uint64_t i = (uint64_t)blockIdx.x * BT + threadIdx.x;
     bool bad = false;
     if (i < n_rows) {
         const int64_t a = x_off[i], b = x_off[i + 1];
         bad = a < 0 || b <= a || b - a > l_max || (uint64_t)b > n_tokens || (i == 0 && a != 0) ||
               (i == n_rows - 1 && (uint64_t)b != n_tokens);
+        if (b - a == l_max) *reached = 1;   // (some row is as long as the file says; all that find one write the same)
     }
     if (i < n_tokens) bad = bad || x_tok[i] < 0 || x_tok[i] >= vocab;
     if (bad) atomicOr(err, 2);
@@ -1253,6 +1253,9 @@ ppv_status load_from_file(FILE *f, ppv_index *ix) {
     if (fread(&h, sizeof(h), 1, f) != 1) return PPV_EINVAL;   // shorter than a header: not an index file
     if (memcmp(h.magic, FILE_MAGIC, 8) != 0 || h.version != 1 || h.header_bytes != sizeof(FileHeader)) return PPV_EINVAL;
     if (h.vocab <= 0 || h.l_max <= 0 || h.n_rows == 0 || h.n_nodes < 2 || h.n_tokens < h.n_rows) return PPV_EINVAL;
+    // No row is longer than what the others leave of the tokens, and the file's length vouches for n_tokens: a longest row
+    // beyond that would ask for arrays, and for loops over the depths, of any size up to 2^31.
+    if ((uint64_t)h.l_max > h.n_tokens - h.n_rows + 1) return PPV_EINVAL;
     if (h.vocab > PPV_MAX_VOCAB || h.n_rows > 0xFFFFFFF0ull || h.n_nodes > 0xFFFFFFF0ull || h.n_tokens > 0xFFFFFFF0ull)
         return PPV_ERANGE;
     const size_t bytes[5] = {((size_t)h.n_nodes + 1) * sizeof(NodeEnt), (size_t)h.n_nodes * sizeof(uint32_t),
@@ -1288,7 +1291,7 @@ ppv_status load_from_file(FILE *f, ppv_index *ix) {
     tmp.add(&sums, scan_words(n_counts));
     tmp.add(&d_tot64, 1);
     tmp.add(&d_word, 1);
-    tmp.add(&d_err, 1);
+    tmp.add(&d_err, 2);
     TRY(tmp.take());
     void *dev[5] = {f_ent, f_lo, f_hi, f_off, f_tok};
     unsigned char *stage = new (std::nothrow) unsigned char[IO_CHUNK];
@@ -1316,13 +1319,13 @@ ppv_status load_from_file(FILE *f, ppv_index *ix) {
     if (!words.w) return PPV_ENOMEM;
     // the checksum guards against damage; these checks guard the kernels against a file that was wrong when written
     hipStream_t s0 = nullptr;
-    PPV_HIP_TRY(hipMemsetAsync(d_err, 0, sizeof(int32_t), s0));
+    PPV_HIP_TRY(hipMemsetAsync(d_err, 0, 2 * sizeof(int32_t), s0));   // what is wrong; whether a row of l_max tokens is there
     hipLaunchKernelGGL(check_loaded_rows, dim3(blocks_for(std::max(h.n_rows, h.n_tokens))), dim3(BT), 0, s0,
-                       (const int32_t *)f_tok, (const int64_t *)f_off, h.n_rows, h.n_tokens, h.vocab, h.l_max, d_err);
+                       (const int32_t *)f_tok, (const int64_t *)f_off, h.n_rows, h.n_tokens, h.vocab, h.l_max, d_err, d_err + 1);
     PPV_HIP_TRY(hipGetLastError());
-    int32_t err = 0;
-    TRY(read_back(&err, d_err, 1, s0));
-    if (err != 0) return PPV_EINVAL;
+    int32_t found[2] = {0, 0}, err = 0;
+    TRY(read_back(found, d_err, 2, s0));
+    if (found[0] != 0 || found[1] != 1) return PPV_EINVAL;
     hipLaunchKernelGGL(meta_of_rows, dim3(blocks_for(n_rows)), dim3(BT), 0, s0, (const int32_t *)f_tok, (const int64_t *)f_off,
                        n_rows, rows, d_err);
     const uint64_t tot64 = h.n_rows << 32;

@@ -135,3 +135,26 @@ def test_structurally_wrong_files_with_a_correct_checksum_are_refused(tmp_path):
     assert status_with(st[3] + 8 * 1, 0, 8) == -1               # row offsets not increasing
     assert status_with(st[4] + 4 * 2, cfg.vocab, 4) == -1       # a member token outside the vocabulary
     assert status_with(ent + 4, 1) == 0                         # (patching a value with itself still loads)
+
+
+@pytest.mark.parametrize("name", ["C1", "C2"])
+def test_files_with_a_wrong_longest_row_are_refused(name, tmp_path):
+    """The longest row's length stands in the header alone, which the checksum does not cover: too small, too large by one,
+    as large as the rows' number allows, and larger than any row of the file could be."""
+    cfg, S, trie, index = setup_case(name)
+    path = tmp_path / "set.ppv"
+    ppv.ppv_index_save(index, str(path))
+    good = path.read_bytes()
+    assert int.from_bytes(good[20:24], "little") == index.l_max
+    n_tokens = len(ppv.ppv_index_export(index)[0])
+    most = n_tokens - index.n_distinct + 1
+    for l_max, status in ((index.l_max, 0), (index.l_max - 1, -1), (index.l_max + 1, -1), (min(most, 5_000), -1), (most + 1, -1),
+                          (0, -1)):
+        p = tmp_path / "wrong.ppv"
+        p.write_bytes(good[:20] + int(l_max).to_bytes(4, "little") + good[24:])
+        try:
+            ppv.ppv_index_load(str(p)).free()
+            got = 0
+        except ppv.PPVError as e:
+            got = e.status
+        assert got == status, l_max
