@@ -5,8 +5,9 @@
 //   1. sort the rows lexicographically -- token order = integer order, left to right, a sequence that ends sorts
 //      before its extensions.  A row's first tokens, as many as fit, make a 64-bit key (token + 1, or 0 past the
 //      row's end, most significant first); the keys are radix-sorted.  Rows with equal keys are neighbours then: groups
-//      of up to about a thousand of them are ordered by counting, for each row, the rows of its group that sort before it;
-//      larger groups take another round on their rows' next tokens, together with the group's number;
+//      of up to about a thousand of them are ordered by counting, for each row, the rows of its group whose next key is
+//      smaller, and the few that agree in that one too token by token; more than a few are counted again by the key after
+//      it, and groups beyond a thousand take a radix sort by their rows' next tokens together with the group's number;
 //   2. longest common prefix of neighbouring sorted rows; duplicates dropped (S is a set);
 //   3. number the prefixes breadth-first.  Row r opens a new prefix of length d+1 iff it is longer than d and shares
 //      at most d tokens with the row before it.  One wavefront takes 64 rows, a lane each: a ballot per depth counts
@@ -298,20 +299,22 @@ ppv_status radix_sort(uint64_t *&key, uint64_t *&key2, uint32_t *&row, uint32_t 
 constexpr int GROUP_PAD = 16;
 constexpr uint8_t GROUP_HEAD = 1;   // the first of its group
 constexpr uint8_t GROUP_DONE = 2;   // nothing left to order in this group (the rows have ended: they are duplicates)
-// Rows of a group are ordered by counting up to this size: size^2 comparisons, nearly all of them of two 64-bit
-// words that lie together.  (The largest group after four tokens of the 1M-sequence Zipf sets: about 500 rows.)  Rows
-// that agree in those words too are compared token by token, so a group of long rows has to be smaller.
-inline uint32_t group_max(int64_t tokens_left) {
-    return (uint32_t)std::max<int64_t>(8, std::min<int64_t>(1024, 16384 / std::max<int64_t>(tokens_left, 1)));
-}
+// Rows of a group are ordered by counting up to this size: size^2 comparisons of two 64-bit words that lie together.
+// (The largest group after four tokens of the 1M-sequence Zipf sets: about 500 rows.)
+constexpr uint32_t GROUP_COUNT = 1024;
+// Rows that agree in the next key too are compared token by token as long as there are no more than this many of them; more
+// stay a group for a further round.  A round (a trip to the host and two launches) costs about as much as a row comparing
+// three tokens with twenty others, one after the other.  Comparing whole groups that way took 52 to 78 ms instead of 8 for
+// 500k rows that share long stems, or are copies of a thousand rows.
+constexpr uint32_t GROUP_TOKENS = 16;
 
-__global__ __launch_bounds__(BT) void mark_groups(const uint64_t *__restrict__ key, uint32_t n, uint64_t last_slot, int complete,
+__global__ __launch_bounds__(BT) void mark_groups(const uint64_t *__restrict__ key, uint32_t n, uint64_t last_slot,
                                                   uint8_t *__restrict__ group, uint8_t *__restrict__ group2) {
     const uint32_t i = blockIdx.x * BT + threadIdx.x;
     if (i < GROUP_PAD) group[n + i] = group2[n + i] = GROUP_HEAD;
     if (i >= n) return;
     const uint64_t k = key[i];
-    group[i] = (uint8_t)(((i == 0u || key[i - 1] != k) ? GROUP_HEAD : 0) | ((complete || (k & last_slot) == 0ull) ? GROUP_DONE : 0));
+    group[i] = (uint8_t)(((i == 0u || key[i - 1] != k) ? GROUP_HEAD : 0) | ((k & last_slot) == 0ull ? GROUP_DONE : 0));
 }
 __device__ inline bool unsettled(const uint8_t *__restrict__ group, uint32_t i, uint32_t n) {
     const uint8_t g = group[i];
@@ -327,15 +330,17 @@ __global__ __launch_bounds__(BT) void next_keys(PackedTokens tok, const uint32_t
     const uint32_t r = row[i], a = off[r];
     key[i] = row_key(tok, a, off[r + 1] - a, depth, ks);
 }
-// Orders the rows of every group of at most `most`; counts the rows of the larger ones.  depth: tokens that
-// `group` and `key` together have covered.
+// Orders the rows of every group of at most GROUP_COUNT, up to groups of more than GROUP_TOKENS that agree in this key too;
+// left[0], left[1]: rows in larger groups, and rows in such groups.  depth: tokens that `group` and `key` together have
+// covered; complete: no row is longer.
 __global__ __launch_bounds__(BT) void order_groups(PackedTokens tok, const uint32_t *__restrict__ off,
                                                    const uint32_t *__restrict__ row, const uint8_t *__restrict__ group,
                                                    const uint64_t *__restrict__ key, uint32_t n, uint32_t depth,
-                                                   uint64_t last_slot, uint32_t most, uint32_t *__restrict__ row_out,
-                                                   uint8_t *__restrict__ group_out, uint32_t *__restrict__ n_large) {
+                                                   uint64_t last_slot, int complete, uint32_t *__restrict__ row_out,
+                                                   uint8_t *__restrict__ group_out, uint32_t *__restrict__ left) {
+    constexpr uint32_t most = GROUP_COUNT;
     const uint32_t i = blockIdx.x * BT + threadIdx.x;
-    bool large = false;
+    bool large = false, split = false;
     if (i < n) {
         const uint32_t r = row[i];
         uint8_t g = group[i];
@@ -367,7 +372,14 @@ __global__ __launch_bounds__(BT) void order_groups(PackedTokens tok, const uint3
                     before += kj < k ? 1u : 0u;
                     equal += kj == k ? 1u : 0u;
                 }
-                if (equal > 1u) {   // rows that agree in this key too: token by token
+                g = GROUP_HEAD | GROUP_DONE;
+                if (equal > GROUP_TOKENS && !complete && (k & last_slot) != 0ull) {   // a group of their own, in the order they are in
+                    uint32_t ahead = 0;
+                    for (uint32_t j = a; j < i; j++) ahead += key[j] == k ? 1u : 0u;
+                    before += ahead;
+                    split = true;
+                    g = ahead == 0u ? GROUP_HEAD : (uint8_t)0;
+                } else if (equal > 1u) {   // rows that agree in this key too: token by token
                     const uint32_t ra = off[r], rl = off[r + 1] - ra;
                     for (uint32_t j = a; j < b; j++) {
                         if (j == i || key[j] != k) continue;
@@ -384,18 +396,20 @@ __global__ __launch_bounds__(BT) void order_groups(PackedTokens tok, const uint3
                     }
                 }
                 to = a + before;
-                g = GROUP_HEAD | GROUP_DONE;
             } else {
                 large = true;
             }
         }
         row_out[to] = r;
-        group_out[i] = g;
+        group_out[to] = g;
     }
-    const uint64_t bal = __ballot(large);
-    if (bal && (threadIdx.x & (WAVE - 1)) == 0) atomicAdd(n_large, (uint32_t)__popcll(bal));
+    const uint64_t is_large = __ballot(large), is_split = __ballot(split);
+    if ((threadIdx.x & (WAVE - 1)) == 0) {
+        if (is_large) atomicAdd(&left[0], (uint32_t)__popcll(is_large));
+        if (is_split) atomicAdd(&left[1], (uint32_t)__popcll(is_split));
+    }
 }
-// what is left after order_groups (large groups): rows of it before each position | groups of it up to there
+// what is left after order_groups: rows of it before each position | groups of it up to there
 struct LargeRows {
     const uint8_t *group;
     uint32_t n;
@@ -811,17 +825,17 @@ struct TempArena : Arena {   // given back at the end of the build, when everyth
 struct BuildWords {
     uint64_t rows_tokens;                 // rows << 32 | tokens, without duplicates
     uint32_t prefixes, all_counts;        // prefixes; prefixes and look-up entries
-    uint32_t large;                       // rows in groups too large to be ordered by counting
+    uint32_t large, split;                // rows in groups too large to be ordered by counting; in groups that are to be counted again
     uint32_t heavy, heavy_limit;          // heavy prefixes, one past the last of them
-    int32_t err;
 };
 static_assert(sizeof(BuildWords) <= PPV_HOST_WORDS_BYTES, "one slot of pinned words");
 __global__ void publish(BuildWords *__restrict__ out, const uint64_t *__restrict__ rows_tokens, const uint32_t *__restrict__ prefixes,
-                        const uint32_t *__restrict__ all_counts, const uint32_t *__restrict__ large) {
+                        const uint32_t *__restrict__ all_counts, const uint32_t *__restrict__ left) {
     out->rows_tokens = *rows_tokens;
     out->prefixes = *prefixes;
     out->all_counts = *all_counts;
-    out->large = *large;
+    out->large = left[0];
+    out->split = left[1];
 }
 __global__ void publish_heavy(BuildWords *__restrict__ out, const uint32_t *__restrict__ heavy) {
     out->heavy = heavy[0];
@@ -992,7 +1006,7 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
     in.add(&place, n);
     in.add(&sums64, scan_words(n));
     in.add(&d_tot64, 1);
-    in.add(&d_word, 2);
+    in.add(&d_word, 3);
     in.add(&rows, n);
     TRY(in.take());
     if (!wide) d_hi = nullptr;
@@ -1022,13 +1036,13 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
     const HostWords words;
     if (!words.w) return PPV_ENOMEM;
 
-    PPV_HIP_TRY(hipMemsetAsync(d_word, 0, 2 * sizeof(uint32_t), st));   // rows in large groups; all counts
-    auto order = [&] {   // groups of rows equal so far, small ones ordered, rows in large ones counted in *d_word
+    PPV_HIP_TRY(hipMemsetAsync(d_word, 0, 3 * sizeof(uint32_t), st));   // what order_groups leaves (two words); all counts
+    auto order = [&] {   // groups of rows equal so far: what can be ordered by counting
         hipLaunchKernelGGL(next_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
                            (const uint8_t *)group, n, (uint32_t)depth, ks, key);
         hipLaunchKernelGGL(order_groups, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
                            (const uint8_t *)group, (const uint64_t *)key, n, (uint32_t)(depth + ks.slots), last_slot,
-                           group_max(l_max - depth - ks.slots), row2, group2, d_word);
+                           depth + ks.slots >= l_max ? 1 : 0, row2, group2, d_word);
         std::swap(row, row2);
         std::swap(group, group2);
     };
@@ -1042,42 +1056,48 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
                            (const uint32_t *)info, (const uint64_t *)place, rows);
         hipLaunchKernelGGL(count_prefixes, dim3((n_groups + BW - 1) / BW), dim3(BT), 0, st, (const RowMeta *)rows,
                            (const uint64_t *)d_tot64, n_groups, l_max, counts, group_lcp);
-        TRY(exclusive_scan<uint32_t>(n_counts, ValueAt<uint32_t>{counts}, counts, sums, d_word + 1, st));
+        TRY(exclusive_scan<uint32_t>(n_counts, ValueAt<uint32_t>{counts}, counts, sums, d_word + 2, st));
         hipLaunchKernelGGL(publish, dim3(1), dim3(1), 0, st, words.dev(), (const uint64_t *)d_tot64,
-                           (const uint32_t *)(counts + (uint64_t)l_max * n_groups), (const uint32_t *)(d_word + 1),
+                           (const uint32_t *)(counts + (uint64_t)l_max * n_groups), (const uint32_t *)(d_word + 2),
                            (const uint32_t *)d_word);
         PPV_HIP_TRY(hipGetLastError());
         PPV_HIP_TRY(hipStreamSynchronize(st));
         return PPV_OK;
     };
     if (depth < l_max) {
-        hipLaunchKernelGGL(mark_groups, dim3(nb), dim3(BT), 0, st, (const uint64_t *)key, n, last_slot, 0, group, group2);
+        hipLaunchKernelGGL(mark_groups, dim3(nb), dim3(BT), 0, st, (const uint64_t *)key, n, last_slot, group, group2);
         order();
     }
     TRY(measure());
-    bool again = false;
-    for (uint32_t m = words.w->large; m > 0;) {
-        // rows in groups too large to count: sorted by their next tokens under the group's number
-        again = true;
-        TRY(exclusive_scan<uint64_t>(n, LargeRows{group, n}, place, sums64, d_tot64, st));
-        uint64_t tot;
-        TRY(read_back(&tot, d_tot64, 1, st));
-        int group_bits = 1;
-        while ((1ull << group_bits) < (tot & 0xFFFFFFFFull)) group_bits++;
-        KeyShape ls = ks;
-        ls.slots = (int)std::min<int64_t>((64 - group_bits) / ks.bits, l_max - depth);
-        uint32_t *lrow = row2, *lrow2 = info, *lplace = (uint32_t *)rows;   // (written by measure, which comes later)
-        uint64_t *lkey = key, *lkey2 = key2;
-        hipLaunchKernelGGL(large_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
-                           (const uint8_t *)group, (const uint64_t *)place, n, (uint32_t)depth, ls, lkey, lrow, lplace);
-        TRY(radix_sort(lkey, lkey2, lrow, lrow2, m, ls.bits * ls.slots + group_bits, hist, digit_total, st));
-        depth += ls.slots;
-        hipLaunchKernelGGL(large_back, dim3(blocks_for(m)), dim3(BT), 0, st, (const uint64_t *)lkey, (const uint32_t *)lrow,
-                           (const uint32_t *)lplace, m, last_slot, depth >= l_max ? 1 : 0, row, group);
+    uint32_t left[2] = {words.w->large, words.w->split};
+    const bool again = left[0] + left[1] > 0;
+    while (left[0] + left[1] > 0) {
+        if (left[0] > 0) {
+            // rows in groups too large to count (and the others that are left): sorted by their next tokens under the group's
+            // number
+            const uint32_t m = left[0] + left[1];
+            TRY(exclusive_scan<uint64_t>(n, LargeRows{group, n}, place, sums64, d_tot64, st));
+            uint64_t tot;
+            TRY(read_back(&tot, d_tot64, 1, st));
+            int group_bits = 1;
+            while ((1ull << group_bits) < (tot & 0xFFFFFFFFull)) group_bits++;
+            KeyShape ls = ks;
+            ls.slots = (int)std::min<int64_t>((64 - group_bits) / ks.bits, l_max - depth);
+            uint32_t *lrow = row2, *lrow2 = info, *lplace = (uint32_t *)rows;   // (written by measure, which comes later)
+            uint64_t *lkey = key, *lkey2 = key2;
+            hipLaunchKernelGGL(large_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
+                               (const uint8_t *)group, (const uint64_t *)place, n, (uint32_t)depth, ls, lkey, lrow, lplace);
+            TRY(radix_sort(lkey, lkey2, lrow, lrow2, m, ls.bits * ls.slots + group_bits, hist, digit_total, st));
+            depth += ls.slots;
+            hipLaunchKernelGGL(large_back, dim3(blocks_for(m)), dim3(BT), 0, st, (const uint64_t *)lkey, (const uint32_t *)lrow,
+                               (const uint32_t *)lplace, m, last_slot, depth >= l_max ? 1 : 0, row, group);
+        } else {
+            depth += ks.slots;   // every group that is left agrees in the tokens of the round before
+        }
         if (depth >= l_max) break;
-        PPV_HIP_TRY(hipMemsetAsync(d_word, 0, sizeof(uint32_t), st));
+        PPV_HIP_TRY(hipMemsetAsync(d_word, 0, 2 * sizeof(uint32_t), st));
         order();
-        TRY(read_back(&m, d_word, 1, st));
+        TRY(read_back(left, d_word, 2, st));
     }
     if (again) TRY(measure());
     const uint32_t n_rows = (uint32_t)(words.w->rows_tokens >> 32), n_tok = (uint32_t)words.w->rows_tokens;

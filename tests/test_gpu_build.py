@@ -73,6 +73,26 @@ def test_groups_of_equal_first_tokens(group, V, stem, tail):
     assert rows_out == sorted({tuple(tokens[a:b]) for a, b in zip(offsets[:-1], offsets[1:])})
 
 
+@pytest.mark.parametrize("copies", [16, 17, 300, 1_024, 1_025])
+@pytest.mark.parametrize("V,length", [(300, 23), (128_256, 18), (90, 400)])
+def test_sets_with_many_copies_and_long_common_stems(copies, V, length):
+    """Groups that stay together for several rounds: copies of whole rows, and rows that differ in their last token only."""
+    rng = np.random.default_rng(copies + V)
+    base = rng.integers(0, V, (5, length))
+    rows = np.repeat(base, copies, axis=0)
+    lens = np.full(len(rows), length)
+    rows[copies:2 * copies, -1] = rng.integers(0, V, copies)              # a stem and its leaves
+    rows[2 * copies:3 * copies, length // 2] = rng.integers(0, 3, copies)  # three branches half way, alike again behind it
+    lens[3 * copies:4 * copies:2] = rng.integers(1, length + 1, len(lens[3 * copies:4 * copies:2]))
+    rows = np.concatenate([rows, rng.integers(0, V, (400, length))])
+    lens = np.concatenate([lens, rng.integers(1, length + 1, 400)])
+    order = rng.permutation(len(rows))
+    tokens, offsets = csr(rows[order], lens[order])
+    got_t, got_o = check(tokens, offsets, V, rng)
+    rows_out = [tuple(got_t[a:b]) for a, b in zip(got_o[:-1], got_o[1:])]
+    assert rows_out == sorted({tuple(tokens[a:b]) for a, b in zip(offsets[:-1], offsets[1:])})
+
+
 @pytest.mark.parametrize("V", [1, 2, 65_535, 65_536, 65_537, ppv.PPV_MAX_VOCAB])
 def test_vocabularies_at_the_edges_of_the_packed_forms(V):
     rng = np.random.default_rng(V)
