@@ -1024,15 +1024,22 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
     hipLaunchKernelGGL(first_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, n, ks, key, row);
     TRY(radix_sort(key, key2, row, row2, n, ks.bits * ks.slots, hist, digit_total, st));
     int64_t depth = ks.slots;                                       // tokens ordered so far
-    const uint32_t n_groups = (n + WAVE - 1) / WAVE;
-    const uint64_t n_counts = ((uint64_t)l_max + 1) * n_groups;
-    if (n_counts > 0xFFFFFFF0ull) return PPV_ERANGE;
-    uint32_t *counts, *group_lcp, *sums;
+    uint32_t n_groups = 0, *counts, *group_lcp, *sums;
+    uint64_t n_counts = 0;
     TempArena cnt;
-    cnt.add(&counts, n_counts);
-    cnt.add(&group_lcp, n_groups);
-    cnt.add(&sums, scan_words(n_counts));
-    TRY(cnt.take());
+    auto room_for = [&](uint32_t rows_at_most) {   // the counts of step 3
+        n_groups = (rows_at_most + WAVE - 1) / WAVE;
+        n_counts = ((uint64_t)l_max + 1) * n_groups;
+        if (n_counts > 0xFFFFFFF0ull) return PPV_ERANGE;
+        cnt.add(&counts, n_counts);
+        cnt.add(&group_lcp, n_groups);
+        cnt.add(&sums, scan_words(n_counts));
+        return cnt.take();
+    };
+    // The counts are laid out for the rows that were given, duplicates and all, so that nothing waits for the host to know
+    // how many are left; unless that is much (256 MB), for one long row among many short ones.
+    const bool by_rows_left = ((uint64_t)l_max + 1) * ((n + WAVE - 1) / WAVE) > (1ull << 26);
+    if (!by_rows_left) TRY(room_for(n));
     const HostWords words;
     if (!words.w) return PPV_ENOMEM;
 
@@ -1046,14 +1053,17 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
         std::swap(row, row2);
         std::swap(group, group2);
     };
-    // Steps 2 and 3 up to the sizes of the arrays, and the host's look at them.  They are run before it is known
-    // whether large groups are left (a trip to the host), and again if there were any.
-    auto measure = [&] {
+    // Step 2, and step 3 up to the sizes of the arrays, and the host's look at them.  They are run before it is known
+    // whether groups are left (a trip to the host), and again if there were any.
+    auto distinct = [&] {
         hipLaunchKernelGGL(neighbour_lcp, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row, n,
                            info, place);
         TRY(exclusive_scan<uint64_t>(n, ValueAt<uint64_t>{place}, place, sums64, d_tot64, st));
         hipLaunchKernelGGL(compact_rows, dim3(nb), dim3(BT), 0, st, (const uint32_t *)d_off, (const uint32_t *)row, n,
                            (const uint32_t *)info, (const uint64_t *)place, rows);
+        return PPV_OK;
+    };
+    auto count = [&] {
         hipLaunchKernelGGL(count_prefixes, dim3((n_groups + BW - 1) / BW), dim3(BT), 0, st, (const RowMeta *)rows,
                            (const uint64_t *)d_tot64, n_groups, l_max, counts, group_lcp);
         TRY(exclusive_scan<uint32_t>(n_counts, ValueAt<uint32_t>{counts}, counts, sums, d_word + 2, st));
@@ -1068,9 +1078,16 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
         hipLaunchKernelGGL(mark_groups, dim3(nb), dim3(BT), 0, st, (const uint64_t *)key, n, last_slot, group, group2);
         order();
     }
-    TRY(measure());
-    uint32_t left[2] = {words.w->large, words.w->split};
-    const bool again = left[0] + left[1] > 0;
+    uint32_t left[2];
+    if (by_rows_left) {
+        TRY(read_back(left, d_word, 2, st));
+    } else {
+        TRY(distinct());
+        TRY(count());
+        left[0] = words.w->large;
+        left[1] = words.w->split;
+    }
+    const bool again = by_rows_left || left[0] + left[1] > 0;
     while (left[0] + left[1] > 0) {
         if (left[0] > 0) {
             // rows in groups too large to count (and the others that are left): sorted by their next tokens under the group's
@@ -1083,7 +1100,7 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
             while ((1ull << group_bits) < (tot & 0xFFFFFFFFull)) group_bits++;
             KeyShape ls = ks;
             ls.slots = (int)std::min<int64_t>((64 - group_bits) / ks.bits, l_max - depth);
-            uint32_t *lrow = row2, *lrow2 = info, *lplace = (uint32_t *)rows;   // (written by measure, which comes later)
+            uint32_t *lrow = row2, *lrow2 = info, *lplace = (uint32_t *)rows;   // (written by step 2, which comes later)
             uint64_t *lkey = key, *lkey2 = key2;
             hipLaunchKernelGGL(large_keys, dim3(nb), dim3(BT), 0, st, tok, (const uint32_t *)d_off, (const uint32_t *)row,
                                (const uint8_t *)group, (const uint64_t *)place, n, (uint32_t)depth, ls, lkey, lrow, lplace);
@@ -1099,9 +1116,17 @@ ppv_status build_on_device(const int32_t *tokens, const int64_t *offsets, int64_
         order();
         TRY(read_back(left, d_word, 2, st));
     }
-    if (again) TRY(measure());
+    if (again) TRY(distinct());
+    auto too_many = [&](uint64_t rows_left) { return (uint64_t)l_max * rows_left + 1 > 0xFFFFFFF0ull; };   // (depth, row) pairs are limited to 32 bits
+    if (by_rows_left) {
+        uint64_t tot;
+        TRY(read_back(&tot, d_tot64, 1, st));
+        if (too_many(tot >> 32)) return PPV_ERANGE;
+        TRY(room_for((uint32_t)(tot >> 32)));
+    }
+    if (again) TRY(count());
     const uint32_t n_rows = (uint32_t)(words.w->rows_tokens >> 32), n_tok = (uint32_t)words.w->rows_tokens;
-    if ((uint64_t)l_max * n_rows + 1 > 0xFFFFFFF0ull) return PPV_ERANGE;   // (depth, row) pairs are limited to 32 bits
+    if (too_many(n_rows)) return PPV_ERANGE;
     return number_prefixes(ix, tok, rows, n_rows, n_tok, l_max, counts, n_groups, group_lcp, words.w->prefixes,
                            words.w->all_counts - words.w->prefixes, vocab, words, st);
 }

@@ -189,3 +189,18 @@ def test_sets_beyond_the_limit_of_depths_times_rows_are_refused(n, ok):
     index = ppv.ppv_build_index(tokens, offsets, 70_000)
     assert (index.n_distinct, index.l_max, index.n_prefixes) == (n, 70_000, 70_000 + n - 1)
     index.free()
+
+
+def test_copies_do_not_count_towards_that_limit():
+    """A row of 2^17 tokens among 2^21 rows of one token, nearly all of them copies: 2^32 (depth, 64 rows) pairs as given,
+    6 rows of the index."""
+    n, length = 1 << 21, 1 << 17
+    rng = np.random.default_rng(3)
+    tokens = np.concatenate([np.arange(n - 1, dtype=np.int32) % 5, rng.integers(0, 1_024, length).astype(np.int32)])
+    offsets = np.append(np.arange(n), n - 1 + length).astype(np.int64)
+    index = ppv.ppv_build_index(tokens, offsets, 1_024)
+    assert (index.n_distinct, index.l_max) == (6, length)
+    got_t, got_o = ppv.ppv_index_export(index)
+    want = sorted([(t,) for t in range(5)] + [tuple(tokens[n - 1:].tolist())])
+    assert [tuple(got_t[a:b].tolist()) for a, b in zip(got_o[:-1], got_o[1:])] == want
+    index.free()
