@@ -295,9 +295,11 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
 // Any reference gives the same sums up to rounding as long as they stay inside fp32's range, so neither the maximum nor
 // the reduction over the wavefront it would need are computed.
 //   without an image   only the sum over all tokens is wanted, and it only ever enters a logarithm: m is the largest of
-//          lane 0's first 16 bytes (one readfirstlane).  Where those hold nothing but -inf, or a token lies about 69 T
-//          above m, the sum is not inside SUM_MOST: the tile is then done again with its exact maximum (exact_stats),
-//          once per wavefront behind its tiles;
+//          the first 16 bytes of lanes 0 to 3 (two steps within a quad).  Where those hold nothing but -inf, or a token
+//          lies more than REF_GUARD * T above m, the sum is not inside SUM_MOST: the tile is then done again with its
+//          exact maximum (exact_stats), once per wavefront behind its tiles.  (The farther a token lies above m, the
+//          larger the arguments of exp and log and the more their rounding weighs.  With sums allowed up to 1e30 and m from
+//          lane 0 alone, the largest error of logZ_valid went from 2e-6 to 1.1e-5 in rows with a token 55 T above the rest.)
 //   IMAGE  the sums over valid tokens set the sampling threshold, and with tens of thousands of valid tokens another
 //          rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
 //          the tile lies more than REF_GUARD * T above it, else the exact maximum.
@@ -307,7 +309,7 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
 // every token was needed twice, 32 registers more: 79 to 94, now 60 (bf16), so that eight wavefronts fit a SIMD and all
 // rows of a batch of 2,048 are on the chip at once.
 constexpr float REF_GUARD = 40.f;   // exp(40) * 2048 tokens is far inside fp32
-constexpr float SUM_MOST = 1e30f;   // 256 tiles of it are still far inside fp32
+constexpr float SUM_MOST = 2.353852668e17f;   // exp(REF_GUARD)
 __device__ __forceinline__ bool in_range(float zall) { return zall <= SUM_MOST; }   // (not so: too large, or NaN)
 template <typename T, bool IMAGE, bool PAD>
 __device__ __forceinline__ void tile_sums(const RawTile &rt, uint32_t tile_word, int lane, int left, float ref, float c,
@@ -352,7 +354,11 @@ template <typename T, bool PAD, int GROUPS> __device__ __forceinline__ float lan
 template <typename T, bool IMAGE, bool PAD>
 __device__ __forceinline__ void tile_stats(const RawTile &rt, uint32_t tile_word, int lane, int left, const Temper &tp,
                                            float &m_out, float &zall_out, float &zval_out) {
-    const float mx = lane_max<T, PAD, IMAGE ? 4 : 1>(rt, left);
+    float mx = lane_max<T, PAD, IMAGE ? 4 : 1>(rt, left);
+    if (!IMAGE) {
+        mx = fmaxf(mx, dpp_self<DPP_QUAD_XOR1>(mx));
+        mx = fmaxf(mx, dpp_self<DPP_QUAD_XOR2>(mx));
+    }
     float ref = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
     if (IMAGE && (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull)) ref = wave_max(mx);   // wave-uniform branch
     m_out = ref;

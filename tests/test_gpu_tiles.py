@@ -78,3 +78,35 @@ def test_row_ends_and_references(tiles, over, dtype, waves):
             near = [i for i in (at - 1, at, at + 1) if 0 <= i < len(valid)]
             assert ids[b] in valid[near] and (ids[b] == valid[min(at, len(valid) - 1)] or
                                               np.abs(cdf - un[b]).min() < CDF_BAND), (b, n_valid, ids[b], valid[near])
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 2_500), ("bf16", 9_000), ("bf16", 130_000)])
+def test_one_token_far_above_the_rest_is_summed_exactly(dtype, V):
+    """A token 40 T or more above every other: its tile has to be summed relative to it, which makes that sum 1 up to
+    2e3 * exp(-40), 1 in fp32.  logZ_all is then that logit, and logZ_valid of a list without it the difference from the
+    listed ones' log-sum: half an ulp each of two numbers below 128 (4e-6 each) and 1e-7 for a sum of five."""
+    rng = np.random.default_rng(V)
+    peaks = np.repeat([50.0, 55.0, 60.0, 65.0, 72.0], 16).astype(np.float32)   # (noise: below 9, as drawn)
+    B = len(peaks)
+    lg = rng.normal(0, 2, size=(B, V)).astype(np.float32).clip(-9, 9)
+    at = rng.integers(0, V, B)
+    lg[np.arange(B), at] = peaks
+    bits = W.f32_to_bf16_bits(lg)
+    x = (W.bf16_bits_to_f32(bits) if dtype == "bf16" else lg).astype(np.float64)
+    mask = np.zeros((B, V), np.uint8)
+    for b in range(B):
+        mask[b, rng.choice(V, 5, replace=False)] = 1
+        mask[b, at[b]] = 0
+    words = np.packbits(np.pad(mask, ((0, 0), (0, (-V) % 32))), axis=1, bitorder="little").view(np.int32)
+    row = -(-V // 8) * 8
+    buf = np.zeros((B, row), np.float32)
+    buf[:, :V] = lg
+    ld = to_dev(W.f32_to_bf16_bits(buf).view(np.int16)).view(torch.bfloat16)[:, :V] if dtype == "bf16" else to_dev(buf)[:, :V]
+    ids = torch.zeros(B, dtype=torch.int32, device=DEV)
+    lzv, lza = torch.zeros(B, device=DEV), torch.zeros(B, device=DEV)
+    ppv.constrained_sample(ld, to_dev(words), to_dev(np.full(B, 0.5, np.float32)), ids, lzv, lza)
+    assert np.array_equal(lza.cpu().numpy(), peaks)
+    for b in range(B):
+        w = x[b, mask[b] != 0]
+        want = np.log(np.exp(w - w.max()).sum()) + w.max() - peaks[b]
+        assert abs(float(lzv[b]) - want) <= 8.2e-6, (b, float(lzv[b]), want)
