@@ -295,22 +295,26 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
 // Any reference gives the same sums up to rounding as long as they stay inside fp32's range, so neither the maximum nor
 // the reduction over the wavefront it would need are computed.
 //   without an image   only the sum over all tokens is wanted, and it only ever enters a logarithm: m is the largest of
-//          the first 16 bytes of lanes 0 to 3 (two steps within a quad).  Where those hold nothing but -inf, or a token
-//          lies more than REF_GUARD * T above m, the sum is not inside SUM_MOST: the tile is then done again with its
-//          exact maximum (exact_stats), once per wavefront behind its tiles.  (The farther a token lies above m, the
-//          larger the arguments of exp and log and the more their rounding weighs.  With sums allowed up to 1e30 and m from
-//          lane 0 alone, the largest error of logZ_valid went from 2e-6 to 1.1e-5 in rows with a token 55 T above the rest.)
+//          the first 16 bytes of lanes 0 to 3 (two steps within a quad).  Where that is -inf, or so low (REF_LOW) that it
+//          is a caller's stand-in for -inf, the row has been filtered and m is the exact maximum from the start; where a
+//          token lies more than REF_GUARD * T above m, the sum is not inside SUM_MOST and the tile, still in its
+//          registers, is summed again with its exact maximum.  (The farther a token lies above m, the larger the arguments
+//          of exp and log and the more their rounding weighs: with sums allowed up to 1e30 and m from lane 0 alone, the
+//          largest error of logZ_valid went from 2e-6 to 1.1e-5 in rows with a token 55 T above the rest.)
 //   IMAGE  the sums over valid tokens set the sampling threshold, and with tens of thousands of valid tokens another
 //          rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
 //          the tile lies more than REF_GUARD * T above it, else the exact maximum.
 // Either way m depends on the row's values alone, not on how the row is split over wavefronts.  m = -inf: an empty tile.
+// The two checks cost rows without a filter 1 to 2.5 % (C3, 2,048 rows, step by step: 561 us without, 569 with them).  Tiles
+// that were set aside and loaded once more behind the others cost none, but took filtered rows up to twice as long
+// (constrained_sample, 50 tokens left of V = 32k, 2,048 rows: 47.5 us, now 25.4; V = 50k fp32, 384 rows: 29.8, now 16.4).
 // What bounds it: per bf16 token one unpacking, one fma, one exp (a quarter of the rate) and one addition, 0.35 us per
 // tile and wavefront.  The running maximum that stood here for all rows was one more instruction in eight and, because
 // every token was needed twice, 32 registers more: 79 to 94, now 60 (bf16), so that eight wavefronts fit a SIMD and all
 // rows of a batch of 2,048 are on the chip at once.
 constexpr float REF_GUARD = 40.f;   // exp(40) * 2048 tokens is far inside fp32
 constexpr float SUM_MOST = 2.353852668e17f;   // exp(REF_GUARD)
-__device__ __forceinline__ bool in_range(float zall) { return zall <= SUM_MOST; }   // (not so: too large, or NaN)
+constexpr float REF_LOW = -8192.f;  // in units of log2: a logit of -5,678 T
 template <typename T, bool IMAGE, bool PAD>
 __device__ __forceinline__ void tile_sums(const RawTile &rt, uint32_t tile_word, int lane, int left, float ref, float c,
                                           float &zall_out, float &zval_out) {
@@ -360,20 +364,22 @@ __device__ __forceinline__ void tile_stats(const RawTile &rt, uint32_t tile_word
         mx = fmaxf(mx, dpp_self<DPP_QUAD_XOR2>(mx));
     }
     float ref = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
-    if (IMAGE && (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull)) ref = wave_max(mx);   // wave-uniform branch
-    m_out = ref;
-    if (IMAGE && ref == -INFINITY) {   // nothing but -inf in this tile
-        zall_out = zval_out = 0.f;
-        return;
+    // (all branches wave-uniform)
+    bool exact = IMAGE ? ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull : !(ref * tp.c > REF_LOW);
+    float zall, zval;   // (handed out once, at the end: written through the references in several places they end up in memory)
+    for (;;) {
+        if (exact) ref = wave_max(IMAGE ? mx : lane_max<T, PAD, 4>(rt, left));
+        if (exact && ref == -INFINITY) {   // nothing but -inf in this tile
+            zall = zval = 0.f;
+            break;
+        }
+        tile_sums<T, IMAGE, PAD>(rt, tile_word, lane, left, ref, tp.c, zall, zval);
+        if (IMAGE || exact || zall <= SUM_MOST) break;   // (not so: too large, or NaN)
+        exact = true;
     }
-    tile_sums<T, IMAGE, PAD>(rt, tile_word, lane, left, ref, tp.c, zall_out, zval_out);   // (m = -inf: NaN)
-}
-template <typename T>
-__device__ __forceinline__ void exact_stats(const RawTile &rt, int lane, int left, const Temper &tp, float &m_out, float &zall_out) {
-    m_out = wave_max(lane_max<T, true, 4>(rt, left));
-    float none;
-    zall_out = 0.f;
-    if (m_out != -INFINITY) tile_sums<T, false, true>(rt, 0u, lane, left, m_out, tp.c, zall_out, none);
+    zall_out = zall;
+    zval_out = zval;
+    m_out = ref;
 }
 
 // Rare path of the image mode (the valid tokens lie far below the row maximum, so sums relative
@@ -542,8 +548,12 @@ __device__ __forceinline__ void stream_tiles(const T *__restrict__ row, int V, R
         mid();
         return;
     }
-    bool again = false;   // some tile has to be done again
-    auto record = [&](int k, float m, float zall, float zval) __attribute__((always_inline)) {
+    auto reduce_tile = [&](const RawTile &t, int k, auto pad) __attribute__((always_inline)) {
+        constexpr bool PAD = decltype(pad)::value;
+        const int left = PAD ? tokens_left<T>(V, k, lane) : 0;
+        float m, zall, zval;
+        if (IMAGE && image) tile_stats<T, true, PAD>(t, tile_word_fix<T>(t.word, k, lane, V), lane, left, tp, m, zall, zval);
+        else tile_stats<T, false, PAD>(t, 0u, lane, left, tp, m, zall, zval);
         if (lane == 0) {
             sh.tile_m[k] = m;
             sh.tile_zall[k] = zall;
@@ -551,15 +561,6 @@ __device__ __forceinline__ void stream_tiles(const T *__restrict__ row, int V, R
             sh.tile_ref[k] = m;
             if (pub) shared_put_tile(pub, k, m, zall, zval, m);
         }
-    };
-    auto reduce_tile = [&](const RawTile &t, int k, auto pad) __attribute__((always_inline)) {
-        constexpr bool PAD = decltype(pad)::value;
-        const int left = PAD ? tokens_left<T>(V, k, lane) : 0;
-        float m, zall, zval;
-        if (IMAGE && image) tile_stats<T, true, PAD>(t, tile_word_fix<T>(t.word, k, lane, V), lane, left, tp, m, zall, zval);
-        else tile_stats<T, false, PAD>(t, 0u, lane, left, tp, m, zall, zval);
-        if (!(IMAGE && image)) again = again || !in_range(zall);
-        record(k, m, zall, zval);
     };
     auto reduce_last = [&](const RawTile &t, int k) __attribute__((always_inline)) {   // the row's last tile is the last one of its wavefront
         if ((k + 1) * G::TILE > V) reduce_tile(t, k, std::true_type());
@@ -589,15 +590,6 @@ __device__ __forceinline__ void stream_tiles(const T *__restrict__ row, int V, R
     }
     reduce_last(X, k);
     if (left == 2) reduce_last(Y, k + nw);
-    if (__builtin_expect(again, 0)) {   // (wave-uniform)
-        for (k = wave; k < nt; k += nw) {
-            if (in_range(sh.tile_zall[k])) continue;
-            load_tile<T>(row, V, k, lane, Y);
-            float m, zall;
-            exact_stats<T>(Y, lane, tokens_left<T>(V, k, lane), tp, m, zall);
-            record(k, m, zall, 0.f);
-        }
-    }
 }
 
 // Row totals from the per-tile statistics in LDS: the largest tile reference M, the sum over all tokens relative
@@ -1586,14 +1578,11 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
                     float m, zall, zval;
                     if ((k + 1) * G::TILE > V) tile_stats<T, false, true>(tile, 0u, lane, left, tp, m, zall, zval);
                     else tile_stats<T, false, false>(tile, 0u, lane, left, tp, m, zall, zval);
-                    if (k < nt) {
-                        if (!in_range(zall)) exact_stats<T>(tile, lane, left, tp, m, zall);
-                        if (lane == 0) {
-                            cur.tile_m[k] = m;
-                            cur.tile_zall[k] = zall;
-                            cur.tile_zval[k] = zval;
-                            cur.tile_ref[k] = m;
-                        }
+                    if (lane == 0 && k < nt) {
+                        cur.tile_m[k] = m;
+                        cur.tile_zall[k] = zall;
+                        cur.tile_zval[k] = zval;
+                        cur.tile_ref[k] = m;
                     }
                 };
                 // one step on the tiles (c0, c1), the next row's tiles requested into (n0, n1) first.
