@@ -76,7 +76,8 @@ ppv_status ppv_build_index(const int32_t *tokens, const int64_t *offsets, int64_
 /* Sizes of a built index.  Any output pointer may be NULL.
  *   n_distinct   |S| after de-duplication        l_max   longest member
  *   n_prefixes   number of distinct non-empty prefixes of members (entries of the per-depth arrays)
- *   device_bytes device memory the index holds */
+ *   device_bytes device memory the index holds (its blocks; memory kept from an earlier index may be up to half as large
+ *                again as the arrays in it) */
 ppv_status ppv_index_info(const ppv_index_t *index, int64_t *n_distinct, int32_t *l_max, int32_t *vocab,
                           int64_t *n_prefixes, int64_t *device_bytes);
 
@@ -85,7 +86,10 @@ ppv_status ppv_index_info(const ppv_index_t *index, int64_t *n_distinct, int32_t
  *   n_tokens     receives the total number of tokens, may be NULL.  Synchronous. */
 ppv_status ppv_index_export(const ppv_index_t *index, int32_t *tokens_out, int64_t *offsets_out, int64_t *n_tokens);
 
-void ppv_free_index(ppv_index_t *index); /* NULL is allowed */
+/* NULL is allowed.  The device memory of indices and builds that are over, at most 1 GB per process, and 48 MB of pinned
+ * host memory for the upload are kept for the next build or load for 20 s; then a thread of the library returns them to the
+ * system.  They go back earlier where an allocation of this library fails. */
+void ppv_free_index(ppv_index_t *index);
 
 /*
  * ppv_index_save / ppv_index_load -- Section 3.2 "Array Preparation": the array is prepared once and

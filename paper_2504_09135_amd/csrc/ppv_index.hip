@@ -803,8 +803,8 @@ struct Arena {
         at[n++] = bytes;
         bytes += ((size_t)(count ? count : 1) * sizeof(T) + 255) / 256 * 256;
     }
-    ppv_status take() {
-        TRY(ppv_pool_take(&block, bytes));
+    ppv_status take() {   // (`bytes` is the block's size from here on)
+        TRY(ppv_pool_take(&block, bytes, &bytes));
         for (int i = 0; i < n; i++) *slot[i] = (char *)block + at[i];
         return PPV_OK;
     }

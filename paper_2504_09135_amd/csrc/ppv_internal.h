@@ -117,8 +117,10 @@ struct ppv_index {
 
 // Device memory kept from one index to the next, and the upload of a set (ppv_pool.hip).  ppv_pool_give:
 // `over` says that the device has finished with the block; where the caller's wait failed, the block is not kept.
-ppv_status ppv_pool_take(void **out, size_t bytes);
+// `got`: the block's size, which may be more than was asked for.  ppv_pool_empty: everything that is kept goes back to the system.
+ppv_status ppv_pool_take(void **out, size_t bytes, size_t *got = nullptr);
 void ppv_pool_give(void *block, bool over);
+void ppv_pool_empty();
 // A little pinned memory that kernels can write (nullptr: none to be had).
 constexpr int PPV_HOST_WORDS_BYTES = 64;
 void *ppv_host_words_take();

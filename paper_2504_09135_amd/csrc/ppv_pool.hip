@@ -6,12 +6,16 @@
 //
 // Device blocks: ppv_pool_take hands out a block of at least the size asked for, from the blocks that were given back
 // or from hipMalloc; ppv_pool_give keeps it for the next taker.  At most POOL_KEEP bytes are kept per process, for at
-// most POOL_SECONDS from their last use (looked at when a block is taken or given), and all of them go back to the
-// system when an allocation fails.  Whoever gives a block back has waited for the device to be done with it;
-// a block whose wait failed goes to hipFree, which waits by itself.
+// most POOL_AGE from their last use, and all of them go back to the system when an allocation of this library fails.
+// Whoever gives a block back has waited for the device to be done with it; a block whose wait failed goes to hipFree, which
+// waits by itself.  The pinned memory of the upload goes back after the same time.
+// The age is looked at by a thread that is there while anything is kept: a process that makes no further call would
+// otherwise hold the memory until it ends.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <condition_variable>
+#include <cstdlib>
 #include <mutex>
 #include <new>
 #include <thread>
@@ -19,46 +23,147 @@
 #include <vector>
 
 #include <sched.h>
+#include <unistd.h>
 
 #include "ppv_internal.h"
+
+#ifndef PPV_POOL_AGE_MS   // (a test builds this file with less)
+#define PPV_POOL_AGE_MS 20000
+#endif
 
 namespace {
 
 using Clock = std::chrono::steady_clock;
 constexpr size_t POOL_KEEP = 1ull << 30;
-constexpr int POOL_SECONDS = 20;
-constexpr size_t POOL_ROUND = 1u << 20;
+constexpr std::chrono::milliseconds POOL_AGE(PPV_POOL_AGE_MS);
+constexpr size_t POOL_ROUND = 256u << 10;
+
+// What is freed here is in nobody's use, so freeing it is no part of a capture that some stream may be in.
+struct OutsideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~OutsideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+bool free_block(void *p) {
+    const OutsideCaptures outside;
+    if (hipFree(p) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
 
 struct Kept {
     void *p;
     size_t bytes;
     int device;
+    bool leaving;               // the watching thread is freeing it
     Clock::time_point since;
 };
 struct Pool {
     std::mutex mu;
+    std::condition_variable cv;
     std::vector<Kept> kept;                                        // oldest first
     std::unordered_map<void *, std::pair<size_t, int>> out;        // blocks in use: size, device
     size_t kept_bytes = 0;
+    std::thread watch;
+    pid_t pid = 0;              // the process `watch` belongs to (a forked child has no such thread)
+    bool watching = false, ending = false;
+    bool more = false;          // something has been kept since `watch` last looked
+
+    void erase(size_t i) {
+        kept_bytes -= kept[i].bytes;
+        kept.erase(kept.begin() + (long)i);
+    }
+    // frees kept blocks, oldest first, until at most `most` bytes are kept; one that cannot be freed stays on the list
+    void shrink(size_t most) {
+        for (size_t i = 0; i < kept.size() && kept_bytes > most;)
+            if (!kept[i].leaving && free_block(kept[i].p)) erase(i);
+            else i++;
+    }
 };
 Pool &pool() {
     static Pool *p = new Pool;   // never destroyed: the HIP runtime may be gone before a static's destructor runs
     return *p;
 }
 
-void drop_front(Pool &p) {
-    (void)hipFree(p.kept.front().p);
-    p.kept_bytes -= p.kept.front().bytes;
-    p.kept.erase(p.kept.begin());
+bool give_back_ring(Clock::time_point now, Clock::time_point *next);   // the upload's pinned memory, below
+
+void watch_kept() {
+    Pool &p = pool();
+    std::unique_lock<std::mutex> lock(p.mu);
+    while (!p.ending) {
+        p.more = false;
+        const Clock::time_point now = Clock::now();
+        Clock::time_point next = now + POOL_AGE;
+        lock.unlock();
+        const bool ring = give_back_ring(now, &next);
+        lock.lock();
+        bool any = false;
+        for (size_t i = 0; i < p.kept.size() && !p.ending;) {
+            any = true;
+            if (p.kept[i].since + POOL_AGE > now) {
+                next = std::min(next, p.kept[i].since + POOL_AGE);
+                break;   // (the others are younger)
+            }
+            void *const q = p.kept[i].p;
+            p.kept[i].leaving = true;
+            lock.unlock();   // (hipFree waits for the device: nobody else has to)
+            const bool gone = free_block(q);
+            lock.lock();
+            i = 0;
+            while (p.kept[i].p != q) i++;   // (only this thread erases a block that is leaving)
+            if (gone) {
+                p.erase(i);
+            } else {   // another time
+                Kept k = p.kept[i];
+                k.leaving = false;
+                k.since = Clock::now();
+                p.kept.erase(p.kept.begin() + (long)i);
+                p.kept.push_back(k);
+            }
+            i = 0;
+        }
+        if (!any && !ring) {
+            if (!p.more) break;
+        } else if (!p.ending) {
+            p.cv.wait_until(lock, next);
+        }
+    }
+    p.watching = false;
 }
-void drop_old(Pool &p) {
-    const Clock::time_point now = Clock::now();
-    while (!p.kept.empty() && now - p.kept.front().since > std::chrono::seconds(POOL_SECONDS)) drop_front(p);
+// At the process's end, before the HIP runtime goes (which was there first).
+void stop_watching() {
+    Pool &p = pool();
+    if (p.pid != getpid()) return;
+    {
+        std::lock_guard<std::mutex> lock(p.mu);
+        p.ending = true;
+        p.cv.notify_all();
+    }
+    if (p.watch.joinable()) p.watch.join();
+}
+// sees to it that the thread is there; with p.mu held
+bool see_to_watch(Pool &p) {
+    p.more = true;
+    if (p.watching && p.pid == getpid()) return true;
+    if (p.ending) return true;   // the process is about to end
+    try {
+        if (p.pid == 0 && atexit(stop_watching) != 0) return false;
+        if (p.watch.joinable()) {
+            if (p.pid == getpid()) p.watch.join();   // (it has left its loop: nothing was kept)
+            else p.watch.detach();
+        }
+        p.pid = getpid();
+        p.watch = std::thread(watch_kept);
+        p.watching = true;
+        return true;
+    } catch (...) {
+        return false;
+    }
 }
 
 }  // namespace
 
-ppv_status ppv_pool_take(void **out, size_t bytes) {
+ppv_status ppv_pool_take(void **out, size_t bytes, size_t *got) {
     *out = nullptr;
     int dev = 0;
     PPV_HIP_TRY(hipGetDevice(&dev));
@@ -68,25 +173,24 @@ ppv_status ppv_pool_take(void **out, size_t bytes) {
     try {
         p.out.reserve(p.out.size() + 1);
         p.kept.reserve(p.kept.size() + p.out.size() + 1);   // so that giving a block back cannot fail
-        drop_old(p);
         size_t best = p.kept.size();
         for (size_t i = 0; i < p.kept.size(); i++)   // the smallest that fits and is not much too large
-            if (p.kept[i].device == dev && p.kept[i].bytes >= need && p.kept[i].bytes <= need + need / 2 + 4 * POOL_ROUND &&
+            if (!p.kept[i].leaving && p.kept[i].device == dev && p.kept[i].bytes >= need && p.kept[i].bytes <= need + need / 2 &&
                 (best == p.kept.size() || p.kept[i].bytes < p.kept[best].bytes))
                 best = i;
         if (best < p.kept.size()) {
             const Kept k = p.kept[best];
             p.out[k.p] = {k.bytes, k.device};
-            p.kept.erase(p.kept.begin() + (long)best);
-            p.kept_bytes -= k.bytes;
+            p.erase(best);
             *out = k.p;
+            if (got) *got = k.bytes;
             return PPV_OK;
         }
         void *q = nullptr;
         hipError_t e = hipMalloc(&q, need);
         if (e == hipErrorOutOfMemory && !p.kept.empty()) {
             (void)hipGetLastError();
-            while (!p.kept.empty()) drop_front(p);
+            p.shrink(0);
             e = hipMalloc(&q, need);
         }
         if (e != hipSuccess) {
@@ -95,6 +199,7 @@ ppv_status ppv_pool_take(void **out, size_t bytes) {
         }
         p.out[q] = {need, dev};
         *out = q;
+        if (got) *got = need;
         return PPV_OK;
     } catch (const std::bad_alloc &) {
         return PPV_ENOMEM;
@@ -110,14 +215,19 @@ void ppv_pool_give(void *q, bool over) {
     const size_t bytes = it->second.first;
     const int dev = it->second.second;
     p.out.erase(it);
-    if (bytes > POOL_KEEP || !over) {
-        (void)hipFree(q);
-    } else {
-        p.kept.push_back({q, bytes, dev, Clock::now()});
-        p.kept_bytes += bytes;
-        while (p.kept_bytes > POOL_KEEP) drop_front(p);
+    if (bytes > POOL_KEEP || !over || !see_to_watch(p)) {
+        (void)free_block(q);
+        return;
     }
-    drop_old(p);
+    p.kept.push_back({q, bytes, dev, false, Clock::now()});
+    p.kept_bytes += bytes;
+    p.shrink(POOL_KEEP);
+}
+
+void ppv_pool_empty() {
+    Pool &p = pool();
+    std::lock_guard<std::mutex> lock(p.mu);
+    p.shrink(0);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -126,28 +236,29 @@ void ppv_pool_give(void *q, bool over) {
 namespace {
 constexpr int WORD_SLOTS = 64;
 std::mutex g_words_mu;
-unsigned char *g_words;      // WORD_SLOTS slots of PPV_HOST_WORDS_BYTES, kept until the process ends
+std::condition_variable g_words_cv;
+unsigned char *g_words;      // WORD_SLOTS slots of PPV_HOST_WORDS_BYTES (4 KB), kept until the process ends
 uint64_t g_words_taken;
 }  // namespace
 
 void *ppv_host_words_take() {
-    std::lock_guard<std::mutex> lock(g_words_mu);
+    std::unique_lock<std::mutex> lock(g_words_mu);
     if (!g_words && hipHostMalloc((void **)&g_words, WORD_SLOTS * PPV_HOST_WORDS_BYTES, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
         (void)hipGetLastError();
         g_words = nullptr;
         return nullptr;
     }
-    for (int i = 0; i < WORD_SLOTS; i++)
-        if (!((g_words_taken >> i) & 1u)) {
-            g_words_taken |= 1ull << i;
-            return g_words + (size_t)i * PPV_HOST_WORDS_BYTES;
-        }
-    return nullptr;
+    // (as many builds at a time as there are slots; the next one waits for any of them to end, which needs no slot)
+    while (g_words_taken == ~0ull) g_words_cv.wait(lock);
+    const int i = __builtin_ctzll(~g_words_taken);
+    g_words_taken |= 1ull << i;
+    return g_words + (size_t)i * PPV_HOST_WORDS_BYTES;
 }
 void ppv_host_words_give(void *p) {
     if (!p) return;
     std::lock_guard<std::mutex> lock(g_words_mu);
     g_words_taken &= ~(1ull << (((unsigned char *)p - g_words) / PPV_HOST_WORDS_BYTES));
+    g_words_cv.notify_one();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -166,7 +277,9 @@ constexpr size_t UP_SLOTS = 64;
 constexpr size_t UP_RUN = 4, UP_RUN_MOST = 16; // slots per copy: at least (but for the last), at most
 struct Stage {
     std::mutex mu;                             // one upload at a time: the bus is the bottleneck
-    unsigned char *buf = nullptr;              // the two rings, pinned, kept until the process ends (48 MB)
+    unsigned char *buf = nullptr;              // the two rings (48 MB), pinned, kept for POOL_AGE after an upload; where
+    bool pinned = false;                       // no pinned memory is to be had, ordinary memory, which the runtime stages
+    Clock::time_point since;                   // the end of the last upload
     hipEvent_t ev[UP_SLOTS] = {};              // the end of the copy whose last slot this is
     int copy_of[UP_SLOTS];                     // the slot that the copy of this slot ended with; -1: none under way
     int device = -1;                           // the device the events belong to
@@ -179,31 +292,55 @@ struct Stage {
             if (c == e) c = -1;
         return true;
     }
-    bool ready(int dev) {
+    ppv_status ready(int dev) {
         if (!buf) {
-            if (hipHostMalloc((void **)&buf, UP_SLOTS * (UP_LO + UP_HI), hipHostMallocPortable) != hipSuccess) {
-                buf = nullptr;
-                return false;
-            }
             for (int &c : copy_of) c = -1;
+            pinned = hipHostMalloc((void **)&buf, UP_SLOTS * (UP_LO + UP_HI), hipHostMallocPortable) == hipSuccess;
+            if (!pinned) {
+                (void)hipGetLastError();
+                buf = (unsigned char *)malloc(UP_SLOTS * (UP_LO + UP_HI));
+            }
+            if (!buf) return PPV_ENOMEM;
         }
-        if (device == dev) return true;
+        if (device == dev) return PPV_OK;
         for (size_t i = 0; i < UP_SLOTS; i++)
-            if (!wait(i)) return false;
+            if (!wait(i)) return PPV_EDEVICE;
+        drop_events();
+        for (hipEvent_t &e : ev) PPV_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        device = dev;
+        return PPV_OK;
+    }
+    void drop_events() {
         for (hipEvent_t &e : ev) {
             if (e) (void)hipEventDestroy(e);
             e = nullptr;
         }
         device = -1;
-        for (hipEvent_t &e : ev)
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return false;
-        device = dev;
-        return true;
+    }
+    void drop() {   // (a copy that may still read the buffer: it stays)
+        if (!buf) return;
+        const OutsideCaptures outside;
+        for (size_t i = 0; i < UP_SLOTS; i++)
+            if (!wait(i)) return;
+        drop_events();
+        if (!pinned) free(buf);
+        else if (hipHostFree(buf) != hipSuccess) (void)hipGetLastError();
+        buf = nullptr;
     }
 };
 Stage &stage() {
     static Stage *s = new Stage;
     return *s;
+}
+
+// Gives the ring back if the last upload is POOL_AGE ago; else lowers *next to when that will be.  Whether there is a ring.
+bool give_back_ring(Clock::time_point now, Clock::time_point *next) {
+    Stage &sg = stage();
+    const std::unique_lock<std::mutex> lock(sg.mu, std::try_to_lock);
+    if (!lock.owns_lock()) return true;   // in use: look again after POOL_AGE
+    if (sg.buf && sg.since + POOL_AGE <= now) sg.drop();
+    if (sg.buf && sg.since + POOL_AGE > now) *next = std::min(*next, sg.since + POOL_AGE);
+    return sg.buf != nullptr;
 }
 
 int cpus() {
@@ -290,7 +427,18 @@ ppv_status ppv_upload_set(const int32_t *tokens, const int64_t *offsets, int64_t
     PPV_HIP_TRY(hipGetDevice(&dev));
     Stage &sg = stage();
     std::lock_guard<std::mutex> lock(sg.mu);
-    bool failed = !sg.ready(dev);
+    struct Used {   // whatever comes of it: the ring's time starts again
+        Stage &sg;
+        ~Used() {
+            sg.since = Clock::now();
+            Pool &p = pool();
+            std::lock_guard<std::mutex> plock(p.mu);
+            if (!see_to_watch(p)) sg.drop();
+        }
+    } used{sg};
+    const ppv_status ready = sg.ready(dev);
+    if (ready != PPV_OK) return ready;
+    bool failed = false;
 
     unsigned char *lo = sg.buf;
     uint8_t *hi = sg.buf + UP_SLOTS * UP_LO;

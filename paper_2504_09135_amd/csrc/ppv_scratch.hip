@@ -28,7 +28,13 @@ SplitScratch *ppv_split_scratch(hipStream_t stream) {
         return nullptr;
     }
     SplitScratch *p = nullptr;
-    if (hipMalloc((void **)&p, sizeof(SplitScratch)) != hipSuccess) {
+    hipError_t e = hipMalloc((void **)&p, sizeof(SplitScratch));
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        ppv_pool_empty();
+        e = hipMalloc((void **)&p, sizeof(SplitScratch));
+    }
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         return nullptr;
     }
