@@ -855,15 +855,19 @@ template <typename T> ppv_status read_back(T *host, const void *dev, size_t coun
 }
 
 // 5. Images and per-word child counts of the heavy prefixes, from the finished entries (G of them plus the sentinel).
-// Sets the heavy part of the index and of its view.  The index's block has room for HEAVY_GUESS of them among the first
+// Sets the heavy part of the index and of its view.  The index's block has room for HEAVY_GUESS of them (or for as many as
+// there can be: with 60 sequences at V = 256,000 for one, 64 KB, where room for all would be 16 MB) among the first
 // HEAVY_REACH prefixes, which are filled before the host knows how many there are; more than that (small
 // vocabularies, where every second prefix is heavy) get a block of their own.  Ends with a synchronisation.
 constexpr uint32_t HEAVY_GUESS = 256, HEAVY_REACH = 1u << 20;
+inline uint32_t heavy_min_of(int32_t vocab) { return (uint32_t)std::min<int64_t>(vocab / 32, PPV_LIST_MAX); }
+inline uint32_t heavy_at_most(uint32_t G, int32_t vocab) {   // of G prefixes: their children are disjoint
+    return (uint32_t)std::max<uint64_t>((G - 1) / (heavy_min_of(vocab) + 1ull), 1);
+}
 ppv_status finish_heavy(ppv_index *ix, uint32_t G, int32_t vocab, const HostWords &words, hipStream_t st) {
     const int n_words = (vocab + 31) / 32;
-    const uint32_t heavy_min = (uint32_t)std::min<int64_t>(vocab / 32, PPV_LIST_MAX);
+    const uint32_t heavy_min = heavy_min_of(vocab), bound = heavy_at_most(G, vocab);
     const uint64_t chunks = ((uint64_t)G + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    const uint64_t bound = G / (heavy_min + 1ull) + 1;   // children are disjoint
     TempArena tmp;
     uint32_t *sums, *d_heavy, *heavy_node;               // d_heavy: heavy prefixes, one past the last of them
     tmp.add(&sums, chunks + 1);
@@ -885,7 +889,7 @@ ppv_status finish_heavy(ppv_index *ix, uint32_t G, int32_t vocab, const HostWord
         PPV_HIP_TRY(hipStreamSynchronize(st));
         return PPV_OK;
     };
-    TRY(fill(std::min(HEAVY_GUESS, (uint32_t)bound), std::min(G, HEAVY_REACH)));
+    TRY(fill(std::min(HEAVY_GUESS, bound), std::min(G, HEAVY_REACH)));
     const uint32_t n_heavy = words.w->heavy, limit = words.w->heavy_limit;
     if (n_heavy > HEAVY_GUESS || limit > HEAVY_REACH) {
         Arena keep;
@@ -930,10 +934,10 @@ ppv_status number_prefixes(ppv_index *ix, TOK tok, const RowMeta *rows, uint32_t
     keep.add(&ix->d_x_off, (uint64_t)n_rows + 1);
     keep.add(&ix->d_node_at, lookup ? n_tok : 0);
     keep.add(&ix->d_lookup, size);
-    const uint64_t n_words = ((uint64_t)vocab + 31) / 32;
+    const uint64_t n_words = ((uint64_t)vocab + 31) / 32, n_images = std::min(HEAVY_GUESS, heavy_at_most(G, vocab));
     keep.add(&ix->d_heavy_slot, std::min(G, HEAVY_REACH));
-    keep.add(&ix->d_heavy_bits, HEAVY_GUESS * n_words);
-    keep.add(&ix->d_heavy_rank, HEAVY_GUESS * n_words);
+    keep.add(&ix->d_heavy_bits, n_images * n_words);
+    keep.add(&ix->d_heavy_rank, n_images * n_words);
     TRY(keep.take());
     ix->block = keep.keep();
     ix->device_bytes = (int64_t)keep.bytes;

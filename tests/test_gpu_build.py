@@ -204,3 +204,13 @@ def test_copies_do_not_count_towards_that_limit():
     want = sorted([(t,) for t in range(5)] + [tuple(tokens[n - 1:].tolist())])
     assert [tuple(got_t[a:b].tolist()) for a, b in zip(got_o[:-1], got_o[1:])] == want
     index.free()
+
+
+@pytest.mark.parametrize("V", [1_024, 256_000])
+def test_a_small_set_holds_little_memory(V):
+    """Room for images is laid out for the heavy prefixes that there can be, not for 256 of them (16 MB at V = 256,000)."""
+    rng = np.random.default_rng(V)
+    tokens, offsets = csr(rng.integers(0, V, (60, 5)), np.full(60, 5))
+    index = ppv.ppv_build_index(tokens, offsets, V)
+    assert index.device_bytes < 1_000_000
+    index.free()
