@@ -155,13 +155,15 @@ struct Logits {
     }
 };
 
-// prefixes as a 2-D matrix (-1 rows if it is not one)
+// prefixes as a 2-D matrix (-1 rows if it is not one); the decoding calls also take further dimensions behind the first two
+// (a column of size 1, say) and read rows of the second one's size from its start
 struct Prefixes {
     int64_t B = -1, stride = 0;
     PyObject *o;
-    explicit Prefixes(PyObject *p) : o(p) {
+    explicit Prefixes(PyObject *p, bool decoding = false) : o(p) {
         const at::Tensor &t = tensor(p, "prefixes");
-        if (t.dim() != 2) return;
+        if (decoding && t.dim() < 2) raise(PyExc_IndexError, "prefixes: need a tensor of shape [B, stride]");
+        if (!decoding && t.dim() != 2) return;
         B = t.size(0);
         stride = t.size(1);
     }
@@ -229,9 +231,9 @@ PyObject *sample(PyObject *, PyObject *const *a, Py_ssize_t n) {
 // index, prefixes, lens, state, active, logx, stream
 PyObject *decode_begin(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return guarded("decode_begin", n, 7, [&] {
-        const Prefixes p(a[1]);
+        const Prefixes p(a[1], true);
         const Arg lens{a[2], "lens"}, state{a[3], "state"}, active{a[4], "active"}, logx{a[5], "logx"};
-        if (p.B < 0 || !lens.fits(p.B) || !state.fits(p.B, PPV_STATE_WORDS) || !active.fits(p.B) || !logx.fits_or_none(p.B))
+        if (!lens.fits(p.B) || !state.fits(p.B, PPV_STATE_WORDS) || !active.fits(p.B) || !logx.fits_or_none(p.B))
             raise(PyExc_ValueError, "ppv_decode_begin: shape mismatch");
         const ppv_index_t *ix = handle(a[0]);
         const int32_t *pp = p.get(), *ln = lens.get<int32_t>(I32);
@@ -248,8 +250,9 @@ PyObject *decode_begin_empty(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return guarded("decode_begin_empty", n, 6, [&] {
         const Arg lens{a[1], "lens"}, state{a[2], "state"}, active{a[3], "active"}, logx{a[4], "logx"};
         const at::Tensor &l = tensor(a[1], "lens");
-        const int64_t B = l.dim() == 1 ? l.size(0) : -1;
-        if (B < 0 || !state.fits(B, PPV_STATE_WORDS) || !active.fits(B) || !logx.fits_or_none(B))
+        if (l.dim() < 1) raise(PyExc_IndexError, "lens: need a tensor of shape [B]");
+        const int64_t B = l.size(0);
+        if (l.dim() != 1 || !state.fits(B, PPV_STATE_WORDS) || !active.fits(B) || !logx.fits_or_none(B))
             raise(PyExc_ValueError, "ppv_decode_begin_empty: shape mismatch");
         const ppv_index_t *ix = handle(a[0]);
         int32_t *ln = lens.get<int32_t>(I32);
@@ -265,10 +268,10 @@ PyObject *decode_begin_empty(PyObject *, PyObject *const *a, Py_ssize_t n) {
 PyObject *decode_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     return guarded("decode_step", n, 13, [&] {
         const Logits l(a[4]);
-        const Prefixes p(a[1]);
+        const Prefixes p(a[1], true);
         const Arg lens{a[2], "lens"}, active{a[3], "active"}, un{a[5], "uniforms"}, ids{a[6], "ids"}, lzv{a[7], "logZ_valid"},
             logx{a[8], "logx"}, state{a[9], "state"};
-        if (p.B < 0 || l.B != p.B || l.V != size_of(a[0], s_vocab) || !lens.fits(p.B) || !active.fits(p.B) || !un.fits(p.B) ||
+        if (l.B != p.B || l.V != size_of(a[0], s_vocab) || !lens.fits(p.B) || !active.fits(p.B) || !un.fits(p.B) ||
             !state.fits_or_none(p.B, PPV_STATE_WORDS))
             raise(PyExc_ValueError, "ppv_decode_step: shape mismatch");
         for (const Arg &x : {ids, lzv, logx})
@@ -296,7 +299,7 @@ PyObject *decode_loop(PyObject *, PyObject *const *a, Py_ssize_t n) {
             raise(PyExc_ValueError, "logits: need a 3-D GPU tensor [n_steps, B, V] with unit stride along the vocabulary");
         const int64_t n_steps = l.size(0), B = l.size(1), V = l.size(2);
         const ppv_dtype dt = logits_dtype(l);
-        const Prefixes p(a[1]);
+        const Prefixes p(a[1], true);
         const Arg lens{a[2], "lens"}, active{a[3], "active"}, un{a[5], "uniforms"}, ids{a[6], "ids"}, lzv{a[7], "logZ_valid"},
             logx{a[8], "logx"}, state{a[9], "state"};
         if (p.B != B || V != size_of(a[0], s_vocab) || !lens.fits(B) || !active.fits(B) || !un.fits(n_steps, B) ||
