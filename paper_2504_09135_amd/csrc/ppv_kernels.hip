@@ -1013,7 +1013,6 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
     const int vwave = sp.part * nw + wave;
     const T *row = logits + (size_t)b * (size_t)row_stride;
     const uint32_t *mrow = mask + (size_t)b * (size_t)n_words;
-    const int nt = (V + G::TILE - 1) / G::TILE;
     // The mask row is read as quads of four words per lane: one wavefront load covers 256 words (8,192 tokens), so a
     // wavefront has few loads to wait for, and those it has are requested two at a time and before the logits tile
     // (memory answers a wavefront in the order of its requests: the few bytes the next steps wait for must not queue

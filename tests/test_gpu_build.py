@@ -2,6 +2,8 @@
 by counting, several rounds of them, vocabularies at and beyond 16 bits, uploads of several slots and more than the ring
 holds, rows too long for the staging in LDS, more heavy prefixes than the index's block has room for, and prefixes that
 leave a member behind the point where it is alone.  Everything against the oracle."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -10,7 +12,7 @@ import oracle
 from paper_2504_09135_amd import binding as ppv
 from paper_2504_09135_amd import workloads as W
 
-from gpu_helpers import assert_query_parity
+from gpu_helpers import DEV, assert_query_parity, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -213,4 +215,78 @@ def test_a_small_set_holds_little_memory(V):
     tokens, offsets = csr(rng.integers(0, V, (60, 5)), np.full(60, 5))
     index = ppv.ppv_build_index(tokens, offsets, V)
     assert index.device_bytes < 1_000_000
+    index.free()
+
+
+def test_builds_from_several_threads():
+    """Threads that build, query and free sets of their own at the same time, each upload several slots long: they
+    share the ring of pinned slots, the kept blocks and the pinned words."""
+    sets = []
+    for k in range(3):
+        rng = np.random.default_rng(100 + k)
+        V = (500, 70_000, 30_000)[k]
+        n = 150_000 + 20_000 * k
+        rows = rng.integers(0, V, (n, 6), dtype=np.int32)
+        rows[:, 0] = rows[:, 0] % 50
+        tokens, offsets = csr(rows, rng.integers(1, 7, n))
+        trie = oracle.Trie(tokens, offsets, V)
+        P, L = prefixes_of(tokens, offsets, V, rng, 128, 8)
+        sets.append((tokens, offsets, V, trie, P, L))
+    errors = []
+
+    def work(k):
+        try:
+            tokens, offsets, V, trie, P, L = sets[k]
+            for _ in range(6):
+                index = ppv.ppv_build_index(tokens, offsets, V)
+                assert (index.n_distinct, index.n_prefixes) == (trie.n_members, trie.n_nodes - 1)
+                with torch.cuda.stream(torch.cuda.Stream()):
+                    assert_query_parity(index, trie, P, L)
+                index.free()
+        except BaseException as e:   # noqa: BLE001 (reported by the test's own thread)
+            errors.append((k, e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(sets))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+
+
+def test_heavy_prefixes_with_large_numbers():
+    """Few heavy prefixes (more than 1,024 children), some of them behind the first 2^20 prefixes: the images are laid out again."""
+    V, heads = 200_000, 4
+    rng = np.random.default_rng(11)
+    base = np.array([(f, c % V, (f + c) % V) for f in range(V) for c in (f, f + 70_000, f + 140_000)], np.int32)
+    stems = base[np.lexsort(base.T[::-1])][[10, -40, -20, -1]]              # low and high numbers at depth 3
+    more = np.concatenate([np.column_stack([np.repeat(s[None], 1_500, 0), rng.choice(V, 1_500, replace=False)]) for s in stems])
+    tokens = np.concatenate([base.ravel(), more.astype(np.int32).ravel()])
+    offsets = np.concatenate([np.arange(len(base)) * 3, base.size + np.arange(len(more) + 1) * 4]).astype(np.int64)
+    trie = oracle.Trie(tokens, offsets, V)
+    index = ppv.ppv_build_index(tokens, offsets, V)
+    assert index.n_prefixes == trie.n_nodes - 1 > (1 << 20)
+    P = np.full((64, 5), W.PAD_TOKEN, np.int32)
+    L = np.zeros(64, np.int32)
+    for i in range(64):
+        row = stems[i % heads] if i < 32 else base[rng.integers(0, len(base))]
+        L[i] = 3 if i < 48 else rng.integers(0, 4)
+        P[i, :L[i]] = row[:L[i]]
+    assert_query_parity(index, trie, P, L)
+    # the same rows through the sampler and a step with a cursor: one valid token, the same one
+    lg, un = torch.randn((64, V), device=DEV), torch.rand(64, device=DEV)
+    pd, ld = to_dev(P), to_dev(L)
+    ids = torch.full((64,), -7, dtype=torch.int32, device=DEV)
+    ppv.ppv_sample_next(index, pd, ld, lg, un, ids)
+    state = torch.zeros((64, ppv.PPV_STATE_WORDS), dtype=torch.int32, device=DEV)
+    active = torch.zeros(64, dtype=torch.uint8, device=DEV)
+    ppv.ppv_decode_begin(index, pd, ld, state, active)
+    active.fill_(1)
+    step = torch.full((64,), -7, dtype=torch.int32, device=DEV)
+    ppv.ppv_decode_step(index, pd, ld, active, lg, un, step, state=state)
+    ids, step = ids.cpu().numpy(), step.cpu().numpy()
+    assert np.array_equal(ids, step)
+    children = {tuple(s): set(more[(more[:, :3] == s).all(axis=1), 3]) for s in stems}
+    for i in range(32):
+        assert ids[i] in children[tuple(P[i, :3])]
     index.free()

@@ -232,9 +232,8 @@ def test_C3_decode_loop_at_the_batch_sizes_of_the_sweep(B):
 
 
 def test_C3_one_launch_loop_in_a_batch_above_1024_rows():
-    """ppv_decode_loop picks another launch shape for batches above 1,024 rows (two wavefronts per row, the three-tile
-    pipeline inside the loop kernel).  It must give, bit for bit, what one ppv_decode_step per step gives on the same
-    logits -- whose results at such batch sizes are checked against the oracle in the test above."""
+    """ppv_decode_loop picks another launch shape for batches above 1,024 rows (two wavefronts per row, lists in LDS).  It
+    must give, bit for bit, what one ppv_decode_step per step gives on the same logits -- whose results at such batch sizes are checked against the oracle in the test above."""
     cfg = W.CONFIGS["C3"]
     S, trie, index = build_both(cfg)
     V, L, B = cfg.vocab, index.l_max, 2048
