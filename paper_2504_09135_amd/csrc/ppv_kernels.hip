@@ -998,7 +998,6 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
                                                                   float *__restrict__ logZ_valid,
                                                                   float *__restrict__ logZ_all, Temper tp,
                                                                   int split_shift, SplitScratch *scratch) {
-    using G = TileGeom<T>;
     using SH = typename std::conditional<SMALL, RowSharedSmall, RowShared>::type;
     __shared__ SH sh;
     // SPLIT: a row is shared by 1 << split_shift consecutive workgroups
