@@ -305,16 +305,14 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
 //          rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
 //          the tile lies more than REF_GUARD * T above it, else the exact maximum.
 // Either way m depends on the row's values alone, not on how the row is split over wavefronts.  m = -inf: an empty tile.
-// The two checks cost rows without a filter 1 to 2.5 % (C3, 2,048 rows, step by step: 561 us without, 569 with them).  Tiles
-// that were set aside and loaded once more behind the others cost none, but took filtered rows up to twice as long
-// (constrained_sample, 50 tokens left of V = 32k, 2,048 rows: 47.5 us, now 25.4; V = 50k fp32, 384 rows: 29.8, now 16.4).
-// What bounds it: per bf16 token one unpacking, one fma, one exp (a quarter of the rate) and one addition, 0.35 us per
-// tile and wavefront.  The running maximum that stood here for all rows was one more instruction in eight and, because
-// every token was needed twice, 32 registers more: 79 to 94, now 60 (bf16), so that eight wavefronts fit a SIMD and all
-// rows of a batch of 2,048 are on the chip at once.
+// The two checks and a second copy of the sums, out of the way of the first, cost rows without a filter 0.4 to 1.2 % (C3, 2,048
+// rows, step by step: 561 us without, 563 with them; 567 with one copy in a loop; 565 where the check for REF_LOW, an integer
+// compare of scalars now, is a float compare).  Tiles that were set aside and loaded once more behind the others cost them
+// nothing, but took filtered rows up to twice as long (constrained_sample, 50 tokens left of V = 32k, 2,048 rows: 47.5 us, now
+// 25.3; V = 50k fp32, 384 rows: 29.8, now 16.4).
 constexpr float REF_GUARD = 40.f;   // exp(40) * 2048 tokens is far inside fp32
 constexpr float SUM_MOST = 2.353852668e17f;   // exp(REF_GUARD)
-constexpr float REF_LOW = -8192.f;  // in units of log2: a logit of -5,678 T
+constexpr float REF_LOW = -5e3f;
 template <typename T, bool IMAGE, bool PAD>
 __device__ __forceinline__ void tile_sums(const RawTile &rt, uint32_t tile_word, int lane, int left, float ref, float c,
                                           float &zall_out, float &zval_out) {
@@ -364,18 +362,22 @@ __device__ __forceinline__ void tile_stats(const RawTile &rt, uint32_t tile_word
         mx = fmaxf(mx, dpp_self<DPP_QUAD_XOR2>(mx));
     }
     float ref = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
+    float zall = 0.f, zval = 0.f;   // (handed out once, at the end: written through the references in several places they end up in memory)
     // (all branches wave-uniform)
-    bool exact = IMAGE ? ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull : !(ref * tp.c > REF_LOW);
-    float zall, zval;   // (handed out once, at the end: written through the references in several places they end up in memory)
-    for (;;) {
-        if (exact) ref = wave_max(IMAGE ? mx : lane_max<T, PAD, 4>(rt, left));
-        if (exact && ref == -INFINITY) {   // nothing but -inf in this tile
-            zall = zval = 0.f;
-            break;
+    if (IMAGE) {
+        if (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull) ref = wave_max(mx);
+        if (ref != -INFINITY) tile_sums<T, true, PAD>(rt, tile_word, lane, left, ref, tp.c, zall, zval);
+    } else {
+        bool redo = __float_as_uint(ref) >= __float_as_uint(REF_LOW);   // (as unsigned numbers, negative floats grow with their size)
+        if (__builtin_expect(!redo, 1)) {
+            tile_sums<T, false, PAD>(rt, 0u, lane, left, ref, tp.c, zall, zval);
+            redo = !(zall <= SUM_MOST);   // (too large, or NaN)
         }
-        tile_sums<T, IMAGE, PAD>(rt, tile_word, lane, left, ref, tp.c, zall, zval);
-        if (IMAGE || exact || zall <= SUM_MOST) break;   // (not so: too large, or NaN)
-        exact = true;
+        if (__builtin_expect(redo, 0)) {
+            ref = wave_max(lane_max<T, PAD, 4>(rt, left));
+            zall = 0.f;
+            if (ref != -INFINITY) tile_sums<T, false, PAD>(rt, 0u, lane, left, ref, tp.c, zall, zval);
+        }
     }
     zall_out = zall;
     zval_out = zval;
@@ -1867,7 +1869,10 @@ int waves_for(int V, ppv_dtype dt, int B, int parts = 1, bool cursor_step = fals
     // sooner.  us with 4 / 8 / 16 wavefronts, decoding loops: V = 200k bf16, B = 1,000: 326 / 289 / 319; V = 128k bf16,
     // B = 1,024: 298 / 287 / 321, B = 1,800: 358 / 341 / 378; V = 50k fp32, B = 1,024: 363 / 352 / 371; V = 32k bf16 (16
     // tiles), B = 1,024: 211 / 219 / 279.  Mask + sample, B = 1,024: V = 200k 92.3 / 89.1 / 88.9, V = 50k fp32
-    // 40.7 / 39.5 / 41.7; ppv_sample_next: V = 128k 49.1 / 48.8 / 56.6, V = 50k fp32 36.7 / 37.0 / 40.6.
+    // 40.7 / 39.5 / 41.7; ppv_sample_next: V = 128k 49.1 / 48.8 / 56.6, V = 50k fp32 36.7 / 37.0 / 40.6.  Below that four are
+    // better or as good (constrained_sample / ppv_sample_next, B = 1,024, 4 against 8, 24, 32, 40 and 48 tiles of bf16: 19.2
+    // 24.8 29.3 34.6 against 21.4 25.7 30.1 35.0 / 18.1 23.4 27.7 33.0 against 19.4 23.8 28.5 33.0; fp32, 32 and 40 tiles: 22.0
+    // 26.5 against 24.8 28.8 / 22.3 26.8 against 23.0 27.3).
     if (nt >= 48 && B > 512) cap = 8;
     if (const int v = ppv_tuning(PPV_TUNE_WAVES_PER_ROW)) cap = v;   // tuning aid (0: the table above)
     int nw = 1;
