@@ -20,6 +20,8 @@ HIPCC_FLAGS = [
     # no multiply-add fusing beyond the fmaf calls in the sources: several kernels promise each other's results bit
     # for bit, which must not hinge on where the compiler happens to find a multiply next to an add
     "-ffp-contract=off",
+    # a kernel's leading scalar arguments arrive in registers (the kernels take first what their first loads need)
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option",
 ]
 

@@ -50,14 +50,20 @@ __device__ __forceinline__ float exp_scale(float d, float c) {
     return fast_exp2(hi) * fmaf(lo, LN2F, 1.0f);
 }
 
+// Arguments.  Every kernel takes first what its first loads need (pointers and sizes, 14 words at most) and the structs
+// last: the leading scalars are in the wavefronts' registers when these start (-amdgpu-kernarg-preload-count; a struct stays
+// in memory), so that a row's words are asked for at once and not after a trip for their addresses.  us per pass before and
+// after, the structs first: mask + sample of 4,096 rows at V = 1,024 fp32 11.71 / 11.03, of 128 at V = 50,265 fp32 16.16 /
+// 15.52; decoding step by step 2,048 rows at V = 32k 566.5 / 559.1 and 1,024 at V = 50k 269.5 / 265.8.
+
 // ------------------------------------------------------------------------------------------
 // ppv_next_token_mask: one workgroup per prefix.
-__global__ __launch_bounds__(MASK_THREADS) void mask_kernel(IndexView ix, const int32_t *__restrict__ prefixes,
-                                                            int32_t stride, const int32_t *__restrict__ lens,
+__global__ __launch_bounds__(MASK_THREADS) void mask_kernel(const int32_t *__restrict__ prefixes,
+                                                            const int32_t *__restrict__ lens, int32_t stride,
                                                             uint32_t *__restrict__ mask,
                                                             uint32_t *__restrict__ range_lo,
                                                             uint32_t *__restrict__ range_hi,
-                                                            uint8_t *__restrict__ member) {
+                                                            uint8_t *__restrict__ member, IndexView ix) {
     extern __shared__ __align__(16) uint32_t smem[];
     const int n_words = ix.n_words;
     uint32_t *img = smem;            // [n_words]
@@ -135,12 +141,12 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(IndexView ix, const 
 // wavefront per prefix, four prefixes per workgroup, no LDS and no barrier.  A listed node has at most V / 32 <= 64
 // children here, one per lane; each child's bit is set by the lane that holds its word.
 constexpr int MASK_SMALL_WORDS = WAVE;
-__global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(IndexView ix, const int32_t *__restrict__ prefixes,
-                                                                 int32_t stride, const int32_t *__restrict__ lens, int B,
+__global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(const int32_t *__restrict__ prefixes,
+                                                                 const int32_t *__restrict__ lens, int32_t stride, int B,
                                                                  uint32_t *__restrict__ mask,
                                                                  uint32_t *__restrict__ range_lo,
                                                                  uint32_t *__restrict__ range_hi,
-                                                                 uint8_t *__restrict__ member) {
+                                                                 uint8_t *__restrict__ member, IndexView ix) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int b = blockIdx.x * (MASK_THREADS / WAVE) + threadIdx.x / WAVE;
     if (b >= B) return;  // uniform per wavefront
@@ -1002,13 +1008,13 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
 // unpacked into the token list, a large one is used as an image.
 template <typename T, bool SMALL, bool SPLIT>
 __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void sample_kernel(const T *__restrict__ logits, int64_t row_stride,
-                                                                  const uint32_t *__restrict__ mask,
-                                                                  const float *__restrict__ uniforms, int V,
-                                                                  int n_words, int list_max,
+                                                                  const uint32_t *__restrict__ mask, int V,
+                                                                  int n_words, int list_max, int split_shift,
+                                                                  const float *__restrict__ uniforms,
                                                                   int32_t *__restrict__ ids,
                                                                   float *__restrict__ logZ_valid,
                                                                   float *__restrict__ logZ_all, Temper tp,
-                                                                  int split_shift, SplitScratch *scratch) {
+                                                                  SplitScratch *scratch) {
     using SH = typename std::conditional<SMALL, RowSharedSmall, RowShared>::type;
     __shared__ SH sh;
     // SPLIT: a row is shared by 1 << split_shift consecutive workgroups
@@ -1146,9 +1152,9 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_one_tile_kernel(co
 // (lane l holds word l of it, which is also word l of the tile's mask).
 template <typename T>
 __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kernel(
-    IndexView ix, const int32_t *__restrict__ prefixes, int32_t stride, const int32_t *__restrict__ lens,
-    const T *__restrict__ logits, int64_t row_stride, const float *__restrict__ uniforms, int B, int32_t *__restrict__ ids,
-    float *__restrict__ logZ_valid, uint8_t *__restrict__ member, Temper tp) {
+    const int32_t *__restrict__ prefixes, const int32_t *__restrict__ lens, const float *__restrict__ uniforms,
+    const T *__restrict__ logits, int64_t row_stride, int32_t stride, int B, int32_t *__restrict__ ids,
+    float *__restrict__ logZ_valid, uint8_t *__restrict__ member, Temper tp, IndexView ix) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int b = blockIdx.x * ONE_TILE_ROWS + threadIdx.x / WAVE;
     if (b >= B) return;   // uniform per wavefront
@@ -1199,11 +1205,11 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
 
 // ------------------------------------------------------------------------------------------
 // ppv_decode_begin: one wavefront per row walks the row's current prefix and leaves the cursor.
-__global__ __launch_bounds__(MASK_THREADS) void decode_begin_kernel(IndexView ix, const int32_t *__restrict__ prefixes,
-                                                                    int32_t stride, const int32_t *__restrict__ lens,
+__global__ __launch_bounds__(MASK_THREADS) void decode_begin_kernel(const int32_t *__restrict__ prefixes,
+                                                                    const int32_t *__restrict__ lens, int32_t stride,
                                                                     int B, RowState *__restrict__ state,
                                                                     uint8_t *__restrict__ active,
-                                                                    float *__restrict__ logx) {
+                                                                    float *__restrict__ logx, IndexView ix) {
     const int lane = threadIdx.x & (WAVE - 1);
     const int b = blockIdx.x * (MASK_THREADS / WAVE) + threadIdx.x / WAVE;
     if (b >= B) return;  // uniform per wave
@@ -1226,10 +1232,10 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_kernel(IndexView ix
 
 // ppv_decode_begin_empty: every row starts from the empty candidate.  The cursor is the root's, the same for all
 // rows: no prefix to read, no walk; the lengths are written too, so that a decode loop needs no separate fill.
-__global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(IndexView ix, int B, int32_t *__restrict__ lens,
+__global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(int B, int32_t *__restrict__ lens,
                                                                           RowState *__restrict__ state,
                                                                           uint8_t *__restrict__ active,
-                                                                          float *__restrict__ logx) {
+                                                                          float *__restrict__ logx, IndexView ix) {
     const int b = blockIdx.x * MASK_THREADS + threadIdx.x;
     if (b >= B) return;
     RowState st;
@@ -1252,11 +1258,10 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(IndexV
 // go on, so nothing is fetched in vain).
 template <typename T, bool LOOP, bool SPLIT, bool REG>
 __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MAX_WAVES * WAVE) void decode_kernel(
-    IndexView ix, int32_t *__restrict__ prefixes, int32_t stride, int32_t *__restrict__ lens,
-    uint8_t *__restrict__ active, RowState *__restrict__ state, const T *__restrict__ logits, int64_t row_stride,
-    int64_t step_stride, const float *__restrict__ uniforms, int n_steps, int B, int32_t *__restrict__ ids,
-    float *__restrict__ logZ_valid, float *__restrict__ logx, Temper tp, int split_shift, SplitScratch *scratch,
-    int flags) {
+    uint8_t *__restrict__ active, int32_t *__restrict__ lens, RowState *__restrict__ state, const float *__restrict__ uniforms,
+    float *__restrict__ logx, const T *__restrict__ logits, int flags, int split_shift, int32_t *__restrict__ prefixes,
+    int32_t stride, int n_steps, int B, int64_t row_stride, int64_t step_stride, int32_t *__restrict__ ids,
+    float *__restrict__ logZ_valid, SplitScratch *scratch, Temper tp, IndexView ix) {
     // flags bit 1 (ppv_decode_first_step): every row starts from the empty candidate here and now -- no flags, length
     // or cursor are read, the root's cursor is taken instead, and all of them are written at the end.
     const int advance = flags & 1;
@@ -1937,8 +1942,8 @@ void launch_sample(bool small, dim3 grid, dim3 block, hipStream_t hs, const T *l
                    const uint32_t *mask, const float *uniforms, int V, int n_words, int list_max, int32_t *ids,
                    float *logZ_valid, float *logZ_all, Temper tp, int split_shift, SplitScratch *scratch) {
 #define PPV_LAUNCH_SAMPLE(SMALL, SPLIT)                                                                                  \
-    hipLaunchKernelGGL((sample_kernel<T, SMALL, SPLIT>), grid, block, 0, hs, lg, row_stride, mask, uniforms, V, n_words, \
-                       list_max, ids, logZ_valid, logZ_all, tp, split_shift, scratch)
+    hipLaunchKernelGGL((sample_kernel<T, SMALL, SPLIT>), grid, block, 0, hs, lg, row_stride, mask, V, n_words, \
+                       list_max, split_shift, uniforms, ids, logZ_valid, logZ_all, tp, scratch)
     if (split_shift) PPV_LAUNCH_SAMPLE(false, true);
     else if (small) PPV_LAUNCH_SAMPLE(true, false);
     else PPV_LAUNCH_SAMPLE(false, false);
@@ -1952,10 +1957,9 @@ void launch_decode_kernel(bool loop, dim3 grid, dim3 block, hipStream_t hs, cons
                           int64_t row_stride, int64_t step_stride, const float *uniforms, int n_steps, int B, int32_t *ids,
                           float *logZ_valid, float *logx, Temper tp, int split_shift, SplitScratch *scratch, int flags) {
     const bool reg = rs && (!loop || B <= REG_MAX_ROWS);
-#define PPV_LAUNCH_DECODE(LOOP, SPLIT, REG)                                                                            \
-    hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, view, prefixes, stride, lens, active, \
-                       rs, lg, row_stride, step_stride, uniforms, n_steps, B, ids, logZ_valid, logx, tp, split_shift,   \
-                       scratch, flags)
+#define PPV_LAUNCH_DECODE(LOOP, SPLIT, REG)                                                                               \
+    hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, active, lens, rs, uniforms, logx, lg, flags, \
+                       split_shift, prefixes, stride, n_steps, B, row_stride, step_stride, ids, logZ_valid, scratch, tp, view)
     if (split_shift && !loop) PPV_LAUNCH_DECODE(false, true, false);
     else if (loop && reg) PPV_LAUNCH_DECODE(true, false, true);
     else if (loop) PPV_LAUNCH_DECODE(true, false, false);
@@ -1975,12 +1979,11 @@ extern "C" ppv_status ppv_next_token_mask(const ppv_index_t *ix, const int32_t *
     if (ix->view.n_words <= MASK_SMALL_WORDS) {
         const int rows_per_wg = MASK_THREADS / WAVE;
         hipLaunchKernelGGL(mask_rows_kernel, dim3((unsigned)((B + rows_per_wg - 1) / rows_per_wg)), dim3(MASK_THREADS), 0,
-                           (hipStream_t)stream, ix->view, prefixes, prefix_stride, lens, B, mask, range_lo, range_hi,
-                           member);
+                           (hipStream_t)stream, prefixes, lens, prefix_stride, B, mask, range_lo, range_hi, member, ix->view);
     } else {
         const size_t lds = ((size_t)ix->view.n_words + 5) * sizeof(uint32_t);
-        hipLaunchKernelGGL(mask_kernel, dim3((unsigned)B), dim3(MASK_THREADS), lds, (hipStream_t)stream, ix->view,
-                           prefixes, prefix_stride, lens, mask, range_lo, range_hi, member);
+        hipLaunchKernelGGL(mask_kernel, dim3((unsigned)B), dim3(MASK_THREADS), lds, (hipStream_t)stream, prefixes,
+                           lens, prefix_stride, mask, range_lo, range_hi, member, ix->view);
     }
     PPV_HIP_TRY(hipGetLastError());
     return PPV_OK;
@@ -2080,8 +2083,8 @@ extern "C" ppv_status ppv_decode_begin(const ppv_index_t *ix, const int32_t *pre
     if (!prefixes || !lens || !state || !active) return PPV_EINVAL;
     const int rows_per_wg = MASK_THREADS / WAVE;
     hipLaunchKernelGGL(decode_begin_kernel, dim3((unsigned)((B + rows_per_wg - 1) / rows_per_wg)), dim3(MASK_THREADS), 0,
-                       (hipStream_t)stream, ix->view, prefixes, prefix_stride, lens, B, (RowState *)state, active,
-                       logx);
+                       (hipStream_t)stream, prefixes, lens, prefix_stride, B, (RowState *)state, active, logx,
+                       ix->view);
     PPV_HIP_TRY(hipGetLastError());
     return PPV_OK;
 }
@@ -2092,7 +2095,7 @@ extern "C" ppv_status ppv_decode_begin_empty(const ppv_index_t *ix, int32_t B, i
     if (B == 0) return PPV_OK;
     if (!lens || !state || !active) return PPV_EINVAL;
     hipLaunchKernelGGL(decode_begin_empty_kernel, dim3((unsigned)((B + MASK_THREADS - 1) / MASK_THREADS)), dim3(MASK_THREADS),
-                       0, (hipStream_t)stream, ix->view, B, lens, (RowState *)state, active, logx);
+                       0, (hipStream_t)stream, B, lens, (RowState *)state, active, logx, ix->view);
     PPV_HIP_TRY(hipGetLastError());
     return PPV_OK;
 }
@@ -2187,13 +2190,13 @@ extern "C" ppv_status ppv_sample_next(const ppv_index_t *ix, const int32_t *pref
     if (V <= tile && ix->view.n_words <= MASK_SMALL_WORDS) {   // the whole row is one tile: one wavefront per row
         const dim3 g1((unsigned)((B + ONE_TILE_ROWS - 1) / ONE_TILE_ROWS)), b1(ONE_TILE_ROWS * WAVE);
         if (dt == PPV_F32)
-            hipLaunchKernelGGL(sample_next_one_tile_kernel<float>, g1, b1, 0, (hipStream_t)stream, ix->view, prefixes,
-                               prefix_stride, lens, (const float *)logits, row_stride, uniforms, B, ids, logZ_valid,
-                               (uint8_t *)nullptr, tp);
+            hipLaunchKernelGGL(sample_next_one_tile_kernel<float>, g1, b1, 0, (hipStream_t)stream, prefixes, lens,
+                               uniforms, (const float *)logits, row_stride, prefix_stride, B, ids, logZ_valid,
+                               (uint8_t *)nullptr, tp, ix->view);
         else
-            hipLaunchKernelGGL(sample_next_one_tile_kernel<uint16_t>, g1, b1, 0, (hipStream_t)stream, ix->view, prefixes,
-                               prefix_stride, lens, (const uint16_t *)logits, row_stride, uniforms, B, ids, logZ_valid,
-                               (uint8_t *)nullptr, tp);
+            hipLaunchKernelGGL(sample_next_one_tile_kernel<uint16_t>, g1, b1, 0, (hipStream_t)stream, prefixes, lens,
+                               uniforms, (const uint16_t *)logits, row_stride, prefix_stride, B, ids, logZ_valid,
+                               (uint8_t *)nullptr, tp, ix->view);
         PPV_HIP_TRY(hipGetLastError());
         return PPV_OK;
     }

@@ -737,12 +737,13 @@ __device__ inline void count_children(const IndexView &ix, const T *__restrict__
 }
 
 template <typename T, int LIST>
-__global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(IndexView ix, const int32_t *__restrict__ prefixes,
-                                                                int32_t stride, const int32_t *__restrict__ lens,
-                                                                const T *__restrict__ logits, int64_t row_stride, int M,
-                                                                int force_streaming, int32_t *__restrict__ top_ids,
+__global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(const int32_t *__restrict__ prefixes,
+                                                                const int32_t *__restrict__ lens,
+                                                                const T *__restrict__ logits, int64_t row_stride,
+                                                                int32_t stride, int M, int force_streaming,
+                                                                int32_t *__restrict__ top_ids,
                                                                 uint8_t *__restrict__ mask_V,
-                                                                uint32_t *__restrict__ mask) {
+                                                                uint32_t *__restrict__ mask, IndexView ix) {
     constexpr int EPL = KeyChunk<T>::EPL;
     extern __shared__ __align__(16) uint32_t smem[];  // max(TOPM_BINS, n_words) words, then heavy_min (1 at least) words for kids
     uint32_t *img = smem;                             // [n_words] the row of the mask, once the histogram is done with
@@ -906,8 +907,8 @@ extern "C" ppv_status ppv_topm_mask(const ppv_index_t *ix, const int32_t *prefix
     const dim3 grid((unsigned)B), block(threads);
     hipStream_t hs = (hipStream_t)stream;
 #define PPV_LAUNCH_TOPM(T, LIST)                                                                                      \
-    hipLaunchKernelGGL((topm_kernel<T, LIST>), grid, block, lds, hs, ix->view, prefixes, prefix_stride, lens,          \
-                       (const T *)logits, row_stride, M, force_streaming, top_ids, mask_V, mask)
+    hipLaunchKernelGGL((topm_kernel<T, LIST>), grid, block, lds, hs, prefixes, lens, (const T *)logits, row_stride,    \
+                       prefix_stride, M, force_streaming, top_ids, mask_V, mask, ix->view)
     // a few hundred tokens reach the bound when M is small and the row not too long (the bound's bin holds a share
     // of the row): then a quarter of the LDS does, and more rows fit a compute unit
     const bool small_list = M <= 128 && V <= 65536;
