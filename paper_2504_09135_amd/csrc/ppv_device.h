@@ -54,13 +54,25 @@ __device__ inline double lane_value(double x, int l) {
                             __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
+// The reductions of floats are written out: from the builtins the compiler makes three or four instructions of a step
+// (a copy, a move across lanes, a NaN made quiet, the operation), and a tile of logits has eight such steps.  A step reads
+// other lanes' results of the step before, which takes two idle cycles.
+#define PPV_DPP_STEP(OP, CTRL) OP " %0, %0, %0 " CTRL "\n\ts_nop 1\n\t"
+#define PPV_DPP_QUAD(OP)                                                      \
+    PPV_DPP_STEP(OP, "quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")        \
+    PPV_DPP_STEP(OP, "quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf")
+#define PPV_DPP_WAVE(OP)                                                                                        \
+    "s_nop 1\n\t" PPV_DPP_QUAD(OP)                                                                              \
+    PPV_DPP_STEP(OP, "row_half_mirror row_mask:0xf bank_mask:0xf")                                              \
+    PPV_DPP_STEP(OP, "row_mirror row_mask:0xf bank_mask:0xf")       /* every lane: result over its row of 16 */ \
+    PPV_DPP_STEP(OP, "row_bcast:15 row_mask:0xa bank_mask:0xf")     /* rows 1, 3 take in rows 0, 2 */           \
+    OP " %0, %0, %0 row_bcast:31 row_mask:0xc bank_mask:0xf"        /* rows 2, 3 take in lane 31 */
+__device__ inline float quad_max(float x) {   // over each four lanes; NaNs are passed over
+    asm("s_nop 1\n\t" PPV_DPP_QUAD("v_max_f32_dpp") : "+v"(x));
+    return x;
+}
 __device__ inline float wave_max(float x) {
-    x = fmaxf(x, dpp_self<DPP_QUAD_XOR1>(x));
-    x = fmaxf(x, dpp_self<DPP_QUAD_XOR2>(x));
-    x = fmaxf(x, dpp_self<DPP_ROW_HALF_MIRROR>(x));
-    x = fmaxf(x, dpp_self<DPP_ROW_MIRROR>(x));           // every lane: maximum of its row of 16
-    x = fmaxf(x, dpp_self<DPP_ROW_BCAST15, 0xA>(x));     // rows 1, 3 take in rows 0, 2
-    x = fmaxf(x, dpp_self<DPP_ROW_BCAST31, 0xC>(x));     // rows 2, 3 take in lane 31
+    asm(PPV_DPP_WAVE("v_max_f32_dpp") : "+v"(x));
     return last_lane(x);
 }
 template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline uint32_t dpp_self(uint32_t x) {
@@ -82,6 +94,10 @@ template <typename V> __device__ inline V wave_sum(V x) {
     x += dpp0<DPP_ROW_MIRROR>(x);
     x += dpp0<DPP_ROW_BCAST15, 0xA>(x);
     x += dpp0<DPP_ROW_BCAST31, 0xC>(x);
+    return last_lane(x);
+}
+__device__ inline float wave_sum(float x) {   // (the same sums in the same order as above)
+    asm(PPV_DPP_WAVE("v_add_f32_dpp") : "+v"(x));
     return last_lane(x);
 }
 // inclusive prefix sum over the 64 lanes (lane order)

@@ -227,24 +227,30 @@ struct RawTile {
     uint32_t word;   // image path: this lane's word of the tile's mask (requested together with the tile)
 };
 
-// A tile is requested with four unconditional 16-byte loads wherever it lies, also at the row's end and behind it: a group
-// of tokens past the end is read from the row's last group instead, and pad_tile puts -inf there when the tile is
-// used.  Nothing is conditional between request and use, so the compiler can count the loads in flight and wait for
-// exactly the ones a use needs, and the ragged last tile is one like the others.  (A group that straddles the row's end
-// is read whole: rows start on 16-byte boundaries, so it lies inside the 16 bytes that hold the row's last token; what
-// is behind that token is not looked at.)
-template <typename T>
-__device__ __forceinline__ void load_tile(const T *__restrict__ row, int V, int tile, int lane, RawTile &rt) {
-    using G = TileGeom<T>;
-    // byte offsets of 32 bits from a uniform address
-    const uint32_t last = (uint32_t)(V - 1) / G::EPL * 16u;
-    const uint32_t base = ((uint32_t)tile * (4 * WAVE) + (uint32_t)lane) * 16u;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        const uint32_t at = base + j * (WAVE * 16u);
-        rt.r[j] = __builtin_nontemporal_load((const u32x4 *)((const char *)row + (at < last ? at : last)));
-    }
+// A row as the memory unit's buffer: its address and its length in bytes, up to the 16 that hold its last token (rows start on
+// 16-byte boundaries).  What is asked for behind the length is not read and arrives as 0.
+struct Row {
+    __amdgpu_buffer_rsrc_t buf;
+};
+template <typename T, uint32_t PAD = 15u> __device__ __forceinline__ Row row_of(const T *row, int V) {
+    // (uniform, which the compiler does not see where the row came with a loop)
+    const uint64_t at = (uint64_t)row;
+    const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32) |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    const uint32_t bytes = (uint32_t)__builtin_amdgcn_readfirstlane(V) * (uint32_t)sizeof(T);
+    return {__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (bytes + PAD) & ~PAD, 0x00027000)};
 }
+// A tile is requested with four unconditional 16-byte loads wherever it lies, also at the row's end and behind it; group_of puts
+// -inf behind the end when the tile is used.  Nothing is conditional between request and use, so the compiler can
+// count the loads in flight and wait for exactly the ones a use needs, and the ragged last tile is one like the others.
+// One addition makes the four addresses (clamped into the row by comparisons, as here before, they took twelve).
+template <typename T>
+__device__ __forceinline__ void load_tile(const Row &row, int tile, int lane, RawTile &rt) {
+    const uint32_t at = (uint32_t)tile * (4 * WAVE * 16u) + (uint32_t)lane * 16u;
+#pragma unroll
+    for (int j = 0; j < 4; j++) rt.r[j] = __builtin_amdgcn_raw_buffer_load_b128(row.buf, at + j * (WAVE * 16u), 0, 2 /* non-temporal */);
+}
+constexpr int NO_TILE = 1 << 18;   // behind every row: a request that reads nothing
 // The tile's tokens that lie inside the row, counted from this lane's first one (PAD: what is behind the row's end counts
 // as -inf; only the row's last tile has any of that).
 template <typename T> __device__ __forceinline__ int tokens_left(int V, int tile, int lane) {
@@ -297,61 +303,68 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
     return (w >> ((lane % G::LANES_PER_WORD) * G::EPL)) & ((1u << G::EPL) - 1u);
 }
 
-// Statistics of one tile: a reference m, sum_all = sum exp(x - m), and (IMAGE) sum_val over valid tokens.
+// Statistics of one tile: a reference m, sum_all = sum exp(x - m), and (image) sum_val over valid tokens.
 // Any reference gives the same sums up to rounding as long as they stay inside fp32's range, so neither the maximum nor
 // the reduction over the wavefront it would need are computed.
-//   without an image   only the sum over all tokens is wanted, and it only ever enters a logarithm: m is the largest of
-//          the first 16 bytes of lanes 0 to 3 (two steps within a quad).  Where that is -inf, or so low (REF_LOW) that it
-//          is a caller's stand-in for -inf, the row has been filtered and m is the exact maximum from the start; where a
-//          token lies more than REF_GUARD * T above m, the sum is not inside SUM_MOST and the tile, still in its
-//          registers, is summed again with its exact maximum.  (The farther a token lies above m, the larger the arguments
+//   without an image   (list_stats) only the sum over all tokens is wanted, and it only ever enters a logarithm: m is the
+//          largest of the first 16 bytes of lanes 0 to 3 (two steps within a quad).  Where that is -inf, or so low (REF_LOW)
+//          that it is a caller's stand-in for -inf, the row has been filtered; where a token lies more than about REF_GUARD * T
+//          above m, the sum is not inside SUM_MOST: then the tile, still in its registers, is summed again with its
+//          exact maximum.  (The farther a token lies above m, the larger the arguments
 //          of exp and log and the more their rounding weighs: with sums allowed up to 1e30 and m from lane 0 alone, the
 //          largest error of logZ_valid went from 2e-6 to 1.1e-5 in rows with a token 55 T above the rest.)
-//   IMAGE  the sums over valid tokens set the sampling threshold, and with tens of thousands of valid tokens another
-//          rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
+//   image  (image_stats) the sums over valid tokens set the sampling threshold, and with tens of thousands of valid tokens
+//          another rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
 //          the tile lies more than REF_GUARD * T above it, else the exact maximum.
 // Either way m depends on the row's values alone, not on how the row is split over wavefronts.  m = -inf: an empty tile.
-// The two checks and a second copy of the sums, out of the way of the first, cost rows without a filter 0.4 to 1.2 % (C3, 2,048
-// rows, step by step: 561 us without, 563 with them; 567 with one copy in a loop; 565 where the check for REF_LOW, an integer
-// compare of scalars now, is a float compare).  Tiles that were set aside and loaded once more behind the others cost them
-// nothing, but took filtered rows up to twice as long (constrained_sample, 50 tokens left of V = 32k, 2,048 rows: 47.5 us, now
-// 25.3; V = 50k fp32, 384 rows: 29.8, now 16.4).
+//
+// exp(x - m) = 2^(x*c - m*c).  m*c is rounded once (mc); its residual is a factor of the tile's sums (rounding_of).  Without
+// an image that factor is left to combine_tiles, which has a tile per lane there.
+//
+// What a tile costs is the instructions a SIMD issues for it: a quarter of a wavefront's lanes a cycle, an exponential a
+// sixteenth.  1,024 fp32 tokens are 16 exponentials, multiply-adds and additions: 384 cycles; 2,048 of bf16, with the
+// unpacking, 896.  What surrounds them (addresses, reference, reduction, checks, keeping the result) took about 50 instructions
+// and an exponential a tile and takes about 20: one addition for the addresses, reductions of one instruction a step, the
+// first group unpacked once, checks by scalar compares, results in a register's lanes until the wavefront's last tile.
+// The second copy of the sums for tiles that are summed again stands out of the way of the first.  Tiles that were set aside
+// and loaded once more behind the others took filtered rows up to twice as long (constrained_sample, 50 tokens left of
+// V = 32k, 2,048 rows: 47.5 us against 25.3; V = 50k fp32, 384 rows: 29.8 against 16.4).
 constexpr float REF_GUARD = 40.f;   // exp(40) * 2048 tokens is far inside fp32
 constexpr float SUM_MOST = 2.353852668e17f;   // exp(REF_GUARD)
-__device__ __forceinline__ bool in_range(float zall) { return zall <= SUM_MOST; }   // (not so: too large, or NaN)
 constexpr float REF_LOW = -5e3f;
-template <typename T, bool IMAGE, bool PAD>
-__device__ __forceinline__ void tile_sums(const RawTile &rt, uint32_t tile_word, int lane, int left, float ref, float c,
-                                          float &zall_out, float &zval_out) {
-    using G = TileGeom<T>;
-    // exp(x - m) = 2^(x*c - m*c); m*c is rounded once (mc), its residual is folded into the tile sums
-    const float mc = ref * c;
-    const float fix = fast_exp2(-fmaf(ref, c, -mc));
-    float zall = 0.f, zval = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-        float x[G::EPL];
-        group_of<T, PAD>(rt, j, left, x);
-        uint32_t bits = 0;
-        if (IMAGE) bits = lane_bits<T>(tile_word, j, lane);
-#pragma unroll
-        for (int k = 0; k < G::EPL; k++) {
-            float e = fast_exp2(fmaf(x[k], c, -mc));
-            zall += e;
-            if (IMAGE) {
-                uint32_t keep = (uint32_t)(-(int32_t)((bits >> k) & 1u));
-                zval += __uint_as_float(__float_as_uint(e) & keep);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);   // one group's tokens in registers at a time
-    }
-    zall_out = wave_sum(zall) * fix;
-    zval_out = IMAGE ? wave_sum(zval) * fix : 0.f;
+// (as unsigned numbers, negative floats grow with their size, and infinities and NaNs are above the other positive ones)
+__device__ __forceinline__ bool settled(float ref, float zall) {
+    return __float_as_uint(ref) < __float_as_uint(REF_LOW) && __float_as_uint(zall) <= __float_as_uint(SUM_MOST);
 }
-template <typename T, bool PAD, int GROUPS> __device__ __forceinline__ float lane_max(const RawTile &rt, int left) {
+__device__ __forceinline__ float rounding_of(float ref, float c) { return fast_exp2(-fmaf(ref, c, -(ref * c))); }
+__device__ __forceinline__ float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+template <int EPL> __device__ __forceinline__ float group_sum(const float x[EPL], float c, float mc, float zall) {
+#pragma unroll
+    for (int k = 0; k < EPL; k++) zall += fast_exp2(fmaf(x[k], c, -mc));
+    return zall;
+}
+template <typename T, bool PAD> __device__ __forceinline__ void list_stats(const RawTile &rt, int left, const Temper &tp, float &m_out, float &zall_out) {
+    using G = TileGeom<T>;
+    float x[G::EPL];
+    group_of<T, PAD>(rt, 0, left, x);
+    float mx = x[0];
+#pragma unroll
+    for (int k = 1; k < G::EPL; k++) mx = fmaxf(mx, x[k]);
+    const float ref = uniform(quad_max(mx)), mc = ref * tp.c;
+    float zall = group_sum<G::EPL>(x, tp.c, mc, 0.f);
+#pragma unroll
+    for (int j = 1; j < 4; j++) {
+        __builtin_amdgcn_sched_barrier(0);   // one group's tokens in registers at a time
+        group_of<T, PAD>(rt, j, left, x);
+        zall = group_sum<G::EPL>(x, tp.c, mc, zall);
+    }
+    m_out = ref;
+    zall_out = wave_sum(zall);
+}
+template <typename T, bool PAD> __device__ __forceinline__ float lane_max(const RawTile &rt, int left) {
     float mx = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < GROUPS; j++) {
+    for (int j = 0; j < 4; j++) {
         float x[TileGeom<T>::EPL];
         group_of<T, PAD>(rt, j, left, x);
 #pragma unroll
@@ -360,43 +373,55 @@ template <typename T, bool PAD, int GROUPS> __device__ __forceinline__ float lan
     }
     return mx;
 }
-// SETTLE = false: without the checks; the caller looks at the sum (in_range) and does the tile again with exact_stats.
-template <typename T, bool IMAGE, bool PAD, bool SETTLE = true>
-__device__ __forceinline__ void tile_stats(const RawTile &rt, uint32_t tile_word, int lane, int left, const Temper &tp,
-                                           float &m_out, float &zall_out, float &zval_out) {
-    float mx = lane_max<T, PAD, IMAGE ? 4 : 1>(rt, left);
-    if (!IMAGE) {
-        mx = fmaxf(mx, dpp_self<DPP_QUAD_XOR1>(mx));
-        mx = fmaxf(mx, dpp_self<DPP_QUAD_XOR2>(mx));
-    }
-    float ref = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(mx)));
-    float zall = 0.f, zval = 0.f;   // (handed out once, at the end: written through the references in several places they end up in memory)
-    // (all branches wave-uniform)
-    if (IMAGE) {
-        if (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull) ref = wave_max(mx);
-        if (ref != -INFINITY) tile_sums<T, true, PAD>(rt, tile_word, lane, left, ref, tp.c, zall, zval);
-    } else {
-        bool redo = SETTLE && __float_as_uint(ref) >= __float_as_uint(REF_LOW);   // (as unsigned numbers, negative floats grow with their size)
-        if (__builtin_expect(!redo, 1)) {
-            tile_sums<T, false, PAD>(rt, 0u, lane, left, ref, tp.c, zall, zval);
-            redo = SETTLE && !in_range(zall);
+// the same relative to the exact maximum, for tiles that are not settled by list_stats
+template <typename T, bool PAD> __device__ __forceinline__ void exact_stats(const RawTile &rt, int left, const Temper &tp, float &m_out, float &zall_out) {
+    using G = TileGeom<T>;
+    const float ref = wave_max(lane_max<T, PAD>(rt, left)), mc = ref * tp.c;
+    float zall = 0.f;
+    if (ref != -INFINITY) {   // (uniform)
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            float x[G::EPL];
+            group_of<T, PAD>(rt, j, left, x);
+            zall = group_sum<G::EPL>(x, tp.c, mc, zall);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (__builtin_expect(redo, 0)) {
-            ref = wave_max(lane_max<T, PAD, 4>(rt, left));
-            zall = 0.f;
-            if (ref != -INFINITY) tile_sums<T, false, PAD>(rt, 0u, lane, left, ref, tp.c, zall, zval);
-        }
+        zall = wave_sum(zall);
     }
+    m_out = ref;
+    zall_out = zall;
+}
+template <typename T, bool PAD>
+__device__ __forceinline__ void image_stats(const RawTile &rt, uint32_t tile_word, int lane, int left, const Temper &tp,
+                                            float &m_out, float &zall_out, float &zval_out) {
+    using G = TileGeom<T>;
+    const float mx = lane_max<T, PAD>(rt, left);
+    float ref = uniform(mx);
+    if (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull) ref = wave_max(mx);   // (uniform)
+    float zall = 0.f, zval = 0.f;
+    if (ref != -INFINITY) {   // (uniform)
+        const float mc = ref * tp.c;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            float x[G::EPL];
+            group_of<T, PAD>(rt, j, left, x);
+            const uint32_t bits = lane_bits<T>(tile_word, j, lane);
+#pragma unroll
+            for (int k = 0; k < G::EPL; k++) {
+                const float e = fast_exp2(fmaf(x[k], tp.c, -mc));
+                zall += e;
+                const uint32_t keep = (uint32_t)(-(int32_t)((bits >> k) & 1u));
+                zval += __uint_as_float(__float_as_uint(e) & keep);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one group's tokens in registers at a time
+        }
+        const float fix = rounding_of(ref, tp.c);
+        zall = wave_sum(zall) * fix;
+        zval = wave_sum(zval) * fix;
+    }
+    m_out = ref;
     zall_out = zall;
     zval_out = zval;
-    m_out = ref;
-}
-template <typename T>
-__device__ __forceinline__ void exact_stats(const RawTile &rt, int lane, int left, const Temper &tp, float &m_out, float &zall_out) {
-    m_out = wave_max(lane_max<T, true, 4>(rt, left));
-    float none;
-    zall_out = 0.f;
-    if (m_out != -INFINITY) tile_sums<T, false, true>(rt, 0u, lane, left, m_out, tp.c, zall_out, none);
 }
 
 // Rare path of the image mode (the valid tokens lie far below the row maximum, so sums relative
@@ -544,72 +569,122 @@ struct Split {
 
 enum ValidMode { VALID_NONE = 0, VALID_LIST = 1, VALID_IMAGE = 2 };
 
-// Streams a row's tiles through one wavefront's share of the work: wave `wave` of `nw` takes the
-// tiles wave, wave+nw, ...  Per tile the statistics go to LDS.
+// A wavefront's share of a row: of `nw` wavefronts number `wave` has the tiles wave, wave + nw, ...  It takes them from a place
+// on that the workgroup's number sets, and the last one, which may be ragged, last.  (Rows that are started together are
+// otherwise read in step, and what is asked for at one time lies at the same place of a thousand rows: us per call, in
+// step and like this, ppv_sample_next, 1,024 rows, V = 256k bf16 96.2 / 88.4, V = 128k 48.8 / 47.1; the decoding loop, 2,048
+// rows at V = 32k, 547.7 / 541.2.  The sixteen places in the order of their bits reversed: neighbours start far apart.)
+struct Share {
+    int wave, nw, n, turn;   // n: tiles
+    __device__ __forceinline__ int first() const { return wave + turn * nw; }
+    __device__ __forceinline__ int at(int i) const {   // the i-th tile it takes
+        int q = i + turn;
+        q = q >= n - 1 ? q - (n - 1) : q;
+        return wave + (i < n - 1 ? q : i) * nw;
+    }
+};
+// `wave_v`: the wavefront's number among all that share the row, over all its workgroups
+__device__ __forceinline__ Share share_of(int nt, int wave_v, int nw) {
+    const int wave = __builtin_amdgcn_readfirstlane(wave_v);   // scalar: loop control stays uniform
+    Share s = {wave, nw, 0, 0};
+    const int up = nt - wave + nw - 1;
+    if ((nw & (nw - 1)) == 0) s.n = up >> __builtin_ctz((unsigned)nw);   // (a division is a hundred cycles before the first load)
+    else for (int x = up; x >= nw; x -= nw) s.n++;
+    // (where a row has sixteen wavefronts it is nearly alone on its compute unit, and the numbers would only be waited for:
+    // constrained_sample, 128 rows at V = 50,265 fp32, 11.0 us without, 11.8 with a turn)
+    if (nw <= 8 && s.n > 2) s.turn = (int)((__brev(blockIdx.x) >> 28) * (uint32_t)(s.n - 1) >> 4);
+    return s;
+}
+// Streams a row's tiles through one wavefront's share of the work.  Per tile the statistics go to LDS: under an image at once;
+// else, two numbers, they are kept in the lanes of two registers (the wavefront's first tile in lane 0, ...) and written together.
 //
 // Two register tiles take turns: while one is reduced, the other is on its way.  No load is conditional (see load_tile:
-// a tile that is not there costs one line of the row), so every wait is for loads issued a known number of loads ago.
+// a tile that is not there costs nothing), so every wait is for loads issued a known number of loads ago.
 // `mid` is work of the caller's that needs no tile (the sums over the listed tokens): it is run once, where this
 // wavefront has just asked for a tile and would only wait for it.
-// `wave_v` of `nw`: the wavefront's number among all wavefronts that share the row (over all its workgroups);
-// `pub`: where a split row's statistics are left for the workgroup that finishes it (nullptr: not split).
+// X: the share's first tile; `pub`: where a split row's statistics are left for the workgroup that finishes it (nullptr: not split).
 // IMAGE: the row may have an image (nullptr: it has none; one loop for both, so that the tiles stay in their registers).
 template <typename T, bool IMAGE, typename SH, typename MID>
-__device__ __forceinline__ void stream_tiles(const T *__restrict__ row, int V, RawTile &X,
-                                    const uint32_t *__restrict__ image, SH &sh, int lane, int wave_v,
-                                    int nw, const Temper &tp, MID &mid, SplitRow *pub) {
+__device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
+                                    const uint32_t *__restrict__ image, SH &sh, int lane, const Share &share,
+                                    const Temper &tp, MID &mid, SplitRow *pub) {
     using G = TileGeom<T>;
-    const int wave = __builtin_amdgcn_readfirstlane(wave_v);   // scalar: loop control stays uniform
-    const int nt = (V + G::TILE - 1) / G::TILE;
-    if (wave >= nt) {
+    if (share.n == 0) {
         mid();
         return;
     }
-    auto reduce_tile = [&](const RawTile &t, int k, auto pad) __attribute__((always_inline)) {
+    float kept_m = 0.f, kept_z = 0.f;   // lane i: the i-th tile since they were written last
+    auto write_kept = [&](int n, int i_first) __attribute__((always_inline)) {
+        if (lane < n) {
+            const int k = share.at(i_first + lane);
+            sh.tile_m[k] = kept_m;
+            sh.tile_zall[k] = kept_z;
+            if (pub) {
+                shared_put(&pub->tile[k].x, kept_m);
+                shared_put(&pub->tile[k].y, kept_z);
+            }
+        }
+    };
+    auto reduce_tile = [&](const RawTile &t, int k, int i, auto pad) __attribute__((always_inline)) {
         constexpr bool PAD = decltype(pad)::value;
         const int left = PAD ? tokens_left<T>(V, k, lane) : 0;
         float m, zall, zval;
-        if (IMAGE && image) tile_stats<T, true, PAD>(t, tile_word_fix<T>(t.word, k, lane, V), lane, left, tp, m, zall, zval);
-        else tile_stats<T, false, PAD>(t, 0u, lane, left, tp, m, zall, zval);
-        if (lane == 0) {
-            sh.tile_m[k] = m;
-            sh.tile_zall[k] = zall;
-            sh.tile_zval[k] = zval;
-            sh.tile_ref[k] = m;
-            if (pub) shared_put_tile(pub, k, m, zall, zval, m);
+        if (IMAGE && image) {
+            image_stats<T, PAD>(t, tile_word_fix<T>(t.word, k, lane, V), lane, left, tp, m, zall, zval);
+            if (lane == 0) {
+                sh.tile_m[k] = m;
+                sh.tile_zall[k] = zall;
+                sh.tile_zval[k] = zval;
+                sh.tile_ref[k] = m;
+                if (pub) shared_put_tile(pub, k, m, zall, zval, m);
+            }
+        } else {
+            list_stats<T, PAD>(t, left, tp, m, zall);
+            if (__builtin_expect(!settled(m, zall), 0)) exact_stats<T, PAD>(t, left, tp, m, zall);
+            kept_m = lane == (i & (WAVE - 1)) ? m : kept_m;
+            kept_z = lane == (i & (WAVE - 1)) ? zall : kept_z;
         }
     };
-    auto reduce_last = [&](const RawTile &t, int k) __attribute__((always_inline)) {   // the row's last tile is the last one of its wavefront
-        if ((k + 1) * G::TILE > V) reduce_tile(t, k, std::true_type());
-        else reduce_tile(t, k, std::false_type());
+    auto reduce_last = [&](const RawTile &t, int k, int i) __attribute__((always_inline)) {   // the row's last tile is the last one of its wavefront
+        if ((k + 1) * G::TILE > V) reduce_tile(t, k, i, std::true_type());
+        else reduce_tile(t, k, i, std::false_type());
     };
-    // a tile and its mask word (without an image: a word of the row, so that the number of loads is the same)
-    const uint32_t *words = image ? image : (const uint32_t *)row;
-    const int n_words = image ? V : 32;
+    // a tile and its mask word (without an image: of a row of no length, so that the number of loads is the same)
+    const Row words = row_of<uint32_t, 3u>(image, IMAGE && image ? (V + 31) / 32 : 0);
     auto fetch_word = [&](RawTile &t, int k) __attribute__((always_inline)) {
-        if (IMAGE) t.word = tile_word_raw<T>(words, k, lane, n_words);
+        if (IMAGE) t.word = __builtin_amdgcn_raw_buffer_load_b32(words.buf, (uint32_t)(k * G::WORDS + lane) * 4u, 0, 0);
     };
     auto fetch = [&](RawTile &t, int k) __attribute__((always_inline)) {
-        load_tile<T>(row, V, k, lane, t);
+        load_tile<T>(row, k, lane, t);
         fetch_word(t, k);
     };
-    int left = (nt - wave + nw - 1) / nw;   // tiles of this wavefront
-    int k = wave;
-    fetch_word(X, k);
+    const int n = share.n;
+    fetch_word(X, share.first());
     RawTile Y;
-    fetch(Y, k + nw);
+    fetch(Y, n > 1 ? share.at(1) : NO_TILE);
     mid();
-    for (; left > 2; left -= 2, k += 2 * nw) {
-        reduce_tile(X, k, std::false_type());
-        fetch(X, k + 2 * nw);
-        reduce_tile(Y, k + nw, std::false_type());
-        fetch(Y, k + 3 * nw);
+    int i = 0, written = 0;
+    for (; i + 2 < n; i += 2) {
+        reduce_tile(X, share.at(i), i, std::false_type());
+        fetch(X, share.at(i + 2));
+        reduce_tile(Y, share.at(i + 1), i + 1, std::false_type());
+        fetch(Y, i + 3 < n ? share.at(i + 3) : NO_TILE);
+        if (i + 2 - written == WAVE) {   // (a wavefront with more tiles than lanes: only where a launch shape is forced)
+            if (!(IMAGE && image)) write_kept(WAVE, written);
+            written += WAVE;
+        }
     }
-    reduce_last(X, k);
-    if (left == 2) reduce_last(Y, k + nw);
+    if (i + 1 < n) {
+        reduce_tile(X, share.at(i), i, std::false_type());
+        reduce_last(Y, share.at(i + 1), i + 1);
+    } else {
+        reduce_last(X, share.at(i), i);
+    }
+    if (!(IMAGE && image)) write_kept(n - written, written);
 }
 
-// Row totals from the per-tile statistics in LDS: the largest tile reference M, the sum over all tokens relative
+// Row totals from the per-tile statistics in LDS (without an image: not yet rid of the rounding of their references, see
+// list_stats): the largest tile reference M, the sum over all tokens relative
 // to it and (image rows) the sum over valid tokens.  Called by a whole wavefront; results are uniform.  The sum over
 // all tokens only ever enters a logarithm, so it is added up in fp32 (a tree over at most 256 positive terms: a few
 // 1e-7 relative); the valid sum sets the sampling threshold and is added up in fp64.
@@ -627,7 +702,7 @@ __device__ __forceinline__ void combine_tiles(const SH &sh, int nt, int lane, co
         double v = 0.0;
         if (m != -INFINITY) {
             const float sc = exp_scale(m - M, tp.c);
-            a = z * sc;
+            a = (image ? z : z * rounding_of(m, tp.c)) * sc;
             if (image) v = (double)zval * (double)sc;
         }
         za = wave_sum(a);
@@ -643,7 +718,8 @@ __device__ __forceinline__ void combine_tiles(const SH &sh, int nt, int lane, co
         const float m = sh.tile_m[k];
         if (m != -INFINITY) {
             const float sc = exp_scale(m - M, tp.c);
-            za += sh.tile_zall[k] * sc;
+            const float z = sh.tile_zall[k];
+            za += (image ? z : z * rounding_of(m, tp.c)) * sc;
             if (image) zv += (double)sh.tile_zval[k] * (double)sc;   // (the other modes have no per-tile valid sums)
         }
     }
@@ -718,13 +794,13 @@ __device__ __forceinline__ ListPick reg_list_pick(float gx, uint32_t tokw, int n
 }
 
 // Streams the row and samples.  Called by every thread of the workgroup with uniform arguments.
-//   first        this wave's first tile, already loaded (the wave owns tiles wave, wave+nw, ...)
+//   first        this wave's first tile, already loaded (share_of(...).first())
 //   next_row     optional: another row whose first tile (per wave) is to be requested into *next_first
 //   mode         VALID_LIST: sh.list_tok[0..n_list) holds the valid tokens (in LDS, barrier done)
 //                VALID_IMAGE: image (global memory, V bits) is the valid set
 //                VALID_NONE: the valid set is empty
 //   ALL          every thread gets the result (one more barrier); otherwise only wavefront 0 does
-//   sp           the row's split over workgroups: `first` is then tile sp.part * nw + wave, and only the
+//   sp           the row's split over workgroups: the wavefronts are then numbered over all its workgroups, and only the
 //                workgroup that arrives last goes on to sample (the others return with mine == false)
 //   SPLIT        compiled in only for kernels that may share a row between workgroups (the others pay nothing for it)
 template <typename T, typename SH, bool ALL, bool SPLIT>
@@ -739,6 +815,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
     const int parts = SPLIT ? sp.parts : 1;
     const int vwave = SPLIT ? sp.part * nw + wave : wave, vnw = parts * nw;
     SplitRow *pub = SPLIT && parts > 1 ? sp.row : nullptr;
+    const Share share = share_of(nt, vwave, vnw);
 
     // ---- list path, part 1: ask for the listed tokens' logits now (they are being streamed
     // anyway, so these are cache hits) so that they arrive while the tiles are reduced
@@ -791,10 +868,10 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
         }
     };
     // ---- stream: every tile once
-    stream_tiles<T, true, SH>(row, V, first, mode == VALID_IMAGE ? image : nullptr, sh, lane, vwave, vnw, tp, list_sums, pub);
+    stream_tiles<T, true, SH>(row_of(row, V), V, first, mode == VALID_IMAGE ? image : nullptr, sh, lane, share, tp, list_sums, pub);
     // (decode loop) the row of the next step is known already: ask for this wave's first tile of it
     // now, so that it travels while this row is combined and sampled
-    if (next_row && wave < nt) load_tile<T>(next_row, V, wave, lane, *next_first);
+    if (next_row && share.n > 0) load_tile<T>(row_of(next_row, V), share.first(), lane, *next_first);
     RowOut none;
     none.id = -1;
     none.pos = -1;
@@ -821,8 +898,10 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
             const float *t = (const float *)&pub->tile[k];
             sh.tile_m[k] = shared_get(t + 0);
             sh.tile_zall[k] = shared_get(t + 1);
-            sh.tile_zval[k] = shared_get(t + 2);
-            sh.tile_ref[k] = shared_get(t + 3);
+            if (mode == VALID_IMAGE) {
+                sh.tile_zval[k] = shared_get(t + 2);
+                sh.tile_ref[k] = shared_get(t + 3);
+            }
         }
         if (mode == VALID_LIST) {
             for (int i = tid; i < n_list; i += nthreads) sh.list_e[i] = shared_get(&pub->list_e[i]);
@@ -850,7 +929,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
         __syncthreads();  // everyone has read tile_zval
         RawTile rt;
         for (int k = wave; k < nt; k += nw) {
-            load_tile<T>(row, V, k, lane, rt);   // (what lies behind the row's end has no mask bit)
+            load_tile<T>(row_of(row, V), k, lane, rt);   // (what lies behind the row's end has no mask bit)
             const uint32_t word = tile_mask_word<T>(image, k, lane, V);
             const float mv = tile_valid_max<T>(rt, word, lane);
             if (lane == 0) sh.tile_ref[k] = mv;
@@ -862,7 +941,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
         __syncthreads();  // everyone has read the per-tile valid maxima
         if (Mv != -INFINITY) {
             for (int k = wave; k < nt; k += nw) {
-                load_tile<T>(row, V, k, lane, rt);
+                load_tile<T>(row_of(row, V), k, lane, rt);
                 const uint32_t word = tile_mask_word<T>(image, k, lane, V);
                 const float z = tile_valid_sum<T>(rt, word, lane, Mv, tp.c);
                 if (lane == 0) {
@@ -922,7 +1001,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
                 }
                 if (kt >= 0) {   // (no tile qualifies only when NaNs have poisoned the sums: then nothing is sampled)
                     RawTile lt;
-                    load_tile<T>(row, V, kt, lane, lt);
+                    load_tile<T>(row_of(row, V), kt, lane, lt);
                     const uint32_t word = tile_mask_word<T>(image, kt, lane, V);
                     id = locate_in_tile<T>(lt, word, kt, lane, sh.tile_ref[kt], target, tp.c);
                 }
@@ -1009,7 +1088,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
 template <typename T, bool SMALL, bool SPLIT>
 __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void sample_kernel(const T *__restrict__ logits, int64_t row_stride,
                                                                   const uint32_t *__restrict__ mask, int V,
-                                                                  int n_words, int list_max, int split_shift,
+                                                                  int n_words, int list_max, int shape,
                                                                   const float *__restrict__ uniforms,
                                                                   int32_t *__restrict__ ids,
                                                                   float *__restrict__ logZ_valid,
@@ -1017,10 +1096,12 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
                                                                   SplitScratch *scratch) {
     using SH = typename std::conditional<SMALL, RowSharedSmall, RowShared>::type;
     __shared__ SH sh;
-    // SPLIT: a row is shared by 1 << split_shift consecutive workgroups
+    // shape: wavefronts per workgroup << 8 (an argument: blockDim would be waited for), and for SPLIT, where a row is shared by
+    // a power of two of consecutive workgroups, that power
+    const int split_shift = shape & 255;
     const int b = SPLIT ? (int)(blockIdx.x >> split_shift) : (int)blockIdx.x;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-    const int nw = blockDim.x / WAVE;
+    const int nw = shape >> 8;
     Split sp;
     sp.parts = SPLIT ? 1 << split_shift : 1;
     sp.part = SPLIT ? (int)(blockIdx.x & (unsigned)(sp.parts - 1)) : 0;
@@ -1054,7 +1135,8 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
     auto bits_of = [](const Quad &q) { return (int)(__popc(q.w[0]) + __popc(q.w[1]) + __popc(q.w[2]) + __popc(q.w[3])); };
     const Quad q0 = load_quad(wave), q1 = load_quad(wave + nw);   // (a group past the row: all zero)
     RawTile first;
-    load_tile<T>(row, V, vwave, lane, first);   // in flight during the mask work
+    const Share share = share_of((V + TileGeom<T>::TILE - 1) / TileGeom<T>::TILE, vwave, sp.parts * nw);
+    load_tile<T>(row_of(row, V), share.first(), lane, first);   // in flight during the mask work
 
     // valid tokens per group of 64 quads (kept in the tile_cnt array: there are fewer groups than tiles)
     const int incl0 = wave_incl_scan(bits_of(q0));
@@ -1116,17 +1198,17 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_one_tile_kernel(co
                                                                               float *__restrict__ logZ_valid,
                                                                               float *__restrict__ logZ_all, Temper tp) {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int b = blockIdx.x * ONE_TILE_ROWS + threadIdx.x / WAVE;
+    const int b = blockIdx.x * ONE_TILE_ROWS + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     if (b >= B) return;   // uniform per wavefront
     const T *row = logits + (size_t)b * (size_t)row_stride;
     const uint32_t word = tile_mask_word<T>(mask + (size_t)b * (size_t)n_words, 0, lane, V);
     const float u = uniforms[b];
     RawTile rt;
-    load_tile<T>(row, V, 0, lane, rt);
+    load_tile<T>(row_of(row, V), 0, lane, rt);
     const int left = tokens_left<T>(V, 0, lane);
     float m, zall, zval;
-    if (V == TileGeom<T>::TILE) tile_stats<T, true, false>(rt, word, lane, left, tp, m, zall, zval);
-    else tile_stats<T, true, true>(rt, word, lane, left, tp, m, zall, zval);
+    if (V == TileGeom<T>::TILE) image_stats<T, false>(rt, word, lane, left, tp, m, zall, zval);
+    else image_stats<T, true>(rt, word, lane, left, tp, m, zall, zval);
     const float l2za = fast_log2(zall);
     int id = -1;
     float lzv = -INFINITY, ref = m;
@@ -1156,14 +1238,14 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     const T *__restrict__ logits, int64_t row_stride, int32_t stride, int B, int32_t *__restrict__ ids,
     float *__restrict__ logZ_valid, uint8_t *__restrict__ member, Temper tp, IndexView ix) {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int b = blockIdx.x * ONE_TILE_ROWS + threadIdx.x / WAVE;
+    const int b = blockIdx.x * ONE_TILE_ROWS + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     if (b >= B) return;   // uniform per wavefront
     const int V = ix.vocab, n_words = ix.n_words;
     const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);   // before the tile: answers come in order
     int t = lens[b];
     const float u = uniforms[b];
     RawTile rt;
-    load_tile<T>(logits + (size_t)b * (size_t)row_stride, V, 0, lane, rt);   // in flight during the walk
+    load_tile<T>(row_of(logits + (size_t)b * (size_t)row_stride, V), 0, lane, rt);   // in flight during the walk
     t = t < 0 ? 0 : (t > stride ? stride : t);
     const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
     uint32_t word = 0u;
@@ -1181,8 +1263,8 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     }
     const int left = tokens_left<T>(V, 0, lane);
     float m, zall, zval;
-    if (V == TileGeom<T>::TILE) tile_stats<T, true, false>(rt, word, lane, left, tp, m, zall, zval);
-    else tile_stats<T, true, true>(rt, word, lane, left, tp, m, zall, zval);
+    if (V == TileGeom<T>::TILE) image_stats<T, false>(rt, word, lane, left, tp, m, zall, zval);
+    else image_stats<T, true>(rt, word, lane, left, tp, m, zall, zval);
     const float l2za = fast_log2(zall);
     int id = -1;
     float lzv = -INFINITY, ref = m;
@@ -1257,9 +1339,9 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(int B,
 // step is sampled (only when no child of the current prefix is a member, i.e. the row is certain to
 // go on, so nothing is fetched in vain).
 template <typename T, bool LOOP, bool SPLIT, bool REG>
-__global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MAX_WAVES * WAVE) void decode_kernel(
+__global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MAX_WAVES * WAVE, LOOP && !REG ? 4 : 1) void decode_kernel(
     uint8_t *__restrict__ active, int32_t *__restrict__ lens, RowState *__restrict__ state, const float *__restrict__ uniforms,
-    float *__restrict__ logx, const T *__restrict__ logits, int flags, int split_shift, int32_t *__restrict__ prefixes,
+    float *__restrict__ logx, const T *__restrict__ logits, int flags, int shape, int32_t *__restrict__ prefixes,
     int32_t stride, int n_steps, int B, int64_t row_stride, int64_t step_stride, int32_t *__restrict__ ids,
     float *__restrict__ logZ_valid, SplitScratch *scratch, Temper tp, IndexView ix) {
     // flags bit 1 (ppv_decode_first_step): every row starts from the empty candidate here and now -- no flags, length
@@ -1273,11 +1355,12 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
     // (the loop kernel's fast steps alternate between two sets of tile statistics, see below)
     __shared__ RowShared shs[LOOP_REG ? 2 : 1];
     RowShared &sh = shs[0];
-    // SPLIT: a row is shared by 1 << split_shift consecutive workgroups (never in the loop kernel)
+    // shape: as for sample_kernel (the loop kernel never splits rows)
+    const int split_shift = shape & 255;
     static_assert(!(LOOP && SPLIT), "the loop kernel keeps a row in one workgroup");
     const int b = SPLIT ? (int)(blockIdx.x >> split_shift) : (int)blockIdx.x;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-    const int nw = blockDim.x / WAVE;
+    const int nw = LOOP ? blockDim.x / WAVE : shape >> 8;   // (the loop kernel's registers come out better with blockDim: 384 rows at V = 50k fp32 142 us against 149)
     Split sp;
     sp.parts = SPLIT ? 1 << split_shift : 1;
     sp.part = SPLIT ? (int)(blockIdx.x & (unsigned)(sp.parts - 1)) : 0;
@@ -1371,7 +1454,8 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         rl.have_gx = __builtin_amdgcn_readfirstlane(rl.have_gx ? 1 : 0) != 0 && wave == 0;
     }
     RawTile first;
-    load_tile<T>(row, V, vwave, lane, first);   // in flight during the index work
+    const Share share = share_of(nt, vwave, sp.parts * nw);
+    load_tile<T>(row_of(row, V), share.first(), lane, first);   // in flight during the index work
     t = t < 0 ? 0 : (t > stride ? stride : t);
     uint32_t only = PPV_NO_SLOT;   // without a cursor, the one child of a prefix of a single member: no node is looked at then
     if (!REG && !state) {  // no cursor: locate the prefix from the root (wave 0), then share it
@@ -1438,7 +1522,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         struct {
             __device__ void operator()() const {}
         } nothing;
-        stream_tiles<T, false, RowShared>(row, V, first, nullptr, sh, lane, wave, nw, tp, nothing, nullptr);
+        stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, sh, lane, share, tp, nothing, nullptr);
         __syncthreads();
         if (wave != 0) return;
         if (lane == 0) {
@@ -1585,22 +1669,20 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             } else {
                 const int k0 = wave_s - 1, k1 = wave_s - 1 + ntw;   // (a tile past the row reads as -inf and is not recorded)
                 RawTile A0, A1, B0, B1;
-                load_tile<T>(row, V, k0, lane, A0);
-                load_tile<T>(row, V, k1, lane, A1);
+                load_tile<T>(row_of(row, V), k0, lane, A0);
+                load_tile<T>(row_of(row, V), k1, lane, A1);
                 auto reduce = [&](const RawTile &tile, int k, RowShared &cur) __attribute__((always_inline)) {
                     const int left = tokens_left<T>(V, k, lane);
-                    float m, zall, zval;
+                    float m, zall;
                     // (one copy of the exact sums for both: 24 steps of 256 rows at V = 32k took 78.4 us with the checks inside and
                     // a copy for each, 75.8 like this)
-                    if ((k + 1) * G::TILE > V) tile_stats<T, false, true, false>(tile, 0u, lane, left, tp, m, zall, zval);
-                    else tile_stats<T, false, false, false>(tile, 0u, lane, left, tp, m, zall, zval);
+                    if ((k + 1) * G::TILE > V) list_stats<T, true>(tile, left, tp, m, zall);
+                    else list_stats<T, false>(tile, left, tp, m, zall);
                     if (k < nt) {
-                        if (!in_range(zall)) exact_stats<T>(tile, lane, left, tp, m, zall);
+                        if (!settled(m, zall)) exact_stats<T, true>(tile, left, tp, m, zall);
                         if (lane == 0) {
                             cur.tile_m[k] = m;
                             cur.tile_zall[k] = zall;
-                            cur.tile_zval[k] = zval;
-                            cur.tile_ref[k] = m;
                         }
                     }
                 };
@@ -1608,10 +1690,9 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
                 // Returns true while the chain goes on.
                 auto chain_step = [&](RawTile &c0, RawTile &c1, RawTile &n0, RawTile &n1) __attribute__((always_inline)) {
                     const bool more = row_goes_on();
-                    const T *nrow = more ? row + step_stride : row;   // no next row: one line of this one (same loads,
-                    const int Vn = more ? V : G::EPL;                 // all clamped to the row's first 16 bytes)
-                    load_tile<T>(nrow, Vn, k0, lane, n0);
-                    load_tile<T>(nrow, Vn, k1, lane, n1);
+                    const Row next = row_of(more ? row + step_stride : row, V);   // (no next row: the same loads of no tile)
+                    load_tile<T>(next, more ? k0 : NO_TILE, lane, n0);
+                    load_tile<T>(next, more ? k1 : NO_TILE, lane, n1);
                     reduce(c0, k0, shs[s & 1]);
                     reduce(c1, k1, shs[s & 1]);
                     __syncthreads();
@@ -1635,7 +1716,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             }
             if (finished) break;
             // a prefix of another kind: its step starts below from the row's first tile as the other steps know it
-            if (wave < nt) load_tile<T>(row, V, wave, lane, first);
+            if (wave < nt) load_tile<T>(row_of(row, V), share.first(), lane, first);
             if (wave_s != 0) u = uniforms[(size_t)s * (size_t)B + b];
             s -= 1;
             continue;
@@ -1707,7 +1788,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             struct {
                 __device__ void operator()() const {}
             } nothing;
-            stream_tiles<T, false, RowShared>(row, V, first, nullptr, cur, lane, wave, nw, tp, nothing, nullptr);
+            stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, cur, lane, share, tp, nothing, nullptr);
             __syncthreads();
             done = hand[s & 1].done != 0;
             const bool drew = hand[s & 1].drew != 0;
@@ -1727,7 +1808,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             }
             if (done || s + 1 == n_steps) break;
             row += step_stride;
-            if (wave < nt) load_tile<T>(row, V, wave, lane, first);
+            if (wave < nt) load_tile<T>(row_of(row, V), share.first(), lane, first);
             u = uniforms[(size_t)(s + 1) * (size_t)B + b];
             continue;
         }
@@ -1831,7 +1912,7 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             first = next_first;
             u = next_u;
         } else {
-            if (wave < nt) load_tile<T>(row, V, wave, lane, first);
+            if (wave < nt) load_tile<T>(row_of(row, V), share.first(), lane, first);
             u = uniforms[(size_t)(s + 1) * (size_t)B + b];
         }
     }
@@ -1943,7 +2024,7 @@ void launch_sample(bool small, dim3 grid, dim3 block, hipStream_t hs, const T *l
                    float *logZ_valid, float *logZ_all, Temper tp, int split_shift, SplitScratch *scratch) {
 #define PPV_LAUNCH_SAMPLE(SMALL, SPLIT)                                                                                  \
     hipLaunchKernelGGL((sample_kernel<T, SMALL, SPLIT>), grid, block, 0, hs, lg, row_stride, mask, V, n_words, \
-                       list_max, split_shift, uniforms, ids, logZ_valid, logZ_all, tp, scratch)
+                       list_max, split_shift | (int)(block.x / WAVE) << 8, uniforms, ids, logZ_valid, logZ_all, tp, scratch)
     if (split_shift) PPV_LAUNCH_SAMPLE(false, true);
     else if (small) PPV_LAUNCH_SAMPLE(true, false);
     else PPV_LAUNCH_SAMPLE(false, false);
@@ -1959,7 +2040,7 @@ void launch_decode_kernel(bool loop, dim3 grid, dim3 block, hipStream_t hs, cons
     const bool reg = rs && (!loop || B <= REG_MAX_ROWS);
 #define PPV_LAUNCH_DECODE(LOOP, SPLIT, REG)                                                                               \
     hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, active, lens, rs, uniforms, logx, lg, flags, \
-                       split_shift, prefixes, stride, n_steps, B, row_stride, step_stride, ids, logZ_valid, scratch, tp, view)
+                       split_shift | (int)(block.x / WAVE) << 8, prefixes, stride, n_steps, B, row_stride, step_stride, ids, logZ_valid, scratch, tp, view)
     if (split_shift && !loop) PPV_LAUNCH_DECODE(false, true, false);
     else if (loop && reg) PPV_LAUNCH_DECODE(true, false, true);
     else if (loop) PPV_LAUNCH_DECODE(true, false, false);
