@@ -26,8 +26,7 @@ namespace {
 
 constexpr int MASK_THREADS = 256;
 constexpr int MAX_WAVES = 16;                 // wavefronts per row (workgroup of up to 1024 threads)
-constexpr int LOOP_WAVES = 8;                 // the decode-loop kernel holds more in registers: at most 512 threads
-constexpr int CHAIN_WAVES = 10;               // ... or, with one wavefront that only draws tokens beside up to nine that stream, 640
+constexpr int LOOP_WAVES = 8;                 // the decode-loop kernel with the list in LDS
 constexpr int MAX_TILES = PPV_MAX_TILES;
 constexpr float LN2F = 0.693147180559945309417f;
 static_assert(PPV_MAX_VOCAB <= MAX_TILES * 1024, "tile bookkeeping too small");
@@ -592,7 +591,7 @@ __device__ __forceinline__ Share share_of(int nt, int wave_v, int nw) {
     else for (int x = up; x >= nw; x -= nw) s.n++;
     // (where a row has sixteen wavefronts it is nearly alone on its compute unit, and the numbers would only be waited for:
     // constrained_sample, 128 rows at V = 50,265 fp32, 11.0 us without, 11.8 with a turn)
-    if (nw <= 8 && s.n > 2) s.turn = (int)((__brev(blockIdx.x) >> 28) * (uint32_t)(s.n - 1) >> 4);
+    if ((nw <= 8 || (nw & (nw - 1)) != 0) && s.n > 2) s.turn = (int)((__brev(blockIdx.x) >> 28) * (uint32_t)(s.n - 1) >> 4);
     return s;
 }
 // Streams a row's tiles through one wavefront's share of the work.  Per tile the statistics go to LDS: under an image at once;
@@ -1339,7 +1338,7 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(int B,
 // step is sampled (only when no child of the current prefix is a member, i.e. the row is certain to
 // go on, so nothing is fetched in vain).
 template <typename T, bool LOOP, bool SPLIT, bool REG>
-__global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MAX_WAVES * WAVE, LOOP && !REG ? 4 : 1) void decode_kernel(
+__global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOOP ? 4 : 1) void decode_kernel(
     uint8_t *__restrict__ active, int32_t *__restrict__ lens, RowState *__restrict__ state, const float *__restrict__ uniforms,
     float *__restrict__ logx, const T *__restrict__ logits, int flags, int shape, int32_t *__restrict__ prefixes,
     int32_t stride, int n_steps, int B, int64_t row_stride, int64_t step_stride, int32_t *__restrict__ ids,
@@ -1571,18 +1570,16 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
         const uint32_t cb = st.cb, ce = st.ce, slot = st.slot;
         const int nchild = (int)(ce - cb);
         const int mode = nchild == 0 ? VALID_NONE : (slot != PPV_NO_SLOT ? VALID_IMAGE : VALID_LIST);
-        if (LOOP_REG && mode == VALID_LIST && nchild == 1 && st.flags == 1u && nw >= 2 &&
-            nt <= 2 * (nw - 1)) {
+        if (LOOP_REG && mode == VALID_LIST && nchild == 1 && st.flags == 1u && (nw >= 8 || nt <= 2 * (nw - 1))) {
             // ---- A chain of prefixes with one child each, the cursor knowing the child (nearly all of a long
             // sequence below its first levels).  Wavefront 0 only draws tokens: each step it takes the listed
             // logit that it asked for a step earlier, advances the cursor, asks for the next step's logit and
-            // look-ahead, and after the step's barrier adds up the row's totals.  The other wavefronts only stream:
-            // two tiles each, the next row's tiles requested before this row's are reduced, in two sets of registers
-            // that swap roles from step to step, so that there is no copy of, no condition on and no wait for a
-            // tile that is still on its way.  One barrier per step; statistics and hand-over alternate between two
-            // buffers as in the fast step below.  The chain ends with the row (its last step asks for 16 bytes of
-            // its own row instead of a next row), or at a prefix that is not of this kind, which the code below
-            // takes from there.
+            // look-ahead, and after the step's barrier adds up the row's totals.  The other wavefronts only stream, over
+            // the steps' ends: the next row's first tiles are requested while this row's last ones are reduced, without a
+            // copy of, a condition on or a wait for a tile that is still on its way.  One barrier per step; statistics and
+            // hand-over alternate between two buffers as in the fast step below.  The chain ends with the row, or at a
+            // prefix that is not of this kind, which the code below takes from there.  (With fewer than eight wavefronts
+            // one that only draws is missed by the others: those rows take the fast step.)
             const int ntw = nw - 1;
             const int wave_s = __builtin_amdgcn_readfirstlane(wave);
             auto next_in_chain = [&](const RowState &c) {
@@ -1667,34 +1664,8 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
                     if (!chain_on) break;
                 }
             } else {
-                const int k0 = wave_s - 1, k1 = wave_s - 1 + ntw;   // (a tile past the row reads as -inf and is not recorded)
-                RawTile A0, A1, B0, B1;
-                load_tile<T>(row_of(row, V), k0, lane, A0);
-                load_tile<T>(row_of(row, V), k1, lane, A1);
-                auto reduce = [&](const RawTile &tile, int k, RowShared &cur) __attribute__((always_inline)) {
-                    const int left = tokens_left<T>(V, k, lane);
-                    float m, zall;
-                    // (one copy of the exact sums for both: 24 steps of 256 rows at V = 32k took 78.4 us with the checks inside and
-                    // a copy for each, 75.8 like this)
-                    if ((k + 1) * G::TILE > V) list_stats<T, true>(tile, left, tp, m, zall);
-                    else list_stats<T, false>(tile, left, tp, m, zall);
-                    if (k < nt) {
-                        if (!settled(m, zall)) exact_stats<T, true>(tile, left, tp, m, zall);
-                        if (lane == 0) {
-                            cur.tile_m[k] = m;
-                            cur.tile_zall[k] = zall;
-                        }
-                    }
-                };
-                // one step on the tiles (c0, c1), the next row's tiles requested into (n0, n1) first.
-                // Returns true while the chain goes on.
-                auto chain_step = [&](RawTile &c0, RawTile &c1, RawTile &n0, RawTile &n1) __attribute__((always_inline)) {
-                    const bool more = row_goes_on();
-                    const Row next = row_of(more ? row + step_stride : row, V);   // (no next row: the same loads of no tile)
-                    load_tile<T>(next, more ? k0 : NO_TILE, lane, n0);
-                    load_tile<T>(next, more ? k1 : NO_TILE, lane, n1);
-                    reduce(c0, k0, shs[s & 1]);
-                    reduce(c1, k1, shs[s & 1]);
+                // after the step's barrier; true while the chain goes on
+                auto step_over = [&](bool more) __attribute__((always_inline)) {
                     __syncthreads();
                     const bool ends = hand[s & 1].done != 0;
                     const bool drew = hand[s & 1].drew != 0;
@@ -1711,8 +1682,44 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
                     row += step_stride;
                     return drew && more && next_in_chain(st);
                 };
-                while (chain_step(A0, A1, B0, B1) && chain_step(B0, B1, A0, A1)) {
-                }
+                auto reduce = [&](const RawTile &tile, int k, RowShared &cur) __attribute__((always_inline)) {
+                    if (k >= nt) return;   // (uniform)
+                    const int left = tokens_left<T>(V, k, lane);
+                    float m, zall;
+                    // (one copy of the exact sums for both: 24 steps of 256 rows at V = 32k took 78.4 us with the checks inside and
+                    // a copy for each, 75.8 like this)
+                    if ((k + 1) * G::TILE > V) list_stats<T, true>(tile, left, tp, m, zall);
+                    else list_stats<T, false>(tile, left, tp, m, zall);
+                    if (!settled(m, zall)) exact_stats<T, true>(tile, left, tp, m, zall);
+                    if (lane == 0) {
+                        cur.tile_m[k] = m;
+                        cur.tile_zall[k] = zall;
+                    }
+                };
+                // Two tiles take turns as in stream_tiles, over the steps' ends: behind a row's last two tiles come the next row's
+                // first two, asked for while these are reduced.  (No next row: the same loads of no tile.)
+                const Share share = share_of(nt, wave_s - 1, ntw);
+                const int n = share.n;
+                auto tile = [&](int i) { return i < n ? share.at(i) : NO_TILE; };
+                RawTile X, Y;
+                load_tile<T>(row_of(row, V), tile(0), lane, X);
+                load_tile<T>(row_of(row, V), tile(1), lane, Y);
+                bool more;
+                do {
+                    more = row_goes_on();
+                    const Row cur = row_of(row, V), next = row_of(more ? row + step_stride : row, more ? V : 0);
+                    int i = 0;
+                    for (; i + 2 < n; i += 2) {
+                        reduce(X, tile(i), shs[s & 1]);
+                        load_tile<T>(cur, tile(i + 2), lane, X);
+                        reduce(Y, tile(i + 1), shs[s & 1]);
+                        load_tile<T>(cur, tile(i + 3), lane, Y);
+                    }
+                    reduce(X, tile(i), shs[s & 1]);
+                    load_tile<T>(next, tile(0), lane, X);
+                    reduce(Y, tile(i + 1), shs[s & 1]);
+                    load_tile<T>(next, tile(1), lane, Y);
+                } while (step_over(more));
             }
             if (finished) break;
             // a prefix of another kind: its step starts below from the row's first tile as the other steps know it
@@ -1834,7 +1841,8 @@ __global__ __launch_bounds__(LOOP ? (REG ? CHAIN_WAVES : LOOP_WAVES) * WAVE : MA
             if (LOOP) member_child = __syncthreads_or(member_child);
             else __syncthreads();
         }
-        const bool more = LOOP && s + 1 < n_steps && t + 1 < stride && mode != VALID_NONE && !member_child;
+        // (REG: a third tile in registers here spills others there: 1,000 rows at V = 32k 145 us, 134 without)
+        const bool more = LOOP && !REG && s + 1 < n_steps && t + 1 < stride && mode != VALID_NONE && !member_child;
         RawTile next_first;
         const T *next_row = more ? row + step_stride : nullptr;
         float next_u = 0.f;
@@ -2040,7 +2048,8 @@ void launch_decode_kernel(bool loop, dim3 grid, dim3 block, hipStream_t hs, cons
     const bool reg = rs && (!loop || B <= REG_MAX_ROWS);
 #define PPV_LAUNCH_DECODE(LOOP, SPLIT, REG)                                                                               \
     hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, active, lens, rs, uniforms, logx, lg, flags, \
-                       split_shift | (int)(block.x / WAVE) << 8, prefixes, stride, n_steps, B, row_stride, step_stride, ids, logZ_valid, scratch, tp, view)
+                       split_shift | (int)(block.x / WAVE) << 8, prefixes, stride, n_steps, B, row_stride, step_stride, ids,  \
+                       logZ_valid, scratch, tp, view)
     if (split_shift && !loop) PPV_LAUNCH_DECODE(false, true, false);
     else if (loop && reg) PPV_LAUNCH_DECODE(true, false, true);
     else if (loop) PPV_LAUNCH_DECODE(true, false, false);
@@ -2200,19 +2209,34 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
     SplitScratch *scratch = nullptr;
     const int parts = (loop || fresh) ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch);
     int nw = waves_for(ix->view.vocab, dt, B, parts, !loop && state != nullptr);
-    if (loop && nw > LOOP_WAVES) nw = LOOP_WAVES;
-    if (loop && B > 512 && nw > 4 && ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0) nw = 4;   // (its rows stay: see below)
-    // The loop kernel in a large batch: a workgroup stays with its row for every step, so what hides one row's
-    // dependent phases (cursor, barrier, draw) is other rows on the same compute unit, and two wavefronts per row
-    // put twice as many there as four (C3 replicas, M prefix-steps/s with 1 / 2 / 4 / 8 wavefronts per row:
-    // 4,096 rows: 72 / 81 / 66 / 39; 16,384 rows: 95 / 98 / 77 / 42 -- 6.3 TB/s; the per-step kernel is best with four).
-    if (loop && B > REG_MAX_ROWS && nw > 2 && ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0) nw = 2;
-    {   // the loop kernel with the list in registers: one wavefront draws, the others stream two tiles each
-        const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
-        const int nt = (ix->view.vocab + tile - 1) / tile;
-        if (loop && state && B <= REG_MAX_ROWS && nt >= 2 && (nt + 1) / 2 + 1 <= CHAIN_WAVES &&
-            ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0)
-            nw = (nt + 1) / 2 + 1;
+    const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
+    const int nt = (ix->view.vocab + tile - 1) / tile;
+    if (loop) {
+        const bool reg = state && B <= REG_MAX_ROWS;
+        const int most = reg ? MAX_WAVES : LOOP_WAVES;
+        if (nw > most) nw = most;
+        // A workgroup of the loop kernel stays with its row for every step, and a row that has no place on the chip waits for
+        // another to end.  128 registers are sixteen wavefronts to a compute unit: a row's own up to 256 rows, half of them to
+        // 512 and for rows of 48 tiles or more, a quarter to 1,024.  us per loop with 16 / 8 / 4: 200 rows, V = 50k fp32
+        // 90 / 89 / 131, V = 40k bf16 54 / 59 / 80; 512 rows, V = 16k fp32 80 / 66 / 69, V = 50k bf16 128 / 119 / 132; 1,000 rows,
+        // V = 50k fp32 354 / 345 / 375.  (With 168 registers and up to ten wavefronts, one row to a compute unit: 384 rows,
+        // V = 50k fp32 142, now 123; 512 rows, V = 32k bf16 98 and 77; 1,000 rows 176 and 134.)  In larger batches two
+        // wavefronts, and the list in LDS: what hides a row's dependent phases is other rows on the same compute unit (C3
+        // replicas, M prefix-steps/s with 1 / 2 / 4 / 8 wavefronts per row:
+        // 4,096 rows: 72 / 81 / 66 / 39; 16,384 rows: 95 / 98 / 77 / 42 -- 6.3 TB/s; the per-step kernel is best with four).
+        if (ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0) {
+            if (reg) {
+                nw = B <= 256 ? 16 : (B <= 512 || nt >= 48 ? 8 : 4);
+                if (nw > nt + 1) nw = nt + 1;   // one draws (see decode_kernel)
+                // (16 to 18 tiles on fifteen wavefronts: a few have two tiles and the rest wait for them.  200 rows, V = 16k fp32
+                // 42.7 us, and 38.5 with nine wavefronts; with 20 tiles eleven are slower than sixteen, 54.3 against 51.8)
+                if (B <= 256 && nt > 15 && nt <= 18) nw = (nt + 1) / 2 + 1;
+            } else if (B > REG_MAX_ROWS && nw > 2) {
+                nw = 2;
+            } else if (B > 512 && nw > 4) {
+                nw = 4;
+            }
+        }
     }
     const dim3 grid((unsigned)B * (unsigned)parts), block(nw * WAVE);
     RowState *rs = (RowState *)state;
