@@ -136,6 +136,36 @@ def test_split_rows_in_the_decode_step(use_state):
             assert np.array_equal(a, b), k
 
 
+@pytest.mark.parametrize("V,dtype", [(20_000, torch.float32), (50_001, torch.bfloat16)])
+def test_split_rows_in_the_first_step(V, dtype):
+    """Rows that start from the empty candidate, under the root's image or its list, in every split: bit for bit the
+    unsplit step, whatever the buffers held."""
+    rng = np.random.default_rng(V)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    B, L = 9, 3
+    logits = torch.randn((B, -(-V // 8) * 8), generator=g, device=DEV).mul_(2).to(dtype)[:, :V]
+    un = torch.rand(B, generator=g, device=DEV)
+    for n, firsts in ((4_000, V), (300, 20)):                      # an image, a list
+        S = rng.integers(0, V, (n, L)).astype(np.int32)
+        S[:, 0] = rng.integers(0, firsts, n)
+        index = ppv.ppv_build_index(S.reshape(-1), np.arange(n + 1, dtype=np.int64) * L, V)
+        base = None
+        for k in SPLITS:
+            P = torch.full((B, L), W.PAD_TOKEN, dtype=torch.int32, device=DEV)
+            lens, act = torch.full((B,), 77, dtype=torch.int32, device=DEV), torch.zeros(B, dtype=torch.uint8, device=DEV)
+            state = torch.full((B, ppv.PPV_STATE_WORDS), -3, dtype=torch.int32, device=DEV)
+            logx, lz = torch.full((B,), 5.0, device=DEV), torch.full((B,), 5.0, device=DEV)
+            ids = torch.full((B,), -5, dtype=torch.int32, device=DEV)
+            with tuning(ppv.PPV_TUNE_ROW_SPLIT, k):
+                ppv.ppv_decode_first_step(index, P, lens, act, logits, un, ids, lz, logx, state=state)
+            torch.cuda.synchronize()
+            got = [t.cpu().numpy() for t in (P, lens, act, ids, lz, logx, state[:, :4].contiguous())]
+            base = base or got
+            assert (got[3] >= 0).all()
+            for a, b in zip(got, base):
+                assert np.array_equal(a, b), k
+
+
 def test_split_rows_under_graph_capture():
     """A stream that is being captured cannot allocate its scratch area: without one the rows are simply not
     split; with one (the stream made a call before the capture) they are.  Replays equal the eager result."""
