@@ -40,7 +40,7 @@ __device__ __forceinline__ float fast_log2(float y) { return __builtin_amdgcn_lo
 struct Temper {
     float c;
     float inv;
-    float guard;   // how far above an image tile's reference a logit may lie (REF_GUARD * T, see tile_stats)
+    float guard;   // how far above an image tile's reference a logit may lie (REF_GUARD * T, see image_stats)
 };
 
 __device__ __forceinline__ float exp_scale(float d, float c) {
@@ -474,7 +474,7 @@ __device__ __forceinline__ int locate_in_tile(const RawTile &rt, uint32_t tile_w
     double before = 0.0;  // valid weight of the loads already passed
     int last_valid = -1;
     for (int j = 0; j < 4; j++) {
-        __builtin_amdgcn_sched_barrier(0);   // (one group at a time, as in tile_sums)
+        __builtin_amdgcn_sched_barrier(0);   // (one group at a time, as in image_stats)
         float x[G::EPL], e[G::EPL];
         unpack_fresh<T>(rt.r[j], x);
         const uint32_t bits = lane_bits<T>(tile_word, j, lane);
