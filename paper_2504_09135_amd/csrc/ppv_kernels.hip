@@ -2222,8 +2222,8 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
         const int most = reg ? MAX_WAVES : LOOP_WAVES;
         if (nw > most) nw = most;
         // A workgroup of the loop kernel stays with its row for every step, and a row that has no place on the chip waits for
-        // another to end.  128 registers are sixteen wavefronts to a compute unit: a row's own up to 256 rows, half of them to
-        // 512 and for rows of 48 tiles or more, a quarter to 1,024.  us per loop with 16 / 8 / 4: 200 rows, V = 50k fp32
+        // another to end.  128 registers are sixteen wavefronts to a compute unit: a row's own up to 256 rows (long rows: up to 320
+        // or always, see below), half of them to 512 and for rows of 48 tiles or more, a quarter to 1,024.  us per loop with 16 / 8 / 4: 200 rows, V = 50k fp32
         // 90 / 89 / 131, V = 40k bf16 54 / 59 / 80; 512 rows, V = 16k fp32 80 / 66 / 69, V = 50k bf16 128 / 119 / 132; 1,000 rows,
         // V = 50k fp32 354 / 345 / 375.  (With 168 registers and up to ten wavefronts, one row to a compute unit: 384 rows,
         // V = 50k fp32 142, now 123; 512 rows, V = 32k bf16 98 and 77; 1,000 rows 176 and 134.)  In larger batches two
@@ -2232,7 +2232,11 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
         // 4,096 rows: 72 / 81 / 66 / 39; 16,384 rows: 95 / 98 / 77 / 42 -- 6.3 TB/s; the per-step kernel is best with four).
         if (ppv_tuning(PPV_TUNE_WAVES_PER_ROW) == 0) {
             if (reg) {
-                nw = B <= 256 ? 16 : (B <= 512 || nt >= 48 ? 8 : 4);
+                // (a few rows above 256, or very long ones: a place to itself is worth more than a place at once.  us per loop with
+                // 16 / 8: V = 240k bf16, 264 rows 266 / 308, 512 rows 355 / 370, 600 rows 412 / 425; V = 130k bf16, 264 rows 127 / 158; V = 76k
+                // fp32, 320 rows 149 / 168, 384 rows 180 / 174; V = 50k fp32, 264 rows 86 / 102, 512 rows 149 / 141)
+                const bool alone = B <= 256 || (B <= 320 && nt >= 48) || nt >= 96;
+                nw = alone ? 16 : (B <= 512 || nt >= 48 ? 8 : 4);
                 if (nw > nt + 1) nw = nt + 1;   // one draws (see decode_kernel)
                 // (16 to 18 tiles on fifteen wavefronts: a few have two tiles and the rest wait for them.  200 rows, V = 16k fp32
                 // 42.7 us, and 38.5 with nine wavefronts; with 20 tiles eleven are slower than sixteen, 54.3 against 51.8)

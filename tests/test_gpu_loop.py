@@ -65,9 +65,9 @@ def test_loop_gives_the_bits_of_its_steps(tiles, B, dtype):
     check(tiles * tile - 5, B, dtype, 5)
 
 
-@pytest.mark.parametrize("B", [40, 520])
-def test_long_rows(B):
-    check(48 * 1024 + 1, B, torch.float32, 4)
+@pytest.mark.parametrize("tiles, B", [(48, 40), (48, 320), (48, 321), (48, 520), (95, 257), (95, 321), (97, 520)])
+def test_long_rows(tiles, B):
+    check(tiles * 1024 + 1, B, torch.float32, 4)
 
 
 @pytest.mark.parametrize("waves", [1, 2, 8])
