@@ -302,6 +302,31 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
     return (w >> ((lane % G::LANES_PER_WORD) * G::EPL)) & ((1u << G::EPL) - 1u);
 }
 
+// References far from 0.  With |m*c| of 2^31 and more the rounding of m*c is beyond the range of exp2, and a product with a
+// stand-in for -inf (the type's lowest number, -1e30) is outside fp32.  An exact maximum is therefore taken no lower than
+// m*c = -FAR (far tokens weigh nothing against that).  Where a whole row, or its largest token, lies beyond that on either side, the
+// differences are taken first: x - m is exact for an x of m's sign, up to twice and down to half its size, and the others weigh nothing.
+// (Checked per row and per exact maximum, not per token: 0 to 1 % of a call.  The difference first for every token of these
+// tiles took filtered rows of V = 32k, 2,048 of them, from 22.8 us to 25.0, and one argument more for the bound took a decoding
+// step of 256 rows from 6.13 to 6.27: a register that the loads ahead of the first tile then waited for.)
+constexpr float FAR = 134217728.f;   // 2^27: below it the rounding of m*c is at most four units of the exponent
+__device__ __forceinline__ bool far_off(float m, float c) { return fabsf(m * c) >= FAR; }
+__device__ __forceinline__ float not_below(float ref, float c) {   // (ref: uniform; -inf, an empty tile, stays that)
+    if (__builtin_expect(ref * c <= -FAR, 0) && ref != -INFINITY) {
+        asm volatile("" : "+s"(c));   // (computed here: as an argument of the kernel, or ahead of a loop, it costs the usual row a register)
+        ref = -FAR * __builtin_amdgcn_rcpf(c);
+    }
+    return ref;
+}
+// what to take from the tokens, and what to weigh them against then
+struct Shifted {
+    float sub, m;
+};
+__device__ __forceinline__ Shifted shifted(float m, float c) {
+    const bool far = far_off(m, c);
+    return {far ? m : 0.f, far ? 0.f : m};
+}
+
 // Statistics of one tile: a reference m, sum_all = sum exp(x - m), and (image) sum_val over valid tokens.
 // Any reference gives the same sums up to rounding as long as they stay inside fp32's range, so neither the maximum nor
 // the reduction over the wavefront it would need are computed.
@@ -314,7 +339,7 @@ template <typename T> __device__ __forceinline__ uint32_t lane_bits(uint32_t til
 //          largest error of logZ_valid went from 2e-6 to 1.1e-5 in rows with a token 55 T above the rest.)
 //   image  (image_stats) the sums over valid tokens set the sampling threshold, and with tens of thousands of valid tokens
 //          another rounding of them moves a draw now and then: m is the largest of lane 0's own tokens, as long as no token of
-//          the tile lies more than REF_GUARD * T above it, else the exact maximum.
+//          the tile lies more than REF_GUARD * T above it and it is no stand-in either, else the exact maximum.
 // Either way m depends on the row's values alone, not on how the row is split over wavefronts.  m = -inf: an empty tile.
 //
 // exp(x - m) = 2^(x*c - m*c).  m*c is rounded once (mc); its residual is a factor of the tile's sums (rounding_of).  Without
@@ -377,7 +402,7 @@ template <typename T, bool PAD> __device__ __forceinline__ float lane_max(const 
 // the same relative to the exact maximum, for tiles that are not settled by list_stats
 template <typename T, bool PAD> __device__ __forceinline__ void exact_stats(const RawTile &rt, int left, const Temper &tp, float &m_out, float &zall_out) {
     using G = TileGeom<T>;
-    const float ref = wave_max(lane_max<T, PAD>(rt, left)), mc = ref * tp.c;
+    const float ref = not_below(wave_max(lane_max<T, PAD>(rt, left)), tp.c), mc = ref * tp.c;
     float zall = 0.f;
     if (ref != -INFINITY) {   // (uniform)
 #pragma unroll
@@ -398,7 +423,7 @@ __device__ __forceinline__ void image_stats(const RawTile &rt, uint32_t tile_wor
     using G = TileGeom<T>;
     const float mx = lane_max<T, PAD>(rt, left);
     float ref = uniform(mx);
-    if (ref == -INFINITY || __ballot(mx > ref + tp.guard) != 0ull) ref = wave_max(mx);   // (uniform)
+    if (too_low(ref) || __ballot(mx > ref + tp.guard) != 0ull) ref = not_below(wave_max(mx), tp.c);   // (uniform)
     float zall = 0.f, zval = 0.f;
     if (ref != -INFINITY) {   // (uniform)
         const float mc = ref * tp.c;
@@ -425,6 +450,35 @@ __device__ __forceinline__ void image_stats(const RawTile &rt, uint32_t tile_wor
     zval_out = zval;
 }
 
+// A row too far from 0 for its tiles' sums shows in their total, which is then 0, infinite or NaN: a scalar compare.
+__device__ __forceinline__ bool no_sum(float za) { return __float_as_uint(za) - 1u >= __float_as_uint(INFINITY) - 1u; }
+// A far row's largest token, and the sum over all tokens relative to it: by one wavefront, from memory, in as little code as it takes.
+template <typename T> __device__ __forceinline__ void far_row(const T *row, int V, int lane, const Temper &tp, float &M, float &za) {
+    constexpr int EPL = Elem<T>::EPL;
+    const Row all = row_of(row, V);
+    float top = -INFINITY, z = 0.f;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; pass++) {
+#pragma unroll 1
+        for (int at = lane * EPL; at < V; at += WAVE * EPL) {
+            float x[EPL];
+            Elem<T>::unpack(__builtin_amdgcn_raw_buffer_load_b128(all.buf, (uint32_t)at * (uint32_t)sizeof(T), 0, 0), x);
+            float m = -INFINITY, e = 0.f;
+#pragma unroll
+            for (int k = 0; k < EPL; k++) {
+                const float v = at + k < V ? x[k] : -INFINITY;
+                m = fmaxf(m, v);
+                e += fast_exp2((v - top) * tp.c);
+            }
+            if (pass == 0) top = fmaxf(top, m);
+            else z += e;
+        }
+        if (pass == 0) top = wave_max(top);
+    }
+    M = top;
+    za = wave_sum(z);
+}
+
 // Rare path of the image mode (the valid tokens lie far below the row maximum, so sums relative
 // to the tile maxima would lose them): maximum over the valid tokens of a tile ...
 template <typename T>
@@ -444,10 +498,10 @@ __device__ __forceinline__ float tile_valid_max(const RawTile &rt, uint32_t tile
 }
 // ... and the valid sum of a tile relative to a given reference (finite)
 template <typename T>
-__device__ __forceinline__ float tile_valid_sum(const RawTile &rt, uint32_t tile_word, int lane, float ref, float c) {
+__device__ __forceinline__ float tile_valid_sum(const RawTile &rt, uint32_t tile_word, int lane, const Shifted &ref, float c) {
     using G = TileGeom<T>;
-    const float mc = ref * c;
-    const float fix = fast_exp2(-fmaf(ref, c, -mc));
+    const float mc = ref.m * c;
+    const float fix = fast_exp2(-fmaf(ref.m, c, -mc));
     float z = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
@@ -456,7 +510,7 @@ __device__ __forceinline__ float tile_valid_sum(const RawTile &rt, uint32_t tile
         const uint32_t bits = lane_bits<T>(tile_word, j, lane);
 #pragma unroll
         for (int k = 0; k < G::EPL; k++)
-            if ((bits >> k) & 1u) z += fast_exp2(fmaf(x[k], c, -mc));
+            if ((bits >> k) & 1u) z += fast_exp2(fmaf(x[k] - ref.sub, c, -mc));
     }
     return wave_sum(z) * fix;
 }
@@ -466,11 +520,11 @@ __device__ __forceinline__ float tile_valid_sum(const RawTile &rt, uint32_t tile
 // token with positive weight.  When rounding lets no token exceed the target, the last valid token
 // with positive weight is returned.
 template <typename T>
-__device__ __forceinline__ int locate_in_tile(const RawTile &rt, uint32_t tile_word, int tile, int lane, float m,
+__device__ __forceinline__ int locate_in_tile(const RawTile &rt, uint32_t tile_word, int tile, int lane, const Shifted &ref,
                                      double target, float tc) {
     using G = TileGeom<T>;
-    const float mc = m * tc;
-    const float fix = fast_exp2(-fmaf(m, tc, -mc));
+    const float mc = ref.m * tc;
+    const float fix = fast_exp2(-fmaf(ref.m, tc, -mc));
     double before = 0.0;  // valid weight of the loads already passed
     int last_valid = -1;
     for (int j = 0; j < 4; j++) {
@@ -482,7 +536,7 @@ __device__ __forceinline__ int locate_in_tile(const RawTile &rt, uint32_t tile_w
         int my_last = -1;
 #pragma unroll
         for (int k = 0; k < G::EPL; k++) {
-            e[k] = ((bits >> k) & 1u) ? fast_exp2(fmaf(x[k], tc, -mc)) * fix : 0.f;
+            e[k] = ((bits >> k) & 1u) ? fast_exp2(fmaf(x[k] - ref.sub, tc, -mc)) * fix : 0.f;
             grp += e[k];
             if (e[k] > 0.f) my_last = k;
         }
@@ -688,9 +742,10 @@ __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
 // list_stats): the largest tile reference M, the sum over all tokens relative
 // to it and (image rows) the sum over valid tokens.  Called by a whole wavefront; results are uniform.  The sum over
 // all tokens only ever enters a logarithm, so it is added up in fp32 (a tree over at most 256 positive terms: a few
-// 1e-7 relative); the valid sum sets the sampling threshold and is added up in fp64.
+// 1e-7 relative); the valid sum sets the sampling threshold and is added up in fp64.  A far row (see far_off) is summed again
+// from memory, and its valid sum left at 0: the caller then sums the valid tokens again, relative to their own maximum.
 template <typename SH>
-__device__ __forceinline__ void combine_tiles(const SH &sh, int nt, int lane, const Temper &tp, bool image, float &M, float &za,
+__device__ __forceinline__ void add_tiles(const SH &sh, int nt, int lane, const Temper &tp, bool image, float &M, float &za,
                                      double &zv) {
     if (nt <= WAVE) {   // (uniform) one tile per lane at most: both words in one round of LDS reads, no loops; the
                         // same operations in the same order as below, so the same bits
@@ -727,6 +782,16 @@ __device__ __forceinline__ void combine_tiles(const SH &sh, int nt, int lane, co
     za = wave_sum(za);
     if (image) zv = wave_sum(zv);
 }
+template <typename T, typename SH>
+__device__ __forceinline__ void combine_tiles(const SH &sh, const T *row, int V, int nt, int lane, const Temper &tp, bool image, float &M,
+                                     float &za, double &zv) {
+    add_tiles(sh, nt, lane, tp, image, M, za, zv);
+    if (__builtin_expect(no_sum(za), 0)) {   // (uniform)
+        if (M == -INFINITY) return;
+        far_row<T>(row, V, lane, tp, M, za);
+        zv = 0.0;
+    }
+}
 
 // A list of at most 63 valid tokens that one wavefront holds in registers, entry i in lane i (the per-step decode
 // kernel): the sums over the list and the sample, with the arithmetic of the list path of row_sample for a list of
@@ -756,7 +821,8 @@ __device__ __forceinline__ ListPick reg_list_pick(float gx, uint32_t tokw, int n
         pk.Mv = m;
         if (m == -INFINITY) return pk;
         const float mc = m * tp.c;
-        const float e = fast_exp2(fmaf(m, tp.c, -mc)) * fast_exp2(-fmaf(m, tp.c, -mc));
+        const float product = fast_exp2(fmaf(m, tp.c, -mc)) * fast_exp2(-fmaf(m, tp.c, -mc));
+        const float e = far_off(m, tp.c) ? fast_exp2(m - m) : product;
         pk.zvl = (double)e;
         if (e > 0.f) {
             pk.pos = 0;
@@ -767,8 +833,13 @@ __device__ __forceinline__ ListPick reg_list_pick(float gx, uint32_t tokw, int n
     const float m = wave_max(gx);
     pk.Mv = m;
     if (m == -INFINITY) return pk;
-    const float mc = m * tp.c;
-    const float fix = fast_exp2(-fmaf(m, tp.c, -mc));
+    float near = m;
+    if (__builtin_expect(far_off(m, tp.c), 0)) {   // (uniform)
+        gx -= m;
+        near = 0.f;
+    }
+    const float mc = near * tp.c;
+    const float fix = fast_exp2(-fmaf(near, tp.c, -mc));
     float e = fast_exp2(fmaf(gx, tp.c, -mc)) * fix;   // gx = -inf gives 0
     const double zvl = (double)wave_sum(e);
     pk.zvl = zvl;
@@ -849,9 +920,10 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
             const float m = wave_max(x);
             float e = 0.f;
             if (m != -INFINITY) {
-                const float mc = m * tp.c;
-                const float fix = fast_exp2(-fmaf(m, tp.c, -mc));
-                e = fast_exp2(fmaf(x, tp.c, -mc)) * fix;   // x = -inf gives 0
+                const Shifted ref = shifted(m, tp.c);
+                const float mc = ref.m * tp.c;
+                const float fix = fast_exp2(-fmaf(ref.m, tp.c, -mc));
+                e = fast_exp2(fmaf(x - ref.sub, tp.c, -mc)) * fix;   // x = -inf gives 0
             }
             if (i < n_list) {
                 sh.list_e[i] = e;
@@ -920,7 +992,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
     // ---- combine (every wave computes the same row totals from LDS; cheap, and saves a broadcast)
     float M, za;
     double zv;
-    combine_tiles(sh, nt, lane, tp, mode == VALID_IMAGE, M, za, zv);
+    combine_tiles<T>(sh, row, V, nt, lane, tp, mode == VALID_IMAGE, M, za, zv);
     float R = M;  // reference of the valid sums of the image path
 
     // ---- image path, rare case: the valid mass is below 2^-18 of the row's largest term, so sums
@@ -944,7 +1016,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
             for (int k = wave; k < nt; k += nw) {
                 load_tile<T>(row_of(row, V), k, lane, rt);
                 const uint32_t word = tile_mask_word<T>(image, k, lane, V);
-                const float z = tile_valid_sum<T>(rt, word, lane, Mv, tp.c);
+                const float z = tile_valid_sum<T>(rt, word, lane, shifted(Mv, tp.c), tp.c);
                 if (lane == 0) {
                     sh.tile_zval[k] = z;
                     sh.tile_ref[k] = Mv;
@@ -1004,7 +1076,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
                     RawTile lt;
                     load_tile<T>(row_of(row, V), kt, lane, lt);
                     const uint32_t word = tile_mask_word<T>(image, kt, lane, V);
-                    id = locate_in_tile<T>(lt, word, kt, lane, sh.tile_ref[kt], target, tp.c);
+                    id = locate_in_tile<T>(lt, word, kt, lane, shifted(sh.tile_ref[kt], tp.c), target, tp.c);
                 }
             }
         } else if (mode == VALID_LIST) {
@@ -1031,7 +1103,8 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
                 } else {
                     double w = 0.0, sc = 0.0;
                     if (lane < ns && sh.slice_m[lane] != -INFINITY) {
-                        sc = (double)exp_scale(sh.slice_m[lane] - Mv, tp.c);
+                        const float d = sh.slice_m[lane] - Mv;
+                        sc = d * tp.c < -1000.f ? 0.0 : (double)exp_scale(d, tp.c);   // (a far difference has no product)
                         w = (double)sh.slice_z[lane] * sc;
                     }
                     const double incl = wave_incl_scan(w);
@@ -1210,17 +1283,21 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_one_tile_kernel(co
     float m, zall, zval;
     if (V == TileGeom<T>::TILE) image_stats<T, false>(rt, word, lane, left, tp, m, zall, zval);
     else image_stats<T, true>(rt, word, lane, left, tp, m, zall, zval);
+    if (__builtin_expect(no_sum(uniform(zall)), 0) && m != -INFINITY) {   // (uniform)
+        far_row<T>(row, V, lane, tp, m, zall);
+        zval = 0.f;
+    }
     const float l2za = fast_log2(zall);
     int id = -1;
     float lzv = -INFINITY, ref = m;
     if (__ballot(word != 0u)) {
         if (zval < 3.814697265625e-06f) {   // below 2^-18 of the largest term: sum again, relative to the valid maximum
             ref = tile_valid_max<T>(rt, word, lane);
-            zval = ref != -INFINITY ? tile_valid_sum<T>(rt, word, lane, ref, tp.c) : 0.f;
+            zval = ref != -INFINITY ? tile_valid_sum<T>(rt, word, lane, shifted(ref, tp.c), tp.c) : 0.f;
         }
         if (zval > 0.f) {
             lzv = fmaf(ref - m, tp.inv, LN2F * (fast_log2(zval) - l2za));
-            id = locate_in_tile<T>(rt, word, 0, lane, ref, (double)u * (double)zval, tp.c);
+            id = locate_in_tile<T>(rt, word, 0, lane, shifted(ref, tp.c), (double)u * (double)zval, tp.c);
         }
     }
     if (lane == 0) {
@@ -1246,7 +1323,8 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     int t = lens[b];
     const float u = uniforms[b];
     RawTile rt;
-    load_tile<T>(row_of(logits + (size_t)b * (size_t)row_stride, V), 0, lane, rt);   // in flight during the walk
+    const T *row = logits + (size_t)b * (size_t)row_stride;
+    load_tile<T>(row_of(row, V), 0, lane, rt);   // in flight during the walk
     t = t < 0 ? 0 : (t > stride ? stride : t);
     const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
     uint32_t word = 0u;
@@ -1266,17 +1344,21 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     float m, zall, zval;
     if (V == TileGeom<T>::TILE) image_stats<T, false>(rt, word, lane, left, tp, m, zall, zval);
     else image_stats<T, true>(rt, word, lane, left, tp, m, zall, zval);
+    if (__builtin_expect(no_sum(uniform(zall)), 0) && m != -INFINITY) {   // (uniform)
+        far_row<T>(row, V, lane, tp, m, zall);
+        zval = 0.f;
+    }
     const float l2za = fast_log2(zall);
     int id = -1;
     float lzv = -INFINITY, ref = m;
     if (__ballot(word != 0u)) {
         if (zval < 3.814697265625e-06f) {   // below 2^-18 of the largest term: sum again, relative to the valid maximum
             ref = tile_valid_max<T>(rt, word, lane);
-            zval = ref != -INFINITY ? tile_valid_sum<T>(rt, word, lane, ref, tp.c) : 0.f;
+            zval = ref != -INFINITY ? tile_valid_sum<T>(rt, word, lane, shifted(ref, tp.c), tp.c) : 0.f;
         }
         if (zval > 0.f) {
             lzv = fmaf(ref - m, tp.inv, LN2F * (fast_log2(zval) - l2za));
-            id = locate_in_tile<T>(rt, word, 0, lane, ref, (double)u * (double)zval, tp.c);
+            id = locate_in_tile<T>(rt, word, 0, lane, shifted(ref, tp.c), (double)u * (double)zval, tp.c);
         }
     }
     if (lane == 0) {
@@ -1551,7 +1633,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         }
         float M, za;
         double zv;
-        combine_tiles(sh, nt, lane, tp, false, M, za, zv);
+        combine_tiles<T>(sh, logits + (size_t)b * (size_t)row_stride, V, nt, lane, tp, false, M, za, zv);
         const float lzv = fmaf(pk.Mv - M, tp.inv, LN2F * (fast_log2((float)pk.zvl) - fast_log2(za)));
         if (lane == 0) {
             if (logZ_valid) logZ_valid[b] = lzv;
@@ -1645,7 +1727,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
                     if (mv != -INFINITY) {
                         float M, za;
                         double zv;
-                        combine_tiles(shs[s & 1], nt, lane, tp, false, M, za, zv);
+                        combine_tiles<T>(shs[s & 1], row, V, nt, lane, tp, false, M, za, zv);
                         const float lzv = fmaf(mv - M, tp.inv, LN2F * (fast_log2((float)zvl) - fast_log2(za)));
                         if (lane == 0) {
                             if (logZ_valid) logZ_valid[(size_t)s * (size_t)B + b] = lzv;
@@ -1808,7 +1890,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
             if (wave == 0 && pk.Mv != -INFINITY) {
                 float M, za;
                 double zv;
-                combine_tiles(cur, nt, lane, tp, false, M, za, zv);
+                combine_tiles<T>(cur, row, V, nt, lane, tp, false, M, za, zv);
                 const float lzv = fmaf(pk.Mv - M, tp.inv, LN2F * (fast_log2((float)pk.zvl) - fast_log2(za)));
                 if (lane == 0) {
                     if (logZ_valid) logZ_valid[(size_t)s * (size_t)B + b] = lzv;

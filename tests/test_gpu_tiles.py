@@ -195,3 +195,126 @@ def test_filtered_rows_take_no_second_pass(dtype, V, B, fill):
             torch.cuda.synchronize()
             best[name] = min(best.get(name, 1e9), a.elapsed_time(b))
     assert best["few"] < 1.4 * best["noise"], best
+
+
+F32_MIN, BF16_MIN = float(np.finfo(np.float32).min), -3.3895313892515355e38   # (torch.finfo(torch.bfloat16).min)
+
+
+def on_device(lg, dtype):
+    """((rows, V) of dtype on the device, the same values in 64 bits)"""
+    V = lg.shape[-1]
+    buf = np.zeros(lg.shape[:-1] + (-(-V // 8) * 8,), np.float32)
+    buf[..., :V] = lg
+    if dtype == "f32":
+        return to_dev(buf)[..., :V], lg.astype(np.float64)
+    bits = W.f32_to_bf16_bits(buf)
+    return to_dev(bits.view(np.int16)).view(torch.bfloat16)[..., :V], W.bf16_bits_to_f32(bits)[..., :V].astype(np.float64)
+
+
+def check_row(x, valid, u, id, lzv, lza=None):
+    """A row of logits over T in 64 bits, its valid tokens and its uniform against what was drawn.  A mass is a difference of
+    two logarithms, each rounded to 2^-24 of itself, beside sums of 2^-24 a term: 2e-5 of the larger; beyond fp32 -inf."""
+    top, vtop = x.max(), x[valid].max()
+    all_ref = top + np.log(np.exp(x - top).sum())
+    w = np.exp(x[valid] - vtop)
+    val_ref = (vtop - top) + np.log(w.sum()) - np.log(np.exp(x - top).sum())
+    for got, want, size in ((lza, all_ref, abs(all_ref)), (lzv, val_ref, max(abs(val_ref), min(abs(all_ref), 1e4)))):
+        if got is None:
+            continue
+        if abs(want) >= 3.4e38:
+            assert got == np.copysign(np.inf, want) or abs(got) > 3.39e38, (got, want)
+        else:
+            assert abs(float(got) - want) <= 2e-5 * max(1.0, size / 64), (got, want)
+    cdf = np.cumsum(w) / w.sum()
+    at = min(int(np.searchsorted(cdf, u, side="right")), len(valid) - 1)
+    assert id == valid[at] or (id in valid and np.abs(cdf - u).min() < CDF_BAND), (id, valid[at])
+
+
+FAR = [(-1e8, 1.0), (-1.2e9, 1.0), (-1e9, 0.3), (-1e10, 1.0), (-3e12, 1.0), (-1e30, 0.3), (BF16_MIN, 1.0), (BF16_MIN, 0.3), (F32_MIN, 1.0), (F32_MIN, 0.3)]
+
+
+@pytest.mark.parametrize("fill,T", FAR)
+@pytest.mark.parametrize("dtype,V", [("f32", 1_024), ("f32", 1_000), ("bf16", 2_047), ("f32", 9_004), ("bf16", 32_000), ("bf16", 131_000)])
+def test_logits_of_any_size(dtype, V, fill, T):
+    """Logits so far from 0 that their products with log2(e) / T are known to whole units only, or not at all: rows filtered
+    with them, made of them, allowed only them; and the same above the rest of the row."""
+    if dtype == "bf16" and fill < BF16_MIN:
+        pytest.skip("no bf16 number")
+    rng = np.random.default_rng(V)
+    lg = np.concatenate([filtered_rows(V, 50, rng, fill), rng.normal(0, 2, size=(5, V)).astype(np.float32)])
+    B = len(lg)
+    step = np.spacing(np.float32(fill / 2))
+    lg[9] = np.float32(-fill / 2) + step * rng.integers(0, 4, V).astype(np.float32)        # neighbours, all of them far from 0
+    lg[10] = -lg[9]
+    lg[6, rng.choice(V, 4, replace=False)] = -fill                         # far above the rest
+    lg[7, rng.choice(V, V // 2, replace=False)] = fill
+    lg[7, rng.choice(V, V // 8, replace=False)] = fill / 2
+    lg[8, :: 256] = -fill                                                  # ... also where references are looked for
+    lg[8, 5] = -fill / 2
+    ld, x = on_device(lg, dtype)
+    x = x / T
+    for n_valid in (1, 30, min(200, V // 3), V // 3):                      # one token, lists of a slice and of several, an image
+        mask = np.zeros((B, V), np.uint8)
+        for b in range(B):
+            mask[b, rng.choice(V, n_valid, replace=False)] = 1
+            if b not in (3, 4, 7):
+                mask[b, np.flatnonzero(lg[b] > fill)[:3]] = 1
+        mask[3] &= lg[3] == np.float32(fill)                               # only what was filtered out
+        mask[3, np.flatnonzero(lg[3] == np.float32(fill))[:2]] = 1
+        mask[4] = 0
+        mask[4, np.flatnonzero(lg[4] == np.float32(fill))[-n_valid:]] = 1
+        words = np.packbits(np.pad(mask, ((0, 0), (0, (-V) % 32))), axis=1, bitorder="little").view(np.int32)
+        un = rng.random(B, dtype=np.float32)
+        ids = torch.full((B,), -9, dtype=torch.int32, device=DEV)
+        lzv, lza = torch.zeros(B, device=DEV), torch.zeros(B, device=DEV)
+        ppv.constrained_sample(ld, to_dev(words), to_dev(un), ids, lzv, lza, temperature=T)
+        ids, lzv, lza = ids.cpu().numpy(), lzv.cpu().numpy(), lza.cpu().numpy()
+        for b in range(B):
+            check_row(x[b], np.flatnonzero(mask[b]), un[b], ids[b], lzv[b], lza[b])
+
+
+@pytest.mark.parametrize("fill,T", FAR)
+@pytest.mark.parametrize("dtype,V", [("f32", 1_000), ("bf16", 9_000), ("f32", 40_000)])
+def test_decoding_under_logits_of_any_size(dtype, V, fill, T):
+    """The same through the root's image, short lists, long lists and chains of the decoding calls: every step against 64
+    bits, one launch per step and one for all bit for bit, ppv_sample_next beside them."""
+    if dtype == "bf16" and fill < BF16_MIN:
+        pytest.skip("no bf16 number")
+    rng = np.random.default_rng(V + 1)
+    n, L, B = 6_000, 5, 24
+    S = rng.integers(0, V, (n, L)).astype(np.int32)
+    S[:3_000, 0] = 1 + rng.integers(0, 4, 3_000)                           # four heavy first tokens
+    S[:1_500, 1] = rng.integers(0, 30, 1_500)                              # ... with short lists below some
+    index = ppv.ppv_build_index(S.reshape(-1), np.arange(n + 1, dtype=np.int64) * L, V)
+    lg = np.concatenate([filtered_rows(V, 50, rng, fill) for _ in range(L * B // 6)]).reshape(L, B, V)
+    lg[0, :, 1:5] = 9.0                                                    # (most rows go below the heavy tokens)
+    lg[1, ::2, :30] = 8.0
+    lg[2:, 3] = -fill                                                      # a row far above 0
+    ld, x = on_device(lg, dtype)
+    un = to_dev(rng.random((L, B), dtype=np.float32))
+    runs = []
+    for one_launch in (False, True):
+        P = torch.full((B, L), 7, dtype=torch.int32, device=DEV)
+        lens, act = torch.zeros(B, dtype=torch.int32, device=DEV), torch.zeros(B, dtype=torch.uint8, device=DEV)
+        state = torch.zeros((B, ppv.PPV_STATE_WORDS), dtype=torch.int32, device=DEV)
+        lx, lz = torch.zeros(B, device=DEV), torch.full((L, B), 7.0, device=DEV)
+        ids = torch.full((L, B), -7, dtype=torch.int32, device=DEV)
+        ppv.ppv_decode_begin_empty(index, lens, state, act, lx)
+        if one_launch:
+            ppv.ppv_decode_loop(index, P, lens, act, ld, un, ids, lz, lx, state=state, temperature=T)
+        else:
+            for s in range(L):
+                words = torch.zeros((B, index.n_words), dtype=torch.int32, device=DEV)
+                nxt, mass = torch.zeros(B, dtype=torch.int32, device=DEV), torch.zeros(B, device=DEV)
+                ppv.ppv_next_token_mask(index, P, lens, words)
+                ppv.ppv_sample_next(index, P, lens, ld[s], un[s], nxt, mass, temperature=T)
+                ppv.ppv_decode_step(index, P, lens, act, ld[s], un[s], ids[s], lz[s], lx, state=state, temperature=T)
+                bits = np.unpackbits(words.cpu().numpy().view(np.uint8), axis=1, bitorder="little")[:, :V]
+                for b in range(B):
+                    for id, mass_of in ((ids[s, b], lz[s, b]), (nxt[b], mass[b])):
+                        check_row(x[s, b] / T, np.flatnonzero(bits[b]), float(un[s, b]), int(id), float(mass_of))
+        torch.cuda.synchronize()
+        runs.append([t.cpu().numpy() for t in (P, lens, act, ids, lz, lx)])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+    assert (runs[0][1] == L).all()
