@@ -81,7 +81,8 @@ struct SplitScratch {
 };
 // The scratch area of (current device, stream), allocated at the first call that needs one; nullptr when it
 // cannot be had (the stream is being captured and has none yet, or out of memory): the row is then not split.
-SplitScratch *ppv_split_scratch(hipStream_t stream);
+// A graph keeps the area of the stream it was captured on, and may be replayed on another; eager_only: none while capturing.
+SplitScratch *ppv_split_scratch(hipStream_t stream, bool eager_only);
 
 // Per-row decoding cursor kept between decode steps (PPV_STATE_WORDS x uint32).  The second half looks one level
 // ahead: the entry of the node's first child and the child offset of the entry after it.  For a node with exactly

@@ -2095,11 +2095,11 @@ int parts_wanted(int V, ppv_dtype dt, int B, double least_kb = 160.0) {
     while (parts > 1 && ((parts & (parts - 1)) != 0 || parts * 2 > nt)) parts--;   // a power of two, two tiles each
     return parts;
 }
-int parts_for(int V, ppv_dtype dt, int B, hipStream_t hs, SplitScratch **scratch, double least_kb = 160.0) {
+int parts_for(int V, ppv_dtype dt, int B, hipStream_t hs, SplitScratch **scratch, double least_kb = 160.0, bool eager_only = false) {
     *scratch = nullptr;
     int parts = parts_wanted(V, dt, B, least_kb);
     if (parts > 1) {
-        *scratch = ppv_split_scratch(hs);
+        *scratch = ppv_split_scratch(hs, eager_only);
         if (!*scratch) parts = 1;
     }
     return parts;
@@ -2294,8 +2294,9 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
     // A step with a cursor has more to lose: unsplit it draws the token while its tiles are on their way (16 rows, V = 50k fp32,
     // steps of 172 KB saved: 120 us per loop split, 115 not; 64 rows, V = 128k bf16, 188 KB: 157 and 160).  The first
     // step, a row under the root's image, is split as constrained_sample's rows are (one row, V = 128k: 15 us unsplit, 8 split;
-    // the loop of 16 steps 97.2 and 90.7 us, 4 rows at V = 250k fp32 101.5 and 87).
-    const int parts = loop ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch, state && !fresh ? 180.0 : 160.0);
+    // the loop of 16 steps 97.2 and 90.7 us, 4 rows at V = 250k fp32 101.5 and 87) -- in eager calls: in a graph it shares memory with
+    // nothing, so that graphs of first steps may be replayed side by side.
+    const int parts = loop ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch, state && !fresh ? 180.0 : 160.0, fresh);
     int nw = waves_for(ix->view.vocab, dt, B, parts, !loop && state != nullptr);
     const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
     const int nt = (ix->view.vocab + tile - 1) / tile;

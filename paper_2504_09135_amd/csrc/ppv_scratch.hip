@@ -10,9 +10,16 @@
 namespace {
 std::mutex g_mu;
 std::map<std::pair<int, hipStream_t>, SplitScratch *> g_scratch;
+bool captured(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    return true;
+}
 }  // namespace
 
-SplitScratch *ppv_split_scratch(hipStream_t stream) {
+SplitScratch *ppv_split_scratch(hipStream_t stream, bool eager_only) {
+    if (eager_only && captured(stream)) return nullptr;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         (void)hipGetLastError();
@@ -22,11 +29,7 @@ SplitScratch *ppv_split_scratch(hipStream_t stream) {
     const auto key = std::make_pair(dev, stream);
     const auto it = g_scratch.find(key);
     if (it != g_scratch.end()) return it->second;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
+    if (captured(stream)) return nullptr;
     SplitScratch *p = nullptr;
     hipError_t e = hipMalloc((void **)&p, sizeof(SplitScratch));
     if (e == hipErrorOutOfMemory) {

@@ -198,3 +198,64 @@ def test_split_rows_under_graph_capture():
             torch.cuda.synchronize()
             assert np.array_equal(ids.cpu().numpy(), want[0])
             assert np.array_equal(lzv.cpu().numpy().view(np.int32), want[1].view(np.int32))
+
+
+def first_step_buffers(B, L):
+    return [torch.full((B, L), 7, dtype=torch.int32, device=DEV), torch.full((B,), 77, dtype=torch.int32, device=DEV),
+            torch.zeros(B, dtype=torch.uint8, device=DEV), torch.full((B,), -5, dtype=torch.int32, device=DEV),
+            torch.full((B,), 5.0, device=DEV), torch.full((B,), 5.0, device=DEV),
+            torch.full((B, ppv.PPV_STATE_WORDS), -3, dtype=torch.int32, device=DEV)]
+
+
+def first_step_setup(V, B, L, seeds):
+    rng = np.random.default_rng(V)
+    S = rng.integers(0, V, (4_000, L)).astype(np.int32)
+    index = ppv.ppv_build_index(S.reshape(-1), np.arange(4_001, dtype=np.int64) * L, V)
+    inputs = []
+    for seed in seeds:
+        g = torch.Generator(device=DEV).manual_seed(seed)
+        inputs.append((torch.randn((B, V), generator=g, device=DEV).mul_(2), torch.rand(B, generator=g, device=DEV)))
+    return index, inputs
+
+
+def first_step(index, x, u, bufs, stream=None):
+    P, lens, act, ids, lz, lx, state = bufs
+    ppv.ppv_decode_first_step(index, P, lens, act, x, u, ids, lz, lx, state=state, stream=stream)
+
+
+def test_graphs_of_first_steps_side_by_side():
+    """Graphs captured on one stream that has an area, replayed on two streams at once, eager calls on the capture's stream
+    beside them: each gives what it gives alone."""
+    V, B, L = 64_000, 6, 3
+    index, inputs = first_step_setup(V, B, L, (1, 2, 3))
+    want = []
+    for x, u in inputs:
+        bufs = first_step_buffers(B, L)
+        first_step(index, x, u, bufs)
+        want.append([t.clone() for t in bufs[:6]])
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    got = [first_step_buffers(B, L) for _ in inputs]
+    graphs = []
+    with torch.cuda.stream(streams[0]):
+        first_step(index, *inputs[0], got[0])             # the stream's area
+    torch.cuda.synchronize()
+    for (x, u), bufs in list(zip(inputs, got))[:2]:
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=streams[0]):
+            for _ in range(20):
+                first_step(index, x, u, bufs)
+    for _ in range(10):
+        for bufs in got:
+            bufs[3].fill_(-9)
+            bufs[4].fill_(9.0)
+        torch.cuda.synchronize()
+        for graph, stream in zip(graphs, streams[1:]):
+            with torch.cuda.stream(stream):
+                graph.replay()
+        with torch.cuda.stream(streams[0]):
+            for _ in range(20):
+                first_step(index, *inputs[2], got[2])
+        torch.cuda.synchronize()
+        for bufs, ref in zip(got, want):
+            for a, b in zip(bufs, ref):
+                assert torch.equal(a, b)
