@@ -1,15 +1,24 @@
 // Scratch areas in which the workgroups that share a row meet (see SplitRow).  One per (device, stream), so that
 // calls on different streams never share one; allocated at the first call that needs it and kept until the
 // process ends.  A stream that is being captured cannot allocate: it gets an area only if it already has one.
+// hipStreamPerThread is one handle for as many streams as there are threads: such a stream is known by its thread's number
+// (never used again after the thread), and the first MOST_THREADS of them have an area.
+#include <atomic>
 #include <map>
 #include <mutex>
-#include <utility>
+#include <tuple>
 
 #include "ppv_internal.h"
 
 namespace {
 std::mutex g_mu;
-std::map<std::pair<int, hipStream_t>, SplitScratch *> g_scratch;
+std::map<std::tuple<int, hipStream_t, uint64_t>, SplitScratch *> g_scratch;
+constexpr uint64_t MOST_THREADS = 64;
+uint64_t thread_number() {   // 1, 2, ...
+    static std::atomic<uint64_t> last{0};
+    thread_local const uint64_t mine = ++last;
+    return mine;
+}
 bool captured(hipStream_t stream) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
@@ -26,7 +35,9 @@ SplitScratch *ppv_split_scratch(hipStream_t stream, bool eager_only) {
         return nullptr;
     }
     std::lock_guard<std::mutex> lock(g_mu);
-    const auto key = std::make_pair(dev, stream);
+    const uint64_t thread = stream == hipStreamPerThread ? thread_number() : 0;
+    if (thread > MOST_THREADS) return nullptr;
+    const auto key = std::make_tuple(dev, stream, thread);
     const auto it = g_scratch.find(key);
     if (it != g_scratch.end()) return it->second;
     if (captured(stream)) return nullptr;

@@ -259,3 +259,39 @@ def test_graphs_of_first_steps_side_by_side():
         for bufs, ref in zip(got, want):
             for a, b in zip(bufs, ref):
                 assert torch.equal(a, b)
+
+
+def test_threads_with_the_per_thread_stream():
+    """hipStreamPerThread is one handle for a stream in each thread: split rows of several threads do not meet."""
+    import threading
+    import types
+    per_thread = types.SimpleNamespace(cuda_stream=2)     # the handle's value
+    V, B, L, N = 64_000, 6, 3, 4
+    index, inputs = first_step_setup(V, B, L, range(N))
+    want = []
+    for x, u in inputs:
+        bufs = first_step_buffers(B, L)
+        first_step(index, x, u, bufs)
+        want.append(bufs)
+    got = [first_step_buffers(B, L) for _ in inputs]
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(k):
+        try:
+            for _ in range(200):
+                first_step(index, *inputs[k], got[k], stream=per_thread)
+            torch.cuda.synchronize()                      # (the thread's stream ends with the thread)
+        except Exception as e:                            # (an assertion in a thread would go unseen)
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(N)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed
+    for bufs, ref in zip(got, want):
+        for a, b in zip(bufs[:6], ref[:6]):
+            assert torch.equal(a, b)
