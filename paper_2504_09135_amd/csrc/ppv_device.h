@@ -30,11 +30,6 @@ template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline d
     return __hiloint2double(dpp0<CTRL, ROW_MASK, BANK_MASK>(__double2hiint(x)),
                             dpp0<CTRL, ROW_MASK, BANK_MASK>(__double2loint(x)));
 }
-// source lane's value, or the lane's own value where it has no source or is masked off
-template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline float dpp_self(float x) {
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, ROW_MASK, BANK_MASK, false));
-}
 __device__ inline float last_lane(float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63)); }
 __device__ inline int last_lane(int x) { return __builtin_amdgcn_readlane(x, 63); }
 __device__ inline uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
@@ -75,6 +70,7 @@ __device__ inline float wave_max(float x) {
     asm(PPV_DPP_WAVE("v_max_f32_dpp") : "+v"(x));
     return last_lane(x);
 }
+// source lane's value, or the lane's own value where it has no source or is masked off
 template <int CTRL, int ROW_MASK = 0xF, int BANK_MASK = 0xF> __device__ inline uint32_t dpp_self(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROW_MASK, BANK_MASK, false);
 }

@@ -52,8 +52,8 @@ __device__ __forceinline__ float exp_scale(float d, float c) {
 // Arguments.  Every kernel takes first what its first loads need (pointers and sizes, 14 words at most) and the structs
 // last: the leading scalars are in the wavefronts' registers when these start (-amdgpu-kernarg-preload-count; a struct stays
 // in memory), so that a row's words are asked for at once and not after a trip for their addresses.  us per pass before and
-// after, the structs first: mask + sample of 4,096 rows at V = 1,024 fp32 11.71 / 11.03, of 128 at V = 50,265 fp32 16.16 /
-// 15.52; decoding step by step 2,048 rows at V = 32k 566.5 / 559.1 and 1,024 at V = 50k 269.5 / 265.8.
+// after, the structs first: mask + sample of 4,096 rows at V = 1,024 fp32 11.71 / 11.03 (of 128 at V = 50,265 fp32: no more than
+// two runs differ); decoding step by step 2,048 rows at V = 32k 566.5 / 559.1 and 1,024 at V = 50k 269.5 / 265.8.
 
 // ------------------------------------------------------------------------------------------
 // ppv_next_token_mask: one workgroup per prefix.
@@ -187,7 +187,6 @@ template <> struct Elem<float> {
         x[0] = __uint_as_float(r.x); x[1] = __uint_as_float(r.y);
         x[2] = __uint_as_float(r.z); x[3] = __uint_as_float(r.w);
     }
-    __device__ static __forceinline__ uint32_t pad() { return 0xFF800000u; }  // -inf
 };
 template <> struct Elem<uint16_t> {  // bf16: widening to fp32 is exact
     static constexpr int EPL = 8;
@@ -197,7 +196,6 @@ template <> struct Elem<uint16_t> {  // bf16: widening to fp32 is exact
         x[4] = __uint_as_float(r.z << 16); x[5] = __uint_as_float(r.z & 0xFFFF0000u);
         x[6] = __uint_as_float(r.w << 16); x[7] = __uint_as_float(r.w & 0xFFFF0000u);
     }
-    __device__ static __forceinline__ uint32_t pad() { return 0xFF80FF80u; }  // two bf16 -inf
 };
 // The same as unpack, with values that the compiler takes for new ones each time: what is unpacked is used at once and
 // not kept in registers for another use of the tile (there is one in a rare case, and tiles are held packed).
@@ -376,7 +374,8 @@ template <typename T, bool PAD> __device__ __forceinline__ void list_stats(const
     const float ref = uniform(quad_max(mx)), mc = ref * tp.c;
     m_out = ref;
     zall_out = INFINITY;   // (not settled)
-    // (before the sums: rows filtered to 50 tokens, 2,048 at V = 32k, take 25 us like this and 31 where every tile is summed first)
+    // (before the sums: rows filtered to 50 tokens, the rest -1e4, 2,048 at V = 32k, take 22.9 us like this and 29.3 where every tile is
+    // summed first)
     if (__builtin_expect(too_low(ref), 0)) return;   // (uniform)
     float zall = group_sum<G::EPL>(x, tp.c, mc, 0.f);
 #pragma unroll
@@ -724,7 +723,7 @@ __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
         fetch(X, share.at(i + 2));
         reduce_tile(Y, share.at(i + 1), i + 1, std::false_type());
         fetch(Y, i + 3 < n ? share.at(i + 3) : NO_TILE);
-        if (i + 2 - written == WAVE) {   // (a wavefront with more tiles than lanes: only where a launch shape is forced)
+        if (i + 2 - written == WAVE) {   // (a wavefront with more tiles than lanes: large batches of the loop kernel, two wavefronts to a row)
             if (!(IMAGE && image)) write_kept(WAVE, written);
             written += WAVE;
         }
@@ -1418,9 +1417,10 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_empty_kernel(int B,
 // ppv_decode_step / ppv_decode_loop: take the children of the row's prefix as the valid set (list, or
 // the ready-made image of a heavy node), stream + sample, append, and report whether the extended
 // row is in S.  LOOP: the same for n_steps steps in one launch, one workgroup staying with its row;
-// the cursor lives in registers and the next step's first tiles are requested before the current
-// step is sampled (only when no child of the current prefix is a member, i.e. the row is certain to
-// go on, so nothing is fetched in vain).
+// the cursor lives in registers.  Where the row is certain to go on (no child of the current prefix is a member),
+// the next step's first tiles are requested early: in chains of single children while this step's last ones are reduced
+// (LOOP with REG), and with the list in LDS before the step is sampled.  The other steps of LOOP with REG start with nothing
+// requested.
 template <typename T, bool LOOP, bool SPLIT, bool REG>
 __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOOP ? 4 : 1) void decode_kernel(
     uint8_t *__restrict__ active, int32_t *__restrict__ lens, RowState *__restrict__ state, const float *__restrict__ uniforms,
@@ -1919,13 +1919,15 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
                     const NodeEnt e = ix.ent[cb + i];
                     sh.list_tok[i] = e.tok;
                     sh.list_child[i] = e.child;
-                    if (i < nchild && (e.tok & PPV_NODE_TERMINAL)) member_child = 1;
+                    if (LOOP && !REG && i < nchild && (e.tok & PPV_NODE_TERMINAL)) member_child = 1;
                 }
             }
-            if (LOOP) member_child = __syncthreads_or(member_child);
+            if (LOOP && !REG) member_child = __syncthreads_or(member_child);
             else __syncthreads();
         }
-        // (REG: a third tile in registers here spills others there: 1,000 rows at V = 32k 145 us, 134 without)
+        // (REG: a third tile in registers here costs more than it saves, in chains, which are spilled for it, and where every step
+        // is of this kind too.  us with / without: 800 rows at V = 130k bf16 432 / 398; sets of 2 to 6 tokens, 1,000 rows at V = 32k
+        // 66.6 / 60.4, 600 at V = 128k 152 / 142; codes, 256 rows at V = 8,192 bf16 22.0 / 20.0, 512 fp32 26.1 / 25.6)
         const bool more = LOOP && !REG && s + 1 < n_steps && t + 1 < stride && mode != VALID_NONE && !member_child;
         RawTile next_first;
         const T *next_row = more ? row + step_stride : nullptr;
