@@ -23,7 +23,8 @@
  *     wherever it is replayed: graphs captured on one stream that hold such calls must not be replayed at the same time as one
  *     another, or as such calls made eagerly on that stream.  A stream that made no such call before its capture has no area:
  *     rows are then not split, and its graphs may be replayed side by side.  So may graphs of ppv_decode_loop, of
- *     ppv_decode_first_step, of the mask calls and of ppv_disc_select, always.
+ *     ppv_decode_first_step, of the mask calls and of ppv_disc_select, always.  hipStreamPerThread counts as one stream of each
+ *     thread that passes it (rows of threads after the first 64 are not split).
  *   - Token order is integer order (Section 2.1, footnote on the ordered vocabulary); sequences
  *     are ordered lexicographically, left to right, a proper prefix before its extensions
  *     (Section 3.2 "Array Preparation").  Query tokens are compared as unsigned 32-bit values:

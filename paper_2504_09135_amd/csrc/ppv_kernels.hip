@@ -451,6 +451,9 @@ __device__ __forceinline__ void image_stats(const RawTile &rt, uint32_t tile_wor
 
 // A row too far from 0 for its tiles' sums shows in their total, which is then 0, infinite or NaN: a scalar compare.
 __device__ __forceinline__ bool no_sum(float za) { return __float_as_uint(za) - 1u >= __float_as_uint(INFINITY) - 1u; }
+// ... as does one of nothing but -inf, or with a NaN or +inf, which is left as it is.  (At temperatures below 1e-4 a reference just
+// above REF_LOW may be far off, whatever the row's largest token is.)
+__device__ __forceinline__ bool is_far(float M, float c) { return fabsf(M) < INFINITY && (far_off(M, c) || REF_LOW * c <= -FAR); }
 // A far row's largest token, and the sum over all tokens relative to it: by one wavefront, from memory, in as little code as it takes.
 template <typename T> __device__ __forceinline__ void far_row(const T *row, int V, int lane, const Temper &tp, float &M, float &za) {
     constexpr int EPL = Elem<T>::EPL;
@@ -786,7 +789,7 @@ __device__ __forceinline__ void combine_tiles(const SH &sh, const T *row, int V,
                                      float &za, double &zv) {
     add_tiles(sh, nt, lane, tp, image, M, za, zv);
     if (__builtin_expect(no_sum(za), 0)) {   // (uniform)
-        if (M == -INFINITY) return;
+        if (!is_far(M, tp.c)) return;
         far_row<T>(row, V, lane, tp, M, za);
         zv = 0.0;
     }
@@ -1282,7 +1285,7 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_one_tile_kernel(co
     float m, zall, zval;
     if (V == TileGeom<T>::TILE) image_stats<T, false>(rt, word, lane, left, tp, m, zall, zval);
     else image_stats<T, true>(rt, word, lane, left, tp, m, zall, zval);
-    if (__builtin_expect(no_sum(uniform(zall)), 0) && m != -INFINITY) {   // (uniform)
+    if (__builtin_expect(no_sum(uniform(zall)), 0) && is_far(m, tp.c)) {   // (uniform)
         far_row<T>(row, V, lane, tp, m, zall);
         zval = 0.f;
     }
@@ -1343,7 +1346,7 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     float m, zall, zval;
     if (V == TileGeom<T>::TILE) image_stats<T, false>(rt, word, lane, left, tp, m, zall, zval);
     else image_stats<T, true>(rt, word, lane, left, tp, m, zall, zval);
-    if (__builtin_expect(no_sum(uniform(zall)), 0) && m != -INFINITY) {   // (uniform)
+    if (__builtin_expect(no_sum(uniform(zall)), 0) && is_far(m, tp.c)) {   // (uniform)
         far_row<T>(row, V, lane, tp, m, zall);
         zval = 0.f;
     }

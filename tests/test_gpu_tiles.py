@@ -230,7 +230,7 @@ def check_row(x, valid, u, id, lzv, lza=None):
     assert id == valid[at] or (id in valid and np.abs(cdf - u).min() < CDF_BAND), (id, valid[at])
 
 
-FAR = [(-1e8, 1.0), (-1.2e9, 1.0), (-1e9, 0.3), (-1e10, 1.0), (-3e12, 1.0), (-1e30, 0.3), (BF16_MIN, 1.0), (BF16_MIN, 0.3), (F32_MIN, 1.0), (F32_MIN, 0.3)]
+FAR = [(-4e3, 1e-6), (-1e8, 1.0), (-1.2e9, 1.0), (-1e9, 0.3), (-1e10, 1.0), (-3e12, 1.0), (-1e30, 0.3), (BF16_MIN, 1.0), (BF16_MIN, 0.3), (F32_MIN, 1.0), (F32_MIN, 0.3)]
 
 
 @pytest.mark.parametrize("fill,T", FAR)
