@@ -17,14 +17,13 @@
  *     enqueue work on it and do not synchronise with the host.  Argument checks that need device
  *     data are not made; checks on host-visible arguments are.
  *   - An index is immutable after it is built; calls on different streams may run concurrently.
- *   - constrained_sample, ppv_sample_next, ppv_decode_step and (in eager calls) ppv_decode_first_step spread the rows of a
- *     small batch over several workgroups, which meet in a scratch area (4.3 MB) that belongs to the call's stream: it is
- *     allocated by the first such call and kept until the process ends.  A graph uses the area of the stream it was captured on,
- *     wherever it is replayed: graphs captured on one stream that hold such calls must not be replayed at the same time as one
- *     another, or as such calls made eagerly on that stream.  A stream that made no such call before its capture has no area:
- *     rows are then not split, and its graphs may be replayed side by side.  So may graphs of ppv_decode_loop, of
- *     ppv_decode_first_step, of the mask calls and of ppv_disc_select, always.  hipStreamPerThread counts as one stream of each
- *     thread that passes it (rows of threads after the first 64 are not split).
+ *   - constrained_sample, ppv_sample_next, ppv_decode_step and ppv_decode_first_step spread the rows of a small batch over
+ *     several workgroups, which meet in a scratch area.  Eager calls use one that belongs to their stream (4.3 MB; with
+ *     hipStreamPerThread to the thread, for the first 64 threads that pass it), captured ones one that belongs to the capture
+ *     (1 MB; up to 256 captures per GPU), so graphs may be replayed at the same time as one another and as eager calls, on any
+ *     streams.  (One graph instantiated twice must not be replayed at the same time as itself.)  The first eager call that needs
+ *     an area on a stream allocates it, and such calls lay areas ready for captures to come; a capture that finds none ready
+ *     does not split its rows, with the same results.  All areas are kept until the process ends.
  *   - Token order is integer order (Section 2.1, footnote on the ordered vocabulary); sequences
  *     are ordered lexicographically, left to right, a proper prefix before its extensions
  *     (Section 3.2 "Array Preparation").  Query tokens are compared as unsigned 32-bit values:

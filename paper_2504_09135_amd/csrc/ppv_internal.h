@@ -79,10 +79,9 @@ struct SplitScratch {
     uint32_t arrivals[PPV_SPLIT_MAX_ROWS];
     SplitRow row[PPV_SPLIT_MAX_ROWS];
 };
-// The scratch area of (current device, stream), allocated at the first call that needs one; nullptr when it
-// cannot be had (the stream is being captured and has none yet, or out of memory): the row is then not split.
-// A graph keeps the area of the stream it was captured on, and may be replayed on another; eager_only: none while capturing.
-SplitScratch *ppv_split_scratch(hipStream_t stream, bool eager_only);
+// The scratch area for `rows` rows (PPV_SPLIT_MAX_ROWS at most) of a call on this stream of the current device, or of the capture
+// that the stream is in; nullptr when there is none to be had: the rows are then not split.
+SplitScratch *ppv_split_scratch(hipStream_t stream, int rows);
 
 // Per-row decoding cursor kept between decode steps (PPV_STATE_WORDS x uint32).  The second half looks one level
 // ahead: the entry of the node's first child and the child offset of the entry after it.  For a node with exactly

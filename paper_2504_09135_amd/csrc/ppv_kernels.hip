@@ -2085,7 +2085,7 @@ int waves_for(int V, ppv_dtype dt, int B, int parts = 1, bool cursor_step = fals
 // row bytes x (1 - 1 / parts) >= 160 KB.  Measured, constrained_sample, bf16, us per call without / with the split:
 // V = 128,256: B = 32: 13.0 / 10.0 (list rows), 17.8 / 11.2 (image rows); B = 128: 13.6 / 14.0, 18.7 / 16.1 (two
 // parts: not split); V = 32,000, B = 64: 7.4 / 9.1 (not split).  PPV_TUNE_ROW_SPLIT forces a number of parts.
-// The scratch area the parts meet in comes with the stream; without one (see ppv_split_scratch) rows are not split.
+// The scratch area the parts meet in comes with the stream or the capture; without one (see ppv_split_scratch) rows are not split.
 int parts_wanted(int V, ppv_dtype dt, int B, double least_kb = 160.0) {
     const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
     const int nt = (V + tile - 1) / tile;
@@ -2100,11 +2100,11 @@ int parts_wanted(int V, ppv_dtype dt, int B, double least_kb = 160.0) {
     while (parts > 1 && ((parts & (parts - 1)) != 0 || parts * 2 > nt)) parts--;   // a power of two, two tiles each
     return parts;
 }
-int parts_for(int V, ppv_dtype dt, int B, hipStream_t hs, SplitScratch **scratch, double least_kb = 160.0, bool eager_only = false) {
+int parts_for(int V, ppv_dtype dt, int B, hipStream_t hs, SplitScratch **scratch, double least_kb = 160.0) {
     *scratch = nullptr;
     int parts = parts_wanted(V, dt, B, least_kb);
     if (parts > 1) {
-        *scratch = ppv_split_scratch(hs, eager_only);
+        *scratch = ppv_split_scratch(hs, B);
         if (!*scratch) parts = 1;
     }
     return parts;
@@ -2299,9 +2299,8 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
     // A step with a cursor has more to lose: unsplit it draws the token while its tiles are on their way (16 rows, V = 50k fp32,
     // steps of 172 KB saved: 120 us per loop split, 115 not; 64 rows, V = 128k bf16, 188 KB: 157 and 160).  The first
     // step, a row under the root's image, is split as constrained_sample's rows are (one row, V = 128k: 15 us unsplit, 8 split;
-    // the loop of 16 steps 97.2 and 90.7 us, 4 rows at V = 250k fp32 101.5 and 87) -- in eager calls: in a graph it shares memory with
-    // nothing, so that graphs of first steps may be replayed side by side.
-    const int parts = loop ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch, state && !fresh ? 180.0 : 160.0, fresh);
+    // the loop of 16 steps 97.2 and 90.7 us, 4 rows at V = 250k fp32 101.5 and 87).
+    const int parts = loop ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch, state && !fresh ? 180.0 : 160.0);
     int nw = waves_for(ix->view.vocab, dt, B, parts, !loop && state != nullptr);
     const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
     const int nt = (ix->view.vocab + tile - 1) / tile;

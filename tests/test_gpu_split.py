@@ -223,42 +223,79 @@ def first_step(index, x, u, bufs, stream=None):
     ppv.ppv_decode_first_step(index, P, lens, act, x, u, ids, lz, lx, state=state, stream=stream)
 
 
-def test_graphs_of_first_steps_side_by_side():
-    """Graphs captured on one stream that has an area, replayed on two streams at once, eager calls on the capture's stream
-    beside them: each gives what it gives alone."""
-    V, B, L = 64_000, 6, 3
-    index, inputs = first_step_setup(V, B, L, (1, 2, 3))
+def split_call(name, index, x, u, bufs, words):
+    """One call of each kind that splits rows, from the empty prefixes; repeatable."""
+    P, lens, act, ids, lz, lx, state = bufs
+    if name == "first":
+        first_step(index, x, u, bufs)
+    elif name == "sample":
+        ppv.constrained_sample(x, words, u, ids, lz)
+    else:
+        lens.zero_()
+        act.fill_(1)
+        if name == "next":
+            ppv.ppv_sample_next(index, P, lens, x, u, ids, lz)
+        else:
+            ppv.ppv_decode_step(index, P, lens, act, x, u, ids, lz)
+
+
+@pytest.mark.parametrize("name", ["first", "step", "sample", "next"])
+def test_graphs_side_by_side(name):
+    """Graphs captured one after the other on one stream (more of them than areas lie ready), replayed on streams of their own
+    at the same time, eager calls on the capture's stream beside them: each gives what it gives alone."""
+    V, B, L, N = 64_000, 6, 3, 7
+    index, inputs = first_step_setup(V, B, L, range(N + 1))
+    words = torch.zeros((B, index.n_words), dtype=torch.int32, device=DEV)
+    ppv.ppv_next_token_mask(index, torch.zeros((B, L), dtype=torch.int32, device=DEV), torch.zeros(B, dtype=torch.int32, device=DEV), words)
     want = []
     for x, u in inputs:
         bufs = first_step_buffers(B, L)
-        first_step(index, x, u, bufs)
+        split_call(name, index, x, u, bufs, words)
         want.append([t.clone() for t in bufs[:6]])
-    streams = [torch.cuda.Stream() for _ in range(3)]
+    side = torch.cuda.Stream()
     got = [first_step_buffers(B, L) for _ in inputs]
-    graphs = []
-    with torch.cuda.stream(streams[0]):
-        first_step(index, *inputs[0], got[0])             # the stream's area
     torch.cuda.synchronize()
-    for (x, u), bufs in list(zip(inputs, got))[:2]:
+    with torch.cuda.stream(side):
+        split_call(name, index, *inputs[N], got[N], words)     # the stream has an area, captures to come have theirs
+    torch.cuda.synchronize()
+    graphs, streams = [], [torch.cuda.Stream() for _ in range(N)]
+    for (x, u), bufs in zip(inputs[:N], got):
         graphs.append(torch.cuda.CUDAGraph())
-        with torch.cuda.graph(graphs[-1], stream=streams[0]):
-            for _ in range(20):
-                first_step(index, x, u, bufs)
-    for _ in range(10):
+        with torch.cuda.graph(graphs[-1], stream=side):
+            for _ in range(10):
+                split_call(name, index, x, u, bufs, words)
+    for _ in range(5):
         for bufs in got:
             bufs[3].fill_(-9)
             bufs[4].fill_(9.0)
         torch.cuda.synchronize()
-        for graph, stream in zip(graphs, streams[1:]):
+        for graph, stream in zip(graphs, streams):
             with torch.cuda.stream(stream):
                 graph.replay()
-        with torch.cuda.stream(streams[0]):
-            for _ in range(20):
-                first_step(index, *inputs[2], got[2])
+        with torch.cuda.stream(side):
+            for _ in range(10):
+                split_call(name, index, *inputs[N], got[N], words)
         torch.cuda.synchronize()
-        for bufs, ref in zip(got, want):
+        for k, (bufs, ref) in enumerate(zip(got, want)):
             for a, b in zip(bufs, ref):
-                assert torch.equal(a, b)
+                assert torch.equal(a, b), k
+
+
+def test_more_rows_than_an_area_of_a_capture_has():
+    """(128; only a forced split has more.)"""
+    V, B, L = 20_000, 129, 3
+    index, inputs = first_step_setup(V, B, L, (1,))
+    want, got = first_step_buffers(B, L), first_step_buffers(B, L)
+    with tuning(ppv.PPV_TUNE_ROW_SPLIT, 2):
+        first_step(index, *inputs[0], want)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            first_step(index, *inputs[0], got)
+        graph.replay()
+        torch.cuda.synchronize()
+    for a, b in zip(got[:6], want):
+        assert torch.equal(a, b)
 
 
 def test_threads_with_the_per_thread_stream():
