@@ -178,7 +178,7 @@ ppv_status constrained_sample(const void *logits, ppv_dtype dt, int64_t row_stri
  *   B     at most PPV_NOALLOC_MAX_ROWS rows (what the array holds): PPV_ERANGE beyond.
  * All calls on one GPU share the array: two calls of this function that overlap on one GPU (different streams)
  * race; calls on one stream, or otherwise ordered, do not.  Nothing has to be cleared between calls: every call
- * leaves the arrival counters at zero, which is what the next one starts from, and writes the statistics it reads.
+ * leaves what it used of the array at zero, which is what the next one starts from.
  * The first call on a device looks up the array's address on that device (no allocation); make that first call
  * outside stream capture.
  * Errors: as constrained_sample; PPV_ERANGE also for B > PPV_NOALLOC_MAX_ROWS.

@@ -64,16 +64,18 @@ struct IndexView {
 
 // A row spread over several workgroups (small batches: fewer rows than compute units).  Every workgroup reduces
 // its share of the row's tiles and of the listed tokens and leaves the per-tile / per-slice statistics here; the
-// workgroup that arrives last (one device-scope counter per row) reads them all back and finishes the row exactly
+// workgroup that arrives last (one device-scope counter per row) takes them all and finishes the row exactly
 // as a single workgroup would: the statistics do not depend on who computed them, so results are bit for bit
-// those of an unsplit row.  The counter is returned to zero by the workgroup that finishes the row.
+// those of an unsplit row.  An area is all zeros between launches: no word that is written is 0, so a word says by itself
+// whether it has arrived, and the workgroup that finishes the row puts the zeros back, the counter's too.
 constexpr int PPV_MAX_TILES = 256;          // PPV_MAX_VOCAB / 1024 (fp32 tiles are 1024 tokens)
 constexpr int PPV_SPLIT_MAX_ROWS = PPV_NOALLOC_MAX_ROWS;   // larger batches fill the chip with one workgroup per row
 constexpr int PPV_SPLIT_MAX_PARTS = 16;
 struct SplitRow {
-    float4 tile[PPV_MAX_TILES];             // (reference, sum over all tokens, sum over valid tokens, its reference)
-    float list_e[PPV_LIST_MAX];
-    float slice_m[PPV_LIST_MAX / 64], slice_z[PPV_LIST_MAX / 64];
+    uint64_t tile[PPV_MAX_TILES];           // (reference, sum over all tokens)
+    uint64_t valid[PPV_MAX_TILES];          // (1.0, sum over valid tokens): rows under an image
+    uint64_t slice[PPV_LIST_MAX / 64];      // (largest of 64 listed logits, the sum relative to it)
+    uint32_t list_e[PPV_LIST_MAX];
 };
 struct SplitScratch {
     uint32_t arrivals[PPV_SPLIT_MAX_ROWS];

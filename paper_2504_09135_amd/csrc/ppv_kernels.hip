@@ -600,19 +600,30 @@ struct RowOut {
                        // every thread of it with ALL)
 };
 
-// Words that the workgroups of a split row hand to one another are written and read with device-scope accesses
-// (each goes to the level of the memory system that all compute units share), so that no fence over the whole
-// cache is needed: a device-wide fence per wavefront cost 30 us per launch, these cost about two.
-__device__ __forceinline__ void shared_put(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float shared_get(const float *p) {
+// Words that the workgroups of a split row hand to one another (see SplitRow) are written and read with device-scope
+// accesses (each goes to the level of the memory system that all compute units share), so that no fence over the whole
+// cache is needed: a device-wide fence per wavefront cost 30 us per launch.  A word of 0 has not been written, so what is
+// written never is: 0.0 goes as -0.0, which is the same number to everything that is done with it.
+__device__ __forceinline__ uint32_t not_zero(float v) {
+    const uint32_t b = __float_as_uint(v);
+    return b ? b : 0x80000000u;
+}
+template <typename W> __device__ __forceinline__ void shared_put(W *p, W v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename W> __device__ __forceinline__ W shared_get(const W *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void shared_put_tile(SplitRow *r, int k, float m, float zall, float zval, float ref) {
-    float *t = (float *)&r->tile[k];
-    shared_put(t + 0, m);
-    shared_put(t + 1, zall);
-    shared_put(t + 2, zval);
-    shared_put(t + 3, ref);
+__device__ __forceinline__ void shared_put_pair(uint64_t *p, float a, float b) {
+    shared_put(p, (uint64_t)__float_as_uint(b) << 32 | not_zero(a));
+}
+__device__ __forceinline__ float pair_first(uint64_t w) { return __uint_as_float((uint32_t)w); }
+__device__ __forceinline__ float pair_second(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
+// A word that has been sent, `seen` being what an earlier look at it gave.  (Bounded, should two launches use one area at a time,
+// which no caller may do.)  Whoever has taken a row's words leaves zeros for the next launch, after the last look: a look waits
+// for what was stored before it.
+constexpr int MOST_LOOKS = 1 << 16;
+template <typename W> __device__ __forceinline__ W shared_take(const W *p, W seen) {
+    for (int n = 0; __builtin_expect(seen == 0, 0) && n < MOST_LOOKS; n++) seen = shared_get(p);
+    return seen;
 }
 
 // A row shared by `parts` workgroups (see SplitRow); parts == 1: one workgroup has the row to itself and
@@ -623,6 +634,34 @@ struct Split {
     SplitRow *row;        // the row's scratch
     uint32_t *arrivals;   // the row's arrival counter
 };
+
+// Where the workgroups of a row meet: by wavefront 0 of each, after a barrier behind the last word the workgroup has sent.  True for the
+// one that arrives last, which then has every tile's statistics in its LDS; nobody waits for a workgroup that has not arrived.
+// A word says by itself whether it is there, so nothing is waited for between the words and the counter, and the words are looked at
+// before the counter has answered: one trip to memory that all compute units share, where there were three (the words acknowledged,
+// the counter, the words).
+template <typename SH> __device__ __forceinline__ bool meet(const Split &sp, SH &sh, int nt, int lane) {
+    constexpr int PER = MAX_TILES / WAVE;
+    uint64_t w[PER];
+#pragma unroll
+    for (int j = 0; j < PER; j++)
+        if (j * WAVE < nt) w[j] = shared_get(&sp.row->tile[min(lane + j * WAVE, nt - 1)]);   // (no lane without a word: conditions are registers)
+    uint32_t before = 0u;   // (last: its answer is waited for at once)
+    if (lane == 0) before = __hip_atomic_fetch_add(sp.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u != (uint32_t)sp.parts) return false;
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        const int k = min(lane + j * WAVE, nt - 1);
+        if (j * WAVE < nt) {
+            w[j] = shared_take(&sp.row->tile[k], w[j]);
+            sh.tile_m[k] = pair_first(w[j]);
+            sh.tile_zall[k] = pair_second(w[j]);
+        }
+    }
+    if (lane == 0) shared_put(sp.arrivals, 0u);
+    for (int k = lane; k < nt; k += WAVE) shared_put(&sp.row->tile[k], (uint64_t)0);
+    return true;
+}
 
 enum ValidMode { VALID_NONE = 0, VALID_LIST = 1, VALID_IMAGE = 2 };
 
@@ -676,10 +715,7 @@ __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
             const int k = share.at(i_first + lane);
             sh.tile_m[k] = kept_m;
             sh.tile_zall[k] = kept_z;
-            if (pub) {
-                shared_put(&pub->tile[k].x, kept_m);
-                shared_put(&pub->tile[k].y, kept_z);
-            }
+            if (pub) shared_put_pair(&pub->tile[k], kept_m, kept_z);
         }
     };
     auto reduce_tile = [&](const RawTile &t, int k, int i, auto pad) __attribute__((always_inline)) {
@@ -693,7 +729,10 @@ __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
                 sh.tile_zall[k] = zall;
                 sh.tile_zval[k] = zval;
                 sh.tile_ref[k] = m;
-                if (pub) shared_put_tile(pub, k, m, zall, zval, m);
+                if (pub) {
+                    shared_put_pair(&pub->tile[k], m, zall);
+                    shared_put_pair(&pub->valid[k], 1.f, zval);
+                }
             }
         } else {
             list_stats<T, PAD>(t, left, tp, m, zall);
@@ -929,16 +968,13 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
             }
             if (i < n_list) {
                 sh.list_e[i] = e;
-                if (pub) shared_put(&pub->list_e[i], e);
+                if (pub) shared_put(&pub->list_e[i], not_zero(e));
             }
             const float z = wave_sum(e);
             if (lane == 0) {
                 sh.slice_m[s] = m;
                 sh.slice_z[s] = z;
-                if (pub) {
-                    shared_put(&pub->slice_m[s], m);
-                    shared_put(&pub->slice_z[s], z);
-                }
+                if (pub) shared_put_pair(&pub->slice[s], m, z);
             }
         }
     };
@@ -954,39 +990,77 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
     none.logZ_all = 0.f;
     none.mine = false;
     if (SPLIT && parts > 1) {
-        // Every wavefront waits until its device-scope stores have been taken by the memory system, then the
-        // workgroup's arrival is counted.  The workgroup that finds all the others already there finishes the
-        // row (its reads are device-scope too, and issued after the count has come back); nobody waits for anybody.
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);     // vmcnt(0) expcnt(0) lgkmcnt(0)
-        __syncthreads();
-        if (tid == 0) {
-            const uint32_t before = __hip_atomic_fetch_add(sp.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const bool last = before + 1u == (uint32_t)parts;
-            if (last) __hip_atomic_store(sp.arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // the next launch starts from zero
-            sh.bc_i[0] = last ? 1 : 0;
-        }
-        __syncthreads();
-        if (!sh.bc_i[0]) return none;      // uniform for the workgroup
-        const int nthreads = nw * WAVE;
-        for (int k = tid; k < nt; k += nthreads) {
-            const float *t = (const float *)&pub->tile[k];
-            sh.tile_m[k] = shared_get(t + 0);
-            sh.tile_zall[k] = shared_get(t + 1);
+        __syncthreads();   // all words of this workgroup have been sent
+        const int listed = mode == VALID_LIST ? n_list : 0;
+        if (mode != VALID_IMAGE && listed <= WAVE) {
+            if (wave != 0) return none;
+            // (the list's words are looked at together with the tiles')
+            uint64_t slice = listed ? shared_get(&pub->slice[0]) : 0u;
+            uint32_t e = listed ? shared_get(&pub->list_e[min(lane, listed - 1)]) : 0u;
+            if (!meet(sp, sh, nt, lane)) return none;
+            if (listed) {
+                slice = shared_take(&pub->slice[0], slice);
+                e = shared_take(&pub->list_e[min(lane, listed - 1)], e);
+                if (lane == 0) {
+                    sh.slice_m[0] = pair_first(slice);
+                    sh.slice_z[0] = pair_second(slice);
+                    shared_put(&pub->slice[0], (uint64_t)0);
+                }
+                if (lane < listed) {
+                    sh.list_e[lane] = __uint_as_float(e);
+                    shared_put(&pub->list_e[lane], 0u);
+                }
+            }
+        } else {
+            // (many words: by every wavefront, which the rare second pass over an image row needs too)
+            const int nthreads = nw * WAVE;
+            uint64_t tile = tid < nt ? shared_get(&pub->tile[tid]) : 0u;
+            uint64_t more = 0u;
+            uint32_t e = 0u;
             if (mode == VALID_IMAGE) {
-                sh.tile_zval[k] = shared_get(t + 2);
-                sh.tile_ref[k] = shared_get(t + 3);
+                if (tid < nt) more = shared_get(&pub->valid[tid]);
+            } else {
+                if (tid < ns) more = shared_get(&pub->slice[tid]);
+                if (tid < listed) e = shared_get(&pub->list_e[tid]);
+            }
+            if (tid == 0) {
+                const uint32_t before = __hip_atomic_fetch_add(sp.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh.bc_i[0] = before + 1u == (uint32_t)parts ? 1 : 0;
+            }
+            __syncthreads();
+            if (!sh.bc_i[0]) return none;      // uniform for the workgroup
+            for (int k = tid; k < nt; k += nthreads) {
+                tile = shared_take(&pub->tile[k], k == tid ? tile : 0u);
+                sh.tile_m[k] = sh.tile_ref[k] = pair_first(tile);
+                sh.tile_zall[k] = pair_second(tile);
+                if (mode == VALID_IMAGE) sh.tile_zval[k] = pair_second(shared_take(&pub->valid[k], k == tid ? more : 0u));
+            }
+            if (mode == VALID_LIST) {
+                if (tid < ns) {   // (at most sixteen slices: a wavefront's lanes)
+                    more = shared_take(&pub->slice[tid], more);
+                    sh.slice_m[tid] = pair_first(more);
+                    sh.slice_z[tid] = pair_second(more);
+                }
+                for (int i = tid; i < listed; i += nthreads) sh.list_e[i] = __uint_as_float(shared_take(&pub->list_e[i], i == tid ? e : 0u));
+            }
+            __syncthreads();
+            // (the zeros by the wavefronts that have little left to do)
+            const int z0 = nw > 1 ? WAVE : 0;
+            if (tid == z0) shared_put(sp.arrivals, 0u);
+            if (tid >= z0) {
+                for (int k = tid - z0; k < nt; k += nthreads - z0) {
+                    shared_put(&pub->tile[k], (uint64_t)0);
+                    if (mode == VALID_IMAGE) shared_put(&pub->valid[k], (uint64_t)0);
+                }
+                for (int i = tid - z0; i < listed; i += nthreads - z0) {
+                    shared_put(&pub->list_e[i], 0u);
+                    if (i < ns) shared_put(&pub->slice[i], (uint64_t)0);
+                }
             }
         }
-        if (mode == VALID_LIST) {
-            for (int i = tid; i < n_list; i += nthreads) sh.list_e[i] = shared_get(&pub->list_e[i]);
-            for (int q = tid; q < ns; q += nthreads) {
-                sh.slice_m[q] = shared_get(&pub->slice_m[q]);
-                sh.slice_z[q] = shared_get(&pub->slice_z[q]);
-            }
-        }
+    } else {
+        __syncthreads();
     }
-    __syncthreads();
 
     // Nobody but wavefront 0 has anything left to do when the result goes to it alone and the set is not an
     // image (whose rare second pass needs every wavefront): the others leave its SIMD to it.
@@ -1454,9 +1528,8 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
     sp.arrivals = SPLIT ? &scratch->arrivals[b] : nullptr;
     const int vwave = sp.part * nw + wave;
     // REG: there is a cursor, and a list of at most 63 children is kept in wavefront 0's registers, with a look one level
-    // ahead for the next cursor (see RowState); split rows, large batches of the loop kernel and calls without a cursor
+    // ahead for the next cursor (see RowState); large batches of the loop kernel and calls without a cursor
     // use the list in LDS.  (C3, B = 2,048, the loop step by step: 594 us with the list in LDS, 559 like this.)
-    static_assert(!REG || !SPLIT, "the register list is for unsplit rows");
     // the independent per-row loads go out together
     uint8_t on = active ? active[b] : (uint8_t)1;
     int t = lens[b];
@@ -1608,9 +1681,12 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         struct {
             __device__ void operator()() const {}
         } nothing;
-        stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, sh, lane, share, tp, nothing, nullptr);
+        stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, sh, lane, share, tp, nothing,
+                                          SPLIT && sp.parts > 1 ? sp.row : nullptr);
         __syncthreads();
         if (wave != 0) return;
+        // (of a split row every workgroup has drawn the token, and the one that finishes the row stores it)
+        if (SPLIT && sp.parts > 1 && !meet(sp, sh, nt, lane)) return;
         if (lane == 0) {
             if (ids) ids[b] = drew ? pk.id : -1;
             if (drew) {
@@ -2071,6 +2147,10 @@ int waves_for(int V, ppv_dtype dt, int B, int parts = 1, bool cursor_step = fals
     // 24.8 29.3 34.6 against 21.4 25.7 30.1 35.0 / 18.1 23.4 27.7 33.0 against 19.4 23.8 28.5 33.0; fp32, 32 and 40 tiles: 22.0
     // 26.5 against 24.8 28.8 / 22.3 26.8 against 23.0 27.3).
     if (nt >= 48 && B > 512) cap = 8;
+    // (a part of a row: us per call with 4 / 8 / 16 wavefronts, constrained_sample, list rows, 32 in 4 parts, V = 50k fp32 7.6 / 6.7 /
+    // 7.6, V = 128k bf16 9.7 / 7.7 / 8.2, V = 64k 6.7 / 6.5 / 6.4; long parts, 128 rows in 2, V = 256k bf16, 8 / 16: 17.6 / 16.8, 16 rows
+    // in 4 11.1 / 9.8, but a step with a cursor 15.4 / 15.8 and 8.8 / 8.9)
+    if (parts > 1) cap = nt >= 32 && !cursor_step ? 16 : 8;
     if (const int v = ppv_tuning(PPV_TUNE_WAVES_PER_ROW)) cap = v;   // tuning aid (0: the table above)
     int nw = 1;
     while (nw < nt && nw * 2 <= cap) nw <<= 1;
@@ -2078,15 +2158,27 @@ int waves_for(int V, ppv_dtype dt, int B, int parts = 1, bool cursor_step = fals
 }
 
 // Workgroups per row.  A batch of fewer rows than the chip has compute units leaves most of it idle with one
-// workgroup per row, and a long row alone on a compute unit is bound by that unit's arithmetic (about 4.8 us per
-// 256 KB of bf16 logits).  Such a row is spread over 2 .. 16 workgroups: a power of two, six tiles or more each, at
-// most one workgroup per compute unit.  Handing the statistics from workgroup to workgroup costs about 3 us (three
-// dependent trips to device-scope memory), so rows are split only where that is less than what the split saves:
-// row bytes x (1 - 1 / parts) >= 160 KB.  Measured, constrained_sample, bf16, us per call without / with the split:
-// V = 128,256: B = 32: 13.0 / 10.0 (list rows), 17.8 / 11.2 (image rows); B = 128: 13.6 / 14.0, 18.7 / 16.1 (two
-// parts: not split); V = 32,000, B = 64: 7.4 / 9.1 (not split).  PPV_TUNE_ROW_SPLIT forces a number of parts.
+// workgroup per row, and a long row alone on a compute unit is bound by that unit's arithmetic.  Such a row is spread over
+// 2 .. 16 workgroups: a power of two, six tiles or more each, at most one workgroup per compute unit -- where that takes
+// enough of the row off each to pay for the hand-over (see meet): bytes of the row x (1 - 1 / parts), and more of fp32, which
+// is half the arithmetic.  us per call unsplit / in 2, 4, 8 parts, list rows of constrained_sample: 32 rows, V = 24k
+// fp32 6.4 / 7.0 6.3 6.6, V = 36k fp32 7.0 / 7.1 6.4 6.8, V = 48k bf16 7.1 / 7.0 6.5 7.0, V = 64k bf16 7.9 / 7.0 6.5 7.0, V = 50k
+// fp32 8.5 / 7.6 6.7 7.1, V = 128k bf16 10.3 / 9.0 7.7 8.0; 128 rows in 2 parts, V = 48k bf16 7.4 / 7.5, V = 64k 8.2 / 7.7, V = 128k 11.0 /
+// 10.7, V = 36k fp32 7.4 / 8.2, V = 50k 9.2 / 9.0.  Rows under an image gain up to twice as much (V = 128k: 32 rows 15.8 / 10.4 in
+// 4, 128 rows 16.6 / 14.6 in 2).  A decode step with a cursor has more to lose, unsplit it draws the token while its tiles travel, and
+// one without a cursor locates the prefix in each part: 32 rows, V = 64k bf16 7.0 / 6.9 in 4, V = 96k 8.4 / 7.3 in 8, V = 36k fp32
+// 6.6 / 7.1 in 4, V = 50k 7.9 / 7.4 in 4; 96 rows in 2, V = 96k bf16 8.8 / 8.9, V = 128k 10.4 / 9.4;
+// 128 rows in 2, every compute unit busy, V = 128k 10.5 / 10.4 (ppv_sample_next 11.8 / 12.2), V = 100k fp32 12.6 / 13.1 (14.0 / 14.8),
+// V = 256k bf16 16.8 / 15.9; as rows retire a loop's later steps gain (27 steps of 111 rows at V = 98k fp32 335 / 325).
+// The first step of a loop, every row under the root's image: 32 rows, V = 48k bf16 10.0 / 9.5 in 4, 128 rows in 2, V = 64k 12.3 / 11.8,
+// V = 50k fp32 12.0 / 12.1.  (With three trips to shared memory in the hand-over the line was 160 KB, 180 with a cursor.)
+// Above 96 rows a split leaves no compute unit idle, and pays for very long rows alone: constrained_sample behind ppv_next_token_mask, 128
+// rows at V = 96k bf16 18.3 / 18.9 in 2, V = 128k 20.6 / 21.0 (behind ppv_topm_mask 30.6 / 31.5), V = 100k fp32 21.2 / 23.2, V = 256k bf16, list
+// rows, 17.3 / 16.7.  (Two workgroups that part again where they find the row to be no image row were slower still: 34.0 for 30.6.)
+// PPV_TUNE_ROW_SPLIT forces a number of parts.
 // The scratch area the parts meet in comes with the stream or the capture; without one (see ppv_split_scratch) rows are not split.
-int parts_wanted(int V, ppv_dtype dt, int B, double least_kb = 160.0) {
+enum RowCall { SAMPLE, LOCATE, STEP, FIRST_STEP };   // LOCATE: without a cursor
+int parts_wanted(int V, ppv_dtype dt, int B, RowCall call) {
     const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
     const int nt = (V + tile - 1) / tile;
     if (B > PPV_SPLIT_MAX_ROWS) return 1;
@@ -2095,14 +2187,16 @@ int parts_wanted(int V, ppv_dtype dt, int B, double least_kb = 160.0) {
         parts = 1;
         while (B * parts * 2 <= 256 && parts * 2 <= PPV_SPLIT_MAX_PARTS && nt / (parts * 2) >= 6) parts *= 2;
         const double row_kb = (double)V * (dt == PPV_F32 ? 4.0 : 2.0) / 1024.0;
+        double least_kb = call == SAMPLE ? (dt == PPV_F32 ? 104.0 : 60.0) : (dt == PPV_F32 ? 140.0 : (call == FIRST_STEP ? 60.0 : 110.0));
+        if (B > 96 && call != FIRST_STEP) least_kb = call != STEP ? 200.0 : (dt == PPV_F32 ? 180.0 : 110.0);
         if (row_kb * (1.0 - 1.0 / parts) < least_kb) parts = 1;
     }
     while (parts > 1 && ((parts & (parts - 1)) != 0 || parts * 2 > nt)) parts--;   // a power of two, two tiles each
     return parts;
 }
-int parts_for(int V, ppv_dtype dt, int B, hipStream_t hs, SplitScratch **scratch, double least_kb = 160.0) {
+int parts_for(int V, ppv_dtype dt, int B, hipStream_t hs, SplitScratch **scratch, RowCall call) {
     *scratch = nullptr;
-    int parts = parts_wanted(V, dt, B, least_kb);
+    int parts = parts_wanted(V, dt, B, call);
     if (parts > 1) {
         *scratch = ppv_split_scratch(hs, B);
         if (!*scratch) parts = 1;
@@ -2139,7 +2233,8 @@ void launch_decode_kernel(bool loop, dim3 grid, dim3 block, hipStream_t hs, cons
     hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, active, lens, rs, uniforms, logx, lg, flags, \
                        split_shift | (int)(block.x / WAVE) << 8, prefixes, stride, n_steps, B, row_stride, step_stride, ids,  \
                        logZ_valid, scratch, tp, view)
-    if (split_shift && !loop) PPV_LAUNCH_DECODE(false, true, false);
+    if (split_shift && !loop && reg) PPV_LAUNCH_DECODE(false, true, true);
+    else if (split_shift && !loop) PPV_LAUNCH_DECODE(false, true, false);
     else if (loop && reg) PPV_LAUNCH_DECODE(true, false, true);
     else if (loop) PPV_LAUNCH_DECODE(true, false, false);
     else if (reg) PPV_LAUNCH_DECODE(false, false, true);
@@ -2213,9 +2308,9 @@ ppv_status sample_call(const void *logits, ppv_dtype dt, int64_t row_stride, con
         if (B > PPV_NOALLOC_MAX_ROWS) return PPV_ERANGE;
         st = fixed_scratch(&scratch);
         if (st != PPV_OK) return st;
-        if (!small && V > tile) parts = parts_wanted(V, dt, B);
+        if (!small && V > tile) parts = parts_wanted(V, dt, B, SAMPLE);
     } else if (!small && V > tile) {
-        parts = parts_for(V, dt, B, hs, &scratch);
+        parts = parts_for(V, dt, B, hs, &scratch, SAMPLE);
     }
     const int threads = waves_for(V, dt, B, parts) * WAVE;
     const dim3 grid((unsigned)B * (unsigned)parts), block(threads);
@@ -2296,11 +2391,7 @@ ppv_status launch_decode(const ppv_index_t *ix, int32_t *prefixes, int32_t prefi
     }
     hipStream_t hs = (hipStream_t)stream;
     SplitScratch *scratch = nullptr;
-    // A step with a cursor has more to lose: unsplit it draws the token while its tiles are on their way (16 rows, V = 50k fp32,
-    // steps of 172 KB saved: 120 us per loop split, 115 not; 64 rows, V = 128k bf16, 188 KB: 157 and 160).  The first
-    // step, a row under the root's image, is split as constrained_sample's rows are (one row, V = 128k: 15 us unsplit, 8 split;
-    // the loop of 16 steps 97.2 and 90.7 us, 4 rows at V = 250k fp32 101.5 and 87).
-    const int parts = loop ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch, state && !fresh ? 180.0 : 160.0);
+    const int parts = loop ? 1 : parts_for(ix->view.vocab, dt, B, hs, &scratch, !state ? LOCATE : (fresh ? FIRST_STEP : STEP));
     int nw = waves_for(ix->view.vocab, dt, B, parts, !loop && state != nullptr);
     const int tile = (dt == PPV_F32) ? TileGeom<float>::TILE : TileGeom<uint16_t>::TILE;
     const int nt = (ix->view.vocab + tile - 1) / tile;

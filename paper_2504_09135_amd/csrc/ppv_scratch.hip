@@ -35,8 +35,9 @@ uint64_t thread_number() {   // 1, 2, ...
     thread_local const uint64_t mine = ++last;
     return mine;
 }
+size_t bytes_for(int rows) { return offsetof(SplitScratch, row) + (size_t)rows * sizeof(SplitRow); }
 SplitScratch *new_area(int rows) {
-    const size_t bytes = offsetof(SplitScratch, row) + (size_t)rows * sizeof(SplitRow);
+    const size_t bytes = bytes_for(rows);
     SplitScratch *p = nullptr;
     hipError_t e = hipMalloc((void **)&p, bytes);
     if (e == hipErrorOutOfMemory) {
@@ -50,7 +51,7 @@ SplitScratch *new_area(int rows) {
     }
     return p;
 }
-// Areas for captures to come.  Their counters are zeroed on a stream of their own and waited for: what is replayed first, and
+// Areas for captures to come.  They are zeroed on a stream of their own and waited for: what is replayed first, and
 // where, is not known.  (Another thread may be capturing: with the capture mode relaxed that does not forbid these calls.)
 void lay_ready(Device &d) {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
@@ -60,7 +61,7 @@ void lay_ready(Device &d) {
     std::vector<SplitScratch *> made;
     while (ok && (int)(d.spare.size() + made.size()) < SPARES && d.made + (int)made.size() < MOST_CAPTURED) {
         SplitScratch *p = new_area(CAPTURED_ROWS);
-        ok = p && hipMemsetAsync(p->arrivals, 0, sizeof(p->arrivals), own) == hipSuccess;
+        ok = p && hipMemsetAsync(p, 0, bytes_for(CAPTURED_ROWS), own) == hipSuccess;
         if (p) made.push_back(p);
     }
     if (own) {
@@ -107,9 +108,9 @@ SplitScratch *area_for(hipStream_t stream, int rows) {
     if (!p) {
         p = new_area(PPV_SPLIT_MAX_ROWS);
         if (!p) return nullptr;
-        // the arrival counters start at zero (afterwards every launch leaves them at zero); in stream order before the
-        // kernel that is about to be launched
-        if (hipMemsetAsync(p->arrivals, 0, sizeof(p->arrivals), stream) != hipSuccess) {
+        // an area starts as zeros (afterwards every launch leaves zeros); in stream order before the kernel that is about to
+        // be launched
+        if (hipMemsetAsync(p, 0, bytes_for(PPV_SPLIT_MAX_ROWS), stream) != hipSuccess) {
             (void)hipGetLastError();
             (void)hipFree(p);
             return nullptr;

@@ -102,6 +102,28 @@ def test_split_rows_with_temperature_and_a_second_smaller_call():
         check_sample_rows(cfg.dtype, ref, lambda b: ref.mask[b], un, ids, lzv, lza)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_one_area_for_calls_of_every_kind(dtype):
+    """A call leaves its area as zeros, whatever kind its rows were and however many: lists of 1, 64, 65 and 1,000 tokens, images and
+    empty sets take each other's places, with values that are themselves 0 (a reference, the weight of a listed token, a tile without
+    a valid one), and each call gives the unsplit call's bits."""
+    V = 50_001
+    g = torch.Generator(device=DEV).manual_seed(8)
+    counts = [0, 1, 64, 65, 1_000, 20_000]
+    words = torch.zeros((len(counts), (V + 31) // 32), dtype=torch.int32)
+    for i, n in enumerate(counts):
+        m = np.zeros((1, V), np.uint8)
+        m[0, np.random.default_rng(i).choice(V // 2, n, replace=False)] = 1   # (whole tiles without a valid token)
+        words[i] = torch.from_numpy(pack(m)[0])
+    for step, B in enumerate([12, 5, 16, 1, 12]):
+        logits = torch.randn((B, -(-V // 8) * 8), generator=g, device=DEV).mul_(2).to(dtype)[:, :V]
+        logits[::3] = logits[::3].sign() * -150   # references and listed weights of 0
+        logits[::3, ::7] = 0
+        un = torch.rand(B, generator=g, device=DEV)
+        kinds = (torch.arange(B) + step) % len(counts)
+        sample_all_splits(logits, words[kinds].to(DEV), un)
+
+
 @pytest.mark.parametrize("use_state", [True, False])
 def test_split_rows_in_the_decode_step(use_state):
     """The fused decode step with its rows split: the whole loop, every split, bit for bit the unsplit loop."""
