@@ -108,3 +108,18 @@ template <typename V> __device__ inline V wave_incl_scan(V x) {
     t += dpp0<DPP_ROW_BCAST31, 0xC>(t);
     return t;
 }
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// A row as the memory unit's buffer: its address and its length in bytes, up to the 16 that hold its last token (rows start on
+// 16-byte boundaries).  What is asked for behind the length is not read and arrives as 0.
+struct Row {
+    __amdgpu_buffer_rsrc_t buf;
+};
+template <typename T, uint32_t PAD = 15u> __device__ __forceinline__ Row row_of(const T *row, int V) {
+    // (uniform, which the compiler does not see where the row came with a loop)
+    const uint64_t at = (uint64_t)row;
+    const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32) |
+                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    const uint32_t bytes = (uint32_t)__builtin_amdgcn_readfirstlane(V) * (uint32_t)sizeof(T);
+    return {__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (bytes + PAD) & ~PAD, 0x00027000)};
+}

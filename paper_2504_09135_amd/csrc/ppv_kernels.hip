@@ -179,7 +179,6 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(const int32_t *
 // Tiles.  A tile is what one wavefront loads with four 16-byte loads per lane: 2048 bf16 or 1024
 // fp32 tokens.  Load j of lane l holds the EPL consecutive tokens starting at
 // tile*TILE + j*64*EPL + l*EPL, so token order inside a tile is (j, lane, k).
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static constexpr int EPL = 4;  // tokens per 16-byte load
@@ -224,19 +223,6 @@ struct RawTile {
     uint32_t word;   // image path: this lane's word of the tile's mask (requested together with the tile)
 };
 
-// A row as the memory unit's buffer: its address and its length in bytes, up to the 16 that hold its last token (rows start on
-// 16-byte boundaries).  What is asked for behind the length is not read and arrives as 0.
-struct Row {
-    __amdgpu_buffer_rsrc_t buf;
-};
-template <typename T, uint32_t PAD = 15u> __device__ __forceinline__ Row row_of(const T *row, int V) {
-    // (uniform, which the compiler does not see where the row came with a loop)
-    const uint64_t at = (uint64_t)row;
-    const uint64_t base = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32) |
-                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
-    const uint32_t bytes = (uint32_t)__builtin_amdgcn_readfirstlane(V) * (uint32_t)sizeof(T);
-    return {__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (bytes + PAD) & ~PAD, 0x00027000)};
-}
 // A tile is requested with four unconditional 16-byte loads wherever it lies, also at the row's end and behind it; group_of puts
 // -inf behind the end when the tile is used.  Nothing is conditional between request and use, so the compiler can
 // count the loads in flight and wait for exactly the ones a use needs, and the ragged last tile is one like the others.

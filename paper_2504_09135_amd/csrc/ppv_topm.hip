@@ -5,26 +5,33 @@
 //   select   P = softmax(logits) is increasing in the logit, so the top M are found on the logits'
 //            bit patterns, through an order-preserving 32-bit key per token.  M is small against
 //            |V|, so almost every token can be turned away with one comparison:
-//              A. the maximum of every 16-byte group of tokens is histogrammed by its leading 11 key
-//                 bits; the bin that holds the M-th largest group maximum gives a bound L that at
-//                 least M tokens reach.  A wavefront holds eight chunks of the row (8 KB of bf16) in
-//                 registers; when its share of the row is longer, A looks only at those eight --
+//              A. the maxima of groups of tokens (half of what a lane holds, or for large M every 16 bytes) are histogrammed by
+//                 their 11 leading key bits; the bin that holds the M-th largest maximum gives a bound that at
+//                 least M tokens reach.  A wavefront holds eight or sixteen chunks of the row (a chunk: 16 bytes a lane) in
+//                 registers; when its share of the row is longer, A looks only at those --
 //                 the M-th largest of a part of the row is still a lower bound of the row's --
 //                 provided the list has room for what the looser bound lets through (else from as
-//                 many more of its chunks as it takes).  When A has looked at one set of eight, the
+//                 many more of its chunks as it takes).  When A has looked at one set of chunks, the
 //                 maxima inside the bound's bin are counted once more by their next five key bits
-//                 and the bound moves up inside the bin;
-//              B. the tokens that are not below L are listed in LDS in token order, each with its
-//                 logit: usually 1.1 to 1.5 M of them, from registers when A saw the whole row,
-//                 else about as many times more as the share is longer than eight chunks, from the
-//                 one pass over the row (the next eight chunks are asked for before these eight are
-//                 looked at).  bf16 rows are compared two tokens at a time on 16-bit keys, and a
-//                 chunk in which no lane has a token for the list costs a ballot;
-//              C. a radix select over that short list (the keys' upper halves, counted from L, in one
+//                 and the bound moves up inside the bin.  A is over when the prefix has been located, or soon after;
+//              B. the tokens that are not below the bound are listed in LDS in token order, each with its
+//                 key: usually 1.1 to 1.5 M of them, from registers when A saw the whole row,
+//                 else about as many times more as the share is longer than what is held, from the
+//                 one pass over the row (the next chunks are asked for before these are
+//                 looked at).  Of a chunk the maxima of its 16-byte groups are compared, two chunks at a time on 16-bit keys; the
+//                 groups that have a token for the list are queued, one a lane, and listed together;
+//              C. a radix select over that short list (the keys' upper halves, counted from the bound, in one
 //                 histogram of 256 bins; two more digits of 8 bits for fp32) finds the key T of the
-//                 M-th largest token; the list is then cut to the
-//                 tokens above T and the first few equal to T, in increasing token id, so the set
+//                 M-th largest token; of the list, the
+//                 tokens above T and the first few equal to T, in increasing token id, are chosen, so the set
 //                 is unique.
+//            What a call of few rows waits for is a chain of steps of the whole workgroup.  128 rows at V = 128,256 bf16, M = 50, us from
+//            a wavefront's start, before / now: prefix located 3.1 / 4.1 and A done 5.3 / 6.2 (the row, 256 KB for one compute
+//            unit, arrives over the first 4 us: A waited for the prefix, and asked for half of the row later), bound 6.7 / 7.2, list 13.1 / 9.7
+//            (2 to 5 us a wavefront for a handful of tokens, each chunk with one listed by itself, and the row's other half on its
+//            way), chosen 16.5 / 11.3, written 17.2 / 11.7.  Per call, us before / now: this shape 18.3 / 13.6, V = 32k, 256 rows 12.0 / 9.5,
+//            V = 32k, 4,096 rows 73 / 60, V = 256k, 1,024 rows 114 / 104, V = 50k fp32, 384 rows 26.9 / 23.6.  Slower by 2 to 4 % where a
+//            tenth of the row and more is asked for (V = 8,192, M = 1,000: 67.1 / 69.0).
 //            If the list does not fit (a flat row with thousands of equal logits at the cut, or a
 //            workgroup too small to hold it) the same radix select runs over the whole row instead,
 //            one histogram pass per digit and two more passes to gather in token order.
@@ -41,6 +48,7 @@
 //            histogram, no list and no second pass.
 // Nothing here is a dense contraction; the row is read from HBM once (64 KB at V = 32k, bf16).
 #include <cstdlib>
+#include <type_traits>
 
 #include "ppv_device.h"
 #include "ppv_internal.h"
@@ -56,16 +64,14 @@ constexpr int TOPM_WAVES = 16;
 constexpr int TOPM_LIST_BIG = 4096, TOPM_LIST_SMALL = 1024;   // capacity of the candidate list (tokens not below the bound),
                                                               // split evenly over the wavefronts; the small one serves M <= 128 at V <= 65,536
 constexpr int TOPM_SLOTS = 16;    // list entries per thread at most: the list path needs at least LIST / 16 threads
-constexpr int TOPM_HELD = 8;      // chunks of the row a wavefront holds in registers at a time (128 bytes per lane)
+constexpr int TOPM_HELD = 8;      // chunks of the row a wavefront holds in registers at a time (128 bytes per lane) ...
+constexpr int TOPM_HELD_LONG = 16;   // ... where that is the whole share of sixteen wavefronts (see topm_held)
 
 // Bit pattern -> key with the same order as the float value (-0 and +0 share a key).
 __device__ inline uint32_t order_key(uint32_t bits) {
     if (bits == 0x80000000u) bits = 0u;
     return bits ^ ((uint32_t)((int32_t)bits >> 31) | 0x80000000u);
 }
-
-// the bit pattern whose key is k
-__device__ inline uint32_t key_to_bits(uint32_t k) { return (k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k; }
 
 template <typename T> struct KeyChunk;   // what one 16-byte load per lane covers
 template <> struct KeyChunk<float> {
@@ -107,26 +113,20 @@ __device__ inline int load_keys(const T *__restrict__ row, int V, int c, int lan
     return n;
 }
 
-// This lane's 16 bytes of chunk c, from an address that is always inside the row: a chunk beyond the last one
-// reads the last one again, a lane beyond the row's end reads the row's first bytes (the caller discards both,
-// and the tokens of the row's last group that lie beyond its end).  No condition stands between the caller and
+// This lane's 16 bytes of chunk c (c from `end` on: nothing is read and 0 arrives, as behind the row's end; the caller discards
+// that, and the tokens of the row's last group that lie beyond its end).  No condition stands between the caller and
 // the load, so loads for the next batch can be in flight while this batch is worked on.  STREAM: the bytes are
 // not read again (they need not stay in cache).
-template <typename T, bool STREAM = true>
-__device__ inline uint4 load_raw_clamped(const T *__restrict__ row, int V, int nc, int c, int lane) {
-    constexpr int EPL = KeyChunk<T>::EPL;
-    const int cc = c < nc ? c : nc - 1;
-    const int g = (cc * WAVE + lane) * EPL;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 *at = (const u32x4 *)(row + (g < V ? g : 0));
-    const u32x4 v = STREAM ? __builtin_nontemporal_load(at) : *at;
+template <bool STREAM = true> __device__ inline uint4 load_chunk(const Row &row, int c, int end, int lane) {
+    const uint32_t at = (uint32_t)(c < end ? c : 1 << 20) * (WAVE * 16u) + (uint32_t)lane * 16u;
+    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(row.buf, at, 0, STREAM ? 2 /* non-temporal */ : 0);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 // four chunks at once (c .. c+3): four loads in flight per lane
-template <typename T, bool STREAM>
-__device__ inline void load_chunks(const T *__restrict__ row, int V, int nc, int c, int lane, uint4 *r) {
+template <bool STREAM>
+__device__ inline void load_chunks(const Row &row, int c, int end, int lane, uint4 *r) {
 #pragma unroll
-    for (int u = 0; u < 4; u++) r[u] = load_raw_clamped<T, STREAM>(row, V, nc, c + u, lane);
+    for (int u = 0; u < 4; u++) r[u] = load_chunk<STREAM>(row, c + u, end, lane);
 }
 // how many of this lane's tokens of chunk c lie inside the row
 template <typename T> __device__ inline int n_inside(int V, int c, int lane) {
@@ -148,19 +148,6 @@ template <typename T> __device__ inline void unpack_vals(const uint4 &r, float x
     }
 }
 
-// inclusive prefix sum of x over the workgroup's threads in thread order; nw wavefronts
-__device__ inline uint32_t block_incl_scan(uint32_t x, uint32_t *wave_tot, int nw) {
-    const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
-    const uint32_t incl = wave_incl_scan(x);
-    if (lane == WAVE - 1) wave_tot[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int w = 0; w < nw; w++)
-        if (w < wave) before += wave_tot[w];
-    __syncthreads();
-    return before + incl;
-}
-
 // The histogram hist[0..bins) is filled (bins <= 4096).  Finds the digit d with #(digit > d) < need <= #(digit >= d)
 // and leaves it in bc[4], with need - #(digit > d) in bc[5].  If fewer than `need` entries were counted,
 // bc[4] = 0 and bc[5] = need.  Every thread calls; ends with a barrier.
@@ -168,10 +155,7 @@ __device__ inline uint32_t block_incl_scan(uint32_t x, uint32_t *wave_tot, int n
 // bins (runs ordered from the top bin down), a scan over the lanes finds the run in which the count reaches
 // `need`, and that run's bins, one per lane, are scanned the same way.  (A scan over all the workgroup's threads
 // costs three barriers and was 1.5 to 2.2 us of a 16 us call.)
-__device__ inline void pick_digit(const uint32_t *hist, int bins, uint32_t need, uint32_t *wave_tot, uint32_t *bc,
-                                  int nthreads) {
-    (void)wave_tot;
-    (void)nthreads;
+__device__ inline void pick_digit(const uint32_t *hist, int bins, uint32_t need, uint32_t *bc) {
     if (threadIdx.x < WAVE) {
         const int lane = threadIdx.x;
         const int per = (bins + WAVE - 1) / WAVE;        // bins per lane, at most 64
@@ -221,6 +205,13 @@ template <typename T> __device__ inline uint32_t full_key(uint32_t hi_part) {
     return sizeof(T) == 4 ? hi_part : ((hi_part << 16) | ((hi_part >> 15) & 1u ? 0u : 0xFFFFu));
 }
 
+// A barrier for what the workgroup has in LDS: loads from memory stay in flight over it.
+__device__ inline void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 struct TopmLds {
     uint32_t *hist;       // [TOPM_BINS]
     uint32_t *hist3;      // [32] the group maxima inside the bound's bin, by their next five key bits
@@ -230,6 +221,8 @@ struct TopmLds {
     uint32_t *sel;        // [PPV_TOPM_MAX]
     uint32_t *seg_a, *seg_b, *wave_tot;   // [TOPM_WAVES] each
     uint32_t *bc;         // [8]
+    uint4 *queue;         // [64] a wavefront: 16 bytes of the row with a token for the list
+    uint32_t *queue_tok;  // [64] a wavefront
 };
 
 // Radix select over the whole row (any workgroup size, any row): fills sel[0..m) in increasing token id.
@@ -257,7 +250,7 @@ __device__ inline void select_streaming(const T *__restrict__ row, int V, int c0
             }
         }
         __syncthreads();
-        pick_digit(s.hist, bins, need, s.wave_tot, s.bc, nthreads);
+        pick_digit(s.hist, bins, need, s.bc);
         hi_part = (hi_part << (prev_shift - shift)) | s.bc[4];
         need = s.bc[5];
         prev_shift = shift;
@@ -340,252 +333,331 @@ __device__ inline uint32_t pk_above(uint32_t keys, uint32_t thresholds) {
     asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(d), "v"(ones));
     return r;
 }
-// Bound, short list, radix select over the list.  Needs nthreads >= LIST / TOPM_SLOTS and nthreads <= LIST.
-// Returns false (for every thread alike) when the list did not fit; sel is then untouched.  r arrives holding
-// the wavefront's first TOPM_HELD chunks; hist, hist2 and bc[6] were cleared before the workgroup's last barrier.
-// The row is read from memory once: a share longer than r gives the bound from its first chunks only (at least m
-// of THEIR groups reach it, so at least m tokens of the row do) -- as many batches of TOPM_HELD chunks as it takes
-// for the list to have room for what the looser bound lets through, which is about share / those chunks times
-// more; B reads the batches after the first again, from cache, and the rest of the share for the first time.
-template <typename T, int LIST>
-__device__ inline bool select_listed(const T *__restrict__ row, int V, int c0, int c1, int m, const TopmLds &s, int lane,
-                                     int wave, int nthreads, uint4 (&r)[TOPM_HELD]) {
+__device__ inline uint32_t pk_max(uint32_t a, uint32_t b) {
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(us2, a), __builtin_bit_cast(us2, b)));
+}
+// How a row is taken by select_listed: a wavefront's share is the chunks c0 .. c1 - 1 of nc.
+struct TopmShare {
+    int nc, cpw;      // chunks of the row, and of a wavefront (the last ones may have fewer)
+    int c0, c1;
+    int a_batches;    // batches of `held` chunks of each share that A looks at
+    bool kept;        // a wavefront's whole share is in its registers
+    bool by_lane;     // A's groups are what a lane has of a batch (its even chunks, its odd ones), not 16 bytes
+};
+// With the bound from the whole row the list holds 1.1 to 1.5 m tokens when the bound is taken to the key's
+// upper 16 bits (possible when A looks at one batch) and about 4 m of a row of noise when it stays at
+// the histogram's bin, a quarter of an octave; from a_batches batches of the share, cpw / (held a_batches)
+// times more.  One batch if the list then has room for twice 1.3 m times that, else as few as leave room for
+// 4 m times that.  (A list that overflows all the same sends the row to the whole-row select.)
+// by_lane: groups of what a lane holds, two of them, where A's histogram takes eight or sixteen additions a lane otherwise, nearly all to
+// the same few bins.  Tokens thrown into n groups are the largest of n (1 - exp(-tokens / n)) of them: with four groups to a candidate
+// the bound lets 1.15 m tokens through.  A vocabulary may be in an order, though, that has all that are likely next to one another, in one
+// wavefront's share: its 128 groups then let 125 through for m = 80, which its part of the list holds, and soon too many beyond that.
+template <typename T>
+__device__ inline TopmShare share_of_row(int V, int m, int list, int held, int wave, int nthreads) {
     constexpr int EPL = KeyChunk<T>::EPL;
-    const int tid = threadIdx.x, nw = nthreads / WAVE;
-    // ---- A. maxima of the 16-byte groups, histogram of their leading key bits.  The row is taken TOPM_HELD
-    // chunks at a time (as many loads in flight per lane), a_batches batches of each wavefront's share.
-    const int nc = (V + WAVE * EPL - 1) / (WAVE * EPL);
-    const int cpw = (nc + nw - 1) / nw;             // chunks per wavefront (the last ones may have fewer)
-    const bool kept = cpw <= TOPM_HELD;             // r holds a wavefront's whole share
-    // With the bound from the whole row the list holds 1.1 to 1.5 m tokens when the bound is taken to the key's
-    // upper 16 bits (below: possible when A looks at one batch) and about 4 m of a row of noise when it stays at
-    // the histogram's bin, a quarter of an octave; from a_batches batches of the share, cpw / (TOPM_HELD a_batches)
-    // times more.  One batch if the list then has room for twice 1.3 m times that, else as few as leave room for
-    // 4 m times that.  (A list that overflows all the same sends the row to the whole-row select.)
-    const int all_batches = (cpw + TOPM_HELD - 1) / TOPM_HELD;
-    const long long want = (long long)m * cpw <= 4ll * LIST ? 1 : ((long long)m * cpw + 2ll * LIST - 1) / (2ll * LIST);
-    const int a_batches = want > all_batches ? all_batches : (int)want;
-    const uint32_t R = (uint32_t)(LIST / nw);
-    const uint32_t base = (uint32_t)wave * R;
-    const int a_end = c0 + a_batches * TOPM_HELD < c1 ? c0 + a_batches * TOPM_HELD : c1;
-    uint32_t gk[TOPM_HELD];   // the keys of this lane's group maxima in the batch A looked at last, and which of them count
-    uint32_t gvalid = 0u;
-    for (int c = c0; c < a_end; c += TOPM_HELD) {
-        gvalid = 0u;
-        if (c != c0) {   // (chunks that A reads from memory are read again in B: from cache)
-            load_chunks<T, false>(row, V, nc, c, lane, r);
-            load_chunks<T, false>(row, V, nc, c + 4, lane, r + 4);
+    const int nw = nthreads / WAVE;
+    TopmShare h;
+    h.nc = (V + WAVE * EPL - 1) / (WAVE * EPL);
+    h.cpw = (h.nc + nw - 1) / nw;
+    h.c0 = wave * h.cpw;
+    h.c1 = (h.c0 + h.cpw < h.nc) ? h.c0 + h.cpw : h.nc;
+    h.kept = held == TOPM_HELD_LONG || h.cpw <= held;
+    const int all = (h.cpw + held - 1) / held;
+    const long long want = 2ll * m * h.cpw <= (long long)held * list ? 1 : ((long long)m * h.cpw * 4 + (long long)held * list - 1) / ((long long)held * list);
+    h.a_batches = h.kept ? 1 : want > all ? all : (int)want;
+    h.by_lane = m <= 80 && nthreads >= 2 * m;
+    return h;
+}
+
+// The upper halves of the largest keys of this lane's 16 bytes of two chunks, c and c + 1, side by side (the first in the lower
+// half); 0, a key that only NaNs have, where there is no token (`end`: the first chunk that is not to be looked at).  A token may have that
+// key too; a group of nothing else then does not count, which makes the bound lower if anything.  -0 is just below +0 here.
+template <typename T> __device__ inline uint32_t pair_key(const uint4 &a, const uint4 &b, int V, int c, int end, int lane) {
+    uint32_t half[2];   // bf16: the largest of the even and of the odd tokens; fp32: the largest, in the upper half
+    const uint4 *w[2] = {&a, &b};
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const bool ragged = (c + i + 1) * WAVE * KeyChunk<T>::EPL > V;   // (wave-uniform) the row ends inside this chunk
+        const int n = ragged ? n_inside<T>(V, c + i, lane) : 0;
+        const uint32_t v[4] = {w[i]->x, w[i]->y, w[i]->z, w[i]->w};
+        uint32_t k[4];
+        if (sizeof(T) == 2) {
+#pragma unroll
+            for (int j = 0; j < 4; j++) k[j] = pk_keys(v[j]);
+            if (ragged) {
+#pragma unroll
+                for (int j = 0; j < 4; j++) k[j] &= (2 * j < n ? 0x0000FFFFu : 0u) | (2 * j + 1 < n ? 0xFFFF0000u : 0u);
+            }
+            half[i] = pk_max(pk_max(k[0], k[1]), pk_max(k[2], k[3]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; j++) k[j] = v[j] ^ ((uint32_t)((int32_t)v[j] >> 31) | 0x80000000u);
+            if (ragged) {
+#pragma unroll
+                for (int j = 0; j < 4; j++) k[j] = j < n ? k[j] : 0u;
+            }
+            half[i] = max(max(k[0], k[1]), max(k[2], k[3]));
         }
+        if (c + i >= end) half[i] = 0u;   // (wave-uniform)
+    }
+    const uint32_t upper = __builtin_amdgcn_perm(half[1], half[0], 0x07060302u);
+    return sizeof(T) == 4 ? upper : pk_max(upper, __builtin_amdgcn_perm(half[1], half[0], 0x05040100u));
+}
+// do_group(key): the upper half of the largest key of each of this lane's groups
+template <int PAIRS, typename DO> __device__ inline void each_group(const TopmShare &h, const uint32_t (&pairs)[PAIRS], DO do_group) {
+    if (h.by_lane) {   // (uniform)
+        uint32_t mx = pairs[0];
 #pragma unroll
-        for (int u = 0; u < TOPM_HELD; u++) {
-            if (c + u >= c1) continue;   // (wave-uniform) short rows: most of r is unused
-            float x[EPL];
-            unpack_vals<T>(r[u], x);
-            const int n = n_inside<T>(V, c + u, lane);
-            if ((c + u + 1) * WAVE * EPL > V) {   // (wave-uniform) the row ends inside this chunk
+        for (int p = 1; p < PAIRS; p++) mx = pk_max(mx, pairs[p]);
+        do_group(mx & 0xFFFFu);
+        do_group(mx >> 16);
+    } else {
 #pragma unroll
-                for (int j = 1; j < EPL; j++)
-                    if (j >= n) x[j] = -INFINITY;
-            }
-            float gm = x[0];
-#pragma unroll
-            for (int j = 1; j < EPL; j++) gm = fmaxf(gm, x[j]);
-            gk[u] = order_key(__float_as_uint(gm));
-            if (n > 0) {
-                atomicAdd(&s.hist[gk[u] >> TOPM_SHIFT], 1u);
-                gvalid |= 1u << u;
-            }
+        for (int p = 0; p < PAIRS; p++) {
+            do_group(pairs[p] & 0xFFFFu);
+            do_group(pairs[p] >> 16);
         }
     }
-    __syncthreads();
-    pick_digit(s.hist, TOPM_BINS, (uint32_t)m, s.wave_tot, s.bc, nthreads);
-    // At least m groups have their maximum in this bin or above, so at least m tokens are not below the bin's
-    // lower edge.  With fewer than m groups in the row the bin is 0 and its edge is a NaN: nothing is below it.
-    uint32_t edge_key16 = s.bc[4] << (16 - TOPM_BITS);
-    if (a_batches == 1 && s.bc[4] != 0u) {   // (uniform)
+}
+// A: the maxima of groups of the row's tokens, and the histogram of their leading key bits (cleared before the workgroup's last
+// barrier).  r arrives holding the wavefront's first HELD chunks; pairs: the maxima of the batch that A looks at last, by 16 bytes.
+template <typename T, int HELD>
+__device__ inline void group_maxima(const Row &buf, int V, const TopmShare &h, uint32_t *hist, int lane, uint4 (&r)[HELD],
+                                    uint32_t (&pairs)[HELD / 2]) {
+    const int a_end = h.c0 + h.a_batches * HELD < h.c1 ? h.c0 + h.a_batches * HELD : h.c1;
+#pragma unroll
+    for (int p = 0; p < HELD / 2; p++) pairs[p] = 0u;   // (a wavefront may have no share)
+    for (int c = h.c0; c < a_end; c += HELD) {
+        if (HELD == TOPM_HELD && c != h.c0) {   // (chunks that A reads from memory are read again in B: from cache)
+#pragma unroll
+            for (int u = 0; u < HELD; u += 4) load_chunks<false>(buf, c + u, h.c1, lane, r + u);
+        }
+#pragma unroll
+        for (int p = 0; p < HELD / 2; p++) {
+            pairs[p] = 0u;
+            if (c + 2 * p < h.c1) pairs[p] = pair_key<T>(r[2 * p], r[2 * p + 1], V, c + 2 * p, h.c1, lane);   // (wave-uniform)
+        }
+        each_group(h, pairs, [&](uint32_t key16) {
+            if (key16 != 0u) atomicAdd(&hist[key16 >> (16 - TOPM_BITS)], 1u);
+        });
+    }
+}
+
+// From A's maxima to the cut list: bound, short list, radix select over the list.  Needs nthreads >= LIST / TOPM_SLOTS and
+// nthreads <= LIST.  Returns false (for every thread alike) when the list did not fit; nothing is chosen then.  Otherwise
+// chosen(position, token) is called for each of the m tokens, whose positions are in increasing token id, after the words
+// img[0..n_words), which may be the histogram's, have been cleared.  r, pairs: as group_maxima left them, with a barrier since;
+// hist2, hist3 and bc[6] were cleared before it.
+// The row is read from memory once: a share longer than r gives the bound from its first chunks only (at least m
+// of THEIR groups reach it, so at least m tokens of the row do) -- as many batches of HELD chunks as it takes
+// for the list to have room for what the looser bound lets through; B reads the batches after the first again, from
+// cache, and the rest of the share for the first time.
+template <typename T, int LIST, int HELD, typename CHOSEN>
+__device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, int m, const TopmLds &s, int lane,
+                                     int wave, int nthreads, uint4 (&r)[HELD], uint32_t (&pairs)[HELD / 2], uint32_t *img,
+                                     int n_words, CHOSEN chosen) {
+    constexpr int EPL = KeyChunk<T>::EPL;
+    const int tid = threadIdx.x, nw = nthreads / WAVE;
+    const int c0 = h.c0, c1 = h.c1;
+    const uint32_t R = (uint32_t)(LIST / nw);
+    const uint32_t base = (uint32_t)wave * R;
+    // At least m groups have their maximum in the bin that is picked or above, so at least m tokens are not below the bin's
+    // lower edge.  With fewer than m groups in the row the bin is 0 and nothing is below it.
+    uint32_t edge_key16 = 0u;
+    if ((V + EPL - 1) / EPL >= m) {   // (uniform)
+        pick_digit(s.hist, TOPM_BINS, (uint32_t)m, s.bc);
+        edge_key16 = s.bc[4] << (16 - TOPM_BITS);
+    }
+    if (h.a_batches == 1 && edge_key16 != 0u) {   // (uniform)
         // A bin is a quarter of an octave wide and holds several times m tokens of a row of noise.  The maxima that
         // A has just seen are still in registers: those inside the bin are counted by their next five key bits, and
         // the bound moves up to the thirty-second of the bin in which the count from the top reaches m.
         const uint32_t bin = s.bc[4], rest = s.bc[5];
-#pragma unroll
-        for (int u = 0; u < TOPM_HELD; u++)
-            if (((gvalid >> u) & 1u) && (gk[u] >> TOPM_SHIFT) == bin) atomicAdd(&s.hist3[(gk[u] >> 16) & 31u], 1u);
+        each_group(h, pairs, [&](uint32_t key16) {
+            if (key16 >> (16 - TOPM_BITS) == bin) atomicAdd(&s.hist3[key16 & 31u], 1u);   // (bin is not 0: no empty group)
+        });
         __syncthreads();
-        pick_digit(s.hist3, 32, rest, s.wave_tot, s.bc, nthreads);
+        pick_digit(s.hist3, 32, rest, s.bc);
         edge_key16 |= s.bc[4];
     }
-    const float L = __uint_as_float(key_to_bits(edge_key16 << 16));
-    // ---- B. the tokens that are not below L, in token order, each wavefront into its own part of the list,
-    // each with its logit
+    // ---- B. the tokens whose keys are not below the edge's, in token order, each wavefront into its own part of the list.
+    // Only the keys' upper halves are compared.  (-0 has the key just under +0's in `pairs` and +0's here; an edge at +0 is lowered by one
+    // there, so that -0 stays listed: the list may hold more than it need, never less.  C goes by the exact keys.)
+    // The groups of 16 bytes that have a token for the list are put into a queue of one per lane, from registers, and then each lane
+    // lists what its group holds: one pass of the code that lists, usually, where a wavefront with a token in each of five chunks
+    // took five (16 chunks a wavefront, M = 50: 2.2 to 4.5 us).
     uint32_t cnt = 0;   // wave-uniform
-    // bf16 rows are compared two tokens at a time on 16-bit keys: everything whose key is not below the edge's.
-    // (-0 has the key just under +0's here; an edge at +0 is lowered by one so that it stays listed.  The list may
-    // hold more than the float comparison would put there, never less: C goes by the exact keys.)
     const uint32_t th16 = edge_key16 == 0x8000u ? 0x7FFEu : edge_key16 - 1u;   // listed: key above th16 (edge 0: all)
-    const uint32_t th_pk = th16 | (th16 << 16);
-    if (a_batches > 1) {   // A has left its last chunks in r
-        load_chunks<T, true>(row, V, nc, c0, lane, r);
-        load_chunks<T, true>(row, V, nc, c0 + 4, lane, r + 4);
-    }
-    auto list_chunk = [&](const uint4 &rr, int cc) {   // chunk cc of the row, this lane's 16 bytes of it in rr
-        // a[i]: word i of the lane's group; bf16: a 1 in each half whose token is listed, fp32: 1 if it is
-        uint32_t a[4];
-        const uint32_t w[4] = {rr.x, rr.y, rr.z, rr.w};
+    const uint32_t th_pk = (th16 & 0xFFFFu) | (th16 << 16);   // bf16 tokens are compared two at a time
+    uint4 *queue = s.queue + wave * WAVE;
+    uint32_t *queue_tok = s.queue_tok + wave * WAVE;   // the group's first token
+    auto list_group = [&](const uint4 &g, uint32_t first_tok, bool have) __attribute__((always_inline)) {
+        const uint32_t w[4] = {g.x, g.y, g.z, g.w};
+        uint32_t pm = 0u;   // bit j: token j of this lane's group is listed
         if (sizeof(T) == 2) {
-            if (edge_key16 == 0u) {   // (uniform)
-                a[0] = a[1] = a[2] = a[3] = 0x00010001u;
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; i++) a[i] = pk_above(pk_keys(w[i]), th_pk);
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; i++) a[i] = !(__uint_as_float(w[i]) < L) ? 1u : 0u;
-        }
-        if ((cc + 1) * WAVE * EPL > V) {   // (wave-uniform) the row's last chunk: nothing behind the row's end
-            const int n = n_inside<T>(V, cc, lane);
 #pragma unroll
             for (int i = 0; i < 4; i++) {
-                if (sizeof(T) == 2) a[i] &= (2 * i < n ? 0x0000FFFFu : 0u) | (2 * i + 1 < n ? 0xFFFF0000u : 0u);
-                else a[i] = i < n ? a[i] : 0u;
+                const uint32_t a = pk_above(pk_keys(w[i]), th_pk);
+                pm |= ((a | (a >> 15)) & 3u) << (2 * i);
             }
-        }
-        const uint64_t hit = __ballot((a[0] | a[1] | a[2] | a[3]) != 0u);
-        if (hit == 0ull) return;   // most chunks of a long row
-        uint32_t pm;   // bit j: token j of this lane's group is listed
-        if (sizeof(T) == 2) {
-            pm = 0u;
+            if (edge_key16 == 0u) pm = 0xFFu;   // (uniform)
+        } else {
 #pragma unroll
-            for (int i = 0; i < 4; i++) pm |= ((a[i] | (a[i] >> 15)) & 3u) << (2 * i);
-        } else {
-            pm = a[0] | (a[1] << 1) | (a[2] << 2) | (a[3] << 3);
+            for (int i = 0; i < 4; i++) pm |= order_key(w[i]) >> 16 >= edge_key16 ? 1u << i : 0u;
         }
+        const int n = V - (int)first_tok;
+        if (n < EPL) pm &= n > 0 ? (1u << n) - 1u : 0u;   // nothing behind the row's end
+        if (!have) pm = 0u;
         const uint32_t pc = (uint32_t)__popc(pm);
-        uint32_t at, tot;
-        if (__ballot(pc > 1u) == 0ull) {   // (wave-uniform) one token per lane at most: positions from the ballot
-            at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u));
-            tot = (uint32_t)__popcll(hit);
-        } else {
-            const uint32_t incl = wave_incl_scan(pc);
-            tot = last_lane(incl);
-            at = cnt + incl - pc;
-        }
-        const uint32_t first_tok = (uint32_t)((cc * WAVE + lane) * EPL);
+        const uint32_t incl = wave_incl_scan(pc);
+        uint32_t at = cnt + incl - pc;
         while (pm) {
             const uint32_t j = (uint32_t)__ffs((int)pm) - 1u;
             // the token's logit out of the group, by masks (no branch, no indexed register)
-            uint32_t key;
+            uint32_t bits;
             if (sizeof(T) == 2) {
                 const uint32_t m4 = 0u - ((j >> 2) & 1u), m2 = 0u - ((j >> 1) & 1u);
                 const uint32_t lo = (w[2] & m4) | (w[0] & ~m4), hi = (w[3] & m4) | (w[1] & ~m4);
                 const uint32_t ww = (hi & m2) | (lo & ~m2);
-                key = (ww << ((~j & 1u) << 4)) & 0xFFFF0000u;
+                bits = (ww << ((~j & 1u) << 4)) & 0xFFFF0000u;
             } else {
                 const uint32_t m2 = 0u - ((j >> 1) & 1u), m1 = 0u - (j & 1u);
                 const uint32_t lo = (w[1] & m1) | (w[0] & ~m1), hi = (w[3] & m1) | (w[2] & ~m1);
-                key = (hi & m2) | (lo & ~m2);
+                bits = (hi & m2) | (lo & ~m2);
             }
+            const uint32_t key = order_key(bits);
             if (at < R) {
                 s.list_tok[base + at] = first_tok + j;
                 s.list_key[base + at] = key;
             }
-            // C's histogram, while the key is at hand: the upper key half, counted from the bound (NaNs that
-            // slipped through the comparison lie below it and are left out here as they are in C)
-            const uint32_t k16 = order_key(key) >> 16;
-            if (k16 >= edge_key16) {
-                const uint32_t rel = k16 - edge_key16;
-                atomicAdd(&s.hist2[rel < (uint32_t)(TOPM_CBINS - 1) ? rel : (uint32_t)(TOPM_CBINS - 1)], 1u);
-            }
+            // C's histogram, while the key is at hand: the upper key half, counted from the bound
+            const uint32_t rel = (key >> 16) - edge_key16;
+            atomicAdd(&s.hist2[rel < (uint32_t)(TOPM_CBINS - 1) ? rel : (uint32_t)(TOPM_CBINS - 1)], 1u);
             at++;
             pm &= pm - 1u;
         }
-        cnt += tot;
+        cnt += last_lane(incl);
     };
-    if (kept) {
+    // N chunks from c + FIRST on, in r[FIRST ..] with their maxima in pairs; what does not fill the queue waits for more (not `last`)
+    uint32_t waiting = 0u;   // wave-uniform: groups in the queue
+    auto list_some = [&](auto first, auto count, int c, bool last) __attribute__((always_inline)) {
+        constexpr int FIRST = decltype(first)::value, N = decltype(count)::value;
+        for (uint32_t round = 0;; round += WAVE) {
+            uint32_t groups = waiting;
 #pragma unroll
-        for (int u = 0; u < TOPM_HELD; u++)
-            if (c0 + u < c1) list_chunk(r[u], c0 + u);
-    } else {
-        // the two halves of r take turns: four chunks are asked for again as soon as they have been looked at,
-        // from addresses that always lie inside the row, while the other four are looked at
-        constexpr int HALF = TOPM_HELD / 2;
-        for (int c = c0; c < c1; c += TOPM_HELD) {
-#pragma unroll
-            for (int h = 0; h < TOPM_HELD; h += HALF) {
-#pragma unroll
-                for (int u = h; u < h + HALF; u++)
-                    if (c + u < c1) list_chunk(r[u], c + u);
-#pragma unroll
-                for (int u = h; u < h + HALF; u++) r[u] = load_raw_clamped<T, true>(row, V, nc, c + TOPM_HELD + u, lane);
+            for (int u = FIRST; u < FIRST + N; u++) {
+                const uint32_t key16 = (u & 1) ? pairs[u / 2] >> 16 : pairs[u / 2] & 0xFFFFu;
+                const bool mine = edge_key16 == 0u ? c + u < c1 : key16 > th16;
+                const uint64_t hit = __ballot(mine);
+                if (hit) {   // (uniform) most chunks of a long row have nothing
+                    const uint32_t pos = groups + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u)) - round;
+                    if (mine && pos < (uint32_t)WAVE) {
+                        queue[pos] = r[u];
+                        queue_tok[pos] = (uint32_t)(((c + u) * WAVE + lane) * EPL);
+                    }
+                    groups += (uint32_t)__popcll(hit);
+                }
+            }
+            const uint32_t left = groups - round;
+            if (left < (uint32_t)WAVE && !(last && left != 0u)) {
+                waiting = left;
+                break;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (the queue is this wavefront's own)
+            const bool have = (uint32_t)lane < left;
+            const int at = have ? lane : 0;
+            list_group(queue[at], queue_tok[at], have);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (left <= (uint32_t)WAVE) {
+                waiting = 0u;
+                break;
             }
         }
+    };
+    constexpr int HALF = HELD / 2;
+    if (HELD == TOPM_HELD_LONG || h.kept) {
+        list_some(std::integral_constant<int, 0>(), std::integral_constant<int, HELD>(), c0, true);
+    } else {
+        if (h.a_batches > 1) {   // A has left its last chunks in r
+#pragma unroll
+            for (int u = 0; u < HELD; u += 4) load_chunks<true>(buf, c0 + u, c1, lane, r + u);
+        }
+        // the two halves of r take turns: half of the chunks are asked for again as soon as they have been looked at,
+        // while the others are looked at
+        auto maxima = [&](int p0, int c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = p0; p < p0 + HALF / 2; p++) pairs[p] = pair_key<T>(r[2 * p], r[2 * p + 1], V, c + 2 * p, c1, lane);
+        };
+        for (int c = c0; c < c1; c += HELD) {
+            maxima(0, c);
+            list_some(std::integral_constant<int, 0>(), std::integral_constant<int, HALF>(), c, false);
+#pragma unroll
+            for (int u = 0; u < HALF; u++) r[u] = load_chunk(buf, c + HELD + u, c1, lane);
+            maxima(HALF / 2, c);
+            list_some(std::integral_constant<int, HALF>(), std::integral_constant<int, HALF>(), c, c + HELD >= c1);
+#pragma unroll
+            for (int u = HALF; u < HELD; u++) r[u] = load_chunk(buf, c + HELD + u, c1, lane);
+        }
     }
-    if (lane == 0) {
-        s.seg_a[wave] = cnt < R ? cnt : R;
-        if (cnt > R) atomicOr(&s.bc[6], 1u);
-    }
+    if (lane == 0 && cnt > R) atomicOr(&s.bc[6], 1u);
     __syncthreads();
     if (s.bc[6] != 0u) return false;
-    const uint32_t edge16 = edge_key16;
+    for (int i = tid; i < n_words; i += nthreads) img[i] = 0u;   // (where the queues were)
 
-    // ---- C. the key T of the m-th largest token, from the list.  Thread t answers for the entries t*S .. t*S+S-1
-    // of the list, which lie in its own wavefront's part (S = R / 64).
-    const int S = LIST / nthreads;
-    const uint32_t mine = s.seg_a[wave];
-    const uint32_t o0 = (uint32_t)(lane * S);
-    const uint32_t n_mine = o0 < mine ? (mine - o0 < (uint32_t)S ? mine - o0 : (uint32_t)S) : 0u;   // entries of this thread
-    const uint32_t *lk = s.list_key + base + o0, *lt = s.list_tok + base + o0;
-    // Every listed token's key is at or above the edge key (NaNs that slipped through the float comparison
-    // aside: they were left out), so the upper 16 key bits, counted from the edge, are small numbers: the one
+    // ---- C. the key T of the m-th largest token, from the list: lane l answers for the entries l, l + 64, ... of its
+    // wavefront's part.
+    const uint32_t *lk = s.list_key + base, *lt = s.list_tok + base;
+    // Every listed token's key is at or above the edge key, so the upper 16 key bits, counted from the edge, are small numbers: the one
     // histogram over them that B has filled settles the upper half of T.  A row whose m-th largest token lies
     // further above the bound than the histogram is long (TOPM_CBINS - 1 values of the upper half) goes to the
     // whole-row select.
-    pick_digit(s.hist2, TOPM_CBINS, (uint32_t)m, s.wave_tot, s.bc, nthreads);
+    pick_digit(s.hist2, TOPM_CBINS, (uint32_t)m, s.bc);
     if (s.bc[4] == (uint32_t)(TOPM_CBINS - 1)) return false;   // T lies in the overflow bin
-    uint32_t hi_part = edge16 + s.bc[4], need = s.bc[5];
+    uint32_t hi_part = edge_key16 + s.bc[4], need = s.bc[5];
     if (sizeof(T) == 4) {   // fp32: the lower half of T, eight bits at a time
         for (int shift = 8; shift >= 0; shift -= 8) {
             __syncthreads();
             for (int i = tid; i < 256; i += nthreads) s.hist[i] = 0u;
             __syncthreads();
-            for (uint32_t q = 0; q < n_mine; q++) {
-                const uint32_t k = order_key(lk[q]);
+            for (uint32_t i = (uint32_t)lane; i < cnt; i += WAVE) {
+                const uint32_t k = lk[i];
                 if ((k >> (shift + 8)) == hi_part) atomicAdd(&s.hist[(k >> shift) & 255u], 1u);
             }
             __syncthreads();
-            pick_digit(s.hist, 256, need, s.wave_tot, s.bc, nthreads);
+            pick_digit(s.hist, 256, need, s.bc);
             hi_part = (hi_part << 8) | s.bc[4];
             need = s.bc[5];
         }
+        for (int i = tid; i < 256; i += nthreads) s.hist[i] = 0u;   // (where img may lie)
     }
-    // (a key at or above T is at or above the edge: the entries dropped above do not come back below)
-    const uint32_t T_key = full_key<T>(hi_part);
+    const uint32_t T_key = sizeof(T) == 4 ? hi_part : full_key<T>(hi_part);
     const uint32_t take_eq = need;
-    // positions: list order is token order, and threads hold consecutive entries
-    uint32_t g = 0, e = 0;
-    for (uint32_t q = 0; q < n_mine; q++) {
-        const uint32_t k = order_key(lk[q]);
-        g += k > T_key ? 1u : 0u;
-        e += k == T_key ? 1u : 0u;
+    // positions: list order is token order
+    uint32_t n_gt = 0, n_eq = 0;   // wave-uniform
+    for (uint32_t q = 0; q < cnt; q += WAVE) {
+        const uint32_t i = q + (uint32_t)lane;
+        const uint32_t k = i < cnt ? lk[i] : 0u;
+        n_gt += (uint32_t)__popcll(__ballot(i < cnt && k > T_key));
+        n_eq += (uint32_t)__popcll(__ballot(i < cnt && k == T_key));
     }
-    const uint32_t packed = g | (e << 16);   // both counts stay below 2^16 (the list has at most 4096 entries)
-    const uint32_t before = block_incl_scan(packed, s.wave_tot, nw) - packed;
-    uint32_t gt_before = before & 0xFFFFu, eq_before = before >> 16;
-    for (uint32_t q = 0; q < n_mine; q++) {
-        const uint32_t k = order_key(lk[q]);
-        if (k > T_key) {
-            const uint32_t pos = gt_before + (eq_before < take_eq ? eq_before : take_eq);
-            if (pos < (uint32_t)m) s.sel[pos] = lt[q];
-            gt_before++;
-        } else if (k == T_key) {
-            if (eq_before < take_eq) {
-                const uint32_t pos = gt_before + eq_before;
-                if (pos < (uint32_t)m) s.sel[pos] = lt[q];
-            }
-            eq_before++;
-        }
-    }
+    if (lane == 0) s.wave_tot[wave] = n_gt | (n_eq << 16);   // both stay below 2^16 (the list has at most 4096 entries)
     __syncthreads();
+    const uint32_t before = wave_sum(lane < wave ? s.wave_tot[lane] : 0u);   // entries of either kind in the wavefronts before this one
+    uint32_t gt_before = before & 0xFFFFu, eq_before = before >> 16;
+    for (uint32_t q = 0; q < cnt; q += WAVE) {
+        const uint32_t i = q + (uint32_t)lane;
+        const uint32_t k = i < cnt ? lk[i] : 0u;
+        const bool is_gt = i < cnt && k > T_key, is_eq = i < cnt && k == T_key;
+        const uint64_t gt = __ballot(is_gt), eq = __ballot(is_eq);
+        const uint32_t g = gt_before + __builtin_amdgcn_mbcnt_hi((uint32_t)(gt >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)gt, 0u));
+        const uint32_t e = eq_before + __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
+        const uint32_t pos = g + (e < take_eq ? e : take_eq);
+        if ((is_gt || (is_eq && e < take_eq)) && pos < (uint32_t)m) chosen((int)pos, lt[i]);
+        gt_before += (uint32_t)__popcll(gt);
+        eq_before += (uint32_t)__popcll(eq);
+    }
     return true;
 }
 
@@ -676,11 +748,11 @@ __device__ inline void count_chunk(const uint4 &raw, int V, int c, int lane, int
 }
 
 // The mask row of a prefix with n <= TOPM_COUNT_MAX children (entries cb .. cb + n - 1, or the one child `only`),
-// restricted to the m most probable tokens.  Every thread of the workgroup calls; r holds the wavefront's first TOPM_HELD chunks; tot[] was
+// restricted to the m most probable tokens.  Every thread of the workgroup calls; r holds the wavefront's first HELD chunks; tot[] was
 // cleared before the last barrier.
-template <typename T>
-__device__ inline void count_children(const IndexView &ix, const T *__restrict__ row, int V, int nc, int c0, int c1,
-                                      int m, uint32_t cb, uint32_t only, int n, uint4 (&r)[TOPM_HELD], uint32_t *tot,
+template <typename T, int HELD>
+__device__ inline void count_children(const IndexView &ix, const T *__restrict__ row, const Row &buf, int V, const TopmShare &share,
+                                      int m, uint32_t cb, uint32_t only, int n, uint4 (&r)[HELD], uint32_t *tot,
                                       uint32_t *__restrict__ out, int n_words, int lane, int nthreads) {
     // child j in lane j: its token and that token's logit
     uint32_t ctok = 0u;
@@ -701,14 +773,14 @@ __device__ inline void count_children(const IndexView &ix, const T *__restrict__
     }
     // the pairs of r take turns: a pair of chunks is asked for again as soon as it has been counted, while the
     // other three pairs are counted or on their way
-    for (int c = c0; c < c1; c += TOPM_HELD) {
+    for (int c = share.c0; c < share.c1; c += HELD) {
 #pragma unroll
-        for (int h = 0; h < TOPM_HELD; h += 2) {
+        for (int h = 0; h < HELD; h += 2) {
 #pragma unroll
             for (int u = h; u < h + 2; u++)
-                if (c + u < c1) count_chunk<T>(r[u], V, c + u, lane, n, tokc, thr, cnt);
+                if (c + u < share.c1) count_chunk<T>(r[u], V, c + u, lane, n, tokc, thr, cnt);
 #pragma unroll
-            for (int u = h; u < h + 2; u++) r[u] = load_raw_clamped<T>(row, V, nc, c + TOPM_HELD + u, lane);
+            for (int u = h; u < h + 2; u++) r[u] = load_chunk(buf, c + HELD + u, share.c1, lane);
         }
     }
 #pragma unroll
@@ -736,44 +808,51 @@ __device__ inline void count_children(const IndexView &ix, const T *__restrict__
     }
 }
 
-template <typename T, int LIST>
-__global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(const int32_t *__restrict__ prefixes,
+// Words of LDS that are the histogram first, then the wavefronts' queues, then the mask row; the children's tokens follow
+__host__ __device__ inline int topm_words(int n_words, int nthreads) {
+    const int queues = nthreads * 5;
+    return max(max(TOPM_BINS, n_words), queues);
+}
+
+template <typename T, int LIST, int HELD>
+__global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM_LIST_SMALL ? 5 : 4) void topm_kernel(const int32_t *__restrict__ prefixes,
                                                                 const int32_t *__restrict__ lens,
                                                                 const T *__restrict__ logits, int64_t row_stride,
                                                                 int32_t stride, int M, int force_streaming,
                                                                 int32_t *__restrict__ top_ids,
                                                                 uint8_t *__restrict__ mask_V,
                                                                 uint32_t *__restrict__ mask, IndexView ix) {
-    constexpr int EPL = KeyChunk<T>::EPL;
-    extern __shared__ __align__(16) uint32_t smem[];  // max(TOPM_BINS, n_words) words, then heavy_min (1 at least) words for kids
-    uint32_t *img = smem;                             // [n_words] the row of the mask, once the histogram is done with
+    constexpr bool WHOLE = HELD == TOPM_HELD_LONG;    // a row is no longer than what its wavefronts hold, and is not counted
+    extern __shared__ __align__(16) uint32_t smem[];  // topm_lds() bytes, the histogram first
     __shared__ uint32_t list_tok[LIST], list_key[LIST];
     __shared__ uint32_t hist2[TOPM_CBINS], hist3[32];
     __shared__ uint32_t sel[PPV_TOPM_MAX];
     __shared__ uint32_t seg_a[TOPM_WAVES], seg_b[TOPM_WAVES], wave_tot[TOPM_WAVES];
     __shared__ uint32_t bc[8];
-    const TopmLds lds = {smem, hist3, hist2, list_tok, list_key, sel, seg_a, seg_b, wave_tot, bc};
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (WAVE - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
     const int nthreads = blockDim.x, nw = nthreads / WAVE;
     const int V = ix.vocab, n_words = ix.n_words;
+    uint32_t *img = smem;                             // [n_words] the row of the mask, in the end
+    uint4 *queue = (uint4 *)smem;                     // [nthreads] once the histogram is done with
+    uint32_t *queue_tok = smem + 4 * nthreads;        // [nthreads]
     const int m = M < V ? M : V;                      // candidates of this row
     // the tokens of the prefix's children, when they are listed (not a heavy prefix: at most heavy_min of them)
-    uint32_t *kids = smem + (n_words > TOPM_BINS ? n_words : TOPM_BINS);
+    uint32_t *kids = smem + topm_words(n_words, nthreads);
+    const TopmLds lds = {smem, hist3, hist2, list_tok, list_key, sel, seg_a, seg_b, wave_tot, bc, queue, queue_tok};
     const T *row = logits + (size_t)b * (size_t)row_stride;
 
-    // this wavefront's contiguous share of the row, in chunks of one 16-byte load per lane
-    const int nc = (V + WAVE * EPL - 1) / (WAVE * EPL);
-    const int cpw = (nc + nw - 1) / nw;
-    const int c0 = wave * cpw, c1 = (c0 + cpw < nc) ? c0 + cpw : nc;
+    const Row buf = row_of(row, V);
+    const TopmShare h = share_of_row<T>(V, m, LIST, HELD, wave, nthreads);
 
     const bool listed = force_streaming != 1 && nthreads * TOPM_SLOTS >= LIST && nthreads <= LIST;
     // a caller that asks for the mask alone: prefixes with few children are settled by counting (see count_children)
     const bool counting = force_streaming == 0 && !top_ids && !mask_V;
-    uint4 r[TOPM_HELD];
-    if (listed || counting) {   // in flight while the prefix is located
-        load_chunks<T, true>(row, V, nc, c0, lane, r);
-        if (cpw > 4) load_chunks<T, true>(row, V, nc, c0 + 4, lane, r + 4);   // (uniform; a short row has no second half)
+    int32_t mine = 0;
+    int t = 0;
+    if (wave == 0) {   // (before the row: memory answers in the order of its requests)
+        mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
+        t = lens[b];
     }
     if (counting && tid < TOPM_COUNT_MAX) seg_a[tid] = 0u;
     if (listed) {   // what the list select starts from
@@ -781,10 +860,15 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(const int32_t *_
         for (int i = tid; i < TOPM_CBINS; i += nthreads) hist2[i] = 0u;
         if (tid < 32) hist3[tid] = 0u;
         if (tid == 0) bc[6] = 0u;
+        lds_barrier();   // (ahead of the row: a wavefront whose requests wait for their turn goes on to nothing else)
+    }
+    uint4 r[HELD];
+    if (listed || counting) {   // in flight while the prefix is located
+#pragma unroll
+        for (int u = 0; u < HELD; u += 4)
+            if (u == 0 || h.cpw > u) load_chunks<true>(buf, h.c0 + u, h.c1, lane, r + u);   // (uniform; a short row has no second half)
     }
     if (wave == 0) {   // the part every candidate row shares: locate the prefix once
-        const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
-        int t = lens[b];
         t = t < 0 ? 0 : (t > stride ? stride : t);
         const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
         if (lane == 0) {
@@ -795,7 +879,19 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(const int32_t *_
             bc[7] = w.only;
         }
     }
-    __syncthreads();   // the walk's verdict
+    // Counting pays where the selection would read part of the row twice, and of rows that are held where M is large or the launch is (then
+    // it saves work, not time on the way).
+    const bool count_few = counting && !WHOLE && (!listed || h.a_batches > 1 || (h.kept && (nw < 8 || m > 256)));
+    auto is_counted = [&]() {   // (after the walk's verdict)
+        const uint32_t few = bc[3] - bc[2];
+        return count_few && few <= (uint32_t)(sizeof(T) == 2 ? TOPM_COUNT_MAX : TOPM_COUNT_MAX / 2) && (bc[7] != PPV_NO_SLOT || few <= ix.heavy_min);
+    };
+    // The maxima are taken while wavefront 0 is on its way through the index, unless the row may do without them.
+    if (count_few) __syncthreads();
+    const bool maxima = listed && !(count_few && is_counted());
+    uint32_t pairs[HELD / 2];
+    if (maxima) group_maxima<T, HELD>(buf, V, h, smem, lane, r, pairs);
+    __syncthreads();   // the walk's verdict, and the maxima's histogram
     const uint32_t node = bc[0];
     const bool found = bc[1] != 0u;
     const uint32_t cb = bc[2], ce = bc[3], only = bc[7];
@@ -810,13 +906,8 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(const int32_t *_
             }
             return;
         }
-        // Counting pays where the selection would hold the row in registers anyway (it skips the bound, the list and
-        // the cut: 9 against 12 us at V = 32k) and where the selection would read part of the row twice; a long row
-        // that the selection reads once (bound from its first chunks alone, see select_listed) is no faster counted
-        // (V = 256k: 120 against 117 us).
-        const bool select_reads_once = listed && (cpw <= TOPM_HELD || (long long)m * cpw <= 4ll * LIST);
-        if (n <= TOPM_COUNT_MAX && (only != PPV_NO_SLOT || (uint32_t)n <= ix.heavy_min) && (cpw <= TOPM_HELD || !select_reads_once)) {
-            count_children<T>(ix, row, V, nc, c0, c1, m, cb, only, n, r, seg_a, out, n_words, lane, nthreads);
+        if (!WHOLE && is_counted()) {   // (r holds the share's first chunks)
+            count_children<T, HELD>(ix, row, buf, V, h, m, cb, only, n, r, seg_a, out, n_words, lane, nthreads);
             return;
         }
     }
@@ -828,36 +919,46 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE) void topm_kernel(const int32_t *_
         for (int i = tid; i < n; i += nthreads) kids[i] = ix.ent[cb + (uint32_t)i].tok & PPV_NODE_TOKEN;
     }
     const uint32_t slot = (found && !kids_listed) ? heavy_slot_of(ix, node) : PPV_NO_SLOT;
-    // ---- select
-    bool done = false;
-    if (listed) done = select_listed<T, LIST>(row, V, c0, c1, m, lds, lane, wave, nthreads, r);
-    if (!done) select_streaming<T>(row, V, c0, c1, m, lds, lane, wave, nthreads);
-    for (int i = tid; i < n_words; i += nthreads) img[i] = 0u;   // the histogram's LDS becomes the mask row
-    __syncthreads();
-
-    // ---- verify: one candidate per thread
+    // ---- select, and verify what is selected: candidate i is token t
     const uint32_t *image = ix.heavy_bits + (size_t)(slot != PPV_NO_SLOT ? slot : 0u) * (size_t)n_words;
-    for (int i = tid; i < M; i += nthreads) {
-        int32_t t = -1;
+    auto verify = [&](int i, uint32_t t) {
         uint32_t ok = 0;
-        if (i < m && sel[i] < (uint32_t)V) {
-            t = (int32_t)sel[i];
+        if (t < (uint32_t)V) {
             if (slot != PPV_NO_SLOT) {
-                ok = (image[t >> 5] >> (t & 31)) & 1u;
+                ok = (image[t >> 5] >> (t & 31u)) & 1u;
             } else if (kids_listed) {   // first child whose token is not below t
                 int lo = 0, hi = n;
                 while (lo < hi) {
                     const int mid = lo + (hi - lo) / 2;
-                    if (kids[mid] < (uint32_t)t) lo = mid + 1;
+                    if (kids[mid] < t) lo = mid + 1;
                     else hi = mid;
                 }
-                ok = (lo < n && kids[lo] == (uint32_t)t) ? 1u : 0u;
+                ok = (lo < n && kids[lo] == t) ? 1u : 0u;
             }
-            if (ok) atomicOr(&img[t >> 5], 1u << (t & 31));
+            if (ok) atomicOr(&img[t >> 5], 1u << (t & 31u));
         }
-        if (top_ids) top_ids[(size_t)b * (size_t)M + i] = t;
+        if (top_ids) top_ids[(size_t)b * (size_t)M + i] = t < (uint32_t)V ? (int32_t)t : -1;
         if (mask_V) mask_V[(size_t)b * (size_t)M + i] = (uint8_t)ok;
+    };
+    // (a wavefront whose part of the list is long has a few of the chosen in each of many rounds: these are verified with all lanes
+    // busy, behind one more barrier)
+    const bool gather = 2 * m >= nthreads;
+    bool done = false;
+    if (listed) {
+        done = select_listed<T, LIST, HELD>(buf, V, h, m, lds, lane, wave, nthreads, r, pairs, img, n_words, [&](int i, uint32_t t) {
+            if (gather) sel[i] = t;   // (uniform)
+            else verify(i, t);
+        });
     }
+    if (!done) {
+        select_streaming<T>(row, V, h.c0, h.c1, m, lds, lane, wave, nthreads);
+        for (int i = tid; i < n_words; i += nthreads) img[i] = 0u;   // the histogram's LDS becomes the mask row
+    }
+    if (!done || gather) {   // (uniform)
+        __syncthreads();
+        for (int i = tid; i < m; i += nthreads) verify(i, sel[i]);
+    }
+    for (int i = m + tid; i < M; i += nthreads) verify(i, PPV_NO_SLOT);   // (fewer tokens than candidates)
     __syncthreads();
 
     // ---- extend
@@ -885,6 +986,19 @@ int topm_waves(int V, ppv_dtype dt, int B) {
     return nw;
 }
 
+// Chunks that a wavefront holds.  The wavefronts of rows with sixteen are alone on their compute unit and may hold sixteen each, which
+// is a row of up to 131,072 bf16 or 65,536 fp32 tokens: all of it is asked for at once and looked at in registers.
+int topm_held(int V, ppv_dtype dt, int nw) {
+    const int per = (dt == PPV_F32 ? 4 : 8) * WAVE;
+    const int cpw = ((V + per - 1) / per + nw - 1) / nw;
+    return nw == TOPM_WAVES && cpw > TOPM_HELD && cpw <= TOPM_HELD_LONG ? TOPM_HELD_LONG : TOPM_HELD;
+}
+
+// LDS besides what the kernel declares
+size_t topm_lds(const IndexView &ix, int threads) {
+    return (size_t)(topm_words(ix.n_words, threads) + (int)(ix.heavy_min ? ix.heavy_min : 1u)) * sizeof(uint32_t);
+}
+
 }  // namespace
 
 extern "C" ppv_status ppv_topm_mask(const ppv_index_t *ix, const int32_t *prefixes, int32_t prefix_stride,
@@ -903,21 +1017,24 @@ extern "C" ppv_status ppv_topm_mask(const ppv_index_t *ix, const int32_t *prefix
     // testing aid: PPV_TUNE_TOPM_STREAMING = 1 sends every row through the whole-row radix select; 2 keeps the usual
     // select but takes the top M also where counting would do (mask-only calls)
     const int force_streaming = ppv_tuning(PPV_TUNE_TOPM_STREAMING);
-    const size_t lds = ((size_t)(ix->view.n_words > TOPM_BINS ? ix->view.n_words : TOPM_BINS) + (ix->view.heavy_min ? ix->view.heavy_min : 1u)) * sizeof(uint32_t);
+    const size_t lds = topm_lds(ix->view, threads);
     const dim3 grid((unsigned)B), block(threads);
     hipStream_t hs = (hipStream_t)stream;
-#define PPV_LAUNCH_TOPM(T, LIST)                                                                                      \
-    hipLaunchKernelGGL((topm_kernel<T, LIST>), grid, block, lds, hs, prefixes, lens, (const T *)logits, row_stride,    \
-                       prefix_stride, M, force_streaming, top_ids, mask_V, mask, ix->view)
+#define PPV_LAUNCH_TOPM(T, LIST, HELD)                                                                                \
+    hipLaunchKernelGGL((topm_kernel<T, LIST, HELD>), grid, block, lds, hs, prefixes, lens, (const T *)logits,          \
+                       row_stride, prefix_stride, M, force_streaming, top_ids, mask_V, mask, ix->view)
     // a few hundred tokens reach the bound when M is small and the row not too long (the bound's bin holds a share
     // of the row): then a quarter of the LDS does, and more rows fit a compute unit
     const bool small_list = M <= 128 && V <= 65536;
+    const bool long_share = topm_held(V, dt, threads / WAVE) == TOPM_HELD_LONG;
     if (dt == PPV_F32) {
-        if (small_list) PPV_LAUNCH_TOPM(float, TOPM_LIST_SMALL);
-        else PPV_LAUNCH_TOPM(float, TOPM_LIST_BIG);
+        if (long_share) PPV_LAUNCH_TOPM(float, TOPM_LIST_BIG, TOPM_HELD_LONG);
+        else if (small_list) PPV_LAUNCH_TOPM(float, TOPM_LIST_SMALL, TOPM_HELD);
+        else PPV_LAUNCH_TOPM(float, TOPM_LIST_BIG, TOPM_HELD);
     } else {
-        if (small_list) PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_SMALL);
-        else PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_BIG);
+        if (long_share) PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_BIG, TOPM_HELD_LONG);
+        else if (small_list) PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_SMALL, TOPM_HELD);
+        else PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_BIG, TOPM_HELD);
     }
 #undef PPV_LAUNCH_TOPM
     PPV_HIP_TRY(hipGetLastError());

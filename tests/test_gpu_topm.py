@@ -205,6 +205,42 @@ def test_topm_long_rows_bound_from_the_first_chunks(dtype):
     index.free()
 
 
+@pytest.mark.parametrize("dtype,chunk", [("f32", 256), ("bf16", 512)])
+@pytest.mark.parametrize("chunks", [128, 129, 241, 256, 257])
+def test_topm_rows_held_whole(dtype, chunk, chunks):
+    """Sixteen wavefronts hold a row of 129 to 256 chunks of one load per lane in registers; beyond, it is streamed.  The last chunk is
+    ragged, the last wavefronts' shares may be short or empty.  M on both sides of where the bound's groups change (80: half a lane's tokens, above: 16
+    bytes) and of where the chosen are gathered before they are verified (512)."""
+    V = chunks * chunk - 7
+    rng = np.random.default_rng(chunks)
+    S = W.constraint_set_from_lists([[int(v)] for v in rng.choice(V, 1500, replace=False)] + [[V - 1, 3], [V - 1, V - 2]], V)
+    X = oracle.SortedArray(S.tokens, S.offsets, V)
+    index = ppv.ppv_build_index(S.tokens, S.offsets, V)
+    P = np.full((6, 2), W.PAD_TOKEN, np.int32)
+    L = np.zeros(6, np.int32)
+    P[1, 0], L[1] = V - 1, 1
+    lf = rng.normal(0, 2, size=(6, V)).astype(np.float32)
+    lf[2, :] = -np.inf
+    lf[2, -3:] = 1.0                                          # fewer values than candidates, in the row's last 16 bytes
+    lf[3, :] = (rng.integers(0, 2000, size=V) == 0) * 1.0     # a few ones, 0 everywhere else
+    lf[4, :] = np.where(np.arange(V) % 2 == 0, -0.0, 0.0)
+    lf[4, rng.choice(V, 40, replace=False)] = 3.0
+    lf[5, :4096] += 30.0                                      # the largest next to one another, in one or two wavefronts' shares
+    if dtype == "bf16":
+        bits = (lf.view(np.uint32) >> 16).astype(np.uint16)
+        lf = (bits.astype(np.uint32) << 16).view(np.float32)
+        padded = np.zeros((6, -(-V // 8) * 8), np.uint16)
+        padded[:, :V] = bits
+        ld = to_dev(padded.view(np.int16)).view(torch.bfloat16)[:, :V]
+    else:
+        padded = np.zeros((6, -(-V // 4) * 4), np.float32)
+        padded[:, :V] = lf
+        ld = to_dev(padded)[:, :V]
+    for M in (1, 50, 80, 81, 511, 512, 1024):
+        assert_topm_parity(index, X, P, L, lf, ld, M)
+    index.free()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("V", [200, 4104])
 def test_topm_mask_alone_counts_the_tokens_before_each_child(dtype, V):
