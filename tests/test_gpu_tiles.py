@@ -318,3 +318,30 @@ def test_decoding_under_logits_of_any_size(dtype, V, fill, T):
     for a, b in zip(*runs):
         assert np.array_equal(a, b)
     assert (runs[0][1] == L).all()
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 1024), ("f32", 997), ("f32", 260), ("f32", 3), ("bf16", 2048), ("bf16", 2041), ("bf16", 520)])
+def test_rows_of_one_tile_find_their_token(dtype, V):
+    """Rows of a single tile: one valid token at the edges of lanes, groups and the row, two in one lane, two at the ends of two groups, and
+    rows that are valid throughout; mask bits behind the vocabulary are set and do not count."""
+    per, group = (8, 512) if dtype == "bf16" else (4, 256)
+    rng = np.random.default_rng(V)
+    spots = sorted({p for p in (0, 1, per - 1, per, group - 1, group, 2 * group, V - 2, V - 1) if 0 <= p < V})
+    sets = [[p] for p in spots] + [[p, p + 1] for p in spots if p + 1 < V] + [[spots[0], spots[-1]], list(range(V)), list(range(0, V, 7))]
+    sets = sets + sets
+    lg = rng.normal(0, 2, size=(len(sets), V)).astype(np.float32)
+    un = np.concatenate([np.zeros(len(sets) // 2), np.full(len(sets) // 2, 1 - 2.0 ** -24)]).astype(np.float32)   # the first and the last
+    un[len(sets) // 2 - 2:len(sets) // 2] = 0.5
+    mask = np.ones((len(sets), -(-V // 32) * 32), np.uint8)
+    mask[:, :V] = 0
+    for b, s in enumerate(sets):
+        mask[b, s] = 1
+    dev, x = on_device(lg, dtype)
+    ids = torch.full((len(sets),), -9, dtype=torch.int32, device=DEV)
+    lzv, lza = torch.zeros(len(sets), device=DEV), torch.zeros(len(sets), device=DEV)
+    ppv.constrained_sample(dev, to_dev(np.packbits(mask, axis=1, bitorder="little").view(np.int32)), to_dev(un), ids, lzv, lza)
+    ids, lzv, lza = ids.cpu().numpy(), lzv.cpu().numpy(), lza.cpu().numpy()
+    for b, s in enumerate(sets):
+        check_row(x[b], np.array(s), un[b], ids[b], lzv[b], lza[b])
+        if len(s) <= 2:
+            assert ids[b] == (s[0] if un[b] == 0 else s[-1])
