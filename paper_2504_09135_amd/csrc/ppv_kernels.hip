@@ -66,7 +66,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(const int32_t *__res
     extern __shared__ __align__(16) uint32_t smem[];
     const int n_words = ix.n_words;
     uint32_t *img = smem;            // [n_words]
-    uint32_t *bc = smem + n_words;   // [5]: node, found, cb, ce, only
+    uint32_t *bc = smem + n_words;   // [5]: slot, found, cb, ce, only
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     if (wave == 0) {
         const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(const int32_t *__res
         t = t < 0 ? 0 : (t > stride ? stride : t);
         Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
         if (lane == 0) {
-            bc[0] = w.node;
+            bc[0] = w.slot;
             bc[1] = w.found ? 1u : 0u;
             bc[2] = w.found ? w.cb : 0u;
             bc[3] = w.found ? w.ce : 0u;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(const int32_t *__res
         }
     }
     __syncthreads();
-    const uint32_t node = bc[0];
+    const uint32_t slot = bc[0];
     const bool found = bc[1] != 0u;
     const uint32_t cb = bc[2], ce = bc[3];
     uint32_t *out = mask + (size_t)b * (size_t)n_words;
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_kernel(const int32_t *__res
         return;
     }
     if (found && ce - cb > ix.heavy_min) {  // ready-made image: plain copy
-        const uint32_t *src = ix.heavy_bits + (size_t)heavy_slot_of(ix, node) * (size_t)n_words;
+        const uint32_t *src = ix.heavy_bits + (size_t)slot * (size_t)n_words;
         if (wide && (((uintptr_t)ix.heavy_bits) & 15u) == 0) {
             for (int i = tid; i < n_quads; i += MASK_THREADS) ((uint4 *)out)[i] = ((const uint4 *)src)[i];
         } else {
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(const int32_t *
     if (w.only != PPV_NO_SLOT) {
         if ((uint32_t)lane == (w.only & PPV_NODE_TOKEN) >> 5) word = 1u << (w.only & 31u);
     } else if (nchild > ix.heavy_min) {   // ready-made image
-        if (lane < n_words) word = ix.heavy_bits[(size_t)heavy_slot_of(ix, w.node) * (size_t)n_words + lane];
+        if (lane < n_words) word = ix.heavy_bits[(size_t)w.slot * (size_t)n_words + lane];
     } else if (nchild > 0u) {      // nchild <= heavy_min <= 64
         const uint32_t tok = (uint32_t)lane < nchild ? (ix.ent[w.cb + (uint32_t)lane].tok & PPV_NODE_TOKEN) : 0u;
         for (uint32_t i = 0; i < nchild; i++) {   // uniform trip count
@@ -1513,7 +1513,7 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     if (w.only != PPV_NO_SLOT) {
         if ((uint32_t)lane == (w.only & PPV_NODE_TOKEN) >> 5) word = 1u << (w.only & 31u);
     } else if (nchild > ix.heavy_min) {   // ready-made image
-        if (lane < n_words) word = ix.heavy_bits[(size_t)heavy_slot_of(ix, w.node) * (size_t)n_words + lane];
+        if (lane < n_words) word = ix.heavy_bits[(size_t)w.slot * (size_t)n_words + lane];
     } else if (nchild > 0u) {      // nchild <= heavy_min <= 64: one child per lane
         const uint32_t tok = (uint32_t)lane < nchild ? (ix.ent[w.cb + (uint32_t)lane].tok & PPV_NODE_TOKEN) : 0u;
         for (uint32_t i = 0; i < nchild; i++) {   // uniform trip count
@@ -1551,7 +1551,7 @@ __global__ __launch_bounds__(MASK_THREADS) void decode_begin_kernel(const int32_
         st.node = w.found ? w.node : PPV_NO_SLOT;
         st.cb = w.found ? w.cb : 0u;
         st.ce = w.found ? w.ce : 0u;
-        st.slot = (w.found && w.ce - w.cb > ix.heavy_min) ? heavy_slot_of(ix, w.node) : PPV_NO_SLOT;
+        st.slot = (w.found && w.ce - w.cb > ix.heavy_min) ? w.slot : PPV_NO_SLOT;
         st.tok0 = st.child0 = st.child1 = st.flags = 0u;   // nothing looked ahead
         state[b] = st;
         active[b] = (w.found && !w.member) ? 1 : 0;
@@ -1700,20 +1700,28 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         }
         rl.have_gx = __builtin_amdgcn_readfirstlane(rl.have_gx ? 1 : 0) != 0 && wave == 0;
     }
+    // without a cursor wavefront 0 locates the prefix from the root: its tokens are asked for before the 4 KB tile as well
+    const bool locate = !REG && !state;
+    int32_t mine = 0;
+    if (locate && wave == 0) mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
     RawTile first;
     const Share share = share_of(nt, vwave, sp.parts * nw);
     load_tile<T>(row_of(row, V), share.first(), lane, first);   // in flight during the index work
     t = t < 0 ? 0 : (t > stride ? stride : t);
     uint32_t only = PPV_NO_SLOT;   // without a cursor, the one child of a prefix of a single member: no node is looked at then
-    if (!REG && !state) {  // no cursor: locate the prefix from the root (wave 0), then share it
+    if (locate) {  // (then it shares what it has found; a single child goes straight into the list)
         if (wave == 0) {
-            const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
             const Walk w = walk_prefix<LOOP>(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
             if (lane == 0) {
+                sh.bc_i[3] = (int)w.slot;
                 sh.bc_i[4] = (int)(w.found ? w.node : PPV_NO_SLOT);
                 sh.bc_i[5] = (int)(w.found ? w.cb : 0u);
                 sh.bc_i[6] = (int)(w.found ? w.ce : 0u);
                 sh.bc_i[7] = (int)w.only;
+                if (!LOOP && w.only != PPV_NO_SLOT) {
+                    sh.list_tok[0] = w.only;
+                    sh.list_child[0] = sh.list_child[1] = 0u;
+                }
             }
         }
         __syncthreads();
@@ -1721,10 +1729,9 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         st.cb = (uint32_t)sh.bc_i[5];
         st.ce = (uint32_t)sh.bc_i[6];
         only = (uint32_t)sh.bc_i[7];
-        st.slot = (st.node != PPV_NO_SLOT && only == PPV_NO_SLOT && st.ce - st.cb > ix.heavy_min)
-                      ? heavy_slot_of(ix, st.node)
-                      : PPV_NO_SLOT;
-        __syncthreads();
+        st.slot = (st.node != PPV_NO_SLOT && only == PPV_NO_SLOT && st.ce - st.cb > ix.heavy_min) ? (uint32_t)sh.bc_i[3]
+                                                                                                : PPV_NO_SLOT;
+        if (LOOP) __syncthreads();
     }
     if (!STEP_REG && (LOOP || only == PPV_NO_SLOT)) check_cursor();
     if (STEP_REG && rl.on) {
@@ -2076,12 +2083,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         if (mode == VALID_LIST) {
             // children are sorted by token: the list is ready as it is.  One entry more than the
             // children is taken along: it closes the last child's own children range.
-            if (!LOOP && only != PPV_NO_SLOT) {
-                if (tid == 0) {
-                    sh.list_tok[0] = only;
-                    sh.list_child[0] = sh.list_child[1] = 0u;
-                }
-            } else {
+            if (LOOP || only == PPV_NO_SLOT) {
                 for (int i = tid; i <= nchild; i += nw * WAVE) {
                     const NodeEnt e = ix.ent[cb + i];
                     sh.list_tok[i] = e.tok;
@@ -2090,7 +2092,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
                 }
             }
             if (LOOP && !REG) member_child = __syncthreads_or(member_child);
-            else __syncthreads();
+            else if (LOOP || only == PPV_NO_SLOT) __syncthreads();
         }
         // (REG: a third tile in registers here costs more than it saves, in chains, which are spilled for it, and where every step
         // is of this kind too.  us with / without: 800 rows at V = 130k bf16 432 / 398; sets of 2 to 6 tokens, 1,000 rows at V = 32k

@@ -872,7 +872,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
         t = t < 0 ? 0 : (t > stride ? stride : t);
         const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
         if (lane == 0) {
-            bc[0] = w.node;
+            bc[0] = w.slot;
             bc[1] = w.found ? 1u : 0u;
             bc[2] = w.found ? w.cb : 0u;
             bc[3] = w.found ? w.ce : 0u;
@@ -892,7 +892,6 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
     uint32_t pairs[HELD / 2];
     if (maxima) group_maxima<T, HELD>(buf, V, h, smem, lane, r, pairs);
     __syncthreads();   // the walk's verdict, and the maxima's histogram
-    const uint32_t node = bc[0];
     const bool found = bc[1] != 0u;
     const uint32_t cb = bc[2], ce = bc[3], only = bc[7];
     const int n = (int)(ce - cb);
@@ -918,7 +917,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
     } else if (kids_listed) {
         for (int i = tid; i < n; i += nthreads) kids[i] = ix.ent[cb + (uint32_t)i].tok & PPV_NODE_TOKEN;
     }
-    const uint32_t slot = (found && !kids_listed) ? heavy_slot_of(ix, node) : PPV_NO_SLOT;
+    const uint32_t slot = (found && !kids_listed) ? bc[0] : PPV_NO_SLOT;
     // ---- select, and verify what is selected: candidate i is token t
     const uint32_t *image = ix.heavy_bits + (size_t)(slot != PPV_NO_SLOT ? slot : 0u) * (size_t)n_words;
     auto verify = [&](int i, uint32_t t) {

@@ -16,10 +16,15 @@ struct Walk {
     uint32_t tok;     // its entry's token word with flags (when found and t > 0)
     uint32_t only;    // PPV_NO_SLOT; or the prefix is one of a single member, and this is its one child's token word (token |
                       // PPV_NODE_TERMINAL): cb, ce say 0, 1 then and node is not known (see walk_prefix)
+    uint32_t slot;    // the node's slot among the heavy ones, PPV_NO_SLOT if it is not heavy or not known
     uint32_t lo, hi;  // rank range in sorted S; lo == hi == insertion rank when not found
     bool found;       // the prefix is a prefix of at least one member
     bool member;      // the prefix itself is in S
 };
+
+__device__ inline uint32_t heavy_slot_of(const IndexView &ix, uint32_t node) {
+    return node < ix.heavy_limit ? ix.heavy_slot[node] : PPV_NO_SLOT;
+}
 
 // Search `key` among the entries [begin, end) (strictly increasing tokens).  `at` is the first
 // position whose token is >= key; on a match tok and child are that entry's and next_child is the child
@@ -82,6 +87,7 @@ __device__ __forceinline__ Walk walk_from(const IndexView &ix, const int32_t *__
             const uint32_t rank = (j < w.ce) ? ix.node_lo[j] : ix.node_hi[w.node];
             w.lo = rank;
             w.hi = rank;
+            w.slot = PPV_NO_SLOT;
             w.found = false;
             w.member = false;
             return w;
@@ -91,6 +97,7 @@ __device__ __forceinline__ Walk walk_from(const IndexView &ix, const int32_t *__
         w.cb = hit.child;
         w.ce = hit.next_child;
     }
+    w.slot = heavy_slot_of(ix, w.node);   // (with the ranks: where a caller asked for it after the walk it was a trip to memory more)
     w.lo = ix.node_lo[w.node];
     w.hi = ix.node_hi[w.node];
     w.member = (w.tok & PPV_NODE_TERMINAL) != 0u;
@@ -184,7 +191,7 @@ __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *
                 if (len == 0) {
                     const bool same = lane > D || ix.x_tok[(size_t)a + lane] == mine;
                     const NodeEnt e0 = ix.ent[g], e1 = ix.ent[g + 1];
-                    const uint32_t g_lo = ix.node_lo[g], g_hi = ix.node_hi[g];
+                    const uint32_t g_lo = ix.node_lo[g], g_hi = ix.node_hi[g], g_slot = heavy_slot_of(ix, g);
                     if (__ballot(!same) == 0ull) {
                         if (D + 1 == t) {   // the whole prefix: nothing left to descend
                             Walk w;
@@ -193,6 +200,7 @@ __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *
                             w.ce = e1.child;
                             w.tok = e0.tok;
                             w.only = PPV_NO_SLOT;
+                            w.slot = g_slot;
                             w.lo = g_lo;
                             w.hi = g_hi;
                             w.found = true;
@@ -215,6 +223,7 @@ __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *
                             Walk w;
                             w.node = 0u;
                             w.cb = 0u;
+                            w.slot = PPV_NO_SLOT;
                             w.found = m == t;
                             if (w.found) {
                                 w.ce = m < len ? 1u : 0u;
@@ -246,10 +255,6 @@ __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *
         }
     }
     return walk_from(ix, prefix, t, lane, mine, depth, node, tok, cb, ce);
-}
-
-__device__ inline uint32_t heavy_slot_of(const IndexView &ix, uint32_t node) {
-    return node < ix.heavy_limit ? ix.heavy_slot[node] : PPV_NO_SLOT;
 }
 
 }  // namespace
