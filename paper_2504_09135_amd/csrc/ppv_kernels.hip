@@ -153,7 +153,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(const int32_t *
     const int32_t mine = first_tokens(prefixes + (size_t)b * (size_t)stride, stride, lane);
     int t = lens[b];
     t = t < 0 ? 0 : (t > stride ? stride : t);
-    const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
+    const Walk w = walk_prefix<false, false>(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
     if (lane == 0) {
         if (range_lo) range_lo[b] = w.lo;
         if (range_hi) range_hi[b] = w.hi;
@@ -164,7 +164,7 @@ __global__ __launch_bounds__(MASK_THREADS) void mask_rows_kernel(const int32_t *
     if (w.only != PPV_NO_SLOT) {
         if ((uint32_t)lane == (w.only & PPV_NODE_TOKEN) >> 5) word = 1u << (w.only & 31u);
     } else if (nchild > ix.heavy_min) {   // ready-made image
-        if (lane < n_words) word = ix.heavy_bits[(size_t)w.slot * (size_t)n_words + lane];
+        if (lane < n_words) word = ix.heavy_bits[(size_t)heavy_slot_of(ix, w.node) * (size_t)n_words + lane];
     } else if (nchild > 0u) {      // nchild <= heavy_min <= 64
         const uint32_t tok = (uint32_t)lane < nchild ? (ix.ent[w.cb + (uint32_t)lane].tok & PPV_NODE_TOKEN) : 0u;
         for (uint32_t i = 0; i < nchild; i++) {   // uniform trip count
@@ -1507,13 +1507,13 @@ __global__ __launch_bounds__(ONE_TILE_ROWS *WAVE) void sample_next_one_tile_kern
     const T *row = logits + (size_t)b * (size_t)row_stride;
     load_tile<T>(row_of(row, V), 0, lane, rt);   // in flight during the walk
     t = t < 0 ? 0 : (t > stride ? stride : t);
-    const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
+    const Walk w = walk_prefix<false, false>(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
     uint32_t word = 0u;
     const uint32_t nchild = w.found ? w.ce - w.cb : 0u;
     if (w.only != PPV_NO_SLOT) {
         if ((uint32_t)lane == (w.only & PPV_NODE_TOKEN) >> 5) word = 1u << (w.only & 31u);
     } else if (nchild > ix.heavy_min) {   // ready-made image
-        if (lane < n_words) word = ix.heavy_bits[(size_t)w.slot * (size_t)n_words + lane];
+        if (lane < n_words) word = ix.heavy_bits[(size_t)heavy_slot_of(ix, w.node) * (size_t)n_words + lane];
     } else if (nchild > 0u) {      // nchild <= heavy_min <= 64: one child per lane
         const uint32_t tok = (uint32_t)lane < nchild ? (ix.ent[w.cb + (uint32_t)lane].tok & PPV_NODE_TOKEN) : 0u;
         for (uint32_t i = 0; i < nchild; i++) {   // uniform trip count

@@ -67,6 +67,7 @@ __device__ __forceinline__ Found wave_search(const NodeEnt *__restrict__ ent, ui
 // The descent from a known node: token i of the prefix is searched among the children of the node reached
 // by tokens 0..i-1, for i = start .. t-1.  `mine` is lane l's token l of the prefix (the first 64 tokens
 // in one coalesced load; token i is broadcast from lane i).
+template <bool SLOT>
 __device__ __forceinline__ Walk walk_from(const IndexView &ix, const int32_t *__restrict__ prefix, int t, int lane,
                                           int32_t mine, int start, uint32_t node, uint32_t tokw, uint32_t cb, uint32_t ce) {
     Walk w;
@@ -97,7 +98,7 @@ __device__ __forceinline__ Walk walk_from(const IndexView &ix, const int32_t *__
         w.cb = hit.child;
         w.ce = hit.next_child;
     }
-    w.slot = heavy_slot_of(ix, w.node);   // (with the ranks: where a caller asked for it after the walk it was a trip to memory more)
+    w.slot = SLOT ? heavy_slot_of(ix, w.node) : PPV_NO_SLOT;   // (with the ranks: where a caller asked for it after the walk it was a trip to memory more)
     w.lo = ix.node_lo[w.node];
     w.hi = ix.node_hi[w.node];
     w.member = (w.tok & PPV_NODE_TERMINAL) != 0u;
@@ -150,11 +151,13 @@ __device__ inline void prefix_hash_finish(uint32_t h1, uint32_t h2, uint32_t siz
 // What bounds it is the chain of loads that wait for each other: prefix, bucket, member's tokens (and the root's children
 // where nothing was found).  Open addressing at half load, a node by node_at and its entry took 14.5 us for the masks of
 // 1,024 prefixes (V = 256k) and 5.6 us for those of 128; 9.4 and 4.1 us this way.
+// SLOT: the slot is wanted in the same trip as the ranks; kernels of a wavefront to a row, of which thousands share the memory's attention,
+// ask for it where they need it (mask + sample of 4,096 rows over codes 9.79 us, 9.88 with the slots of all).
 // `mine` = first_tokens(prefix, stride, lane), requested by the caller before the prefix's length is known.
 __device__ inline int32_t first_tokens(const int32_t *__restrict__ prefix, int stride, int lane) {
     return (lane < stride) ? prefix[lane] : 0;
 }
-template <bool NODE = false>
+template <bool NODE = false, bool SLOT = true>
 __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *__restrict__ prefix, int32_t mine, int t,
                                             int lane) {
     uint32_t node = 0u, tok = 0u, cb = ix.ent[0].child, ce = ix.ent[1].child;   // where the descent starts: the root, or
@@ -191,7 +194,7 @@ __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *
                 if (len == 0) {
                     const bool same = lane > D || ix.x_tok[(size_t)a + lane] == mine;
                     const NodeEnt e0 = ix.ent[g], e1 = ix.ent[g + 1];
-                    const uint32_t g_lo = ix.node_lo[g], g_hi = ix.node_hi[g], g_slot = heavy_slot_of(ix, g);
+                    const uint32_t g_lo = ix.node_lo[g], g_hi = ix.node_hi[g], g_slot = SLOT ? heavy_slot_of(ix, g) : PPV_NO_SLOT;
                     if (__ballot(!same) == 0ull) {
                         if (D + 1 == t) {   // the whole prefix: nothing left to descend
                             Walk w;
@@ -254,7 +257,7 @@ __device__ __forceinline__ Walk walk_prefix(const IndexView &ix, const int32_t *
             }
         }
     }
-    return walk_from(ix, prefix, t, lane, mine, depth, node, tok, cb, ce);
+    return walk_from<SLOT>(ix, prefix, t, lane, mine, depth, node, tok, cb, ce);
 }
 
 }  // namespace
