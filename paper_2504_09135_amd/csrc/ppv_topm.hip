@@ -29,7 +29,7 @@
 //            a wavefront's start, before / now: prefix located 3.1 / 4.1 and A done 5.3 / 6.2 (the row, 256 KB for one compute
 //            unit, arrives over the first 4 us: A waited for the prefix, and asked for half of the row later), bound 6.7 / 7.2, list 13.1 / 9.7
 //            (2 to 5 us a wavefront for a handful of tokens, each chunk with one listed by itself, and the row's other half on its
-//            way), chosen 16.5 / 11.3, written 17.2 / 11.7.  Per call, us before / now: this shape 18.3 / 13.6, V = 32k, 256 rows 12.0 / 9.5,
+//            way), chosen 16.5 / 11.3, written 17.2 / 11.7.  Per call, us before / now: this shape 18.3 / 13.6, V = 32k, 256 rows 12.0 / 9.9,
 //            V = 32k, 4,096 rows 73 / 60, V = 256k, 1,024 rows 114 / 104, V = 50k fp32, 384 rows 26.9 / 23.6.  Slower by 2 to 4 % where a
 //            tenth of the row and more is asked for (V = 8,192, M = 1,000: 67.1 / 69.0).
 //            If the list does not fit (a flat row with thousands of equal logits at the cut, or a
@@ -353,7 +353,8 @@ struct TopmShare {
 // by_lane: groups of what a lane holds, two of them, where A's histogram takes eight or sixteen additions a lane otherwise, nearly all to
 // the same few bins.  Tokens thrown into n groups are the largest of n (1 - exp(-tokens / n)) of them: with four groups to a candidate
 // the bound lets 1.15 m tokens through.  A vocabulary may be in an order, though, that has all that are likely next to one another, in one
-// wavefront's share: its 128 groups then let 125 through for m = 80, which its part of the list holds, and soon too many beyond that.
+// wavefront's share: its 128 groups then let 125 through for m = 80, which a part of 256 holds, and soon too many beyond that.  (In a part of
+// 128 logits that fall as 1.5 log of the id, V = 32k, 256 rows, M = 50, did not fit: 36 us with the whole-row select, 13 with groups of 16 bytes.)
 template <typename T>
 __device__ inline TopmShare share_of_row(int V, int m, int list, int held, int wave, int nthreads) {
     constexpr int EPL = KeyChunk<T>::EPL;
@@ -367,7 +368,7 @@ __device__ inline TopmShare share_of_row(int V, int m, int list, int held, int w
     const int all = (h.cpw + held - 1) / held;
     const long long want = 2ll * m * h.cpw <= (long long)held * list ? 1 : ((long long)m * h.cpw * 4 + (long long)held * list - 1) / ((long long)held * list);
     h.a_batches = h.kept ? 1 : want > all ? all : (int)want;
-    h.by_lane = m <= 80 && nthreads >= 2 * m;
+    h.by_lane = m <= 80 && nthreads >= 2 * m && list / nw >= 256;
     return h;
 }
 
