@@ -18,9 +18,9 @@
  *     data are not made; checks on host-visible arguments are.
  *   - An index is immutable after it is built; calls on different streams may run concurrently.
  *   - constrained_sample, ppv_sample_next, ppv_decode_step and ppv_decode_first_step spread the rows of a small batch over
- *     several workgroups, which meet in a scratch area.  Eager calls use one that belongs to their stream (4.3 MB; with
+ *     several workgroups, which meet in a scratch area.  Eager calls use one that belongs to their stream (7.5 MB; with
  *     hipStreamPerThread to the thread, for the first 64 threads that pass it), captured ones one that belongs to the capture
- *     (1 MB; up to 256 captures per GPU), so graphs may be replayed at the same time as one another and as eager calls, on any
+ *     (1.9 MB; up to 256 captures per GPU), so graphs may be replayed at the same time as one another and as eager calls, on any
  *     streams.  (One graph instantiated twice must not be replayed at the same time as itself.)  The first eager call that needs
  *     an area on a stream allocates it, and such calls lay areas ready for captures to come; a capture that finds none ready
  *     does not split its rows, with the same results.  All areas are kept until the process ends.
@@ -172,13 +172,16 @@ ppv_status constrained_sample(const void *logits, ppv_dtype dt, int64_t row_stri
  * constrained_sample_noalloc -- constrained_sample for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  constrained_sample spreads the rows
  * of a small batch over several workgroups, which meet in a scratch area that it allocates per stream on first
- * use; this call uses a fixed scratch array in device memory instead (about 4.3 MB, held on every GPU the library
+ * use; this call uses a fixed scratch array in device memory instead (about 7.5 MB, held on every GPU the library
  * runs on until the process ends) and calls no hipMalloc, hipFree or other allocating routine, ever.  Same
  * arguments, same results bit for bit.
  *   B     at most PPV_NOALLOC_MAX_ROWS rows (what the array holds): PPV_ERANGE beyond.
  * All calls on one GPU share the array: two calls of this function that overlap on one GPU (different streams)
- * race; calls on one stream, or otherwise ordered, do not.  Nothing has to be cleared between calls: every call
- * leaves what it used of the array at zero, which is what the next one starts from.
+ * race; calls on one stream, or otherwise ordered, do not.  What a race spoils is the results of the calls that
+ * overlap: a row of theirs may be wrong, or not written, or say that a part of it did not arrive (id -1, masses NaN).
+ * Nothing has to be cleared between calls, after a race either: what a call leaves in the array carries that
+ * call's mark, and later calls take none of it.  (The replays of one captured call have one mark: that graph must not
+ * be replayed at the same time as itself.)
  * The first call on a device looks up the array's address on that device (no allocation); make that first call
  * outside stream capture.
  * Errors: as constrained_sample; PPV_ERANGE also for B > PPV_NOALLOC_MAX_ROWS.

@@ -66,16 +66,22 @@ struct IndexView {
 // its share of the row's tiles and of the listed tokens and leaves the per-tile / per-slice statistics here; the
 // workgroup that arrives last (one device-scope counter per row) takes them all and finishes the row exactly
 // as a single workgroup would: the statistics do not depend on who computed them, so results are bit for bit
-// those of an unsplit row.  An area is all zeros between launches: no word that is written is 0, so a word says by itself
-// whether it has arrived, and the workgroup that finishes the row puts the zeros back, the counter's too.
+// those of an unsplit row.  Every word carries the mark of the call that wrote it, so it says by itself whether it has arrived,
+// and what another call has left is never taken for it.  (The workgroup that finishes the row puts zeros in their place, for a graph,
+// whose replays have one mark.)
 constexpr int PPV_MAX_TILES = 256;          // PPV_MAX_VOCAB / 1024 (fp32 tiles are 1024 tokens)
 constexpr int PPV_SPLIT_MAX_ROWS = PPV_NOALLOC_MAX_ROWS;   // larger batches fill the chip with one workgroup per row
 constexpr int PPV_SPLIT_MAX_PARTS = 16;
+typedef uint64_t Marked;                    // a float, and above it the call's mark: never 0, another for every one of 2^29 calls, and
+                                            // one for all replays of a captured call
+struct MarkedPair {
+    Marked first, second;
+};
 struct SplitRow {
-    uint64_t tile[PPV_MAX_TILES];           // (reference, sum over all tokens)
-    uint64_t valid[PPV_MAX_TILES];          // (1.0, sum over valid tokens): rows under an image
-    uint64_t slice[PPV_LIST_MAX / 64];      // (largest of 64 listed logits, the sum relative to it)
-    uint32_t list_e[PPV_LIST_MAX];
+    MarkedPair tile[PPV_MAX_TILES];         // reference, sum over all tokens
+    Marked valid[PPV_MAX_TILES];            // sum over valid tokens: rows under an image
+    MarkedPair slice[PPV_LIST_MAX / 64];    // largest of 64 listed logits, the sum relative to it
+    Marked list_e[PPV_LIST_MAX];
 };
 struct SplitScratch {
     uint32_t arrivals[PPV_SPLIT_MAX_ROWS];
@@ -84,6 +90,10 @@ struct SplitScratch {
 // The scratch area for `rows` rows (PPV_SPLIT_MAX_ROWS at most) of a call on this stream of the current device, or of the capture
 // that the stream is in; nullptr when there is none to be had: the rows are then not split.
 SplitScratch *ppv_split_scratch(hipStream_t stream, int rows);
+// The area of eager calls on a stream, or constrained_sample_noalloc's array: its address, its size and where the rows' words begin,
+// for the tests that look at one or disturb it; look_again 0: calls from now on look once at a word.  (Exported, and not declared in
+// ppv.h.)
+extern "C" ppv_status ppv_split_area_for_tests(void *stream, int32_t fixed, int32_t look_again, void **area, int64_t *bytes, int64_t *words_at);
 
 // Per-row decoding cursor kept between decode steps (PPV_STATE_WORDS x uint32).  The second half looks one level
 // ahead: the entry of the node's first child and the child offset of the entry after it.  For a node with exactly

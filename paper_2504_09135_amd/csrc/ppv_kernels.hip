@@ -14,7 +14,9 @@
 //          operations per element) and the sample is located by re-reading one tile.
 // Nothing here is a dense contraction, so no MFMA; the bound is HBM bandwidth, with the exp
 // (quarter-rate v_exp_f32) as the main ALU cost.
+#include <atomic>
 #include <cmath>
+#include <cstddef>
 #include <mutex>
 #include <type_traits>
 
@@ -588,28 +590,10 @@ struct RowOut {
 
 // Words that the workgroups of a split row hand to one another (see SplitRow) are written and read with device-scope
 // accesses (each goes to the level of the memory system that all compute units share), so that no fence over the whole
-// cache is needed: a device-wide fence per wavefront cost 30 us per launch.  A word of 0 has not been written, so what is
-// written never is: 0.0 goes as -0.0, which is the same number to everything that is done with it.
-__device__ __forceinline__ uint32_t not_zero(float v) {
-    const uint32_t b = __float_as_uint(v);
-    return b ? b : 0x80000000u;
-}
+// cache is needed: a device-wide fence per wavefront cost 30 us per launch.
 template <typename W> __device__ __forceinline__ void shared_put(W *p, W v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 template <typename W> __device__ __forceinline__ W shared_get(const W *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void shared_put_pair(uint64_t *p, float a, float b) {
-    shared_put(p, (uint64_t)__float_as_uint(b) << 32 | not_zero(a));
-}
-__device__ __forceinline__ float pair_first(uint64_t w) { return __uint_as_float((uint32_t)w); }
-__device__ __forceinline__ float pair_second(uint64_t w) { return __uint_as_float((uint32_t)(w >> 32)); }
-// A word that has been sent, `seen` being what an earlier look at it gave.  (Bounded, should two launches use one area at a time,
-// which no caller may do.)  Whoever has taken a row's words leaves zeros for the next launch, after the last look: a look waits
-// for what was stored before it.
-constexpr int MOST_LOOKS = 1 << 16;
-template <typename W> __device__ __forceinline__ W shared_take(const W *p, W seen) {
-    for (int n = 0; __builtin_expect(seen == 0, 0) && n < MOST_LOOKS; n++) seen = shared_get(p);
-    return seen;
 }
 
 // A row shared by `parts` workgroups (see SplitRow); parts == 1: one workgroup has the row to itself and
@@ -619,33 +603,99 @@ struct Split {
     int part;             // this workgroup's number, 0 .. parts-1
     SplitRow *row;        // the row's scratch
     uint32_t *arrivals;   // the row's arrival counter
+    uint32_t mark;        // of the call
 };
+template <bool SPLIT> __device__ __forceinline__ Split split_of(int shift) {
+    if (!SPLIT) return {1, 0, nullptr, nullptr, 0u};
+    return {1 << shift, (int)(blockIdx.x & ((1u << shift) - 1u)), nullptr, nullptr, 0u};
+}
+// (Where it is needed, not when the kernel starts: on the way through the index there is no room for it in the scalar registers.)
+template <bool SPLIT> __device__ __forceinline__ void find_area(Split &sp, SplitScratch *scratch, int b, uint32_t mark) {
+    if (!SPLIT) return;
+    sp.row = &scratch->row[b];
+    sp.arrivals = &scratch->arrivals[b];
+    sp.mark = mark;
+}
+__device__ __forceinline__ void send(Marked *p, float v, uint32_t mark) { shared_put(p, (uint64_t)mark << 32 | __float_as_uint(v)); }
+__device__ __forceinline__ void send(MarkedPair *p, float a, float b, uint32_t mark) {
+    send(&p->first, a, mark);
+    send(&p->second, b, mark);
+}
+__device__ __forceinline__ void clear(MarkedPair *p) {
+    shared_put(&p->first, (Marked)0);
+    shared_put(&p->second, (Marked)0);
+}
+__device__ __forceinline__ MarkedPair look(const MarkedPair *p) { return {shared_get(&p->first), shared_get(&p->second)}; }
+__device__ __forceinline__ bool has(Marked w, uint32_t mark) { return (uint32_t)(w >> 32) == mark; }
+__device__ __forceinline__ bool has(const MarkedPair &w, uint32_t mark) { return has(w.first, mark) && has(w.second, mark); }
+__device__ __forceinline__ float value(Marked w) { return __uint_as_float((uint32_t)w); }
+// Waits for words that have been sent, by a whole wavefront: look_again() at all of them as long as one lane's there() is false.  False if they
+// do not come: two launches use one area at a time, which no caller may do.  (The row then has no result, and says so: id -1, masses NaN.)
+constexpr uint32_t MOST_LOOKS = 1u << 16;      // a word that has been sent comes within microseconds
+constexpr uint32_t LOOK_ONCE = 1u << 29;       // of a mark (tests): no further look
+template <typename THERE, typename LOOK> __device__ __forceinline__ bool wait_for(const Split &sp, THERE there, LOOK look_again) {
+    uint32_t n = 0;
+    while (__ballot(!there()) != 0ull) {   // (uniform: what is live here is in scalar registers, of which there are too few)
+        if (n++ >= MOST_LOOKS || (sp.mark & LOOK_ONCE)) return false;
+        look_again();
+    }
+    return true;
+}
+// Counts this workgroup: true for the one that arrives last.  (The count goes from parts - 1 to 0, and from anything that is more: what launches
+// that may not have met here leave in it makes some workgroup of a later one the last, which waits for the words of the others.)
+__device__ __forceinline__ bool arrive(const Split &sp) { return atomicInc(sp.arrivals, (uint32_t)sp.parts - 1u) >= (uint32_t)sp.parts - 1u; }
 
 // Where the workgroups of a row meet: by wavefront 0 of each, after a barrier behind the last word the workgroup has sent.  True for the
 // one that arrives last, which then has every tile's statistics in its LDS; nobody waits for a workgroup that has not arrived.
 // A word says by itself whether it is there, so nothing is waited for between the words and the counter, and the words are looked at
 // before the counter has answered: one trip to memory that all compute units share, where there were three (the words acknowledged,
 // the counter, the words).
-template <typename SH> __device__ __forceinline__ bool meet(const Split &sp, SH &sh, int nt, int lane) {
+// `listed`: of the row's listed tokens, at most 64 (0: there are none, or they need no sums).
+template <typename SH> __device__ __forceinline__ bool meet(const Split &sp, SH &sh, int nt, int listed, int lane, bool &lost) {
     constexpr int PER = MAX_TILES / WAVE;
-    uint64_t w[PER];
+    MarkedPair w[PER], slice = {0u, 0u};
+    Marked e = 0u;
+    auto look_at_all = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < PER; j++)
-        if (j * WAVE < nt) w[j] = shared_get(&sp.row->tile[min(lane + j * WAVE, nt - 1)]);   // (no lane without a word: conditions are registers)
-    uint32_t before = 0u;   // (last: its answer is waited for at once)
-    if (lane == 0) before = __hip_atomic_fetch_add(sp.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)before) + 1u != (uint32_t)sp.parts) return false;
+        for (int j = 0; j < PER; j++)
+            if (j * WAVE < nt) w[j] = look(&sp.row->tile[min(lane + j * WAVE, nt - 1)]);   // (no lane without a word: conditions are registers)
+        if (listed) {
+            slice = look(&sp.row->slice[0]);
+            e = shared_get(&sp.row->list_e[min(lane, listed - 1)]);
+        }
+    };
+    look_at_all();
+    int last = 0;   // (its answer is waited for at once)
+    if (lane == 0) last = arrive(sp) ? 1 : 0;
+    if (!__builtin_amdgcn_readfirstlane(last)) return false;
+    const uint32_t mark = sp.mark;
+    auto there = [&]() __attribute__((always_inline)) {
+        bool all = !listed || (has(slice, mark) && has(e, mark));
+#pragma unroll
+        for (int j = 0; j < PER; j++)
+            if (j * WAVE < nt) all = all && has(w[j], mark);
+        return all;
+    };
+    lost = !wait_for(sp, there, look_at_all);
 #pragma unroll
     for (int j = 0; j < PER; j++) {
         const int k = min(lane + j * WAVE, nt - 1);
         if (j * WAVE < nt) {
-            w[j] = shared_take(&sp.row->tile[k], w[j]);
-            sh.tile_m[k] = pair_first(w[j]);
-            sh.tile_zall[k] = pair_second(w[j]);
+            sh.tile_m[k] = value(w[j].first);
+            sh.tile_zall[k] = value(w[j].second);
         }
     }
-    if (lane == 0) shared_put(sp.arrivals, 0u);
-    for (int k = lane; k < nt; k += WAVE) shared_put(&sp.row->tile[k], (uint64_t)0);
+    if (listed) {
+        if (lane == 0) {
+            sh.slice_m[0] = value(slice.first);
+            sh.slice_z[0] = value(slice.second);
+        }
+        if (lane < listed) sh.list_e[lane] = value(e);
+    }
+    // (zeros, for a graph, all of whose replays have one mark; after the last look, which waits for what was stored before it)
+    for (int k = lane; k < nt; k += WAVE) clear(&sp.row->tile[k]);
+    if (lane < listed) shared_put(&sp.row->list_e[lane], (Marked)0);
+    if (listed && lane == 0) clear(&sp.row->slice[0]);
     return true;
 }
 
@@ -684,12 +734,12 @@ __device__ __forceinline__ Share share_of(int nt, int wave_v, int nw) {
 // a tile that is not there costs nothing), so every wait is for loads issued a known number of loads ago.
 // `mid` is work of the caller's that needs no tile (the sums over the listed tokens): it is run once, where this
 // wavefront has just asked for a tile and would only wait for it.
-// X: the share's first tile; `pub`: where a split row's statistics are left for the workgroup that finishes it (nullptr: not split).
+// X: the share's first tile; `pub`: of a split row, the statistics are left for the workgroup that finishes it.
 // IMAGE: the row may have an image (nullptr: it has none; one loop for both, so that the tiles stay in their registers).
 template <typename T, bool IMAGE, typename SH, typename MID>
 __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
                                     const uint32_t *__restrict__ image, SH &sh, int lane, const Share &share,
-                                    const Temper &tp, MID &mid, SplitRow *pub) {
+                                    const Temper &tp, MID &mid, bool pub, const Split sp) {
     using G = TileGeom<T>;
     if (share.n == 0) {
         mid();
@@ -701,7 +751,7 @@ __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
             const int k = share.at(i_first + lane);
             sh.tile_m[k] = kept_m;
             sh.tile_zall[k] = kept_z;
-            if (pub) shared_put_pair(&pub->tile[k], kept_m, kept_z);
+            if (pub) send(&sp.row->tile[k], kept_m, kept_z, sp.mark);
         }
     };
     auto reduce_tile = [&](const RawTile &t, int k, int i, auto pad) __attribute__((always_inline)) {
@@ -716,8 +766,8 @@ __device__ __forceinline__ void stream_tiles(const Row &row, int V, RawTile &X,
                 sh.tile_zval[k] = zval;
                 sh.tile_ref[k] = m;
                 if (pub) {
-                    shared_put_pair(&pub->tile[k], m, zall);
-                    shared_put_pair(&pub->valid[k], 1.f, zval);
+                    send(&sp.row->tile[k], m, zall, sp.mark);
+                    send(&sp.row->valid[k], zval, sp.mark);
                 }
             }
         } else {
@@ -913,7 +963,7 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
     // the wavefront's number and count over all workgroups of the row: tiles and list slices are dealt out by these
     const int parts = SPLIT ? sp.parts : 1;
     const int vwave = SPLIT ? sp.part * nw + wave : wave, vnw = parts * nw;
-    SplitRow *pub = SPLIT && parts > 1 ? sp.row : nullptr;
+    const bool pub = SPLIT && parts > 1;
     const Share share = share_of(nt, vwave, vnw);
 
     // ---- list path, part 1: ask for the listed tokens' logits now (they are being streamed
@@ -954,18 +1004,18 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
             }
             if (i < n_list) {
                 sh.list_e[i] = e;
-                if (pub) shared_put(&pub->list_e[i], not_zero(e));
+                if (pub) send(&sp.row->list_e[i], e, sp.mark);
             }
             const float z = wave_sum(e);
             if (lane == 0) {
                 sh.slice_m[s] = m;
                 sh.slice_z[s] = z;
-                if (pub) shared_put_pair(&pub->slice[s], m, z);
+                if (pub) send(&sp.row->slice[s], m, z, sp.mark);
             }
         }
     };
     // ---- stream: every tile once
-    stream_tiles<T, true, SH>(row_of(row, V), V, first, mode == VALID_IMAGE ? image : nullptr, sh, lane, share, tp, list_sums, pub);
+    stream_tiles<T, true, SH>(row_of(row, V), V, first, mode == VALID_IMAGE ? image : nullptr, sh, lane, share, tp, list_sums, pub, sp);
     // (decode loop) the row of the next step is known already: ask for this wave's first tile of it
     // now, so that it travels while this row is combined and sampled
     if (next_row && share.n > 0) load_tile<T>(row_of(next_row, V), share.first(), lane, *next_first);
@@ -980,67 +1030,72 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
         const int listed = mode == VALID_LIST ? n_list : 0;
         if (mode != VALID_IMAGE && listed <= WAVE) {
             if (wave != 0) return none;
-            // (the list's words are looked at together with the tiles')
-            uint64_t slice = listed ? shared_get(&pub->slice[0]) : 0u;
-            uint32_t e = listed ? shared_get(&pub->list_e[min(lane, listed - 1)]) : 0u;
-            if (!meet(sp, sh, nt, lane)) return none;
-            if (listed) {
-                slice = shared_take(&pub->slice[0], slice);
-                e = shared_take(&pub->list_e[min(lane, listed - 1)], e);
-                if (lane == 0) {
-                    sh.slice_m[0] = pair_first(slice);
-                    sh.slice_z[0] = pair_second(slice);
-                    shared_put(&pub->slice[0], (uint64_t)0);
-                }
-                if (lane < listed) {
-                    sh.list_e[lane] = __uint_as_float(e);
-                    shared_put(&pub->list_e[lane], 0u);
-                }
-            }
+            bool lost = false;
+            if (!meet(sp, sh, nt, listed, lane, lost)) return none;
+            if (lane == 0) sh.bc_i[0] = lost ? 2 : 1;
         } else {
-            // (many words: by every wavefront, which the rare second pass over an image row needs too)
+            // (many words: by every wavefront, which the rare second pass over an image row needs too; no thread without a word)
             const int nthreads = nw * WAVE;
-            uint64_t tile = tid < nt ? shared_get(&pub->tile[tid]) : 0u;
-            uint64_t more = 0u;
-            uint32_t e = 0u;
-            if (mode == VALID_IMAGE) {
-                if (tid < nt) more = shared_get(&pub->valid[tid]);
-            } else {
-                if (tid < ns) more = shared_get(&pub->slice[tid]);
-                if (tid < listed) e = shared_get(&pub->list_e[tid]);
-            }
-            if (tid == 0) {
-                const uint32_t before = __hip_atomic_fetch_add(sp.arrivals, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                sh.bc_i[0] = before + 1u == (uint32_t)parts ? 1 : 0;
-            }
+            const SplitRow *words = sp.row;
+            const bool image_row = mode == VALID_IMAGE;
+            const uint32_t mark = sp.mark;
+            int k = min(tid, nt - 1), i = min(tid, listed - 1);
+            const int q = min(tid, ns - 1);   // (at most sixteen slices)
+            MarkedPair tile, slice = {0u, 0u};
+            Marked valid = 0u, e = 0u;
+            auto look_at_tile = [&]() __attribute__((always_inline)) {
+                tile = look(&words->tile[k]);
+                if (image_row) valid = shared_get(&words->valid[k]);
+            };
+            auto look_at_list = [&]() __attribute__((always_inline)) {
+                if (!image_row) {
+                    slice = look(&words->slice[q]);
+                    e = shared_get(&words->list_e[i]);
+                }
+            };
+            auto there = [&]() __attribute__((always_inline)) {
+                return has(tile, mark) && (image_row ? has(valid, mark) : has(slice, mark) && has(e, mark));
+            };
+            look_at_tile();
+            look_at_list();
+            if (tid == 0) sh.bc_i[0] = arrive(sp) ? 1 : 0;
             __syncthreads();
             if (!sh.bc_i[0]) return none;      // uniform for the workgroup
-            for (int k = tid; k < nt; k += nthreads) {
-                tile = shared_take(&pub->tile[k], k == tid ? tile : 0u);
-                sh.tile_m[k] = sh.tile_ref[k] = pair_first(tile);
-                sh.tile_zall[k] = pair_second(tile);
-                if (mode == VALID_IMAGE) sh.tile_zval[k] = pair_second(shared_take(&pub->valid[k], k == tid ? more : 0u));
-            }
-            if (mode == VALID_LIST) {
-                if (tid < ns) {   // (at most sixteen slices: a wavefront's lanes)
-                    more = shared_take(&pub->slice[tid], more);
-                    sh.slice_m[tid] = pair_first(more);
-                    sh.slice_z[tid] = pair_second(more);
+            bool came = true;
+            // the first tiles and listed tokens of all threads together, then the second ones, ...
+            for (int done = 0; done < nt || done < listed; done += nthreads) {
+                k = min(tid + done, nt - 1);
+                i = min(tid + done, listed - 1);
+                if (done) {
+                    look_at_tile();
+                    look_at_list();
                 }
-                for (int i = tid; i < listed; i += nthreads) sh.list_e[i] = __uint_as_float(shared_take(&pub->list_e[i], i == tid ? e : 0u));
+                came = wait_for(sp, there, [&]() __attribute__((always_inline)) {
+                    look_at_tile();
+                    look_at_list();
+                }) && came;
+                sh.tile_m[k] = sh.tile_ref[k] = value(tile.first);
+                sh.tile_zall[k] = value(tile.second);
+                if (image_row) {
+                    sh.tile_zval[k] = value(valid);
+                } else {
+                    sh.slice_m[q] = value(slice.first);
+                    sh.slice_z[q] = value(slice.second);
+                    sh.list_e[i] = value(e);
+                }
             }
+            if (!came) sh.bc_i[0] = 2;
             __syncthreads();
             // (the zeros by the wavefronts that have little left to do)
             const int z0 = nw > 1 ? WAVE : 0;
-            if (tid == z0) shared_put(sp.arrivals, 0u);
             if (tid >= z0) {
                 for (int k = tid - z0; k < nt; k += nthreads - z0) {
-                    shared_put(&pub->tile[k], (uint64_t)0);
-                    if (mode == VALID_IMAGE) shared_put(&pub->valid[k], (uint64_t)0);
+                    clear(&sp.row->tile[k]);
+                    if (image_row) shared_put(&sp.row->valid[k], (Marked)0);
                 }
                 for (int i = tid - z0; i < listed; i += nthreads - z0) {
-                    shared_put(&pub->list_e[i], 0u);
-                    if (i < ns) shared_put(&pub->slice[i], (uint64_t)0);
+                    shared_put(&sp.row->list_e[i], (Marked)0);
+                    if (i < ns) clear(&sp.row->slice[i]);
                 }
             }
         }
@@ -1201,6 +1256,10 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
         out.pos = pos;
         out.logZ_valid = lzv;
         out.logZ_all = fmaf(M, tp.inv, LN2F * l2za);
+        if (SPLIT && __builtin_expect(sh.bc_i[0] == 2, 0)) {
+            out.id = out.pos = -1;
+            out.logZ_valid = out.logZ_all = NAN;
+        }
         if (ALL && lane == 0) {
             sh.bc_i[0] = out.id;
             sh.bc_i[1] = out.pos;
@@ -1224,25 +1283,20 @@ __device__ __forceinline__ RowOut row_sample(const T *__restrict__ row, int V, R
 template <typename T, bool SMALL, bool SPLIT>
 __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void sample_kernel(const T *__restrict__ logits, int64_t row_stride,
                                                                   const uint32_t *__restrict__ mask, int V,
-                                                                  int n_words, int list_max, int shape,
+                                                                  int n_words, int list_max, int shape, SplitScratch *scratch,
                                                                   const float *__restrict__ uniforms,
                                                                   int32_t *__restrict__ ids,
                                                                   float *__restrict__ logZ_valid,
-                                                                  float *__restrict__ logZ_all, Temper tp,
-                                                                  SplitScratch *scratch) {
+                                                                  float *__restrict__ logZ_all, Temper tp, uint32_t mark) {
     using SH = typename std::conditional<SMALL, RowSharedSmall, RowShared>::type;
     __shared__ SH sh;
     // shape: wavefronts per workgroup << 8 (an argument: blockDim would be waited for), and for SPLIT, where a row is shared by
-    // a power of two of consecutive workgroups, that power
+    // a power of two of consecutive workgroups, that power; mark: the call's
     const int split_shift = shape & 255;
     const int b = SPLIT ? (int)(blockIdx.x >> split_shift) : (int)blockIdx.x;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const int nw = shape >> 8;
-    Split sp;
-    sp.parts = SPLIT ? 1 << split_shift : 1;
-    sp.part = SPLIT ? (int)(blockIdx.x & (unsigned)(sp.parts - 1)) : 0;
-    sp.row = SPLIT ? &scratch->row[b] : nullptr;
-    sp.arrivals = SPLIT ? &scratch->arrivals[b] : nullptr;
+    Split sp = split_of<SPLIT>(split_shift);
     const int vwave = sp.part * nw + wave;
     const T *row = logits + (size_t)b * (size_t)row_stride;
     const uint32_t *mrow = mask + (size_t)b * (size_t)n_words;
@@ -1314,6 +1368,7 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
         }
         __syncthreads();
     }
+    find_area<SPLIT>(sp, scratch, b, mark);
     RowOut r = row_sample<T, SH, false, SPLIT>(row, V, first, mode, mode == VALID_LIST ? total : 0, mrow, uniforms[b], sh, tid, nw, tp, sp);
     if (r.mine && tid == 0) {
         ids[b] = r.id;
@@ -1592,7 +1647,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
     float *__restrict__ logx, const T *__restrict__ logits, int flags, int shape, int32_t *__restrict__ prefixes,
     int32_t stride, int n_steps, int B, int64_t row_stride, int64_t step_stride, int32_t *__restrict__ ids,
     float *__restrict__ logZ_valid, SplitScratch *scratch, Temper tp, IndexView ix) {
-    // flags bit 1 (ppv_decode_first_step): every row starts from the empty candidate here and now -- no flags, length
+    // flags: from bit 2 on the call's mark (see SplitRow); bit 1 (ppv_decode_first_step): every row starts from the empty candidate here and now -- no flags, length
     // or cursor are read, the root's cursor is taken instead, and all of them are written at the end.
     const int advance = flags & 1;
     const bool fresh = (flags & 2) != 0;
@@ -1609,11 +1664,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
     const int b = SPLIT ? (int)(blockIdx.x >> split_shift) : (int)blockIdx.x;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
     const int nw = LOOP ? blockDim.x / WAVE : shape >> 8;   // (the loop kernel's registers come out better with blockDim: 384 rows at V = 50k fp32 142 us against 149)
-    Split sp;
-    sp.parts = SPLIT ? 1 << split_shift : 1;
-    sp.part = SPLIT ? (int)(blockIdx.x & (unsigned)(sp.parts - 1)) : 0;
-    sp.row = SPLIT ? &scratch->row[b] : nullptr;
-    sp.arrivals = SPLIT ? &scratch->arrivals[b] : nullptr;
+    Split sp = split_of<SPLIT>(split_shift);
     const int vwave = sp.part * nw + wave;
     // REG: there is a cursor, and a list of at most 63 children is kept in wavefront 0's registers, with a look one level
     // ahead for the next cursor (see RowState); large batches of the loop kernel and calls without a cursor
@@ -1734,6 +1785,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         if (LOOP) __syncthreads();
     }
     if (!STEP_REG && (LOOP || only == PPV_NO_SLOT)) check_cursor();
+    find_area<SPLIT>(sp, scratch, b, (uint32_t)flags >> 2);
     if (STEP_REG && rl.on) {
         // ---- a short list in wavefront 0's registers.  The sample depends on the listed logits alone, not on the
         // row's totals: wavefront 0 draws the token and works out the next cursor while its tile is still on its
@@ -1777,11 +1829,15 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
             __device__ void operator()() const {}
         } nothing;
         stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, sh, lane, share, tp, nothing,
-                                          SPLIT && sp.parts > 1 ? sp.row : nullptr);
+                                          SPLIT && sp.parts > 1, sp);
         __syncthreads();
         if (wave != 0) return;
         // (of a split row every workgroup has drawn the token, and the one that finishes the row stores it)
-        if (SPLIT && sp.parts > 1 && !meet(sp, sh, nt, lane)) return;
+        bool lost = false;
+        if (SPLIT && sp.parts > 1) {
+            if (!meet(sp, sh, nt, 0, lane, lost)) return;
+            drew = drew && !lost;
+        }
         if (lane == 0) {
             if (ids) ids[b] = drew ? pk.id : -1;
             if (drew) {
@@ -1808,7 +1864,8 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
         float M, za;
         double zv;
         combine_tiles<T>(sh, logits + (size_t)b * (size_t)row_stride, V, nt, lane, tp, false, M, za, zv);
-        const float lzv = fmaf(pk.Mv - M, tp.inv, LN2F * (fast_log2((float)pk.zvl) - fast_log2(za)));
+        float lzv = fmaf(pk.Mv - M, tp.inv, LN2F * (fast_log2((float)pk.zvl) - fast_log2(za)));
+        if (SPLIT && __builtin_expect(lost, 0)) lzv = NAN;
         if (lane == 0) {
             if (logZ_valid) logZ_valid[b] = lzv;
             if (advance && logx && drew) logx[b] = logx_in + lzv;
@@ -2053,7 +2110,7 @@ __global__ __launch_bounds__((LOOP && !REG ? LOOP_WAVES : MAX_WAVES) * WAVE, LOO
             struct {
                 __device__ void operator()() const {}
             } nothing;
-            stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, cur, lane, share, tp, nothing, nullptr);
+            stream_tiles<T, false, RowShared>(row_of(row, V), V, first, nullptr, cur, lane, share, tp, nothing, false, sp);
             __syncthreads();
             done = hand[s & 1].done != 0;
             const bool drew = hand[s & 1].drew != 0;
@@ -2299,13 +2356,22 @@ int shift_of(int parts) {
     return sh;
 }
 
+// A mark for a call that splits rows (see SplitRow); 0 for the others.
+std::atomic<uint32_t> g_mark_flags{0};
+uint32_t mark_for(int split_shift) {
+    static std::atomic<uint32_t> last{0};
+    uint32_t mark = 0;
+    while (split_shift && !mark) mark = ++last & (LOOK_ONCE - 1u);
+    return mark | g_mark_flags.load(std::memory_order_relaxed);
+}
+
 template <typename T>
 void launch_sample(bool small, dim3 grid, dim3 block, hipStream_t hs, const T *lg, int64_t row_stride,
                    const uint32_t *mask, const float *uniforms, int V, int n_words, int list_max, int32_t *ids,
                    float *logZ_valid, float *logZ_all, Temper tp, int split_shift, SplitScratch *scratch) {
 #define PPV_LAUNCH_SAMPLE(SMALL, SPLIT)                                                                                  \
     hipLaunchKernelGGL((sample_kernel<T, SMALL, SPLIT>), grid, block, 0, hs, lg, row_stride, mask, V, n_words, \
-                       list_max, split_shift | (int)(block.x / WAVE) << 8, uniforms, ids, logZ_valid, logZ_all, tp, scratch)
+                       list_max, split_shift | (int)(block.x / WAVE) << 8, scratch, uniforms, ids, logZ_valid, logZ_all, tp, mark_for(split_shift))
     if (split_shift) PPV_LAUNCH_SAMPLE(false, true);
     else if (small) PPV_LAUNCH_SAMPLE(true, false);
     else PPV_LAUNCH_SAMPLE(false, false);
@@ -2320,7 +2386,7 @@ void launch_decode_kernel(bool loop, dim3 grid, dim3 block, hipStream_t hs, cons
                           float *logZ_valid, float *logx, Temper tp, int split_shift, SplitScratch *scratch, int flags) {
     const bool reg = rs && (!loop || B <= REG_MAX_ROWS);
 #define PPV_LAUNCH_DECODE(LOOP, SPLIT, REG)                                                                               \
-    hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, active, lens, rs, uniforms, logx, lg, flags, \
+    hipLaunchKernelGGL((decode_kernel<T, LOOP, SPLIT, REG>), grid, block, 0, hs, active, lens, rs, uniforms, logx, lg, flags | (int)(mark_for(split_shift) << 2), \
                        split_shift | (int)(block.x / WAVE) << 8, prefixes, stride, n_steps, B, row_stride, step_stride, ids,  \
                        logZ_valid, scratch, tp, view)
     if (split_shift && !loop && reg) PPV_LAUNCH_DECODE(false, true, true);
@@ -2425,6 +2491,20 @@ ppv_status sample_call(const void *logits, ppv_dtype dt, int64_t row_stride, con
     return PPV_OK;
 }
 }  // namespace
+
+ppv_status ppv_split_area_for_tests(void *stream, int32_t fixed, int32_t look_again, void **area, int64_t *bytes, int64_t *words_at) {
+    SplitScratch *p = fixed ? nullptr : ppv_split_scratch((hipStream_t)stream, PPV_SPLIT_MAX_ROWS);
+    if (fixed) {
+        const ppv_status st = fixed_scratch(&p);
+        if (st != PPV_OK) return st;
+    }
+    if (!p) return PPV_ENOMEM;
+    g_mark_flags = look_again ? 0u : LOOK_ONCE;
+    *area = p;
+    *bytes = (int64_t)sizeof(SplitScratch);
+    *words_at = (int64_t)offsetof(SplitScratch, row);
+    return PPV_OK;
+}
 
 extern "C" ppv_status constrained_sample(const void *logits, ppv_dtype dt, int64_t row_stride, const uint32_t *mask,
                                          const float *uniforms, int32_t B, int32_t V, int32_t *ids,

@@ -18,7 +18,7 @@
 
 namespace {
 constexpr uint64_t MOST_THREADS = 64;
-constexpr int SPARES = 4, MOST_CAPTURED = 256;   // 1.07 MB each
+constexpr int SPARES = 4, MOST_CAPTURED = 256;   // 1.9 MB each
 constexpr int CAPTURED_ROWS = 128;               // twice as many rows as workgroups for them are not split
 
 std::mutex g_mu;
@@ -108,8 +108,7 @@ SplitScratch *area_for(hipStream_t stream, int rows) {
     if (!p) {
         p = new_area(PPV_SPLIT_MAX_ROWS);
         if (!p) return nullptr;
-        // an area starts as zeros (afterwards every launch leaves zeros); in stream order before the kernel that is about to
-        // be launched
+        // an area starts as zeros, which no call has for a mark; in stream order before the kernel that is about to be launched
         if (hipMemsetAsync(p, 0, bytes_for(PPV_SPLIT_MAX_ROWS), stream) != hipSuccess) {
             (void)hipGetLastError();
             (void)hipFree(p);

@@ -1,6 +1,8 @@
 """Rows spread over several workgroups (small batches): every number of workgroups per row gives bit for bit the
 result of one workgroup per row, which in turn is checked against the oracle.  The split is a launch detail
 (PPV_TUNE_ROW_SPLIT forces it; the library picks it from the batch size and the row length otherwise)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -89,8 +91,8 @@ def test_split_rows_hand_made_masks(dtype, waves):
 
 
 def test_split_rows_with_temperature_and_a_second_smaller_call():
-    """The scratch area keeps what the last call left: a second, smaller call right after a larger one, at another
-    temperature and on other rows, must not see any of it."""
+    """The scratch area is the same for one call after the other: a second, smaller call right after a larger one, at
+    another temperature and on other rows, must not see any of it."""
     cfg, S, trie, index = setup_case("C2")
     pb = W.make_prefix_batch(cfg, S)
     for step, (rows, T) in enumerate([(slice(0, 64), 0.7), (slice(5, 22), 1.9), (slice(0, 64), 1.0)]):
@@ -104,9 +106,9 @@ def test_split_rows_with_temperature_and_a_second_smaller_call():
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_one_area_for_calls_of_every_kind(dtype):
-    """A call leaves its area as zeros, whatever kind its rows were and however many: lists of 1, 64, 65 and 1,000 tokens, images and
-    empty sets take each other's places, with values that are themselves 0 (a reference, the weight of a listed token, a tile without
-    a valid one), and each call gives the unsplit call's bits."""
+    """Calls whose rows are of other kinds and numbers one after the other in one area: lists of 1, 64, 65 and 1,000 tokens, images and
+    empty sets take each other's places, with listed weights and valid sums of 0, and each call gives the unsplit call's bits.  (That
+    nothing of another call is taken: test_no_word_of_another_call_is_taken.)"""
     V = 50_001
     g = torch.Generator(device=DEV).manual_seed(8)
     counts = [0, 1, 64, 65, 1_000, 20_000]
@@ -117,11 +119,138 @@ def test_one_area_for_calls_of_every_kind(dtype):
         words[i] = torch.from_numpy(pack(m)[0])
     for step, B in enumerate([12, 5, 16, 1, 12]):
         logits = torch.randn((B, -(-V // 8) * 8), generator=g, device=DEV).mul_(2).to(dtype)[:, :V]
-        logits[::3] = logits[::3].sign() * -150   # references and listed weights of 0
+        logits[::3] = logits[::3].sign() * -150   # listed weights of 0
         logits[::3, ::7] = 0
         un = torch.rand(B, generator=g, device=DEV)
         kinds = (torch.arange(B) + step) % len(counts)
         sample_all_splits(logits, words[kinds].to(DEV), un)
+
+
+class Area:
+    """The area that calls on the default stream meet in, or the fixed array: each row's count of workgroups that have arrived, then the
+    words of all rows, a value and a call's mark each."""
+    def __init__(self, fixed=False):
+        self.fixed = fixed
+        at, n, words = self.look_again(True)
+        self.__cuda_array_interface__ = {"shape": (n // 4,), "typestr": "<i4", "data": (at, False), "version": 3}
+        everything = torch.as_tensor(self, device=DEV)
+        self.arrived, self.words = everything[:words // 4], everything[words // 4:].view(-1, 2)
+
+    def look_again(self, on):
+        """Whether calls from here on wait for a word that is not there when they first look."""
+        at, n, words = C.c_void_p(), C.c_int64(), C.c_int64()
+        torch.cuda.synchronize()
+        lib = ppv.load_library()
+        assert lib.ppv_split_area_for_tests(None, int(self.fixed), int(on), C.byref(at), C.byref(n), C.byref(words)) == 0
+        return at.value, n.value, words.value
+
+    def disturb(self, B, arrived):
+        """As calls that overlap may leave it: words of a call, with plausible values, and workgroups of no call counted."""
+        self.words[:, 0] = torch.tensor(1.5).view(torch.int32).item()
+        self.words[:, 1] = 0x7FFFFFFF
+        self.arrived[:B] = arrived
+        torch.cuda.synchronize()
+
+
+def sample_case(dtype, seed, V=100_000):
+    """Rows of every kind: an empty set, lists of 1, 64, 65 and 1,000 tokens, an image."""
+    counts = [0, 1, 64, 65, 1_000, 20_000] * 2
+    words = torch.zeros((len(counts), (V + 31) // 32), dtype=torch.int32)
+    for i, n in enumerate(counts):
+        m = np.zeros((1, V), np.uint8)
+        m[0, np.random.default_rng(100 * seed + i).choice(V, n, replace=False)] = 1
+        words[i] = torch.from_numpy(pack(m)[0])
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    logits = torch.randn((len(counts), V), generator=g, device=DEV).mul_(2).to(dtype)
+    return logits, words.to(DEV), torch.rand(len(counts), generator=g, device=DEV)
+
+
+def sample_bits(case, fixed):
+    B = case[0].shape[0]
+    ids = torch.full((B,), -7, dtype=torch.int32, device=DEV)
+    lzv, lza = torch.full((B,), 3.0, device=DEV), torch.full((B,), 3.0, device=DEV)
+    (ppv.constrained_sample_noalloc if fixed else ppv.constrained_sample)(*case, ids, lzv, lza)
+    torch.cuda.synchronize()
+    return torch.stack([ids, lzv.view(torch.int32), lza.view(torch.int32)], 1).cpu()
+
+
+def cursor_step_bits(index, P, state, logits, un):
+    """One step of every row from the given cursors; the buffers that it changes are the caller's copies."""
+    B = P.shape[0]
+    P, state = P.clone(), state.clone()
+    lens, act = torch.ones(B, dtype=torch.int32, device=DEV), torch.ones(B, dtype=torch.uint8, device=DEV)
+    ids = torch.full((B,), -7, dtype=torch.int32, device=DEV)
+    lz, logx = torch.full((B,), 3.0, device=DEV), torch.zeros(B, device=DEV)
+    ppv.ppv_decode_step(index, P, lens, act, logits, un, ids, lz, logx, state=state)
+    torch.cuda.synchronize()
+    return torch.cat([t.view(torch.int32).reshape(B, -1) for t in (P, lens, ids, lz, logx, state)], 1).cpu()
+
+
+def cursor_case(dtype, V=100_000, B=12):
+    """Rows one token into S: a few children each, then one."""
+    rng = np.random.default_rng(5)
+    S = np.concatenate([rng.integers(0, 40, (400, 1)), rng.integers(0, V, (400, 3))], axis=1).astype(np.int32)
+    index = ppv.ppv_build_index(S.reshape(-1), np.arange(401, dtype=np.int64) * 4, V)
+    P = torch.zeros((B, 4), dtype=torch.int32, device=DEV)
+    P[:, 0] = to_dev(S[rng.integers(0, 400, B), 0])
+    state = torch.zeros((B, ppv.PPV_STATE_WORDS), dtype=torch.int32, device=DEV)
+    lens, act = torch.ones(B, dtype=torch.int32, device=DEV), torch.ones(B, dtype=torch.uint8, device=DEV)
+    ppv.ppv_decode_begin(index, P, lens, state, act)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    logits = torch.randn((B, V), generator=g, device=DEV).mul_(2).to(dtype)
+    return index, P, state, logits, torch.rand(B, generator=g, device=DEV)
+
+
+@pytest.mark.parametrize("kind", ["sample", "fixed", "cursor"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_no_word_of_another_call_is_taken(dtype, kind):
+    """Whatever an area holds, and whichever workgroup its counts make the last of a row: a call's results are the unsplit call's bits.
+    And calls in an area that is as it should be, with rows of every kind, leave it so: nothing of theirs in it, which is what a graph's
+    replays start from."""
+    fixed = kind == "fixed"
+    case = cursor_case(dtype) if kind == "cursor" else sample_case(dtype, 1)
+    run = (lambda: cursor_step_bits(*case)) if kind == "cursor" else (lambda: sample_bits(case, fixed))
+    with tuning(ppv.PPV_TUNE_ROW_SPLIT, 1):
+        want = run()
+    area, B = Area(fixed), want.shape[0]
+    for k in SPLITS[1:]:
+        with tuning(ppv.PPV_TUNE_ROW_SPLIT, k):
+            for arrived in (k - 1, 1, 16, 100, k - 1):
+                area.disturb(B, arrived)
+                for _ in range(3):
+                    assert torch.equal(run(), want), (k, arrived)
+            area.arrived[:] = 0
+            area.words[:] = 0
+            for _ in range(3):
+                assert torch.equal(run(), want), k
+                assert not area.arrived.any() and not area.words.any(), k
+
+
+@pytest.mark.parametrize("fixed", [False, True])
+def test_a_row_whose_words_do_not_arrive_says_so(fixed):
+    """With no further look at a word that is not there yet, rows finished by the first workgroup to arrive are those of the unsplit
+    call or have id -1 and masses that are NaN; the calls after that are as ever, whatever is left in the area."""
+    case = sample_case(torch.bfloat16, 2)
+    with tuning(ppv.PPV_TUNE_ROW_SPLIT, 1):
+        want = sample_bits(case, fixed)
+    area, B, said = Area(fixed), want.shape[0], 0
+    for k in SPLITS[1:]:
+        with tuning(ppv.PPV_TUNE_ROW_SPLIT, k):
+            area.disturb(B, k - 1)
+            area.look_again(False)
+            try:
+                got = sample_bits(case, fixed)
+            finally:
+                area.look_again(True)
+            masses = got[:, 1:].contiguous().view(torch.float32)
+            none = (got[:, 0] == -1) & masses.isnan().all(1)
+            assert (none | (got == want).all(1)).all(), k
+            said += int(none.sum())
+            for _ in range(3):
+                assert torch.equal(sample_bits(case, fixed), want), k
+            area.arrived[:] = 0
+            area.words[:] = 0
+    assert said > 0
 
 
 @pytest.mark.parametrize("use_state", [True, False])
