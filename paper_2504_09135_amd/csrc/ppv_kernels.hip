@@ -1385,16 +1385,17 @@ __global__ __launch_bounds__(SMALL ? SMALL_TILES * WAVE : MAX_WAVES * WAVE) void
 // tokens' weights that the sums are made of stay in registers and the token is found from them, where they were computed a second time
 // (with the mask's bits brought to their lanes again, and the last token of each lane that has a weight); a row with one valid token needs no
 // search.  The lanes' mask bits come from memory, a byte each, not over four exchanges between lanes.  us per call before / after:
-// 4,096 rows of constrained_sample at V = 1,024 fp32 5.7 / 4.7, V = 2,048 bf16 8.1 / 5.9; 16,384 rows 14.4 / 10.8, 20.8 / 14.8;
-// ppv_sample_next, 4,096 rows 7.1 / 6.3, 9.3 / 7.6.
+// 4,096 rows of constrained_sample at V = 1,024 fp32 5.7 / 4.5, V = 2,048 bf16 8.1 / 5.9; 16,384 rows 14.4 / 11.1, 22.3 / 16.6;
+// ppv_sample_next, 4,096 rows 7.1 / 6.3, 9.4 / 7.8.
 constexpr int ONE_TILE_ROWS = 4;
 struct TileDraw {
     int id;                  // sampled token or -1
     float logZ_valid;
     float m, l2za;           // reference of the row's sum, and log2 of it
 };
-// bits: this lane's mask bits, group j's in the byte j.  The statistics are image_stats', in the same order; the token is the first whose
-// cumulative valid weight exceeds u times the sum (as locate_in_tile finds it, before the rounding of the reference is taken out of both).
+// bits: this lane's mask bits, group j's in the byte j.  The statistics are image_stats', and the token is locate_in_tile's, with the same
+// operations in the same order: a decode step on a row under an image gives the same bits.  (Without the rounding of the reference in the
+// weights and in the threshold, sixteen or 32 multiplications and 1 to 3 % of a call fewer, a uniform at the edge between two tokens went to the other one now and then.)
 template <typename T, bool PAD>
 __device__ __forceinline__ TileDraw draw_in_tile(const T *row, const RawTile &rt, uint32_t bits, float u, int V, int lane, const Temper &tp) {
     using G = TileGeom<T>;
@@ -1402,7 +1403,7 @@ __device__ __forceinline__ TileDraw draw_in_tile(const T *row, const RawTile &rt
     const float mx = lane_max<T, PAD>(rt, left);
     float m = uniform(mx);
     if (too_low(m) || __ballot(mx > m + tp.guard) != 0ull) m = not_below(wave_max(mx), tp.c);   // (uniform)
-    float zall = 0.f, zval = 0.f, fix = 0.f, raw = 0.f;
+    float zall = 0.f, zval = 0.f, fix = 0.f;
     float w[4][G::EPL];      // weights of this lane's valid tokens
     if (m != -INFINITY) {    // (uniform)
         const float mc = m * tp.c;
@@ -1421,8 +1422,7 @@ __device__ __forceinline__ TileDraw draw_in_tile(const T *row, const RawTile &rt
         }
         fix = rounding_of(m, tp.c);
         zall = wave_sum(zall) * fix;
-        raw = wave_sum(zval);
-        zval = raw * fix;
+        zval = wave_sum(zval) * fix;
     }
     if (__builtin_expect(no_sum(uniform(zall)), 0) && is_far(m, tp.c)) {   // (uniform)
         far_row<T>(row, V, lane, tp, m, zall);
@@ -1431,7 +1431,8 @@ __device__ __forceinline__ TileDraw draw_in_tile(const T *row, const RawTile &rt
     TileDraw d = {-1, -INFINITY, m, fast_log2(zall)};
     const uint64_t some = __ballot(bits != 0u);
     if (!some) return d;
-    if (__builtin_expect(zval < 3.814697265625e-06f, 0)) {   // below 2^-18 of the largest term: sum again, relative to the valid maximum
+    const bool low = zval < 3.814697265625e-06f;   // below 2^-18 of the largest term: sum again, relative to the valid maximum
+    if (__builtin_expect(low || far_off(m, tp.c), 0)) {   // (uniform)
         // (the mask's words from the lanes' bits: word i of the tile in lane i)
         uint32_t word = 0u;
         for (int j = 0; j < 4; j++) {
@@ -1441,8 +1442,11 @@ __device__ __forceinline__ TileDraw draw_in_tile(const T *row, const RawTile &rt
                 if (lane / (G::WORDS / 4) == j) word |= b << (p * G::EPL);
             }
         }
-        const float ref = tile_valid_max<T>(rt, word, lane);
-        zval = ref != -INFINITY ? tile_valid_sum<T>(rt, word, lane, shifted(ref, tp.c), tp.c) : 0.f;
+        float ref = m;
+        if (low) {
+            ref = tile_valid_max<T>(rt, word, lane);
+            zval = ref != -INFINITY ? tile_valid_sum<T>(rt, word, lane, shifted(ref, tp.c), tp.c) : 0.f;
+        }
         if (zval > 0.f) {
             d.logZ_valid = fmaf(ref - m, tp.inv, LN2F * (fast_log2(zval) - d.l2za));
             d.id = locate_in_tile<T>(rt, word, 0, lane, shifted(ref, tp.c), (double)u * (double)zval, tp.c);
@@ -1460,13 +1464,16 @@ __device__ __forceinline__ TileDraw draw_in_tile(const T *row, const RawTile &rt
             return d;
         }
     }
-    const double target = (double)u * (double)raw;
+    const double target = (double)u * (double)zval;
     double before = 0.0;   // valid weight of the groups already passed
 #pragma unroll
     for (int j = 0; j < 4; j++) {
-        float grp = w[j][0];
+        float grp = 0.f;
 #pragma unroll
-        for (int k = 1; k < G::EPL; k++) grp += w[j][k];
+        for (int k = 0; k < G::EPL; k++) {
+            w[j][k] *= fix;
+            grp += w[j][k];
+        }
         const double incl = before + wave_incl_scan((double)grp);
         const uint64_t cross = __ballot(incl > target);
         if (cross) {   // (uniform)

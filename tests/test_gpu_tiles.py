@@ -345,3 +345,44 @@ def test_rows_of_one_tile_find_their_token(dtype, V):
         check_row(x[b], np.array(s), un[b], ids[b], lzv[b], lza[b])
         if len(s) <= 2:
             assert ids[b] == (s[0] if un[b] == 0 else s[-1])
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 1_024), ("f32", 777), ("bf16", 2_048), ("bf16", 1_500)])
+@pytest.mark.parametrize("scale", [1.0, 1e8])
+def test_one_tile_rows_under_an_image_are_the_decode_step_s(dtype, V, scale):
+    """constrained_sample and ppv_sample_next have kernels of their own for rows of one tile, the first decode step has not: the same
+    tokens and the same bits of the masses, for uniforms on the very edges between two tokens.  (Logits of 1e8 are taken apart differently
+    from usual ones.)"""
+    rng = np.random.default_rng(V)
+    B, per = 2_000, 8
+    first = np.sort(rng.choice(V, V // 2, replace=False)).astype(np.int32)
+    index = ppv.ppv_build_index(first, np.arange(len(first) + 1, dtype=np.int64), V)
+    lg = rng.normal(0, 2, size=(B, -(-V // per) * per)).astype(np.float32)
+    if scale != 1.0:
+        lg = (scale + np.round(lg) * 8).astype(np.float32)     # (neighbours at 1e8)
+    ld = to_dev(lg)
+    if dtype == "bf16":
+        ld = ld.to(torch.bfloat16)
+    ld = ld[:, :V]
+    x = ld.float().cpu().numpy().astype(np.float64)[:, first]
+    w = np.exp(x - x.max(1, keepdims=True))
+    cdf = np.cumsum(w, 1) / w.sum(1, keepdims=True)
+    un = cdf[np.arange(B), rng.integers(0, len(first) - 1, B)].astype(np.float32)
+    un = to_dev(np.minimum(un, np.float32(1) - np.float32(2 ** -24)))
+    P, lens = torch.zeros((B, 2), dtype=torch.int32, device=DEV), torch.zeros(B, dtype=torch.int32, device=DEV)
+    words = torch.zeros((B, index.n_words), dtype=torch.int32, device=DEV)
+    ppv.ppv_next_token_mask(index, P, lens, words)
+    got = []
+    for name in ("step", "next", "sample"):
+        ids, lz = torch.full((B,), -9, dtype=torch.int32, device=DEV), torch.zeros(B, device=DEV)
+        if name == "step":
+            act, state = torch.ones(B, dtype=torch.uint8, device=DEV), torch.zeros((B, ppv.PPV_STATE_WORDS), dtype=torch.int32, device=DEV)
+            ppv.ppv_decode_first_step(index, P.clone(), lens.clone(), act, ld, un, ids, lz, torch.zeros(B, device=DEV), state=state)
+        elif name == "next":
+            ppv.ppv_sample_next(index, P, lens, ld, un, ids, lz)
+        else:
+            ppv.constrained_sample(ld, words, un, ids, lz)
+        got.append((ids.cpu().numpy(), lz.cpu().numpy().view(np.int32)))
+    for ids, lz in got[1:]:
+        assert np.array_equal(ids, got[0][0]), np.flatnonzero(ids != got[0][0])[:8]
+        assert np.array_equal(lz, got[0][1])
