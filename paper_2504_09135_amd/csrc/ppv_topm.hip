@@ -465,13 +465,14 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
     const uint32_t R = (uint32_t)(LIST / nw);
     const uint32_t base = (uint32_t)wave * R;
     // At least m groups have their maximum in the bin that is picked or above, so at least m tokens are not below the bin's
-    // lower edge.  With fewer than m groups in the row the bin is 0 and nothing is below it.
-    uint32_t edge_key16 = 0u;
-    if ((V + EPL - 1) / EPL >= m) {   // (uniform)
-        pick_digit(s.hist, TOPM_BINS, (uint32_t)m, s.bc);
-        edge_key16 = s.bc[4] << (16 - TOPM_BITS);
-    }
-    if (h.a_batches == 1 && edge_key16 != 0u) {   // (uniform)
+    // lower edge.  Where nearly all of the row's groups are asked for, that is below nearly all tokens, and fewer groups than m
+    // give no bound at all: the list is not begun.  (us, list / whole-row select, bf16, 64 and 1,024 rows: M = 0.98 of the groups, V = 8,192, 17.5
+    // 43.9 / 12.2 36.0; 0.8 of them, V = 10,000 13.0 35.0 / 14.9 45.1, V = 6,000 11.2 25.3 / 12.7 30.3.)
+    if (m > (V + EPL - 1) / EPL / 8 * 7) return false;   // (uniform)
+    pick_digit(s.hist, TOPM_BINS, (uint32_t)m, s.bc);
+    uint32_t edge_key16 = s.bc[4] << (16 - TOPM_BITS);
+    if (edge_key16 == 0u) return false;   // (uniform)
+    if (h.a_batches == 1) {   // (uniform)
         // A bin is a quarter of an octave wide and holds several times m tokens of a row of noise.  The maxima that
         // A has just seen are still in registers: those inside the bin are counted by their next five key bits, and
         // the bound moves up to the thirty-second of the bin in which the count from the top reaches m.
@@ -490,8 +491,8 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
     // lists what its group holds: one pass of the code that lists, usually, where a wavefront with a token in each of five chunks
     // took five (16 chunks a wavefront, M = 50: 2.2 to 4.5 us).
     uint32_t cnt = 0;   // wave-uniform
-    const uint32_t th16 = edge_key16 == 0x8000u ? 0x7FFEu : edge_key16 - 1u;   // listed: key above th16 (edge 0: all)
-    const uint32_t th_pk = (th16 & 0xFFFFu) | (th16 << 16);   // bf16 tokens are compared two at a time
+    const uint32_t th16 = edge_key16 == 0x8000u ? 0x7FFEu : edge_key16 - 1u;   // listed: key above th16
+    const uint32_t th_pk = th16 | (th16 << 16);   // bf16 tokens are compared two at a time
     uint4 *queue = s.queue + wave * WAVE;
     uint32_t *queue_tok = s.queue_tok + wave * WAVE;   // the group's first token
     auto list_group = [&](const uint4 &g, uint32_t first_tok, bool have) __attribute__((always_inline)) {
@@ -503,7 +504,6 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
                 const uint32_t a = pk_above(pk_keys(w[i]), th_pk);
                 pm |= ((a | (a >> 15)) & 3u) << (2 * i);
             }
-            if (edge_key16 == 0u) pm = 0xFFu;   // (uniform)
         } else {
 #pragma unroll
             for (int i = 0; i < 4; i++) pm |= order_key(w[i]) >> 16 >= edge_key16 ? 1u << i : 0u;
@@ -550,7 +550,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
 #pragma unroll
             for (int u = FIRST; u < FIRST + N; u++) {
                 const uint32_t key16 = (u & 1) ? pairs[u / 2] >> 16 : pairs[u / 2] & 0xFFFFu;
-                const bool mine = edge_key16 == 0u ? c + u < c1 : key16 > th16;
+                const bool mine = key16 > th16;
                 const uint64_t hit = __ballot(mine);
                 if (hit) {   // (uniform) most chunks of a long row have nothing
                     const uint32_t pos = groups + __builtin_amdgcn_mbcnt_hi((uint32_t)(hit >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hit, 0u)) - round;
@@ -571,7 +571,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
             const int at = have ? lane : 0;
             list_group(queue[at], queue_tok[at], have);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (left <= (uint32_t)WAVE) {
+            if (left <= (uint32_t)WAVE || cnt > R) {   // (a list that does not fit is not gone on with)
                 waiting = 0u;
                 break;
             }
@@ -591,7 +591,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
 #pragma unroll
             for (int p = p0; p < p0 + HALF / 2; p++) pairs[p] = pair_key<T>(r[2 * p], r[2 * p + 1], V, c + 2 * p, c1, lane);
         };
-        for (int c = c0; c < c1; c += HELD) {
+        for (int c = c0; c < c1 && cnt <= R; c += HELD) {
             maxima(0, c);
             list_some(std::integral_constant<int, 0>(), std::integral_constant<int, HALF>(), c, false);
 #pragma unroll

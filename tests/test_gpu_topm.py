@@ -294,6 +294,52 @@ def test_topm_mask_alone_counts_the_tokens_before_each_child(dtype, V):
     index.free()
 
 
+@pytest.mark.parametrize("dtype,V,B,Ms", [
+    ("bf16", 8_192, 12, (896, 897, 1_000)), ("f32", 4_100, 12, (896, 897, 1_000)),      # 7/8 of the row's groups of 16 bytes, and one more
+    ("bf16", 700, 12, (77, 78, 87, 88, 89)),                                            # ... and as many as it has
+    ("bf16", 32_768, 12, (50, 128, 129, 256, 257)), ("bf16", 32_776, 12, (50, 129)),     # a wavefront's share is just held, and not
+    ("f32", 16_384, 12, (50, 129)), ("f32", 16_388, 12, (50, 129)),
+    ("bf16", 32_768, 257, (50, 256)), ("bf16", 9_001, 257, (50, 100)),                   # more rows than compute units
+    ("bf16", 70_000, 12, (80, 81, 136, 137)), ("f32", 50_000, 12, (80, 81, 136, 137)),   # groups of two, four and sixteen a lane
+    ("bf16", 16_000, 1_000, (80, 81, 137)),
+])
+def test_topm_edges_of_the_rules_on_sizes(dtype, V, B, Ms):
+    """Where a call goes another way: a row taken as a whole, held or not, counted or not, its maxima grouped more or less coarsely.  Prefixes
+    with 0 to 12 children; noise, logits that fall with the id, all that are likely side by side at one end or the other, few distinct values,
+    most of them -inf.  The reference sorts the row."""
+    rng = np.random.default_rng(V + B)
+    kids = {n: np.sort(rng.choice(V, size=n, replace=False)) for n in range(13)}
+    for n in kids:
+        kids[n][:n // 2] = np.sort(rng.choice(60, size=n // 2, replace=False))     # (some among the first ids)
+        kids[n] = np.unique(kids[n])
+    S = W.constraint_set_from_lists([[n, int(c)] for n in kids for c in kids[n]] + [[0]], V)
+    index = ppv.ppv_build_index(S.tokens, S.offsets, V)
+    P, L = np.full((B, 2), W.PAD_TOKEN, np.int32), np.ones(B, np.int32)
+    P[:, 0] = np.arange(B) % 13
+    n_kinds = 6
+    x = rng.normal(0, 2, size=(n_kinds, V)).astype(np.float32)
+    x[1] = -1.5 * np.log(np.arange(1, V + 1)) + 0.3 * x[1]
+    x[2, :300] += 30
+    x[3, -300:] += 30
+    x[4] = rng.integers(-2, 3, V)
+    x[5, rng.choice(V, V - 40, replace=False)] = -np.inf
+    rows = np.arange(B) // 13 % n_kinds if B > 13 * n_kinds else (np.arange(B) // 2) % n_kinds
+    per = 8 if dtype == "bf16" else 4
+    padded = torch.zeros((n_kinds, -(-V // per) * per), dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+    padded[:, :V] = torch.from_numpy(x)
+    order = [np.argsort(-r, kind="stable") for r in padded[:, :V].float().numpy()]
+    ld = padded.to(DEV)[torch.from_numpy(rows).to(DEV)][:, :V]
+    for M in Ms:
+        mask, top, mv = gpu_topm(index, P, L, ld, M)
+        got = unpack_mask(mask.cpu().numpy().view(np.uint32), V)
+        best = [np.sort(o[:M]) for o in order]
+        for b in range(B):
+            want, ok = best[rows[b]], np.isin(best[rows[b]], kids[P[b, 0]])
+            assert np.array_equal(top[b, :len(want)], want) and np.array_equal(mv[b, :len(want)], ok), (M, b)
+            assert np.array_equal(np.flatnonzero(got[b]), want[ok]), (M, b)
+    index.free()
+
+
 def test_topm_largest_vocabulary():
     """V = PPV_MAX_VOCAB: the mask row fills the LDS that the histogram used; fp32 rows of 256 chunks per wavefront."""
     V = ppv.PPV_MAX_VOCAB
