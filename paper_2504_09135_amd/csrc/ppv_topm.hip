@@ -212,6 +212,10 @@ __device__ inline void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// A word that is the same in all lanes, which the compiler does not see of one from LDS.  (Branches on words of LDS were joined again by masks:
+// what one side holds was kept, and spilled, on the other.)
+__device__ inline uint32_t uniform_word(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
 struct TopmLds {
     uint32_t *hist;       // [TOPM_BINS]
     uint32_t *hist3;      // [32] the group maxima inside the bound's bin, by their next five key bits
@@ -342,7 +346,6 @@ struct TopmShare {
     int nc, cpw;      // chunks of the row, and of a wavefront (the last ones may have fewer)
     int c0, c1;
     int a_batches;    // batches of `held` chunks of each share that A looks at
-    bool kept;        // a wavefront's whole share is in its registers
     bool by_lane;     // A's groups are what a lane has of a batch (its even chunks, its odd ones), not 16 bytes
 };
 // With the bound from the whole row the list holds 1.1 to 1.5 m tokens when the bound is taken to the key's
@@ -355,7 +358,7 @@ struct TopmShare {
 // the bound lets 1.15 m tokens through.  A vocabulary may be in an order, though, that has all that are likely next to one another, in one
 // wavefront's share: its 128 groups then let 125 through for m = 80, which a part of 256 holds, and soon too many beyond that.  (In a part of
 // 128 logits that fall as 1.5 log of the id, V = 32k, 256 rows, M = 50, did not fit: 36 us with the whole-row select, 13 with groups of 16 bytes.)
-template <typename T>
+template <typename T, bool KEPT>
 __device__ inline TopmShare share_of_row(int V, int m, int list, int held, int wave, int nthreads) {
     constexpr int EPL = KeyChunk<T>::EPL;
     const int nw = nthreads / WAVE;
@@ -364,10 +367,9 @@ __device__ inline TopmShare share_of_row(int V, int m, int list, int held, int w
     h.cpw = (h.nc + nw - 1) / nw;
     h.c0 = wave * h.cpw;
     h.c1 = (h.c0 + h.cpw < h.nc) ? h.c0 + h.cpw : h.nc;
-    h.kept = held == TOPM_HELD_LONG || h.cpw <= held;
     const int all = (h.cpw + held - 1) / held;
     const long long want = 2ll * m * h.cpw <= (long long)held * list ? 1 : ((long long)m * h.cpw * 4 + (long long)held * list - 1) / ((long long)held * list);
-    h.a_batches = h.kept ? 1 : want > all ? all : (int)want;
+    h.a_batches = KEPT ? 1 : want > all ? all : (int)want;
     h.by_lane = m <= 80 && nthreads >= 2 * m && list / nw >= 256;
     return h;
 }
@@ -424,14 +426,14 @@ template <int PAIRS, typename DO> __device__ inline void each_group(const TopmSh
 }
 // A: the maxima of groups of the row's tokens, and the histogram of their leading key bits (cleared before the workgroup's last
 // barrier).  r arrives holding the wavefront's first HELD chunks; pairs: the maxima of the batch that A looks at last, by 16 bytes.
-template <typename T, int HELD>
+template <typename T, int HELD, bool KEPT>
 __device__ inline void group_maxima(const Row &buf, int V, const TopmShare &h, uint32_t *hist, int lane, uint4 (&r)[HELD],
                                     uint32_t (&pairs)[HELD / 2]) {
     const int a_end = h.c0 + h.a_batches * HELD < h.c1 ? h.c0 + h.a_batches * HELD : h.c1;
 #pragma unroll
     for (int p = 0; p < HELD / 2; p++) pairs[p] = 0u;   // (a wavefront may have no share)
     for (int c = h.c0; c < a_end; c += HELD) {
-        if (HELD == TOPM_HELD && c != h.c0) {   // (chunks that A reads from memory are read again in B: from cache)
+        if (!KEPT && c != h.c0) {   // (chunks that A reads from memory are read again in B: from cache)
 #pragma unroll
             for (int u = 0; u < HELD; u += 4) load_chunks<false>(buf, c + u, h.c1, lane, r + u);
         }
@@ -455,7 +457,7 @@ __device__ inline void group_maxima(const Row &buf, int V, const TopmShare &h, u
 // of THEIR groups reach it, so at least m tokens of the row do) -- as many batches of HELD chunks as it takes
 // for the list to have room for what the looser bound lets through; B reads the batches after the first again, from
 // cache, and the rest of the share for the first time.
-template <typename T, int LIST, int HELD, typename CHOSEN>
+template <typename T, int LIST, int HELD, bool KEPT, typename CHOSEN>
 __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, int m, const TopmLds &s, int lane,
                                      int wave, int nthreads, uint4 (&r)[HELD], uint32_t (&pairs)[HELD / 2], uint32_t *img,
                                      int n_words, CHOSEN chosen) {
@@ -470,9 +472,9 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
     // 43.9 / 12.2 36.0; 0.8 of them, V = 10,000 13.0 35.0 / 14.9 45.1, V = 6,000 11.2 25.3 / 12.7 30.3.)
     if (m > (V + EPL - 1) / EPL / 8 * 7) return false;   // (uniform)
     pick_digit(s.hist, TOPM_BINS, (uint32_t)m, s.bc);
-    uint32_t edge_key16 = s.bc[4] << (16 - TOPM_BITS);
+    uint32_t edge_key16 = uniform_word(s.bc[4]) << (16 - TOPM_BITS);
     if (edge_key16 == 0u) return false;   // (uniform)
-    if (h.a_batches == 1) {   // (uniform)
+    if (KEPT || h.a_batches == 1) {   // (uniform)
         // A bin is a quarter of an octave wide and holds several times m tokens of a row of noise.  The maxima that
         // A has just seen are still in registers: those inside the bin are counted by their next five key bits, and
         // the bound moves up to the thirty-second of the bin in which the count from the top reaches m.
@@ -482,7 +484,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
         });
         __syncthreads();
         pick_digit(s.hist3, 32, rest, s.bc);
-        edge_key16 |= s.bc[4];
+        edge_key16 |= uniform_word(s.bc[4]);
     }
     // ---- B. the tokens whose keys are not below the edge's, in token order, each wavefront into its own part of the list.
     // Only the keys' upper halves are compared.  (-0 has the key just under +0's in `pairs` and +0's here; an edge at +0 is lowered by one
@@ -578,7 +580,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
         }
     };
     constexpr int HALF = HELD / 2;
-    if (HELD == TOPM_HELD_LONG || h.kept) {
+    if (KEPT) {
         list_some(std::integral_constant<int, 0>(), std::integral_constant<int, HELD>(), c0, true);
     } else {
         if (h.a_batches > 1) {   // A has left its last chunks in r
@@ -604,7 +606,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
     }
     if (lane == 0 && cnt > R) atomicOr(&s.bc[6], 1u);
     __syncthreads();
-    if (s.bc[6] != 0u) return false;
+    if (uniform_word(s.bc[6]) != 0u) return false;
     for (int i = tid; i < n_words; i += nthreads) img[i] = 0u;   // (where the queues were)
 
     // ---- C. the key T of the m-th largest token, from the list: lane l answers for the entries l, l + 64, ... of its
@@ -615,7 +617,7 @@ __device__ inline bool select_listed(const Row &buf, int V, const TopmShare &h, 
     // further above the bound than the histogram is long (TOPM_CBINS - 1 values of the upper half) goes to the
     // whole-row select.
     pick_digit(s.hist2, TOPM_CBINS, (uint32_t)m, s.bc);
-    if (s.bc[4] == (uint32_t)(TOPM_CBINS - 1)) return false;   // T lies in the overflow bin
+    if (uniform_word(s.bc[4]) == (uint32_t)(TOPM_CBINS - 1)) return false;   // T lies in the overflow bin
     uint32_t hi_part = edge_key16 + s.bc[4], need = s.bc[5];
     if (sizeof(T) == 4) {   // fp32: the lower half of T, eight bits at a time
         for (int shift = 8; shift >= 0; shift -= 8) {
@@ -751,7 +753,7 @@ __device__ inline void count_chunk(const uint4 &raw, int V, int c, int lane, int
 // The mask row of a prefix with n <= TOPM_COUNT_MAX children (entries cb .. cb + n - 1, or the one child `only`),
 // restricted to the m most probable tokens.  Every thread of the workgroup calls; r holds the wavefront's first HELD chunks; tot[] was
 // cleared before the last barrier.
-template <typename T, int HELD>
+template <typename T, int HELD, bool KEPT>
 __device__ inline void count_children(const IndexView &ix, const T *__restrict__ row, const Row &buf, int V, const TopmShare &share,
                                       int m, uint32_t cb, uint32_t only, int n, uint4 (&r)[HELD], uint32_t *tot,
                                       uint32_t *__restrict__ out, int n_words, int lane, int nthreads) {
@@ -781,8 +783,10 @@ __device__ inline void count_children(const IndexView &ix, const T *__restrict__
             for (int u = h; u < h + 2; u++)
                 if (c + u < share.c1) count_chunk<T>(r[u], V, c + u, lane, n, tokc, thr, cnt);
 #pragma unroll
-            for (int u = h; u < h + 2; u++) r[u] = load_chunk(buf, c + HELD + u, share.c1, lane);
+            for (int u = h; u < h + 2; u++)
+                if (!KEPT) r[u] = load_chunk(buf, c + HELD + u, share.c1, lane);
         }
+        if (KEPT) break;
     }
 #pragma unroll
     for (int j = 0; j < TOPM_COUNT_MAX; j++) {
@@ -815,7 +819,9 @@ __host__ __device__ inline int topm_words(int n_words, int nthreads) {
     return max(max(TOPM_BINS, n_words), queues);
 }
 
-template <typename T, int LIST, int HELD>
+// KEPT: a wavefront's whole share of the row is in its registers.  (In kernels of their own: held rows need none of the registers of the loop over
+// longer shares, 70 for 96 and six spilled, and neither form spills.  us, 1,024 and 4,096 rows at V = 32k bf16, M = 50: 18.6 60.8 / 16.6 55.5.)
+template <typename T, int LIST, int HELD, bool KEPT>
 __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM_LIST_SMALL ? 5 : 4) void topm_kernel(const int32_t *__restrict__ prefixes,
                                                                 const int32_t *__restrict__ lens,
                                                                 const T *__restrict__ logits, int64_t row_stride,
@@ -844,7 +850,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
     const T *row = logits + (size_t)b * (size_t)row_stride;
 
     const Row buf = row_of(row, V);
-    const TopmShare h = share_of_row<T>(V, m, LIST, HELD, wave, nthreads);
+    const TopmShare h = share_of_row<T, KEPT>(V, m, LIST, HELD, wave, nthreads);
 
     const bool listed = force_streaming != 1 && nthreads * TOPM_SLOTS >= LIST && nthreads <= LIST;
     // a caller that asks for the mask alone: prefixes with few children are settled by counting (see count_children)
@@ -882,19 +888,20 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
     }
     // Counting pays where the selection would read part of the row twice, and of rows that are held where M is large or the launch is (then
     // it saves work, not time on the way).
-    const bool count_few = counting && !WHOLE && (!listed || h.a_batches > 1 || (h.kept && (nw < 8 || m > 256)));
+    const bool count_few = counting && !WHOLE && (!listed || h.a_batches > 1 || (KEPT && (nw < 8 || m > 256)));
+    auto verdict = [&](int i) { return uniform_word(bc[i]); };
     auto is_counted = [&]() {   // (after the walk's verdict)
-        const uint32_t few = bc[3] - bc[2];
-        return count_few && few <= (uint32_t)(sizeof(T) == 2 ? TOPM_COUNT_MAX : TOPM_COUNT_MAX / 2) && (bc[7] != PPV_NO_SLOT || few <= ix.heavy_min);
+        const uint32_t few = verdict(3) - verdict(2);
+        return count_few && few <= (uint32_t)(sizeof(T) == 2 ? TOPM_COUNT_MAX : TOPM_COUNT_MAX / 2) && (verdict(7) != PPV_NO_SLOT || few <= ix.heavy_min);
     };
     // The maxima are taken while wavefront 0 is on its way through the index, unless the row may do without them.
     if (count_few) __syncthreads();
     const bool maxima = listed && !(count_few && is_counted());
     uint32_t pairs[HELD / 2];
-    if (maxima) group_maxima<T, HELD>(buf, V, h, smem, lane, r, pairs);
+    if (maxima) group_maxima<T, HELD, KEPT>(buf, V, h, smem, lane, r, pairs);
     __syncthreads();   // the walk's verdict, and the maxima's histogram
-    const bool found = bc[1] != 0u;
-    const uint32_t cb = bc[2], ce = bc[3], only = bc[7];
+    const bool found = verdict(1) != 0u;
+    const uint32_t cb = verdict(2), ce = verdict(3), only = verdict(7);
     const int n = (int)(ce - cb);
     if (counting) {
         uint32_t *out = mask + (size_t)b * (size_t)n_words;
@@ -907,7 +914,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
             return;
         }
         if (!WHOLE && is_counted()) {   // (r holds the share's first chunks)
-            count_children<T, HELD>(ix, row, buf, V, h, m, cb, only, n, r, seg_a, out, n_words, lane, nthreads);
+            count_children<T, HELD, KEPT>(ix, row, buf, V, h, m, cb, only, n, r, seg_a, out, n_words, lane, nthreads);
             return;
         }
     }
@@ -945,7 +952,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
     const bool gather = 2 * m >= nthreads;
     bool done = false;
     if (listed) {
-        done = select_listed<T, LIST, HELD>(buf, V, h, m, lds, lane, wave, nthreads, r, pairs, img, n_words, [&](int i, uint32_t t) {
+        done = select_listed<T, LIST, HELD, KEPT>(buf, V, h, m, lds, lane, wave, nthreads, r, pairs, img, n_words, [&](int i, uint32_t t) {
             if (gather) sel[i] = t;   // (uniform)
             else verify(i, t);
         });
@@ -986,11 +993,15 @@ int topm_waves(int V, ppv_dtype dt, int B) {
     return nw;
 }
 
+int chunks_per_wave(int V, ppv_dtype dt, int nw) {
+    const int per = (dt == PPV_F32 ? 4 : 8) * WAVE;
+    return ((V + per - 1) / per + nw - 1) / nw;
+}
+
 // Chunks that a wavefront holds.  The wavefronts of rows with sixteen are alone on their compute unit and may hold sixteen each, which
 // is a row of up to 131,072 bf16 or 65,536 fp32 tokens: all of it is asked for at once and looked at in registers.
 int topm_held(int V, ppv_dtype dt, int nw) {
-    const int per = (dt == PPV_F32 ? 4 : 8) * WAVE;
-    const int cpw = ((V + per - 1) / per + nw - 1) / nw;
+    const int cpw = chunks_per_wave(V, dt, nw);
     return nw == TOPM_WAVES && cpw > TOPM_HELD && cpw <= TOPM_HELD_LONG ? TOPM_HELD_LONG : TOPM_HELD;
 }
 
@@ -1020,22 +1031,25 @@ extern "C" ppv_status ppv_topm_mask(const ppv_index_t *ix, const int32_t *prefix
     const size_t lds = topm_lds(ix->view, threads);
     const dim3 grid((unsigned)B), block(threads);
     hipStream_t hs = (hipStream_t)stream;
-#define PPV_LAUNCH_TOPM(T, LIST, HELD)                                                                                \
-    hipLaunchKernelGGL((topm_kernel<T, LIST, HELD>), grid, block, lds, hs, prefixes, lens, (const T *)logits,          \
+#define PPV_LAUNCH_TOPM(T, LIST, HELD, KEPT)                                                                          \
+    hipLaunchKernelGGL((topm_kernel<T, LIST, HELD, KEPT>), grid, block, lds, hs, prefixes, lens, (const T *)logits,    \
                        row_stride, prefix_stride, M, force_streaming, top_ids, mask_V, mask, ix->view)
     // a few hundred tokens reach the bound when M is small and the row not too long (the bound's bin holds a share
     // of the row): then a quarter of the LDS does, and more rows fit a compute unit
     const bool small_list = M <= 128 && V <= 65536;
-    const bool long_share = topm_held(V, dt, threads / WAVE) == TOPM_HELD_LONG;
+    const bool long_share = topm_held(V, dt, threads / WAVE) == TOPM_HELD_LONG, kept = chunks_per_wave(V, dt, threads / WAVE) <= TOPM_HELD;
+#define PPV_LAUNCH_TOPM_OF(T)                                                         \
+    if (long_share) PPV_LAUNCH_TOPM(T, TOPM_LIST_BIG, TOPM_HELD_LONG, true);          \
+    else if (small_list && kept) PPV_LAUNCH_TOPM(T, TOPM_LIST_SMALL, TOPM_HELD, true); \
+    else if (small_list) PPV_LAUNCH_TOPM(T, TOPM_LIST_SMALL, TOPM_HELD, false);       \
+    else if (kept) PPV_LAUNCH_TOPM(T, TOPM_LIST_BIG, TOPM_HELD, true);                \
+    else PPV_LAUNCH_TOPM(T, TOPM_LIST_BIG, TOPM_HELD, false)
     if (dt == PPV_F32) {
-        if (long_share) PPV_LAUNCH_TOPM(float, TOPM_LIST_BIG, TOPM_HELD_LONG);
-        else if (small_list) PPV_LAUNCH_TOPM(float, TOPM_LIST_SMALL, TOPM_HELD);
-        else PPV_LAUNCH_TOPM(float, TOPM_LIST_BIG, TOPM_HELD);
+        PPV_LAUNCH_TOPM_OF(float);
     } else {
-        if (long_share) PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_BIG, TOPM_HELD_LONG);
-        else if (small_list) PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_SMALL, TOPM_HELD);
-        else PPV_LAUNCH_TOPM(uint16_t, TOPM_LIST_BIG, TOPM_HELD);
+        PPV_LAUNCH_TOPM_OF(uint16_t);
     }
+#undef PPV_LAUNCH_TOPM_OF
 #undef PPV_LAUNCH_TOPM
     PPV_HIP_TRY(hipGetLastError());
     return PPV_OK;
