@@ -875,6 +875,19 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
         for (int u = 0; u < HELD; u += 4)
             if (u == 0 || h.cpw > u) load_chunks<true>(buf, h.c0 + u, h.c1, lane, r + u);   // (uniform; a short row has no second half)
     }
+    // Counting pays where the selection would read part of the row twice, and of rows that are held.  Of these, where M is large or the launch is,
+    // it saves work, and the maxima wait for the walk's verdict; else it saves time on the way, and only wavefront 0's wait, which
+    // knows: the others have nothing to do meanwhile, and a row that is not counted is not kept.  (us, mask alone, V = 32k bf16, M = 50, with counting /
+    // without, 64, 256 and 512 rows: prefixes with one continuation each 6.7 7.1 9.8 / 8.9 9.3 12.0, prefixes of all kinds 9.4 9.9 12.3 / 9.5 9.9 12.4.  Rows
+    // whose maxima all fall into one or two bins, and whose additions take long, 7.8 to 9.2 / 9.8 to 54.  Many continuations are much work where compute
+    // units have more than one row: there two are counted at most; with up to eight, prefixes of all kinds took 13.9 us at 512 rows.)
+    const bool count_few = counting && !WHOLE && (!listed || h.a_batches > 1 || KEPT);
+    const bool count_first = count_few && (!KEPT || nw < 8 || m > 256);
+    const uint32_t most = !count_first && gridDim.x > 256u ? 2u : (uint32_t)(sizeof(T) == 2 ? TOPM_COUNT_MAX : TOPM_COUNT_MAX / 2);
+    auto is_counted = [&](uint32_t only, uint32_t few) {
+        return count_few && few <= most && (only != PPV_NO_SLOT || few <= ix.heavy_min);
+    };
+    bool maxima = listed;
     if (wave == 0) {   // the part every candidate row shares: locate the prefix once
         t = t < 0 ? 0 : (t > stride ? stride : t);
         const Walk w = walk_prefix(ix, prefixes + (size_t)b * (size_t)stride, mine, t, lane);
@@ -885,18 +898,14 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
             bc[3] = w.found ? w.ce : 0u;
             bc[7] = w.only;
         }
+        if (uniform_word(w.found ? 1u : 0u) == 0u || is_counted(uniform_word(w.only), uniform_word(w.ce - w.cb))) maxima = maxima && !count_few;
     }
-    // Counting pays where the selection would read part of the row twice, and of rows that are held where M is large or the launch is (then
-    // it saves work, not time on the way).
-    const bool count_few = counting && !WHOLE && (!listed || h.a_batches > 1 || (KEPT && (nw < 8 || m > 256)));
     auto verdict = [&](int i) { return uniform_word(bc[i]); };
-    auto is_counted = [&]() {   // (after the walk's verdict)
-        const uint32_t few = verdict(3) - verdict(2);
-        return count_few && few <= (uint32_t)(sizeof(T) == 2 ? TOPM_COUNT_MAX : TOPM_COUNT_MAX / 2) && (verdict(7) != PPV_NO_SLOT || few <= ix.heavy_min);
-    };
+    if (count_first) {
+        __syncthreads();
+        maxima = maxima && !is_counted(verdict(7), verdict(3) - verdict(2));
+    }
     // The maxima are taken while wavefront 0 is on its way through the index, unless the row may do without them.
-    if (count_few) __syncthreads();
-    const bool maxima = listed && !(count_few && is_counted());
     uint32_t pairs[HELD / 2];
     if (maxima) group_maxima<T, HELD, KEPT>(buf, V, h, smem, lane, r, pairs);
     __syncthreads();   // the walk's verdict, and the maxima's histogram
@@ -913,7 +922,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
             }
             return;
         }
-        if (!WHOLE && is_counted()) {   // (r holds the share's first chunks)
+        if (!WHOLE && is_counted(only, ce - cb)) {   // (r holds the share's first chunks)
             count_children<T, HELD, KEPT>(ix, row, buf, V, h, m, cb, only, n, r, seg_a, out, n_words, lane, nthreads);
             return;
         }
