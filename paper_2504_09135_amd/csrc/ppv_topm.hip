@@ -346,18 +346,20 @@ struct TopmShare {
     int nc, cpw;      // chunks of the row, and of a wavefront (the last ones may have fewer)
     int c0, c1;
     int a_batches;    // batches of `held` chunks of each share that A looks at
-    bool by_lane;     // A's groups are what a lane has of a batch (its even chunks, its odd ones), not 16 bytes
+    int by_lane;      // 2, 4: A's groups are what a lane has of a batch in every second, every fourth chunk; 0: 16 bytes
 };
 // With the bound from the whole row the list holds 1.1 to 1.5 m tokens when the bound is taken to the key's
 // upper 16 bits (possible when A looks at one batch) and about 4 m of a row of noise when it stays at
 // the histogram's bin, a quarter of an octave; from a_batches batches of the share, cpw / (held a_batches)
 // times more.  One batch if the list then has room for twice 1.3 m times that, else as few as leave room for
 // 4 m times that.  (A list that overflows all the same sends the row to the whole-row select.)
-// by_lane: groups of what a lane holds, two of them, where A's histogram takes eight or sixteen additions a lane otherwise, nearly all to
+// by_lane: groups of what a lane holds, two or four of them, where A's histogram takes eight or sixteen additions a lane otherwise, nearly all to
 // the same few bins.  Tokens thrown into n groups are the largest of n (1 - exp(-tokens / n)) of them: with four groups to a candidate
 // the bound lets 1.15 m tokens through.  A vocabulary may be in an order, though, that has all that are likely next to one another, in one
-// wavefront's share: its 128 groups then let 125 through for m = 80, which a part of 256 holds, and soon too many beyond that.  (In a part of
-// 128 logits that fall as 1.5 log of the id, V = 32k, 256 rows, M = 50, did not fit: 36 us with the whole-row select, 13 with groups of 16 bytes.)
+// wavefront's share: its 128 groups then let 125 through for m = 80, its 256 groups 194 for m = 136, which a part of 256 holds, and soon too many
+// beyond that.  (In a part of 128 logits that fall as 1.5 log of the id, V = 32k, 256 rows, M = 50, did not fit: 36 us with the whole-row select, 13 with
+// groups of 16 bytes.  M = 100, V = 128k bf16, 128 rows, groups of 16 bytes / four a lane: 14.8 / 14.0, logits that fall as above with noise 22.5 / 18.5.
+// Of a longer share A sees too little for four: V = 32k, 4,096 rows, M = 100 98 / 69.)
 template <typename T, bool KEPT>
 __device__ inline TopmShare share_of_row(int V, int m, int list, int held, int wave, int nthreads) {
     constexpr int EPL = KeyChunk<T>::EPL;
@@ -370,7 +372,7 @@ __device__ inline TopmShare share_of_row(int V, int m, int list, int held, int w
     const int all = (h.cpw + held - 1) / held;
     const long long want = 2ll * m * h.cpw <= (long long)held * list ? 1 : ((long long)m * h.cpw * 4 + (long long)held * list - 1) / ((long long)held * list);
     h.a_batches = KEPT ? 1 : want > all ? all : (int)want;
-    h.by_lane = m <= 80 && nthreads >= 2 * m && list / nw >= 256;
+    h.by_lane = nthreads < 2 * m || list / nw < 256 ? 0 : m <= 80 ? 2 : KEPT && m <= 136 ? 4 : 0;
     return h;
 }
 
@@ -411,11 +413,19 @@ template <typename T> __device__ inline uint32_t pair_key(const uint4 &a, const 
 // do_group(key): the upper half of the largest key of each of this lane's groups
 template <int PAIRS, typename DO> __device__ inline void each_group(const TopmShare &h, const uint32_t (&pairs)[PAIRS], DO do_group) {
     if (h.by_lane) {   // (uniform)
-        uint32_t mx = pairs[0];
+        uint32_t a = pairs[0], b = pairs[1];
 #pragma unroll
-        for (int p = 1; p < PAIRS; p++) mx = pk_max(mx, pairs[p]);
-        do_group(mx & 0xFFFFu);
-        do_group(mx >> 16);
+        for (int p = 2; p < PAIRS; p += 2) {
+            a = pk_max(a, pairs[p]);
+            b = pk_max(b, pairs[p + 1]);
+        }
+        if (h.by_lane == 2) a = pk_max(a, b);   // (uniform)
+        do_group(a & 0xFFFFu);
+        do_group(a >> 16);
+        if (h.by_lane == 4) {
+            do_group(b & 0xFFFFu);
+            do_group(b >> 16);
+        }
     } else {
 #pragma unroll
         for (int p = 0; p < PAIRS; p++) {
