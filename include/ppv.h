@@ -180,8 +180,9 @@ ppv_status constrained_sample(const void *logits, ppv_dtype dt, int64_t row_stri
  * race; calls on one stream, or otherwise ordered, do not.  What a race spoils is the results of the calls that
  * overlap: a row of theirs may be wrong, or not written, or say that a part of it did not arrive (id -1, masses NaN).
  * Nothing has to be cleared between calls, after a race either: what a call leaves in the array carries that
- * call's mark, and later calls take none of it.  (The replays of one captured call have one mark: that graph must not
- * be replayed at the same time as itself.)
+ * call's mark, and later calls take none of it.  The replays of one captured call have one mark, though: a graph must not
+ * be replayed at the same time as itself, and where one of its replays has overlapped with another call of this function
+ * the call is captured again before it is relied on (what the race left may pass for a later replay's).
  * The first call on a device looks up the array's address on that device (no allocation); make that first call
  * outside stream capture.
  * Errors: as constrained_sample; PPV_ERANGE also for B > PPV_NOALLOC_MAX_ROWS.

@@ -5,7 +5,7 @@
 //   select   P = softmax(logits) is increasing in the logit, so the top M are found on the logits'
 //            bit patterns, through an order-preserving 32-bit key per token.  M is small against
 //            |V|, so almost every token can be turned away with one comparison:
-//              A. the maxima of groups of tokens (half of what a lane holds, or for large M every 16 bytes) are histogrammed by
+//              A. the maxima of groups of tokens (half or a quarter of what a lane holds, or for large M every 16 bytes) are histogrammed by
 //                 their 11 leading key bits; the bin that holds the M-th largest maximum gives a bound that at
 //                 least M tokens reach.  A wavefront holds eight or sixteen chunks of the row (a chunk: 16 bytes a lane) in
 //                 registers; when its share of the row is longer, A looks only at those --
@@ -29,10 +29,10 @@
 //            a wavefront's start, before / now: prefix located 3.1 / 4.1 and A done 5.3 / 6.2 (the row, 256 KB for one compute
 //            unit, arrives over the first 4 us: A waited for the prefix, and asked for half of the row later), bound 6.7 / 7.2, list 13.1 / 9.7
 //            (2 to 5 us a wavefront for a handful of tokens, each chunk with one listed by itself, and the row's other half on its
-//            way), chosen 16.5 / 11.3, written 17.2 / 11.7.  Per call, us before / now: this shape 18.3 / 13.6, V = 32k, 256 rows 12.0 / 9.9,
-//            V = 32k, 4,096 rows 73 / 60, V = 256k, 1,024 rows 114 / 104, V = 50k fp32, 384 rows 26.9 / 23.6.  Slower by 2 to 4 % where a
-//            tenth of the row and more is asked for (V = 8,192, M = 1,000: 67.1 / 69.0).
-//            If the list does not fit (a flat row with thousands of equal logits at the cut, or a
+//            way), chosen 16.5 / 11.3, written 17.2 / 11.7.  Per call, us before / now: this shape 18.4 / 13.6, V = 32k, 256 rows 11.8 / 9.8,
+//            V = 32k, 4,096 rows 73.7 / 56.0, V = 256k, 1,024 rows 115.6 / 98.4, V = 50k fp32, 384 rows 26.5 / 21.2, V = 8,192, 512 rows, M = 1,000
+//            20.9 / 16.5.
+//            If the list does not fit (a flat row with thousands of equal logits at the cut, M near the number of the row's 16-byte groups, or a
 //            workgroup too small to hold it) the same radix select runs over the whole row instead,
 //            one histogram pass per digit and two more passes to gather in token order.
 //   verify   the M candidate rows share their first |a| tokens, so the prefix is located once

@@ -151,8 +151,9 @@ __device__ inline void prefix_hash_finish(uint32_t h1, uint32_t h2, uint32_t siz
 // What bounds it is the chain of loads that wait for each other: prefix, bucket, member's tokens (and the root's children
 // where nothing was found).  Open addressing at half load, a node by node_at and its entry took 14.5 us for the masks of
 // 1,024 prefixes (V = 256k) and 5.6 us for those of 128; 9.4 and 4.1 us this way.
-// SLOT: the slot is wanted in the same trip as the ranks; kernels of a wavefront to a row, of which thousands share the memory's attention,
-// ask for it where they need it (mask + sample of 4,096 rows over codes 9.79 us, 9.88 with the slots of all).
+// SLOT: the slot is wanted in the same trip as the ranks, by kernels that hand it over; kernels of a wavefront to a row ask for it where they
+// need it, which is no more than the noise of these calls (us, with the slots of all / so, 4,096 rows: mask + sample over codes 9.7 / 9.5, V = 2,000
+// bf16 13.4 / 13.1; ppv_sample_next 6.9 / 7.05, 10.3 / 10.2).
 // `mine` = first_tokens(prefix, stride, lane), requested by the caller before the prefix's length is known.
 __device__ inline int32_t first_tokens(const int32_t *__restrict__ prefix, int stride, int lane) {
     return (lane < stride) ? prefix[lane] : 0;
