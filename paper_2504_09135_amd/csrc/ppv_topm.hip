@@ -452,9 +452,24 @@ __device__ inline void group_maxima(const Row &buf, int V, const TopmShare &h, u
             pairs[p] = 0u;
             if (c + 2 * p < h.c1) pairs[p] = pair_key<T>(r[2 * p], r[2 * p + 1], V, c + 2 * p, h.c1, lane);   // (wave-uniform)
         }
-        each_group(h, pairs, [&](uint32_t key16) {
-            if (key16 != 0u) atomicAdd(&hist[key16 >> (16 - TOPM_BITS)], 1u);
-        });
+        // A lane with many groups adds those in its first one's bin at once: rows whose maxima fall into one or two bins wait for their additions, one
+        // lane after the other, and where the row is counted in the end for nothing.  (us, V = 32k bf16, 256 rows, M = 50, mask alone, one by one / so:
+        // logits around 12, prefixes of all kinds 10.7 / 10.1, of one continuation 8.1 / 7.5, falling as 1.5 log of the id 8.8 / 7.8; around 0
+        // 9.8 / 9.9, 7.1 / 7.2.  With few groups a lane 1 to 3 % slower.)
+        if (!h.by_lane && h.cpw > 4) {   // (uniform)
+            const uint32_t first = (pairs[0] & 0xFFFFu) >> (16 - TOPM_BITS);
+            uint32_t same = 0u;
+            each_group(h, pairs, [&](uint32_t key16) {
+                const uint32_t bin = key16 >> (16 - TOPM_BITS);
+                same += bin == first ? 1u : 0u;
+                if (bin != first && key16 != 0u) atomicAdd(&hist[bin], 1u);
+            });
+            if (first != 0u && same != 0u) atomicAdd(&hist[first], same);   // (bin 0 need not be counted: see select_listed's edge)
+        } else {
+            each_group(h, pairs, [&](uint32_t key16) {
+                if (key16 != 0u) atomicAdd(&hist[key16 >> (16 - TOPM_BITS)], 1u);
+            });
+        }
     }
 }
 
@@ -888,8 +903,7 @@ __global__ __launch_bounds__(TOPM_WAVES *WAVE, HELD == TOPM_HELD && LIST == TOPM
     // Counting pays where the selection would read part of the row twice, and of rows that are held.  Of these, where M is large or the launch is,
     // it saves work, and the maxima wait for the walk's verdict; else it saves time on the way, and only wavefront 0's wait, which
     // knows: the others have nothing to do meanwhile, and a row that is not counted is not kept.  (us, mask alone, V = 32k bf16, M = 50, with counting /
-    // without, 64, 256 and 512 rows: prefixes with one continuation each 6.7 7.1 9.8 / 8.9 9.3 12.0, prefixes of all kinds 9.4 9.9 12.3 / 9.5 9.9 12.4.  Rows
-    // whose maxima all fall into one or two bins, and whose additions take long, 7.8 to 9.2 / 9.8 to 54.  Many continuations are much work where compute
+    // without, 64, 256 and 512 rows: prefixes with one continuation each 6.8 7.2 9.9 / 8.9 9.3 12.0, prefixes of all kinds 9.6 10.0 12.4 / 9.6 9.8 12.4.  Many continuations are much work where compute
     // units have more than one row: there two are counted at most; with up to eight, prefixes of all kinds took 13.9 us at 512 rows.)
     const bool count_few = counting && !WHOLE && (!listed || h.a_batches > 1 || KEPT);
     const bool count_first = count_few && (!KEPT || nw < 8 || m > 256);
